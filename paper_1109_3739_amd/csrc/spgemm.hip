@@ -1322,6 +1322,13 @@ struct LoadBucket {
 };
 
 // ------------------------------------------------------------------ numeric: parts
+// Most parts per work-queue ticket.  A launch takes one part per ticket until
+// every workgroup of its grid would get two of them: with fewer parts a ticket
+// of four leaves workgroups idle while others take four parts in turn (R-MAT
+// scale 14: 176 parts on 44 of 176 workgroups, 172 us; scale 20 has 1900 parts
+// per workgroup and keeps four, which save ticket round trips).
+constexpr int kPartBatch = 4;
+
 template <typename T>
 __device__ __forceinline__ void block_bitonic_sort(uint64_t* a, int n2) {
   for (int k = 2; k <= n2; k <<= 1) {
@@ -1349,12 +1356,11 @@ template <int SR, typename T, int QC, bool OFF32>
 __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, ProdSrc S,
                                                         const int64_t* mults,
                                                         const int64_t* cnt, const Part* parts, const int64_t* qoff,
-                                                        int nq, int nhome, unsigned long long* qctr,
+                                                        int nq, int nhome, int batch, unsigned long long* qctr,
                                                         const uint64_t* gbm, int64_t gbm_words,
                                                         const int32_t* qlist, int32_t* cir, T* cnum, unsigned* err) {
   using SR_ = Semiring<SR, T>;
   constexpr bool kVal = SR != SPX_OR_AND;
-  constexpr int kPartBatch = 4;
   extern __shared__ __align__(16) unsigned char lds[];
   __shared__ int64_t s_pi;
   __shared__ int s_nbat;
@@ -1369,8 +1375,8 @@ __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, Pr
   // the XCDs round robin, so one queue's rows of A stay in one L2), then
   // takes the shared queue nq-1, then helps the others.
   const int home = nhome > 1 ? (int)(blockIdx.x % nhome) : 0;
-  // A ticket is a batch of up to kPartBatch consecutive parts (often of one
-  // column), whose descriptors are loaded together.
+  // A ticket is a batch of up to `batch` (<= kPartBatch) consecutive parts
+  // (often of one column), whose descriptors are loaded together.
   int qi = 0;
   for (;;) {
     if (threadIdx.x == 0) {
@@ -1378,10 +1384,10 @@ __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, Pr
       int nbat = 0;
       while (qi < nq) {
         const int q = qi == 0 ? home : (qi == 1 ? nq - 1 : (home + qi - 1) % (nq - 1));
-        const int64_t first = qoff[q] + (int64_t)atomicAdd(&qctr[q], (unsigned long long)kPartBatch);
+        const int64_t first = qoff[q] + (int64_t)atomicAdd(&qctr[q], (unsigned long long)batch);
         if (first < qoff[q + 1]) {
           got = first;
-          nbat = (int)(qoff[q + 1] - first < kPartBatch ? qoff[q + 1] - first : kPartBatch);
+          nbat = (int)(qoff[q + 1] - first < batch ? qoff[q + 1] - first : batch);
           break;
         }
         ++qi;
@@ -1896,17 +1902,18 @@ static int launch_numeric(GemmPlan* P, spx_mat* C, hipStream_t st) {
     const int64_t* qoff = r == 0 ? P->qoff_multi : P->qoff_single;
     const int nq = r == 0 ? P->nq_multi : 1;
     unsigned long long* qctr = r == 0 ? P->qctr : P->qctr + P->nq_multi;
+    const int batch = (int)std::max<int64_t>(1, std::min<int64_t>(kPartBatch, (n1 - n0) / (2 * grid)));
     if (r == 0 && P->wide)
       hipLaunchKernelGGL((k_numeric_parts<SR, T, kQChunkWide, false>), dim3((unsigned)grid), dim3(blk), (size_t)L, st,
-                         P->A, P->B, P->src, P->mults_d, P->cnt, P->parts, qoff, nq, P->nslice, qctr, P->gbm,
+                         P->A, P->B, P->src, P->mults_d, P->cnt, P->parts, qoff, nq, P->nslice, batch, qctr, P->gbm,
                          P->gbm_words, P->qlist, cir, cnum, err);
     else if (P->src.off32)  // A's positions fit 29 bits: gathers through 32-bit offsets
       hipLaunchKernelGGL((k_numeric_parts<SR, T, kQChunk, true>), dim3((unsigned)grid), dim3(blk), (size_t)L, st, P->A,
-                         P->B, P->src, P->mults_d, P->cnt, P->parts, qoff, nq, r == 0 ? P->nslice : 1, qctr, P->gbm,
+                         P->B, P->src, P->mults_d, P->cnt, P->parts, qoff, nq, r == 0 ? P->nslice : 1, batch, qctr, P->gbm,
                          P->gbm_words, P->qlist, cir, cnum, err);
     else
       hipLaunchKernelGGL((k_numeric_parts<SR, T, kQChunk, false>), dim3((unsigned)grid), dim3(blk), (size_t)L, st, P->A,
-                         P->B, P->src, P->mults_d, P->cnt, P->parts, qoff, nq, r == 0 ? P->nslice : 1, qctr, P->gbm,
+                         P->B, P->src, P->mults_d, P->cnt, P->parts, qoff, nq, r == 0 ? P->nslice : 1, batch, qctr, P->gbm,
                          P->gbm_words, P->qlist, cir, cnum, err);
     SPX_HIP(hipGetLastError());
     if (r == 0) P->mark(kEvMulti, st);
