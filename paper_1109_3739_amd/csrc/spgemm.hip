@@ -26,27 +26,20 @@
 #include <memory>
 
 #include "common.h"
+#include "mid.h"
 #include "operand.h"
 #include "plan.h"
 #include "scan.h"
+#include "wave.h"
 
 namespace spx {
-
-// Semiring for the boolean (pattern only) case; values are never touched.
-template <typename T>
-struct Semiring<SPX_OR_AND, T> {
-  static constexpr bool kUsesA = false, kUsesB = false;
-  __device__ static T mul(T a, T) { return a; }
-  __device__ static T add(T acc, T) { return acc; }
-  __device__ static T ident() { return T(0); }
-  __device__ static void lds_acc(T*, T) {}
-};
 
 // ------------------------------------------------------------------ bins
 // Columns (slots of B) are binned by their number of multiplications mu.
 // The bin id is also the processing order: heavy columns first.
 //   0 .. 40   bitmap-counted columns, id = 40 - floor(log2 mu)
-//   41 .. 48  hash-counted columns, table of 2^(15 - (id - 41)) keys
+//   41 .. 48  hash-counted columns, table of 2^(15 - (id - 41)) keys; the last
+//             three (at most kMidMax products) are mid columns, one wave each
 //   49        tiny columns (mu <= tiny_max, at most 64): one wave each
 //   50        columns without products
 constexpr int kBinHash0 = 41;
@@ -55,11 +48,9 @@ constexpr int kBinEmpty = 50;
 constexpr int kNumBins = 51;
 constexpr int kHashLog2Max = 15;
 constexpr int kHashLog2Min = 8;
+constexpr int kBinMid = kBinHash0 + kHashLog2Max - kMidHashLog2;
 constexpr int kBitmapChunkLog2 = 20;                          // rows per bitmap-count chunk
 constexpr int32_t kSplitMin = 32;  // A columns longer than this get a split-table row
-
-__device__ __forceinline__ int floor_log2_u64(uint64_t x) { return 63 - __clzll(x); }
-__device__ __forceinline__ int ceil_log2_u64(uint64_t x) { return x <= 1 ? 0 : 64 - __clzll(x - 1); }
 
 struct BinCfg {
   int64_t tiny_max, hash_max;
@@ -280,25 +271,6 @@ __device__ __forceinline__ int32_t lower_bound_i32(const int32_t* a, int32_t n, 
   }
   return lo;
 }
-
-// Where the products of one output column come from.  For every stored
-// B(k,j) (index q): the start and length of A(:,k), and for long columns of
-// A a row of the split table, whose entry b is the first position in A(:,k)
-// with row >= b * 2^rbshift (b = 0..nblk; the last entry is the length).
-// Parts of the row space start and end on those block boundaries, so a
-// part's range inside a long column costs two loads; short columns are
-// filtered entry by entry.
-struct ProdSrc {
-  const int32_t* air;
-  const int64_t* a0;
-  const int32_t* alen;
-  const int32_t* split;
-  const int32_t* splits;
-  int32_t sstride;
-  int32_t rbshift;
-  int32_t m;
-  int32_t off32;  // 1: positions in A fit 29 bits, loads take 32-bit byte offsets
-};
 
 // A's row and value at position o through a 32-bit byte offset from the base
 // (valid when o < 2^29, so o * 8 does not wrap).
@@ -596,44 +568,6 @@ __device__ __forceinline__ uint32_t hash_row(int32_t r, int log2s) {
 }
 
 // ------------------------------------------------------------------ count: tiny (one wave)
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Group-wide helpers over G lanes: the whole wave (G = 64) or one of its
-// aligned halves (G = 32); exchanges stay inside the group.
-// Inclusive scan with op by DPP: shifts by 1, 2, 4, 8 inside each 16-lane
-// row, then the last lane of row 0 (2) is added into row 1 (3), and for
-// G = 64 lane 31 into rows 2 and 3.  Lanes without a source receive ident.
-template <int G, class Op>
-__device__ __forceinline__ int group_scan(int v, int ident, Op op) {
-  static_assert(G == 32 || G == 64, "groups of 32 or 64 lanes");
-  v = op(v, __builtin_amdgcn_update_dpp(ident, v, 0x111, 0xF, 0xF, false));  // row_shr:1
-  v = op(v, __builtin_amdgcn_update_dpp(ident, v, 0x112, 0xF, 0xF, false));  // row_shr:2
-  v = op(v, __builtin_amdgcn_update_dpp(ident, v, 0x114, 0xF, 0xF, false));  // row_shr:4
-  v = op(v, __builtin_amdgcn_update_dpp(ident, v, 0x118, 0xF, 0xF, false));  // row_shr:8
-  v = op(v, __builtin_amdgcn_update_dpp(ident, v, 0x142, 0xA, 0xF, false));  // row_bcast:15
-  if constexpr (G == 64) v = op(v, __builtin_amdgcn_update_dpp(ident, v, 0x143, 0xC, 0xF, false));  // row_bcast:31
-  return v;
-}
-
-// Value of the next lane (lane + 1; 0 in lane 63) by a DPP wave shift.
-template <typename T>
-__device__ __forceinline__ T lane_next(T v) {
-  if constexpr (sizeof(T) == 4) {
-    const int u = __builtin_bit_cast(int, v);
-    return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(0, u, 0x130, 0xF, 0xF, false));  // wave_shl:1
-  } else {
-    static_assert(sizeof(T) == 8, "32- or 64-bit values");
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x130, 0xF, 0xF, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x130, 0xF, 0xF, false);
-    return __builtin_bit_cast(T, ((uint64_t)hi << 32) | lo);
-  }
-}
-
 template <int G>
 __device__ __forceinline__ int group_incl_scan(int v, int) {
   return group_scan<G>(v, 0, [](int x, int y) { return x + y; });
@@ -1125,7 +1059,7 @@ __device__ int64_t cut_parts(const PartCfg& p, const uint32_t* blk, int32_t t, i
   return np;
 }
 
-// Number of parts of every non-tiny, nonempty column (list positions
+// Number of parts of every column above the mid ones (list positions
 // [0, npos)), or the parts themselves (emit).
 // In the counting pass, setup_acc (if given) receives the sums over the cut
 // columns of (B entries x parts) and of their multiplications, which tell
@@ -1919,6 +1853,9 @@ static int launch_numeric(GemmPlan* P, spx_mat* C, hipStream_t st) {
     if (r == 0) P->mark(kEvMulti, st);
   }
   if (P->psplit == 0) P->mark(kEvMulti, st);
+  for (int b = kBinMid; b < kBinTiny; ++b)  // mid columns, the longest first
+    SPX_TRY(launch_mid(P->sr, P->vt, 8 >> (b - kBinMid), P->A, P->B, P->src, P->list, P->binoff_h[b],
+                       P->binoff_h[b + 1], P->off, cir, cnum, st));
   P->mark(kEvParts, st);
   const int64_t ntiny = P->binoff_h[kBinTiny + 1] - P->binoff_h[kBinTiny];
   if (ntiny > 0) {
@@ -2094,7 +2031,7 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
   P->mults = (int64_t)hs.mults;
   const int64_t* bo = P->binoff_h;
   // columns with more than single_part_max products get row-block counts
-  const int64_t multi_begin = bo[0], multi_end = bo[std::min(kBinHash0 + 14 - sp_log2, kBinTiny)];
+  const int64_t multi_begin = bo[0], multi_end = bo[std::min(kBinHash0 + 14 - sp_log2, kBinMid)];
   const int64_t nmulti = multi_end - multi_begin;
   uint32_t* blkcnt = nullptr;
   if (nmulti > 0) {
@@ -2110,7 +2047,8 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
         P->A, P->B, P->bq_a0, P->bq_alen, P->mults_d, P->list, P->binoff, P->cnt, nullptr, nullptr, nullptr);
     SPX_HIP(hipGetLastError());
   }
-  for (int b = kBinHash0; b < kBinTiny; ++b) {
+  SPX_TRY(launch_mid_count(P->B, P->src, P->mults_d, P->list, bo[kBinMid], bo[kBinTiny], P->cnt, err, st));
+  for (int b = kBinHash0; b < kBinMid; ++b) {
     const int64_t nb = bo[b + 1] - bo[b];
     if (nb == 0) continue;
     const int log2s = kHashLog2Max - (b - kBinHash0);
@@ -2157,8 +2095,8 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
   // column pointers and nonempty-column offsets
   SPX_TRY(exclusive_scan(LoadI64{P->cnt}, nslots, P->off, scr, st));
   SPX_TRY(exclusive_scan(NonzeroFlag{P->cnt}, nslots, P->zoff, scr, st));
-  // parts of the non-tiny columns: list positions [0, bo[kBinTiny])
-  const int64_t npos = bo[kBinTiny];
+  // parts of the columns above the mid ones: list positions [0, bo[kBinMid])
+  const int64_t npos = bo[kBinMid];
   int64_t *np = nullptr, *poff = nullptr;
   int nslice = std::max(1, std::min(tune.xcd_slices, 64));
   int64_t slice_blocks = ceil_div(nblk, nslice);
@@ -2381,7 +2319,7 @@ extern "C" int spx_plan_get_info(const spx_plan* plan, spx_plan_info* info) {
   info->cols_tiny = bo[kBinTiny + 1] - bo[kBinTiny];
   info->cols_medium = bo[kBinTiny] - bo[kBinHash0];
   info->cols_heavy = bo[kBinHash0] - bo[0];
-  info->heavy_parts = P->nparts;
+  info->heavy_parts = P->nparts + bo[kBinTiny] - bo[kBinMid];  // a mid column is one part
   info->nnz_tiny = P->nnz_tiny;
   info->nnz_multi = P->nnz_multi;
   info->multi_parts = P->psplit;
