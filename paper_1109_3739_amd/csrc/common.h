@@ -110,7 +110,7 @@ int device_cu_count();
 int fill_i64(int64_t* p, int64_t n, int64_t v, hipStream_t stream);
 int fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t stream);
 // Zeroes up to kMaxZeroRuns runs of 8-byte words with one launch.
-constexpr int kMaxZeroRuns = 8;
+constexpr int kMaxZeroRuns = 10;
 struct ZeroRun {
   void* p;
   int64_t words;

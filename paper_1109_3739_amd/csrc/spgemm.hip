@@ -69,18 +69,17 @@ __device__ __forceinline__ int bin_of(int64_t mu, const BinCfg& c) {
 }
 
 // ------------------------------------------------------------------ kernels: setup
-// For every stored B(k,j): where column k of A starts, how long it is, and
-// its row of the split table (-1 for short columns).
-__global__ void k_rowinfo(Operand A, Operand B, const int64_t* aux, int64_t chunk, const int64_t* sid_off,
-                          int64_t* bq_a0, int32_t* bq_alen, int32_t* bq_split, unsigned* err) {
+// For every stored B(k,j): where column k of A starts and how long it is.
+__global__ void k_rowinfo(Operand A, Operand B, const int64_t* aux, int64_t chunk, int64_t* bq_a0, int32_t* bq_alen,
+                          unsigned* err) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < B.nnz; q += stride) {
     const int32_t k = B.ir[q];
-    int64_t a0 = 0, a1 = 0, slot = -1;
+    int64_t a0 = 0, a1 = 0;
     if (k < 0 || k >= A.n) {
       atomicOr(err, 1u);
     } else {
-      slot = column_slot(A, aux, chunk, k);
+      const int64_t slot = column_slot(A, aux, chunk, k);
       if (slot >= 0) {
         a0 = load_ptr(A.cp, A.ptr_t, slot);
         a1 = load_ptr(A.cp, A.ptr_t, slot + 1);
@@ -88,28 +87,124 @@ __global__ void k_rowinfo(Operand A, Operand B, const int64_t* aux, int64_t chun
     }
     bq_a0[q] = a0;
     bq_alen[q] = (int32_t)(a1 - a0);
-    bq_split[q] = (sid_off && a1 - a0 > kSplitMin) ? (int32_t)sid_off[slot] : -1;
   }
 }
 
-// Split table of the long columns of A (see ProdSrc).
-struct LongColumn {
-  Operand A;
-  __device__ int64_t operator()(int64_t k) const { return slot_begin(A, k + 1) - slot_begin(A, k) > kSplitMin; }
+// Split table (see ProdSrc): rows are made only for the long columns of A that
+// some column with row-block counts names, since only parts and row chunks read
+// them.  A product without such columns makes no table (a restriction of R-MAT
+// scale 23 wrote 1 GB of rows for all its long columns in 0.81 ms, and reads few
+// of them).
+//   k_split_mark:    flags the columns of A named by the B entries of those
+//                    columns.  Groups of 16 lanes take one column each; columns
+//                    with more than kLongSlot B entries (the list longs, made by
+//                    k_slot_mults) are shared by kLongShare workgroups each.
+//   k_split_rows:    after a scan of the flags, numbers the flagged columns
+//                    (flag[k] becomes row + 1, 0: none) and lists them.
+//   k_split_assign:  notes the row at every B entry of those columns, or at all
+//                    entries of B (flat) where such columns are not rare: a flat
+//                    pass has no chain of list, pointer and entry loads.
+constexpr int64_t kLongSlot = 256;
+constexpr int kLongShare = 16;
+
+// Calls f(q) for the B entries of the columns list[multi_begin, multi_end)
+// with at most kLongSlot entries (workgroups below short_blocks), and of all
+// columns in longs (the others, a multiple of kLongShare).
+template <class F>
+__device__ __forceinline__ void for_multi_entries(const Operand& B, const int32_t* list, int64_t multi_begin,
+                                                  int64_t multi_end, const int32_t* longs, int64_t nlong,
+                                                  unsigned short_blocks, F&& f) {
+  if (blockIdx.x < short_blocks) {
+    constexpr int G = 16;
+    const int gl = lane_id() & (G - 1);
+    const int64_t grp = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / G;
+    const int64_t ngrp = (int64_t)short_blocks * blockDim.x / G;
+    for (int64_t pos = multi_begin + grp; pos < multi_end; pos += ngrp) {
+      const int32_t t = list[pos];
+      const int64_t b0 = slot_begin(B, t), b1 = slot_begin(B, t + 1);
+      if (b1 - b0 > kLongSlot) continue;
+      for (int64_t q = b0 + gl; q < b1; q += 4 * G) f(q, G, b1);
+    }
+  } else {
+    const unsigned lb = blockIdx.x - short_blocks, nlb = gridDim.x - short_blocks;
+    for (int64_t i = lb / kLongShare; i < nlong; i += nlb / kLongShare) {
+      const int32_t t = longs[i];
+      const int64_t b0 = slot_begin(B, t), b1 = slot_begin(B, t + 1);
+      const int64_t step = (int64_t)kLongShare * blockDim.x;
+      for (int64_t q = b0 + (int64_t)(lb % kLongShare) * blockDim.x + threadIdx.x; q < b1; q += 4 * step) f(q, step, b1);
+    }
+  }
+}
+
+__global__ void __launch_bounds__(256) k_split_mark(Operand A, Operand B, const int64_t* aux, int64_t chunk,
+                                                    const int32_t* list, int64_t multi_begin, int64_t multi_end,
+                                                    const int32_t* longs, const unsigned long long* nlong,
+                                                    unsigned short_blocks, const int32_t* bq_alen, int32_t* flag) {
+  for_multi_entries(B, list, multi_begin, multi_end, longs, (int64_t)*nlong, short_blocks,
+                    [&](int64_t q, int64_t step, int64_t end) {  // four entries in flight
+    int32_t al[4], k[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t x = q + u * step;
+      al[u] = x < end ? bq_alen[x] : 0;
+      k[u] = x < end ? B.ir[x] : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (al[u] > kSplitMin) flag[column_slot(A, aux, chunk, k[u])] = 1;  // longer than zero, so it is stored
+  });
+}
+
+struct LoadFlag {
+  const int32_t* p;
+  __device__ int64_t operator()(int64_t i) const { return (int64_t)p[i]; }
 };
 
-__global__ void k_split_rows(Operand A, int64_t nslots, const int64_t* sid_off, int32_t* slot_of_split) {
+__global__ void k_split_rows(int64_t nslots, const int64_t* sid_off, int32_t* flag, int32_t* slot_of_split) {
   for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < nslots; k += (int64_t)gridDim.x * blockDim.x)
-    if (slot_begin(A, k + 1) - slot_begin(A, k) > kSplitMin) slot_of_split[sid_off[k]] = (int32_t)k;
+    if (flag[k]) {
+      const int32_t sid = (int32_t)sid_off[k];
+      slot_of_split[sid] = (int32_t)k;
+      flag[k] = sid + 1;
+    }
+}
+
+__global__ void __launch_bounds__(256) k_split_assign(Operand A, Operand B, const int64_t* aux, int64_t chunk,
+                                                      const int32_t* list, int64_t multi_begin, int64_t multi_end,
+                                                      const int32_t* longs, const unsigned long long* nlong,
+                                                      unsigned short_blocks, int flat, const int32_t* bq_alen,
+                                                      const int32_t* flag, int32_t* bq_split) {
+  auto four = [&](int64_t q, int64_t step, int64_t end) {
+    int32_t al[4], k[4], sid[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t x = q + u * step;
+      al[u] = x < end ? bq_alen[x] : 0;
+      k[u] = x < end ? B.ir[x] : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) sid[u] = al[u] > kSplitMin ? flag[column_slot(A, aux, chunk, k[u])] - 1 : -1;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (q + u * step < end) bq_split[q + u * step] = sid[u];
+  };
+  if (flat) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < B.nnz; q += 4 * stride) four(q, stride, B.nnz);
+  } else {
+    for_multi_entries(B, list, multi_begin, multi_end, longs, (int64_t)*nlong, short_blocks, four);
+  }
 }
 
 // Row of the split table of one long column: entry b (< sstride - 1) is the
 // first position whose row lies in row block b or later, the last entry the
 // column length.  One wave per column walks its rows once: the entry at
 // position e fills the blocks after its predecessor's block up to its own.
-__global__ void k_split_fill(Operand A, const int64_t* nsplit_d, int64_t cap, const int32_t* slot_of_split,
+// Very long columns are searched instead, a lane per block: the walk of R-MAT
+// scale 23's longest column (1600 rounds of a wave) took 0.58 ms.
+__global__ void k_split_fill(Operand A, const int64_t* nsplit_d, const int32_t* slot_of_split,
                              int32_t* splits, int32_t sstride, int32_t rbshift) {
-  const int64_t nsplit = *nsplit_d < cap ? *nsplit_d : cap;
+  const int64_t nsplit = *nsplit_d;
   const int lane = lane_id();
   const int64_t w0 = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave;
   const int64_t nw = (int64_t)gridDim.x * blockDim.x / kWave;
@@ -119,6 +214,23 @@ __global__ void k_split_fill(Operand A, const int64_t* nsplit_d, int64_t cap, co
     const int32_t al = (int32_t)(slot_begin(A, k + 1) - a0);
     const int32_t* col = A.ir + a0;
     int32_t* out = splits + sidx * sstride;
+    // rounds of the walk against dependent loads of the searches
+    const int32_t searches = (sstride + kWave - 1) / kWave * (floor_log2_u64((uint64_t)al) + 1);
+    if (al / kWave > 2 * searches) {
+      for (int32_t b = lane; b < sstride; b += kWave) {
+        int32_t lo = 0, hi = al;
+        if (b == sstride - 1) lo = al;
+        while (lo < hi) {
+          const int32_t mid = (int32_t)(((uint32_t)lo + (uint32_t)hi) >> 1);
+          if ((col[mid] >> rbshift) < b)
+            lo = mid + 1;
+          else
+            hi = mid;
+        }
+        out[b] = lo;
+      }
+      continue;
+    }
     for (int32_t e = lane; e < al; e += kWave) {
       const int32_t cur = col[e] >> rbshift;
       const int32_t prev = e == 0 ? -1 : (col[e - 1] >> rbshift);
@@ -131,10 +243,17 @@ __global__ void k_split_fill(Operand A, const int64_t* nsplit_d, int64_t cap, co
 
 // mults[t] = number of multiplications of output column (slot) t.  Groups
 // of 8 lanes take one slot each (most columns hold a few B entries); slots
-// with more than kLongSlot entries are listed for whole waves instead
+// with more than kLongSlot entries are listed and take a workgroup each
 // (k_slot_mults_long), so a long column holds up no group.  The total goes
 // to *total with one atomic per workgroup.
-constexpr int64_t kLongSlot = 512;
+// Device totals spread over kSpread counters, one per 128-byte line: a single
+// counter serialises the workgroups' atomics at about 10 ns each (31 us for
+// 3126 workgroups).  k_cnt_apply adds them up.
+constexpr int kSpread = 16;
+constexpr int kSpreadWords = kSpread * 16;
+__device__ __forceinline__ unsigned long long* spread(unsigned long long* total) {
+  return total + (blockIdx.x % kSpread) * 16;
+}
 
 __device__ __forceinline__ void add_total(int64_t acc, bool mine, unsigned long long* total) {
   __shared__ unsigned long long s_acc;
@@ -142,11 +261,12 @@ __device__ __forceinline__ void add_total(int64_t acc, bool mine, unsigned long 
   __syncthreads();
   if (mine && acc) atomicAdd(&s_acc, (unsigned long long)acc);
   __syncthreads();
-  if (threadIdx.x == 0 && s_acc) atomicAdd(total, s_acc);
+  if (threadIdx.x == 0 && s_acc) atomicAdd(spread(total), s_acc);
 }
 
-__global__ void k_slot_mults(Operand B, const int32_t* bq_alen, int64_t nslots, int64_t* mults,
-                             unsigned long long* total, int32_t* longs, unsigned long long* nlong) {
+__global__ void __launch_bounds__(256) k_slot_mults(Operand B, const int32_t* bq_alen, int64_t nslots, int64_t* mults,
+                                                    unsigned long long* total, int32_t* longs,
+                                                    unsigned long long* nlong) {
   constexpr int G = 8;
   const int gl = lane_id() & (G - 1);
   const int64_t grp = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / G;
@@ -159,7 +279,12 @@ __global__ void k_slot_mults(Operand B, const int32_t* bq_alen, int64_t nslots, 
       continue;
     }
     int64_t s = 0;
-    for (int64_t q = b0 + gl; q < b1; q += G) s += bq_alen[q];
+    for (int64_t q = b0 + gl; q < b1; q += 4 * G) {
+      int32_t v[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = q + k * G < b1 ? bq_alen[q + k * G] : 0;
+      s += (int64_t)v[0] + v[1] + v[2] + v[3];
+    }
 #pragma unroll
     for (int d = 1; d < G; d <<= 1) s += __shfl_xor(s, d, G);
     if (gl == 0) {
@@ -170,25 +295,35 @@ __global__ void k_slot_mults(Operand B, const int32_t* bq_alen, int64_t nslots, 
   add_total(acc, gl == 0, total);
 }
 
-__global__ void k_slot_mults_long(Operand B, const int32_t* bq_alen, const int32_t* longs,
-                                  const unsigned long long* nlong, int64_t* mults, unsigned long long* total) {
-  const int lane = lane_id();
+// Four loads in flight per thread: the longest column of R-MAT scale 20 (23,516
+// entries) took 89 us on one wave.
+__global__ void __launch_bounds__(256) k_slot_mults_long(Operand B, const int32_t* bq_alen, const int32_t* longs,
+                                                         const unsigned long long* nlong, int64_t* mults,
+                                                         unsigned long long* total) {
+  __shared__ int64_t red[4];
   const int64_t n = (int64_t)*nlong;
-  const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave;
-  const int64_t nwaves = (int64_t)gridDim.x * blockDim.x / kWave;
   int64_t acc = 0;
-  for (int64_t i = wave; i < n; i += nwaves) {
+  for (int64_t i = blockIdx.x; i < n; i += gridDim.x) {
     const int32_t t = longs[i];
     const int64_t b0 = slot_begin(B, t), b1 = slot_begin(B, t + 1);
     int64_t s = 0;
-    for (int64_t q = b0 + lane; q < b1; q += kWave) s += bq_alen[q];
+    for (int64_t q = b0 + threadIdx.x; q < b1; q += 4 * 256) {
+      int32_t v[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = q + k * 256 < b1 ? bq_alen[q + k * 256] : 0;
+      s += (int64_t)v[0] + v[1] + v[2] + v[3];
+    }
     s = wave_sum(s);
-    if (lane == 0) {
+    if (lane_id() == 0) red[threadIdx.x / kWave] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      s = red[0] + red[1] + red[2] + red[3];
       mults[t] = s;
       acc += s;
     }
+    __syncthreads();
   }
-  add_total(acc, lane == 0, total);
+  if (threadIdx.x == 0 && acc) atomicAdd(spread(total), (unsigned long long)acc);
 }
 
 // Counting sort of slots into bins: histogram, offsets, fill.
@@ -804,62 +939,67 @@ __global__ void __launch_bounds__(256) k_tiny(Operand A, Operand B, const int64_
 // ------------------------------------------------------------------ count: hash
 // One workgroup per column; key-only open-addressing table of 2^log2s
 // slots (at least twice the number of products).  Columns listed before
-// position `multi_end` also get their distinct rows counted per row block.
+// position `multi_end` also get their distinct rows counted per row block, as
+// they are inserted.  (A pass over the table for these counts, and clearing it
+// word by word, took longer than the insertions: at 8192 products each thread
+// handles 16 products but 32 slots.)
+constexpr int kCountLds = 6912;  // static LDS of the count kernels, rounded up
+
 __global__ void k_count_hash(Operand B, ProdSrc S, const int64_t* mults,
-                             const int32_t* list, const int64_t* binoff, int bin, int log2s, int64_t multi_end,
+                             const int32_t* list, int64_t beg, int64_t end, int64_t multi_begin, int64_t multi_end,
                              int rbshift, int64_t nblk, uint32_t* blkcnt, int64_t* cnt, unsigned* err) {
   extern __shared__ __align__(16) unsigned char lds[];
   uint32_t* keys = (uint32_t*)lds;
-  const uint32_t TS = 1u << log2s;
-  uint32_t* lblk = keys + TS;  // per-block counters when they fit
   __shared__ int64_t red[1024 / kWave + 1];
   __shared__ RangeLds s_rng;
-  const int64_t beg = binoff[bin], end = binoff[bin + 1];
   for (int64_t pos = beg + blockIdx.x; pos < end; pos += gridDim.x) {
     const int32_t t = list[pos];
+    const int log2s = std::max(ceil_log2_u64((uint64_t)mults[t]) + 1, kHashLog2Min);  // as bin_of
+    const uint32_t TS = 1u << log2s;
+    uint32_t* lblk = keys + TS;  // per-block counters when they fit
     const int64_t b0 = slot_begin(B, t), b1 = slot_begin(B, t + 1);
     const bool want_blk = pos < multi_end;
     const bool lds_blk = nblk <= 1024;
-    for (uint32_t i = threadIdx.x; i < TS; i += blockDim.x) keys[i] = 0xffffffffu;
+    uint32_t* dst = blkcnt + (pos - multi_begin) * nblk;  // zero (used with want_blk only)
+    uint32_t* blk = lds_blk ? lblk : dst;
+    for (uint32_t i = threadIdx.x; i < TS / 4; i += blockDim.x)
+      reinterpret_cast<uint4*>(keys)[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
     if (want_blk && lds_blk)
       for (int64_t i = threadIdx.x; i < nblk; i += blockDim.x) lblk[i] = 0;
     __syncthreads();
     int64_t mine = 0;
-    block_products<4, int, false, false, false, true>(S, nullptr, nullptr, b0, b1, 0, 0, true, s_rng, red, nullptr,
-                                                      each_product<4>([&](int32_t r, int, int) {
-      if (r < 0) return;
-      uint32_t h = hash_row(r, log2s);
-      for (uint32_t probe = 0; probe < TS; ++probe) {
-        const uint32_t old = atomicCAS(&keys[h], 0xffffffffu, (uint32_t)r);
-        if (old == 0xffffffffu) {
-          ++mine;
-          return;
-        }
-        if (old == (uint32_t)r) return;
-        h = (h + 1) & (TS - 1);
-      }
-      atomicOr(err, 2u);
-    }));
+    block_products<4, int, false, false, false, true>(
+        S, nullptr, nullptr, b0, b1, 0, 0, true, s_rng, red, nullptr,
+        [&](const int32_t(&r)[4], const int(&)[4], const int(&)[4]) {
+          // first probes of the four windows together
+          uint32_t h[4], old[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            h[u] = hash_row(r[u], log2s);
+            old[u] = r[u] >= 0 ? atomicCAS(&keys[h[u]], ~0u, (uint32_t)r[u]) : (uint32_t)r[u];
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            for (uint32_t probe = 1; old[u] != ~0u && old[u] != (uint32_t)r[u]; ++probe) {
+              if (probe >= TS) {
+                atomicOr(err, 2u);
+                break;
+              }
+              h[u] = (h[u] + 1) & (TS - 1);
+              old[u] = atomicCAS(&keys[h[u]], ~0u, (uint32_t)r[u]);
+            }
+            if (r[u] >= 0 && old[u] == ~0u) {
+              ++mine;
+              if (want_blk) atomicAdd(&blk[r[u] >> rbshift], 1u);
+            }
+          }
+        });
     __syncthreads();
     int64_t total;
     block_excl_scan1(mine, red, &total);
     if (threadIdx.x == 0) cnt[t] = total;
-    if (want_blk) {
-      uint32_t* dst = blkcnt + (pos - binoff[0]) * nblk;
-      for (uint32_t i = threadIdx.x; i < TS; i += blockDim.x) {
-        const uint32_t key = keys[i];
-        if (key != 0xffffffffu) {
-          if (lds_blk)
-            atomicAdd(&lblk[key >> rbshift], 1u);
-          else
-            atomicAdd(&dst[key >> rbshift], 1u);
-        }
-      }
-      if (lds_blk) {
-        __syncthreads();
-        for (int64_t i = threadIdx.x; i < nblk; i += blockDim.x) dst[i] = lblk[i];
-      }
-    }
+    if (want_blk && lds_blk)
+      for (int64_t i = threadIdx.x; i < nblk; i += blockDim.x) dst[i] = lblk[i];
     __syncthreads();
   }
 }
@@ -878,7 +1018,7 @@ __global__ void k_count_bitmap(Operand B, ProdSrc S, const int64_t* mults, const
   const int blk_per_chunk = (int)(chunk_rows >> rbshift);
   uint32_t* lblk = bm + (chunk_rows >> 5);
   __shared__ int64_t red[1024 / kWave + 1];
-  __shared__ RangeLds s_rng;
+  __shared__ RangeLdsT<kQChunkWide> s_rng;  // heavy columns have many B entries
   const int64_t beg = binoff[0], end = binoff[kBinHash0];
   const int64_t ncols = end - beg;
   // workgroup w works on row chunk w mod nchunks (the grid is a multiple of
@@ -978,12 +1118,12 @@ struct PartCfg {
   int64_t nblk;
   int64_t slice_blocks;  // row blocks per slice (parts never straddle slices); 0: one slice
   int32_t nslice;
-  int32_t pad;
+  int32_t hash_max;  // most outputs of a hash-mode part that fits L (0: none)
 };
 
 __device__ __forceinline__ int64_t bitmap_bytes(const PartCfg& p, int64_t span, int64_t c) {
-  const int64_t w = (span + 63) >> 6;
-  return w * 8 + ((w * 2 + 7) & ~7ll) + c * (p.sz > 4 ? p.sz : 4) + 64;
+  const int32_t w = (int32_t)((span + 63) >> 6);  // below 2^25
+  return (int64_t)w * 8 + ((w * 2 + 7) & ~7) + c * (p.sz > 4 ? p.sz : 4) + 64;
 }
 __device__ __forceinline__ bool bitmap_ok(const PartCfg& p, int64_t span, int64_t c) {
   return c < 65536 && bitmap_bytes(p, span, c) <= p.L;
@@ -991,13 +1131,11 @@ __device__ __forceinline__ bool bitmap_ok(const PartCfg& p, int64_t span, int64_
 // Rows a hash-mode part may span for the two-level rank (longer: sorted).
 constexpr int64_t kRankSpan = 1ll << 20;
 
-__device__ __forceinline__ int64_t hash_bytes(const PartCfg& p, int64_t c) {
-  int64_t p2 = 64;
-  while (p2 < c) p2 <<= 1;
+__host__ __device__ inline int64_t hash_bytes(int64_t p2, int64_t sz) {  // p2: a power of two, at least 64
   const int64_t S = 2 * p2;
-  return S * 4 + ((S * p.sz + 7) & ~7ll) + p2 * 10 + (kRankSpan >> 9) + (kRankSpan >> 11) + 64;
+  return S * 4 + ((S * sz + 7) & ~7ll) + p2 * 10 + (kRankSpan >> 9) + (kRankSpan >> 11) + 64;
 }
-__device__ __forceinline__ bool hash_ok(const PartCfg& p, int64_t c) { return hash_bytes(p, c) <= p.L; }
+__device__ __forceinline__ bool hash_ok(const PartCfg& p, int64_t c) { return c <= p.hash_max; }
 
 __device__ __forceinline__ int choose_mode(const PartCfg& p, int64_t span, int64_t c) {
   const bool bok = bitmap_ok(p, span, c), hok = hash_ok(p, c);
@@ -1010,46 +1148,55 @@ __device__ __forceinline__ int choose_mode(const PartCfg& p, int64_t span, int64
   return bok ? 0 : 1;
 }
 
-// Walks the row blocks of one multi-part column greedily: a part grows while
-// it still fits the LDS budget in one of the two modes.  With emit == false
-// only counts parts.
-__device__ int64_t cut_parts(const PartCfg& p, const uint32_t* blk, int32_t t, int64_t base_off, bool emit, Part* out,
-                             int32_t bmi, int64_t b0, int32_t nb, unsigned* err) {
+// Cuts one column into parts, greedily over its row blocks: a part grows while
+// it still fits the LDS budget in one of the two modes.  One wave: its lanes
+// test 64 ends of the part at once (whether a part fits only changes from yes
+// to no as it grows).  blk: the column's row-block counts, in LDS or global
+// memory; with PREF, their inclusive prefix sums.  Returns the number of parts;
+// writes them if out is given.
+template <bool PREF>
+__device__ int64_t cut_parts(const PartCfg& p, const uint32_t* blk, int32_t t, int64_t base_off, Part* out, int32_t bmi,
+                             int64_t b0, int32_t nb, unsigned* err) {
   const int64_t RB = 1ll << p.rbshift;
+  const int lane = lane_id();
+  const int32_t nblk = (int32_t)p.nblk, sb = (int32_t)p.slice_blocks;
   int64_t np = 0, run = 0;
-  int64_t b = 0;
-  while (b < p.nblk) {
-    int64_t c = blk[b];
-    int64_t e = b + 1;
-    while (e < p.nblk) {
-      if (p.slice_blocks && e % p.slice_blocks == 0) break;
-      const int64_t c2 = c + blk[e];
-      const int64_t r1 = (e + 1) * RB < p.m ? (e + 1) * RB : p.m;
-      const int64_t span2 = r1 - b * RB;
-      if (bitmap_ok(p, span2, c2) || hash_ok(p, c2)) {
-        c = c2;
-        ++e;
-      } else {
-        break;
-      }
+  uint32_t before = 0;  // outputs of row blocks [0, b)
+  for (int32_t b = 0; b < nblk;) {
+    uint32_t c = 0;  // outputs of row blocks [b, e)
+    int32_t e = b;
+    for (int f = kWave; f == kWave;) {
+      const int32_t i = e + lane;
+      const uint32_t x = i < nblk ? blk[i] : 0;
+      const uint32_t ci = PREF ? x - before : c + (uint32_t)wave_incl_scan((int32_t)x);
+      const int64_t r1 = (i + 1) * RB < p.m ? (i + 1) * RB : p.m;
+      const bool fits = i < nblk && (i == b || (!(sb && i % sb == 0) &&
+                                                (ci <= (uint32_t)p.hash_max || bitmap_ok(p, r1 - b * RB, ci))));
+      const uint64_t no = __ballot(!fits);
+      f = no ? __ffsll((long long)no) - 1 : kWave;
+      if (f > 0) c = (uint32_t)__builtin_amdgcn_readlane((int)ci, f - 1);
+      e += f;
     }
+    before += c;
     if (c > 0) {
       const int64_t r0 = b * RB;
       const int64_t r1 = e * RB < p.m ? e * RB : p.m;
-      if (!bitmap_ok(p, r1 - r0, c) && !hash_ok(p, c)) atomicOr(err, 4u);
-      if (emit) {
-        Part P;
-        P.off = base_off + run;
-        P.t = t;
-        P.c = (int32_t)c;
-        P.r0 = (int32_t)r0;
-        P.r1 = (int32_t)r1;
-        P.mode = choose_mode(p, r1 - r0, c);
-        P.slice = p.slice_blocks ? (int32_t)(b / p.slice_blocks) : 0;
-        P.bmi = bmi;
-        P.b0 = b0;
-        P.nb = nb;
-        out[np] = P;
+      if (lane == 0) {
+        if (!bitmap_ok(p, r1 - r0, c) && !hash_ok(p, c)) atomicOr(err, 4u);
+        if (out) {
+          Part P;
+          P.off = base_off + run;
+          P.t = t;
+          P.c = (int32_t)c;
+          P.r0 = (int32_t)r0;
+          P.r1 = (int32_t)r1;
+          P.mode = choose_mode(p, r1 - r0, c);
+          P.slice = p.slice_blocks ? (int32_t)(b / p.slice_blocks) : 0;
+          P.bmi = bmi;
+          P.b0 = b0;
+          P.nb = nb;
+          out[np] = P;
+        }
       }
       ++np;
       run += c;
@@ -1060,52 +1207,84 @@ __device__ int64_t cut_parts(const PartCfg& p, const uint32_t* blk, int32_t t, i
 }
 
 // Number of parts of every column above the mid ones (list positions
-// [0, npos)), or the parts themselves (emit).
+// [0, npos)), or the parts themselves (parts given).  The first cut_blocks
+// workgroups take the columns with row-block counts, a wave each with the
+// counts in LDS (a thread each, walking them one by one in memory, took 0.21 ms
+// on R-MAT scale 20, and 57 us on 128 long columns); the others the rest, a
+// thread each.
 // In the counting pass, setup_acc (if given) receives the sums over the cut
 // columns of (B entries x parts) and of their multiplications, which tell
 // how many range set-ups the multi-part launch makes per product.
-__global__ void k_parts(Operand B, PartCfg p, PartCfg ps, const int32_t* list, int64_t npos, int64_t multi_begin, int64_t multi_end,
-                        int64_t nbm, const int64_t* cnt, const int64_t* off, const uint32_t* blkcnt,
-                        int64_t* nparts, const int64_t* poff, Part* parts, const int64_t* mults,
-                        unsigned long long* setup_acc, unsigned* err) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  const bool emit = parts != nullptr;
+constexpr int kCutBlk = 1024;  // row blocks held in LDS (more are read from memory)
+
+__global__ void __launch_bounds__(256) k_parts(Operand B, PartCfg p, PartCfg ps, const int32_t* list, int64_t npos,
+                                               int64_t multi_begin, int64_t multi_end, unsigned cut_blocks, int64_t nbm,
+                                               const int64_t* cnt, const int64_t* off, const uint32_t* blkcnt,
+                                               int64_t* nparts, const int64_t* poff, Part* parts, const int64_t* mults,
+                                               unsigned long long* setup_acc, unsigned* err) {
+  __shared__ uint32_t s_blk[4][kCutBlk];  // prefix sums of the counts
   unsigned long long my_setup = 0, my_mults = 0;
-  for (int64_t pos = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; pos < npos; pos += stride) {
-    const int32_t t = list[pos];
-    const int64_t c = cnt[t];
-    int64_t np;
-    if (c == 0) {
-      np = 0;
-    } else if (pos >= multi_begin && pos < multi_end && !(bitmap_ok(p, p.m, c) || hash_ok(p, c))) {
-      const int64_t cb0 = slot_begin(B, t);
-      np = cut_parts(p, blkcnt + (pos - multi_begin) * p.nblk, t, off[t], emit, emit ? parts + poff[pos] : nullptr,
-                     pos - multi_begin < nbm ? (int32_t)(pos - multi_begin) : -1, cb0,
-                     (int32_t)(slot_begin(B, t + 1) - cb0), err);
-      if (setup_acc && np > 1) {
-        my_setup += (unsigned long long)(slot_begin(B, t + 1) - cb0) * (unsigned long long)np;
-        my_mults += (unsigned long long)mults[t];
-      }
-    } else {
-      np = 1;
-      const PartCfg& q = pos < multi_end ? p : ps;
-      if (!emit && !(bitmap_ok(q, q.m, c) || hash_ok(q, c))) atomicOr(err, 4u);
-      if (emit) {
-        Part P;
-        P.off = off[t];
-        P.t = t;
-        P.c = (int32_t)c;
-        P.r0 = 0;
-        P.r1 = (int32_t)q.m;
-        P.mode = choose_mode(q, q.m, c);
-        P.slice = q.nslice;  // full row range: any queue
-        P.bmi = pos - multi_begin < nbm ? (int32_t)(pos - multi_begin) : -1;
-        P.b0 = slot_begin(B, t);
-        P.nb = (int32_t)(slot_begin(B, t + 1) - P.b0);
-        parts[poff[pos]] = P;
-      }
+  // a column in one part
+  auto whole = [&](int64_t pos, int32_t t, int64_t c, const PartCfg& q) {
+    if (!parts) {
+      if (!(bitmap_ok(q, q.m, c) || hash_ok(q, c))) atomicOr(err, 4u);
+      return;
     }
-    if (!emit) nparts[pos] = np;
+    Part P;
+    P.off = off[t];
+    P.t = t;
+    P.c = (int32_t)c;
+    P.r0 = 0;
+    P.r1 = (int32_t)q.m;
+    P.mode = choose_mode(q, q.m, c);
+    P.slice = q.nslice;  // full row range: any queue
+    P.bmi = pos - multi_begin < nbm ? (int32_t)(pos - multi_begin) : -1;
+    P.b0 = slot_begin(B, t);
+    P.nb = (int32_t)(slot_begin(B, t + 1) - P.b0);
+    parts[poff[pos]] = P;
+  };
+  if (blockIdx.x < cut_blocks) {
+    const int w = threadIdx.x / kWave, lane = lane_id();
+    for (int64_t pos = multi_begin + (int64_t)blockIdx.x * 4 + w; pos < multi_end; pos += (int64_t)cut_blocks * 4) {
+      const int32_t t = list[pos];
+      const int64_t c = cnt[t];
+      int64_t np = c > 0;
+      if (c > 0 && !(bitmap_ok(p, p.m, c) || hash_ok(p, c))) {
+        const int64_t cb0 = slot_begin(B, t), nb = slot_begin(B, t + 1) - cb0;
+        const uint32_t* blk = blkcnt + (pos - multi_begin) * p.nblk;
+        if (p.nblk <= kCutBlk) {
+          uint32_t carry = 0;
+          for (int i0 = 0; i0 < p.nblk; i0 += kWave) {
+            const int i = i0 + lane;
+            const uint32_t s = carry + (uint32_t)wave_incl_scan(i < p.nblk ? (int32_t)blk[i] : 0);
+            if (i < p.nblk) s_blk[w][i] = s;
+            carry = (uint32_t)__builtin_amdgcn_readlane((int)s, kWave - 1);
+          }
+          wave_sync();
+        }
+        Part* out = parts ? parts + poff[pos] : nullptr;
+        const int32_t bmi = pos - multi_begin < nbm ? (int32_t)(pos - multi_begin) : -1;
+        np = p.nblk <= kCutBlk ? cut_parts<true>(p, s_blk[w], t, off[t], out, bmi, cb0, (int32_t)nb, err)
+                               : cut_parts<false>(p, blk, t, off[t], out, bmi, cb0, (int32_t)nb, err);
+        if (setup_acc && np > 1 && lane == 0) {
+          my_setup += (unsigned long long)nb * (unsigned long long)np;
+          my_mults += (unsigned long long)mults[t];
+        }
+        wave_sync();
+      } else if (c > 0 && lane == 0) {
+        whole(pos, t, c, p);
+      }
+      if (!parts && lane == 0) nparts[pos] = np;
+    }
+  } else {
+    const int64_t stride = (int64_t)(gridDim.x - cut_blocks) * blockDim.x;
+    for (int64_t pos = multi_end + (int64_t)(blockIdx.x - cut_blocks) * blockDim.x + threadIdx.x; pos < npos;
+         pos += stride) {
+      const int32_t t = list[pos];
+      const int64_t c = cnt[t];
+      if (c > 0) whole(pos, t, c, ps);
+      if (!parts) nparts[pos] = c > 0;
+    }
   }
   if (setup_acc) {  // one pair of atomics per workgroup
     __shared__ unsigned long long s_acc[2];
@@ -1262,6 +1441,7 @@ struct LoadBucket {
 // scale 14: 176 parts on 44 of 176 workgroups, 172 us; scale 20 has 1900 parts
 // per workgroup and keeps four, which save ticket round trips).
 constexpr int kPartBatch = 4;
+constexpr int kMaxQueues = 65;  // of the multi-part launch: at most 64 row slices and a shared queue
 
 template <typename T>
 __device__ __forceinline__ void block_bitonic_sort(uint64_t* a, int n2) {
@@ -1290,7 +1470,8 @@ template <int SR, typename T, int QC, bool OFF32>
 __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, ProdSrc S,
                                                         const int64_t* mults,
                                                         const int64_t* cnt, const Part* parts, const int64_t* qoff,
-                                                        int nq, int nhome, int batch, unsigned long long* qctr,
+                                                        int64_t plo, int64_t phi, int nq, int nhome, int batch,
+                                                        unsigned long long* qctr,
                                                         const uint64_t* gbm, int64_t gbm_words,
                                                         const int32_t* qlist, int32_t* cir, T* cnum, unsigned* err) {
   using SR_ = Semiring<SR, T>;
@@ -1304,7 +1485,8 @@ __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, Pr
   __shared__ RangeLdsT<QC> s_rng;
   const T* an = (const T*)A.num;
   const T* bn = (const T*)B.num;
-  // work queues: queue k holds parts [qoff[k], qoff[k+1]); a workgroup
+  // work queues: queue k holds parts [qoff[k], qoff[k+1]) (without qoff: one
+  // queue of [plo, phi), its bounds passed by value); a workgroup
   // starts with its home queue (blockIdx.x % nhome: workgroups are placed on
   // the XCDs round robin, so one queue's rows of A stay in one L2), then
   // takes the shared queue nq-1, then helps the others.
@@ -1318,10 +1500,11 @@ __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, Pr
       int nbat = 0;
       while (qi < nq) {
         const int q = qi == 0 ? home : (qi == 1 ? nq - 1 : (home + qi - 1) % (nq - 1));
-        const int64_t first = qoff[q] + (int64_t)atomicAdd(&qctr[q], (unsigned long long)batch);
-        if (first < qoff[q + 1]) {
+        const int64_t qlo = qoff ? qoff[q] : plo, qhi = qoff ? qoff[q + 1] : phi;
+        const int64_t first = qlo + (int64_t)atomicAdd(&qctr[q], (unsigned long long)batch);
+        if (first < qhi) {
           got = first;
-          nbat = (int)(qoff[q + 1] - first < batch ? qoff[q + 1] - first : batch);
+          nbat = (int)(qhi - first < batch ? qhi - first : batch);
           break;
         }
         ++qi;
@@ -1571,17 +1754,16 @@ __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, Pr
 }
 
 // ------------------------------------------------------------------ output pointers
-__global__ void k_nonzero_flags_count(const int64_t* cnt, int64_t n, unsigned long long* nz) {
-  int64_t s = 0;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += stride) s += cnt[i] > 0;
-  s = wave_sum(s);
-  if (lane_id() == 0 && s) atomicAdd(nz, (unsigned long long)s);
-}
-
 // CSC output: cp[j] = start of column j.  For a DCSC B, column j's start is
 // the offset of the first slot whose column id is >= j.
-__global__ void k_write_csc_cp(Operand B, const int64_t* off, int64_t nslots, int64_t n, void* cp, int32_t ptr_t) {
+// Clears the exec's queue counters for the plan's next exec.
+__device__ __forceinline__ void reset_queues(unsigned long long* qctr) {
+  if (blockIdx.x == 0 && threadIdx.x <= kMaxQueues) qctr[threadIdx.x] = 0;
+}
+
+__global__ void k_write_csc_cp(Operand B, const int64_t* off, int64_t nslots, int64_t n, void* cp, int32_t ptr_t,
+                               unsigned long long* qctr) {
+  reset_queues(qctr);
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j <= n; j += stride) {
     int64_t t = j;
@@ -1602,7 +1784,8 @@ __global__ void k_write_csc_cp(Operand B, const int64_t* off, int64_t nslots, in
 
 // DCSC output: nonempty slot t becomes entry zoff[t] of jc / cp.
 __global__ void k_write_dcsc(Operand B, const int64_t* cnt, const int64_t* off, const int64_t* zoff, int64_t nslots,
-                             int32_t* jc, void* cp, int32_t ptr_t) {
+                             int32_t* jc, void* cp, int32_t ptr_t, unsigned long long* qctr) {
+  reset_queues(qctr);
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < nslots; t += stride) {
     if (cnt[t] > 0) {
@@ -1614,15 +1797,88 @@ __global__ void k_write_dcsc(Operand B, const int64_t* cnt, const int64_t* off, 
   }
 }
 
-// Sum of the exact counts of the columns in bin `bin`.
-__global__ void k_bin_sum(const int32_t* list, const int64_t* binoff, int bin, const int64_t* cnt,
-                          unsigned long long* out) {
-  const int64_t beg = binoff[bin], end = binoff[bin + 1];
-  int64_t s = 0;
-  for (int64_t p = beg + blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < end; p += (int64_t)gridDim.x * blockDim.x)
-    s += cnt[list[p]];
+// Column pointers from the exact counts: off = exclusive scan of cnt, zoff =
+// of the nonempty flags (DCSC output; else only its total), nnz_tiny = sum over
+// the columns of 1..tiny_max products.  One pass of block sums and one that
+// applies them, for all three results (a scan each and a sum took five launches).
+__global__ void __launch_bounds__(kScanThreads) k_cnt_reduce(const int64_t* cnt, const int64_t* mults, int64_t tiny_max,
+                                                             int64_t n, int64_t* sums, int64_t* zsums,
+                                                             unsigned long long* nnz_tiny) {
+  __shared__ int64_t red[3][kScanThreads / kWave];
+  const int64_t base = (int64_t)blockIdx.x * kScanTile;
+  int64_t s = 0, z = 0, ti = 0;
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) {
+    const int64_t i = base + (int64_t)k * kScanThreads + threadIdx.x;
+    if (i < n) {
+      const int64_t c = cnt[i];
+      s += c;
+      z += c > 0;
+      if (mults[i] <= tiny_max) ti += c;
+    }
+  }
   s = wave_sum(s);
-  if (lane_id() == 0 && s) atomicAdd(out, (unsigned long long)s);
+  z = wave_sum(z);
+  ti = wave_sum(ti);
+  const int w = threadIdx.x / kWave;
+  if (lane_id() == 0) {
+    red[0][w] = s;
+    red[1][w] = z;
+    red[2][w] = ti;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int k = 1; k < kScanThreads / kWave; ++k) {
+      s += red[0][k];
+      z += red[1][k];
+      ti += red[2][k];
+    }
+    sums[blockIdx.x] = s;
+    zsums[blockIdx.x] = z;
+    if (ti) atomicAdd(spread(nnz_tiny), (unsigned long long)ti);
+  }
+}
+
+// carry / zcarry: the scanned block sums; else sums / zsums: the block sums.
+// Also adds up the spread totals of the multiplications and of nnz_tiny.
+__global__ void __launch_bounds__(kScanThreads) k_cnt_apply(const int64_t* cnt, int64_t n, const int64_t* carry,
+                                                            const int64_t* zcarry, const int64_t* sums,
+                                                            const int64_t* zsums, int64_t* off, int64_t* zoff,
+                                                            int zfull, const unsigned long long* totals,
+                                                            unsigned long long* mults, unsigned long long* nnz_tiny) {
+  __shared__ int64_t red[kScanThreads / kWave + 1];
+  if (blockIdx.x == 0 && threadIdx.x < 2) {
+    unsigned long long s = 0;
+    for (int i = 0; i < kSpread; ++i) s += totals[threadIdx.x * kSpreadWords + i * 16];
+    *(threadIdx.x == 0 ? mults : nnz_tiny) = s;
+  }
+  const int64_t cin = carry ? carry[blockIdx.x] : carry_from_sums(sums, blockIdx.x, red);
+  const int64_t zin = zcarry ? zcarry[blockIdx.x] : carry_from_sums(zsums, blockIdx.x, red);
+  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
+  int64_t v[kScanItems];
+  int64_t s = 0, z = 0;
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) {
+    v[k] = base + k < n ? cnt[base + k] : 0;
+    s += v[k];
+    z += v[k] > 0;
+  }
+  int64_t total, ztotal;
+  int64_t run = block_excl_scan(s, red, &total) + cin;
+  int64_t zrun = block_excl_scan(z, red, &ztotal) + zin;
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) {
+    if (base + k < n) {
+      off[base + k] = run;
+      if (zfull) zoff[base + k] = zrun;
+    }
+    run += v[k];
+    zrun += v[k] > 0;
+  }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == blockDim.x - 1) {
+    off[n] = run;
+    zoff[n] = zrun;
+  }
 }
 
 __global__ void k_parts_sum(const Part* parts, int64_t n, unsigned long long* out) {
@@ -1682,11 +1938,6 @@ __global__ void k_part_scatter(const Part* in, int64_t n, unsigned long long* cu
   }
 }
 
-struct NonzeroFlag {
-  const int64_t* cnt;
-  __device__ int64_t operator()(int64_t i) const { return cnt[i] > 0 ? 1 : 0; }
-};
-
 }  // namespace spx
 
 // ==================================================================== host
@@ -1741,11 +1992,11 @@ struct GemmPlan : spx_plan {
   int32_t* list = nullptr;
   int64_t* binoff = nullptr;
   Part* parts = nullptr;
-  int64_t* qoff_multi = nullptr;
+  int64_t* qoff_multi = nullptr;  // bounds of the multi-part launch's queues (several row slices only)
   unsigned long long* qctr = nullptr;
-  int64_t* qoff_single = nullptr;
   int32_t nq_multi = 1, nslice = 1, nslice_req = 1;
   Summary* sum = nullptr;
+  unsigned long long* totals = nullptr;  // spread counters: multiplications, entries of the tiny columns
   int64_t L = 0, L_single = 0;
   bool wide = false;  // the multi-part launch uses the wide range list
   int32_t* qlist = nullptr;  // B entries of the parts of bucketed columns, grouped by part
@@ -1777,6 +2028,35 @@ int build_aux(const Operand& X, Scratch& scr, hipStream_t st, int64_t** aux, int
   const int64_t naux = ceil_div(std::max<int64_t>(X.n, 1), *chunk);
   SPX_TRY(scr.get_n(naux + 1, aux));
   k_build_aux<<<grid_for(naux + 1, 256), 256, 0, st>>>(X.jc, X.nzc, *chunk, naux, *aux);
+  SPX_HIP(hipGetLastError());
+  return SPX_OK;
+}
+
+// Most outputs of a hash-mode part in L bytes (hash_bytes steps at the powers of two).
+static int32_t hash_most(int64_t L, int64_t sz) {
+  int64_t p2 = 32;
+  while (hash_bytes(2 * p2, sz) <= L) p2 *= 2;
+  return p2 >= 64 ? (int32_t)p2 : 0;
+}
+
+// Column pointers of C (see k_cnt_reduce).
+static int scan_counts(GemmPlan* P, Scratch& scr, hipStream_t st) {
+  const int64_t n = P->nslots;
+  if (n <= 0) return zero_words(st, {{P->off, 1}, {P->zoff, 1}});
+  const int64_t nb = ceil_div(n, kScanTile);
+  int64_t *sums = nullptr, *zsums = nullptr, *carry = nullptr, *zcarry = nullptr;
+  SPX_TRY(scr.get_many({Scratch::part(&sums, nb), Scratch::part(&zsums, nb)}));
+  k_cnt_reduce<<<(unsigned)nb, kScanThreads, 0, st>>>(P->cnt, P->mults_d, P->tune.tiny_max, n, sums, zsums,
+                                                      P->totals + kSpreadWords);
+  SPX_HIP(hipGetLastError());
+  if (nb > kFusedCarry) {
+    SPX_TRY(scr.get_many({Scratch::part(&carry, nb + 1), Scratch::part(&zcarry, nb + 1)}));
+    SPX_TRY(exclusive_scan(LoadI64{sums}, nb, carry, scr, st));
+    SPX_TRY(exclusive_scan(LoadI64{zsums}, nb, zcarry, scr, st));
+  }
+  k_cnt_apply<<<(unsigned)nb, kScanThreads, 0, st>>>(P->cnt, n, carry, zcarry, sums, zsums, P->off, P->zoff,
+                                                     P->c_fmt == SPX_DCSC, P->totals, &P->sum->mults,
+                                                     &P->sum->nnz_tiny);
   SPX_HIP(hipGetLastError());
   return SPX_OK;
 }
@@ -1824,7 +2104,7 @@ static int launch_numeric(GemmPlan* P, spx_mat* C, hipStream_t st) {
   unsigned* err = &P->sum->err;
   const int cus = device_cu_count();
   // parts of multi-part columns [0, psplit), single-part columns [psplit, nparts)
-  if (P->nparts > 0) SPX_TRY(fill_i64((int64_t*)P->qctr, P->nq_multi + 2, 0, st));
+  // (the queue counters are zero: cleared by the plan, then by every exec's last launch)
   for (int r = 0; r < 2; ++r) {
     const int64_t n0 = r == 0 ? 0 : P->psplit, n1 = r == 0 ? P->psplit : P->nparts;
     if (n1 <= n0) continue;
@@ -1833,21 +2113,21 @@ static int launch_numeric(GemmPlan* P, spx_mat* C, hipStream_t st) {
     const int per_cu = (int)std::max<int64_t>(1, std::min<int64_t>((160 * 1024) / (L + 8192), 2048 / blk));
     int64_t grid = std::min<int64_t>(n1 - n0, (int64_t)cus * per_cu);
     if (r == 0 && P->nslice > 1) grid = std::max<int64_t>(P->nslice, grid / P->nslice * P->nslice);
-    const int64_t* qoff = r == 0 ? P->qoff_multi : P->qoff_single;
-    const int nq = r == 0 ? P->nq_multi : 1;
-    unsigned long long* qctr = r == 0 ? P->qctr : P->qctr + P->nq_multi;
+    const int64_t* qoff = r == 0 ? P->qoff_multi : nullptr;
+    const int nq = qoff ? P->nq_multi : 1;
+    unsigned long long* qctr = r == 0 ? P->qctr : P->qctr + kMaxQueues;
     const int batch = (int)std::max<int64_t>(1, std::min<int64_t>(kPartBatch, (n1 - n0) / (2 * grid)));
     if (r == 0 && P->wide)
       hipLaunchKernelGGL((k_numeric_parts<SR, T, kQChunkWide, false>), dim3((unsigned)grid), dim3(blk), (size_t)L, st,
-                         P->A, P->B, P->src, P->mults_d, P->cnt, P->parts, qoff, nq, P->nslice, batch, qctr, P->gbm,
+                         P->A, P->B, P->src, P->mults_d, P->cnt, P->parts, qoff, n0, n1, nq, P->nslice, batch, qctr, P->gbm,
                          P->gbm_words, P->qlist, cir, cnum, err);
     else if (P->src.off32)  // A's positions fit 29 bits: gathers through 32-bit offsets
       hipLaunchKernelGGL((k_numeric_parts<SR, T, kQChunk, true>), dim3((unsigned)grid), dim3(blk), (size_t)L, st, P->A,
-                         P->B, P->src, P->mults_d, P->cnt, P->parts, qoff, nq, r == 0 ? P->nslice : 1, batch, qctr, P->gbm,
+                         P->B, P->src, P->mults_d, P->cnt, P->parts, qoff, n0, n1, nq, r == 0 ? P->nslice : 1, batch, qctr, P->gbm,
                          P->gbm_words, P->qlist, cir, cnum, err);
     else
       hipLaunchKernelGGL((k_numeric_parts<SR, T, kQChunk, false>), dim3((unsigned)grid), dim3(blk), (size_t)L, st, P->A,
-                         P->B, P->src, P->mults_d, P->cnt, P->parts, qoff, nq, r == 0 ? P->nslice : 1, batch, qctr, P->gbm,
+                         P->B, P->src, P->mults_d, P->cnt, P->parts, qoff, n0, n1, nq, r == 0 ? P->nslice : 1, batch, qctr, P->gbm,
                          P->gbm_words, P->qlist, cir, cnum, err);
     SPX_HIP(hipGetLastError());
     if (r == 0) P->mark(kEvMulti, st);
@@ -1970,50 +2250,36 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
   unsigned long long *bincount = nullptr, *binfill = nullptr, *nlong = nullptr;
   int32_t* longs = nullptr;  // slots with more than kLongSlot B entries
   SPX_TRY(scr.get_many({Scratch::part(&P->sum, 1), Scratch::part(&P->bq_a0, B->nnz),
-                        Scratch::part(&P->bq_alen, B->nnz), Scratch::part(&P->bq_split, B->nnz),
+                        Scratch::part(&P->bq_alen, B->nnz),
                         Scratch::part(&P->mults_d, nslots), Scratch::part(&P->cnt, nslots),
                         Scratch::part(&P->off, nslots + 1), Scratch::part(&P->zoff, nslots + 1),
                         Scratch::part(&P->list, nslots), Scratch::part(&P->binoff, kNumBins + 1),
                         Scratch::part(&bincount, kNumBins), Scratch::part(&binfill, kNumBins),
-                        Scratch::part(&longs, std::max<int64_t>(nslots, 1)), Scratch::part(&nlong, 1)}));
+                        Scratch::part(&longs, std::max<int64_t>(nslots, 1)), Scratch::part(&nlong, 1),
+                        Scratch::part(&P->qctr, kMaxQueues + 1), Scratch::part(&P->totals, 2 * kSpreadWords)}));
   // bin offsets stay zero when there are no slots (k_bin_fill writes them otherwise)
   SPX_TRY(zero_words(st, {{P->sum, (int64_t)(sizeof(Summary) / 8)}, {bincount, kNumBins}, {binfill, kNumBins},
-                          {P->cnt, std::max<int64_t>(nslots, 1)}, {nlong, 1}, {P->binoff, kNumBins + 1}}));
+                          {P->cnt, std::max<int64_t>(nslots, 1)}, {nlong, 1}, {P->binoff, kNumBins + 1},
+                          {P->qctr, kMaxQueues + 1}, {P->totals, 2 * kSpreadWords}}));
   unsigned* err = &P->sum->err;
 
   // AUX index for a DCSC A
   int64_t chunk = 1;
   SPX_TRY(build_aux(P->A, scr, st, &P->aux, &chunk));
-  // split table of A's long columns
-  const int64_t nslots_a = nslots_of(P->A);
-  const int64_t split_cap = A->nnz / (kSplitMin + 1) + 1;
-  const int32_t sstride = (int32_t)nblk + 1;
-  int64_t* sid_off = nullptr;
-  if (A->nnz > kSplitMin && nslots_a > 0) {
-    int32_t* slot_of_split = nullptr;
-    SPX_TRY(scr.get_n(nslots_a + 1, &sid_off));
-    SPX_TRY(scr.get_n(split_cap, &slot_of_split));
-    SPX_TRY(scr.get_n(split_cap * sstride, &P->splits));
-    SPX_TRY(exclusive_scan(LongColumn{P->A}, nslots_a, sid_off, scr, st));
-    k_split_rows<<<grid_for(nslots_a, 256, 65536), 256, 0, st>>>(P->A, nslots_a, sid_off, slot_of_split);
-    SPX_HIP(hipGetLastError());
-    k_split_fill<<<grid_for(split_cap * kWave, 256, (int64_t)cus * 32), 256, 0, st>>>(
-        P->A, sid_off + nslots_a, split_cap, slot_of_split, P->splits, sstride, rb);
-    SPX_HIP(hipGetLastError());
-  }
   if (B->nnz > 0) {
-    k_rowinfo<<<grid_for(B->nnz, 256, (int64_t)cus * 32), 256, 0, st>>>(P->A, P->B, P->aux, chunk, sid_off, P->bq_a0,
-                                                                         P->bq_alen, P->bq_split, err);
+    k_rowinfo<<<grid_for(B->nnz, 256, (int64_t)cus * 32), 256, 0, st>>>(P->A, P->B, P->aux, chunk, P->bq_a0,
+                                                                         P->bq_alen, err);
     SPX_HIP(hipGetLastError());
   }
-  P->src = ProdSrc{A->ir, P->bq_a0, P->bq_alen, P->bq_split, P->splits, sstride, rb, (int32_t)m,
+  const int32_t sstride = (int32_t)nblk + 1;
+  P->src = ProdSrc{A->ir, P->bq_a0, P->bq_alen, nullptr, nullptr, sstride, rb, (int32_t)m,
                    (A->nnz < (1ll << 29) && !tune.force_off64) ? 1 : 0};
   BinCfg bc{tune.tiny_max, tune.hash_count_max};
   if (nslots > 0) {
     k_slot_mults<<<grid_for(nslots * 8, 256, (int64_t)cus * 16), 256, 0, st>>>(P->B, P->bq_alen, nslots, P->mults_d,
-                                                                              &P->sum->mults, longs, nlong);
+                                                                              P->totals, longs, nlong);
     SPX_HIP(hipGetLastError());
-    k_slot_mults_long<<<(unsigned)cus * 4, 256, 0, st>>>(P->B, P->bq_alen, longs, nlong, P->mults_d, &P->sum->mults);
+    k_slot_mults_long<<<(unsigned)cus * 8, 256, 0, st>>>(P->B, P->bq_alen, longs, nlong, P->mults_d, P->totals);
     SPX_HIP(hipGetLastError());
     k_bin_count<<<grid_for(nslots, 256, (int64_t)cus * 8), 256, 0, st>>>(P->mults_d, nslots, bc, bincount);
     SPX_HIP(hipGetLastError());
@@ -2028,7 +2294,6 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
   static_assert(sizeof(P->binoff_h) == (kNumBins + 1) * sizeof(int64_t), "bin offsets are read as words");
   SPX_TRY(summary_sync(P, st, &hs, {{P->binoff, 8, kNumBins + 1}}, P->binoff_h));
   if (hs.err & 1u) return fail(SPX_EINVAL, "B has a row index outside A's columns");
-  P->mults = (int64_t)hs.mults;
   const int64_t* bo = P->binoff_h;
   // columns with more than single_part_max products get row-block counts
   const int64_t multi_begin = bo[0], multi_end = bo[std::min(kBinHash0 + 14 - sp_log2, kBinMid)];
@@ -2036,8 +2301,54 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
   uint32_t* blkcnt = nullptr;
   if (nmulti > 0) {
     if ((double)nmulti * (double)nblk * 4.0 > 8e9) return fail(SPX_EUNSUPPORTED, "row-block table too large");
-    SPX_TRY(scr.get_n(nmulti * nblk, &blkcnt));
-    SPX_TRY(fill_u32(blkcnt, nmulti * nblk, 0, st));
+    SPX_TRY(scr.get_n(nmulti * nblk + 1, &blkcnt));
+  }
+  const int64_t nbitmap = bo[kBinHash0] - bo[0];
+  // bitmap chunks: a power of two of rows, a multiple of the row block;
+  // 0 = one chunk per row slice
+  int want = tune.bitmap_chunk_log2;
+  if (want <= 0) {  // auto: one chunk per row slice, at most 2^18 rows (four workgroups per CU)
+    want = 0;
+    while ((1ll << want) < ceil_div(m, std::max(1, P->nslice_req))) ++want;
+    want = std::min(want, 18);
+  }
+  int clog = std::max<int>(rb, std::min<int>(want, 20));
+  while (clog > rb && (1ll << (clog - 1)) >= m) --clog;
+  const int64_t nchunks = std::max<int64_t>(1, ceil_div(m, 1ll << clog));
+  unsigned long long* bqctr = nullptr;  // per-chunk column counters of the bitmap count
+  if (nbitmap > 0) SPX_TRY(scr.get_n(nchunks, &bqctr));
+  // split table of the long columns of A that these columns name
+  const bool split = nmulti > 0 && A->nnz > kSplitMin;
+  const int64_t nslots_a = nslots_of(P->A);
+  int32_t *flag = nullptr, *slot_of_split = nullptr;
+  int64_t* sid_off = nullptr;
+  if (split) {
+    const int64_t cap = std::min(A->nnz / (kSplitMin + 1) + 1, B->nnz);  // distinct long columns named by B
+    SPX_TRY(scr.get_many({Scratch::part(&flag, nslots_a + 1), Scratch::part(&sid_off, nslots_a + 1),
+                          Scratch::part(&slot_of_split, cap), Scratch::part(&P->bq_split, B->nnz),
+                          Scratch::part(&P->splits, cap * sstride)}));
+  }
+  if (nmulti > 0)
+    SPX_TRY(zero_words(st, {{blkcnt, ceil_div(nmulti * nblk, 2)}, {flag, split ? ceil_div(nslots_a, 2) : 0},
+                            {bqctr, nbitmap > 0 ? nchunks : 0}}));
+  if (split) {
+    const unsigned sb = grid_for(nmulti, 16, (int64_t)cus * 16), lb = kLongShare * std::max(1u, (unsigned)cus / 4);
+    k_split_mark<<<sb + lb, 256, 0, st>>>(P->A, P->B, P->aux, chunk, P->list, multi_begin, multi_end, longs, nlong, sb,
+                                          P->bq_alen, flag);
+    SPX_HIP(hipGetLastError());
+    SPX_TRY(exclusive_scan(LoadFlag{flag}, nslots_a, sid_off, scr, st));
+    k_split_rows<<<grid_for(nslots_a, 256, (int64_t)cus * 32), 256, 0, st>>>(nslots_a, sid_off, flag, slot_of_split);
+    SPX_HIP(hipGetLastError());
+    const int flat = nmulti > nslots / 64;
+    k_split_assign<<<flat ? grid_for(B->nnz, 1024, (int64_t)cus * 16) : sb + lb, 256, 0, st>>>(
+        P->A, P->B, P->aux, chunk, P->list, multi_begin, multi_end, longs, nlong, sb, flat, P->bq_alen, flag,
+        P->bq_split);
+    SPX_HIP(hipGetLastError());
+    k_split_fill<<<grid_for(std::min(nslots_a, B->nnz) * kWave, 256, (int64_t)cus * 32), 256, 0, st>>>(
+        P->A, sid_off + nslots_a, slot_of_split, P->splits, sstride, rb);
+    SPX_HIP(hipGetLastError());
+    P->src.split = P->bq_split;
+    P->src.splits = P->splits;
   }
 
   // exact counts
@@ -2048,37 +2359,30 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
     SPX_HIP(hipGetLastError());
   }
   SPX_TRY(launch_mid_count(P->B, P->src, P->mults_d, P->list, bo[kBinMid], bo[kBinTiny], P->cnt, err, st));
-  for (int b = kBinHash0; b < kBinMid; ++b) {
-    const int64_t nb = bo[b + 1] - bo[b];
-    if (nb == 0) continue;
-    const int log2s = kHashLog2Max - (b - kBinHash0);
+  // hash-counted columns: a launch per table size, so that each runs at its own
+  // occupancy; few columns go in one launch sized for the largest (four launches
+  // of 13 to 355 columns took 60 us one after the other)
+  const auto count_hash = [&](int bin, int64_t beg, int64_t end) -> int {
+    const int log2s = kHashLog2Max - (bin - kBinHash0);
     const size_t lds = ((size_t)4 << log2s) + (nblk <= 1024 ? (size_t)nblk * 4 : 0);
     const int blk = log2s >= 15 ? 1024 : (log2s >= 13 ? std::max(tune.count_threads, 512) : tune.count_threads);
-    const int per_cu = std::max<int>(1, (int)((160 * 1024) / (lds + 8192)));
-    k_count_hash<<<(unsigned)std::min<int64_t>(nb, (int64_t)cus * per_cu), blk, lds, st>>>(
-        P->B, P->src, P->mults_d, P->list, P->binoff, b, log2s, multi_end, rb, nblk, blkcnt, P->cnt, err);
+    const int per_cu = std::max<int>(1, std::min<int>((int)((160 * 1024) / (lds + kCountLds)), 2048 / blk));
+    k_count_hash<<<(unsigned)std::min<int64_t>(end - beg, (int64_t)cus * per_cu), blk, lds, st>>>(
+        P->B, P->src, P->mults_d, P->list, beg, end, multi_begin, multi_end, rb, nblk, blkcnt, P->cnt, err);
     SPX_HIP(hipGetLastError());
+    return SPX_OK;
+  };
+  const bool together = bo[kBinMid] - bo[kBinHash0] <= 4 * (int64_t)cus;
+  for (int b = kBinHash0; b < kBinMid; ++b) {
+    if (bo[b + 1] == bo[b]) continue;
+    SPX_TRY(count_hash(b, bo[b], together ? bo[kBinMid] : bo[b + 1]));
+    if (together) break;
   }
-  const int64_t nbitmap = bo[kBinHash0] - bo[0];
   if (nbitmap > 0) {
-    // bitmap chunks: a power of two of rows, a multiple of the row block;
-    // 0 = one chunk per row slice
-    int want = tune.bitmap_chunk_log2;
-    if (want <= 0) {  // auto: one chunk per row slice, at most 2^18 rows (four workgroups per CU)
-      want = 0;
-      while ((1ll << want) < ceil_div(m, std::max(1, P->nslice_req))) ++want;
-      want = std::min(want, 18);
-    }
-    int clog = std::max<int>(rb, std::min<int>(want, 20));
-    while (clog > rb && (1ll << (clog - 1)) >= m) --clog;
-    const int64_t nchunks = ceil_div(m, 1ll << clog);
     const size_t lds = ((size_t)1 << clog) / 8 + (((size_t)1 << clog) >> rb) * 4 + 16;
-    const int per_cu = std::max<int>(1, std::min<int>((int)((160 * 1024) / (lds + 8192)), 2048 / tune.bitmap_threads));
+    const int per_cu = std::max<int>(1, std::min<int>((int)((160 * 1024) / (lds + kCountLds + kWideExtraLds)), 2048 / tune.bitmap_threads));
     int64_t bgrid = std::min<int64_t>(nbitmap * nchunks, (int64_t)cus * per_cu);
     bgrid = std::max<int64_t>(nchunks, bgrid / nchunks * nchunks);
-    unsigned long long* bqctr = nullptr;  // per-chunk column counters
-    SPX_TRY(scr.get_n(nchunks, &bqctr));
-    SPX_TRY(fill_i64((int64_t*)bqctr, nchunks, 0, st));
     // keep the bitmaps for the numeric phase when they fit the cap
     const int64_t words = ceil_div(m, 64);
     if (tune.bitmap_store_mb > 0 && (double)nbitmap * words * 8.0 <= (double)tune.bitmap_store_mb * 1048576.0) {
@@ -2093,8 +2397,7 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
     SPX_HIP(hipGetLastError());
   }
   // column pointers and nonempty-column offsets
-  SPX_TRY(exclusive_scan(LoadI64{P->cnt}, nslots, P->off, scr, st));
-  SPX_TRY(exclusive_scan(NonzeroFlag{P->cnt}, nslots, P->zoff, scr, st));
+  SPX_TRY(scan_counts(P, scr, st));
   // parts of the columns above the mid ones: list positions [0, bo[kBinMid])
   const int64_t npos = bo[kBinMid];
   int64_t *np = nullptr, *poff = nullptr;
@@ -2103,21 +2406,19 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
   nslice = (int)ceil_div(nblk, slice_blocks);
   if (nslice <= 1) slice_blocks = 0;
   P->nslice = nslice;
-  PartCfg pc{L, m, sz, rb, nblk, slice_blocks, nslice, 0};
-  PartCfg pcs{P->L_single, m, sz, rb, nblk, 0, nslice, 0};
+  PartCfg pc{L, m, sz, rb, nblk, slice_blocks, nslice, hash_most(L, sz)};
+  PartCfg pcs{P->L_single, m, sz, rb, nblk, 0, nslice, hash_most(P->L_single, sz)};
+  const unsigned cut_blocks = nmulti > 0 ? grid_for(nmulti, 4, (int64_t)cus * 8) : 0;
+  const unsigned pgrid = cut_blocks + (npos > multi_end ? grid_for(npos - multi_end, 256, (int64_t)cus * 8) : 0);
   if (npos > 0) {
     SPX_TRY(scr.get_n(npos, &np));
     SPX_TRY(scr.get_n(npos + 1, &poff));
-    k_parts<<<grid_for(npos, 256, (int64_t)cus * 16), 256, 0, st>>>(P->B, pc, pcs, P->list, npos, multi_begin, multi_end,
-                                                                    P->gbm ? nbitmap : 0, P->cnt,
+    k_parts<<<pgrid, 256, 0, st>>>(P->B, pc, pcs, P->list, npos, multi_begin, multi_end,
+                                                                    cut_blocks, P->gbm ? nbitmap : 0, P->cnt,
                                                                     P->off, blkcnt, np, nullptr, nullptr, P->mults_d,
                                                                     &P->sum->setup, err);
     SPX_HIP(hipGetLastError());
     SPX_TRY(exclusive_scan(LoadI64{np}, npos, poff, scr, st));
-  }
-  if (ntiny > 0) {
-    k_bin_sum<<<grid_for(ntiny, 256, 1024), 256, 0, st>>>(P->list, P->binoff, kBinTiny, P->cnt, &P->sum->nnz_tiny);
-    SPX_HIP(hipGetLastError());
   }
   // sync 2: sizes
   int64_t tail[4] = {0, 0, 0, 0};
@@ -2140,9 +2441,10 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
       P->wide = true;
       P->L = Lw;
       pc.L = Lw;
+      pc.hash_max = hash_most(Lw, sz);
       SPX_TRY(fill_i64(reinterpret_cast<int64_t*>(&P->sum->setup), 2, 0, st));  // the cut columns may change
-      k_parts<<<grid_for(npos, 256, (int64_t)cus * 16), 256, 0, st>>>(
-          P->B, pc, pcs, P->list, npos, multi_begin, multi_end, P->gbm ? nbitmap : 0, P->cnt, P->off, blkcnt, np,
+      k_parts<<<pgrid, 256, 0, st>>>(
+          P->B, pc, pcs, P->list, npos, multi_begin, multi_end, cut_blocks, P->gbm ? nbitmap : 0, P->cnt, P->off, blkcnt, np,
           nullptr, nullptr, P->mults_d, &P->sum->setup, err);
       SPX_HIP(hipGetLastError());
       SPX_TRY(exclusive_scan(LoadI64{np}, npos, poff, scr, st));
@@ -2150,6 +2452,7 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
       if (hs.err & 4u) return fail(SPX_EUNSUPPORTED, "a row block is too dense for the LDS budget");
     }
   }
+  P->mults = (int64_t)hs.mults;
   P->nnz = tail[0];
   P->nzc = tail[1];
   P->nparts = tail[2];
@@ -2157,8 +2460,8 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
   P->nnz_tiny = (int64_t)hs.nnz_tiny;
   if (P->nparts > 0) {
     SPX_TRY(scr.get_n(P->nparts, &P->parts));
-    k_parts<<<grid_for(npos, 256, (int64_t)cus * 16), 256, 0, st>>>(P->B, pc, pcs, P->list, npos, multi_begin, multi_end,
-                                                                    P->gbm ? nbitmap : 0, P->cnt,
+    k_parts<<<pgrid, 256, 0, st>>>(P->B, pc, pcs, P->list, npos, multi_begin, multi_end,
+                                                                    cut_blocks, P->gbm ? nbitmap : 0, P->cnt,
                                                                     P->off, blkcnt, nullptr, poff, P->parts,
                                                                     P->mults_d, nullptr, err);
     SPX_HIP(hipGetLastError());
@@ -2198,18 +2501,8 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
     // work queues of the multi-part launch: one per row slice plus a
     // shared one (parts spanning all rows); the single-part launch has one
     P->nq_multi = pc.nslice + 1;
-    SPX_TRY(scr.get_n(P->nq_multi + 1, &P->qoff_multi));
-    SPX_TRY(scr.get_n(2, &P->qoff_single));
-    SPX_TRY(scr.get_n(P->nq_multi + 2, &P->qctr));
-    {
-      const int64_t h[2] = {P->psplit, P->nparts};
-      SPX_HIP(hipMemcpyAsync(P->qoff_single, h, sizeof(h), hipMemcpyHostToDevice, st));
-    }
-    if (P->psplit > 0 && pc.nslice <= 1) {
-      // one queue with every multi part, the shared queue empty
-      const int64_t h[3] = {0, P->psplit, P->psplit};
-      SPX_HIP(hipMemcpyAsync(P->qoff_multi, h, sizeof(h), hipMemcpyHostToDevice, st));
-    } else if (P->psplit > 0) {
+    if (P->psplit > 0 && pc.nslice > 1) {
+      SPX_TRY(scr.get_n(P->nq_multi + 1, &P->qoff_multi));
       unsigned long long* hist = nullptr;
       Part* sorted = nullptr;
       SPX_TRY(scr.get_n(P->nq_multi + 1, &hist));
@@ -2224,11 +2517,7 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
                                hipMemcpyDeviceToDevice, st));
       P->parts = sorted;
     }
-    if (P->psplit > 0) {
-      k_parts_sum<<<grid_for(P->psplit, 256, 1024), 256, 0, st>>>(P->parts, P->psplit, &P->sum->nnz_multi);
-      SPX_HIP(hipGetLastError());
-      P->nnz_multi = -1;  // read by spx_plan_get_info
-    }
+    if (P->psplit > 0) P->nnz_multi = -1;  // summed up by spx_plan_get_info
   }
   P->mark(kEvPlan1, st);
   if (nnz_c) *nnz_c = P->nnz;
@@ -2261,10 +2550,11 @@ extern "C" int spx_spgemm_exec(spx_plan* plan, spx_mat* C) {
     P->mark(kEvTiny, st);
   }
   if (C->fmt == SPX_CSC) {
-    k_write_csc_cp<<<grid_for(C->n + 1, 256, 65536), 256, 0, st>>>(P->B, P->off, P->nslots, C->n, C->cp, C->ptr_t);
+    k_write_csc_cp<<<grid_for(C->n + 1, 256, 65536), 256, 0, st>>>(P->B, P->off, P->nslots, C->n, C->cp, C->ptr_t,
+                                                                         P->qctr);
   } else if (P->nslots > 0) {
     k_write_dcsc<<<grid_for(P->nslots, 256, 65536), 256, 0, st>>>(P->B, P->cnt, P->off, P->zoff, P->nslots, C->jc,
-                                                                   C->cp, C->ptr_t);
+                                                                   C->cp, C->ptr_t, P->qctr);
   } else {
     if (C->ptr_t == SPX_PTR_I64)
       SPX_TRY(fill_i64((int64_t*)C->cp, 1, 0, st));
@@ -2307,8 +2597,12 @@ extern "C" int spx_plan_get_info(const spx_plan* plan, spx_plan_info* info) {
   if (plan->kind != kPlanGemm) return SPX_OK;
   auto* P = const_cast<GemmPlan*>(static_cast<const GemmPlan*>(plan));
   if (P->nnz_multi < 0) {
+    hipStream_t st = stream_of(&P->ctx);
+    SPX_TRY(fill_i64((int64_t*)&P->sum->nnz_multi, 1, 0, st));
+    k_parts_sum<<<grid_for(P->psplit, 256, 1024), 256, 0, st>>>(P->parts, P->psplit, &P->sum->nnz_multi);
+    SPX_HIP(hipGetLastError());
     int64_t v = 0;
-    SPX_TRY(read_device_words(stream_of(&P->ctx), {{&P->sum->nnz_multi, 8}}, &v));
+    SPX_TRY(read_device_words(st, {{&P->sum->nnz_multi, 8}}, &v));
     P->nnz_multi = v;
   }
   const int64_t* bo = P->binoff_h;

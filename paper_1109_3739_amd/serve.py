@@ -135,7 +135,7 @@ def gemm_bytes(m: int, k: int, n: int, nnz_a: int, nnz_b: int, mults: int, value
     out = (n + 1) * 8 + mults * (4 + value_bytes)
     concat = (4 + value_bytes) * (nnz_a + nnz_b) + 8 * (k + n + 2)
     scratch = (16 * nnz_b + 64 * (n + 1)
-               + 8 * (k + 1) + 4 * (nnz_a // 33 + 1) * (nblk + 3)
+               + 12 * (k + 1) + 4 * (nnz_a // 33 + 1) * (nblk + 3)
                + 4 * heavy * nblk
                + min(counted * ((m + 63) // 64) * 8, bitmap_store_mb << 20)
                + 2 * 48 * parts
