@@ -126,12 +126,8 @@ typedef struct spx_ctx {
  *                    phase, which then reads them instead of gathering those
  *                    rows again; 0: off.  Above the cap, or if the allocation
  *                    fails, the numeric phase recomputes them.
- *   range_chunk      B entries per range set-up round of the multi-part
- *                    launch: 256, 512, or 0 = chosen per product (512 when the
- *                    cut columns would make more than one set-up per two
- *                    multiplications, as with a tall-skinny B); 512 costs
- *                    5 KiB of the part budget and is skipped if a dense row
- *                    block would then no longer fit.
+ *   range_chunk      most B entries per range set-up round of the part launches:
+ *                    256 or 512; 0 = 512.
  *   bucket_parts     1: every part of a cut column visits only the B entries
  *                    whose A column has rows in the part's range (lists built
  *                    by the plan, one entry per B entry and part reached);

@@ -24,6 +24,7 @@
 #include <algorithm>
 #include <cstring>
 #include <memory>
+#include <type_traits>
 
 #include "common.h"
 #include "mid.h"
@@ -384,29 +385,6 @@ __global__ void k_bin_fill(const int64_t* mults, int64_t nslots, BinCfg cfg, con
 }
 
 // ------------------------------------------------------------------ product iteration
-// Work on one output column is spread over groups of G lanes (G a power of
-// two, at most 64); each group takes one stored B(k,j) at a time and its G
-// lanes stride through A(:,k).  Only rows in [r0, r1) are visited (a part
-// of the row space); the start inside A(:,k) is found by binary search.
-__device__ __forceinline__ int pick_group(int64_t mults, int64_t nq, int blk) {
-  int64_t avg = nq > 0 ? (mults + nq - 1) / nq : 1;
-  int g = 1;
-  while (g < avg && g < kWave && g < blk) g <<= 1;
-  return g;
-}
-
-__device__ __forceinline__ int32_t lower_bound_i32(const int32_t* a, int32_t n, int32_t key) {
-  int32_t lo = 0, hi = n;
-  while (lo < hi) {
-    const int32_t mid = (lo + hi) >> 1;
-    if (a[mid] < key)
-      lo = mid + 1;
-    else
-      hi = mid;
-  }
-  return lo;
-}
-
 // A's row and value at position o through a 32-bit byte offset from the base
 // (valid when o < 2^29, so o * 8 does not wrap).
 __device__ __forceinline__ int32_t load_row32(const int32_t* air, uint32_t o) {
@@ -419,280 +397,170 @@ __device__ __forceinline__ T load_val32(const T* an, uint32_t o) {
 
 
 // Block-cooperative iteration over the products of one output column.
-// The column's stored B entries are taken in chunks of kQChunk: all threads
-// first load, in parallel, each entry's range in A (start, length -- from
-// the split table for long columns of A -- and B's value) into an LDS range
-// list with a prefix sum of the lengths; then the products of the chunk are
-// numbered 0..total-1 and taken in windows of 64 (one per lane of a wave),
-// U windows per wave and round.  A lane finds the range of its product by a
-// binary search over a short stretch of the list (see below), then loads
-// A's row and value.  The work of the U windows is laid out in phases
-// (search bounds, searches, range data, loads, callback) so that the loads
-// of one phase are in flight together: a round costs a few LDS latencies
-// and one global-memory latency for up to blockDim*U products.
+// The column's stored B entries are taken in chunks of at most QC, one per
+// thread: all threads load, in parallel, their entry's range in A (start,
+// length -- from the split table for long columns of A -- and B's value), and
+// a scan numbers the chunk's products 0..total-1 and the nonempty ranges.
+// Products are taken in windows of 64 (one per lane of a wave), U consecutive
+// windows per wave and round, all loads of a round in flight together; a chunk
+// with more than WIN windows is taken in tiles of WIN.
+// Which range a lane's product lies in comes from a bit per product: wst[k] is
+// the (nonempty) range holding the first product of window k, and bits[k] has
+// bit i - 1 set when a range starts at product i >= 1 of the window, so lane i
+// lies in range wst[k] + (bits set below bit i).  That is two instructions per
+// window and no search (a binary search over range starts bounded by ballots
+// cost about 35 vector and 35 scalar instructions per window, and issuing them
+// is what bounds the callers).  base[] holds each range's start in A less its
+// first product's number, so a product's position is base + number.
 // qidx (if given) lists the B entries to visit: qidx[b0, b1) instead of
 // b0 .. b1-1.
-// f receives the U products of a lane at once: rows r[u] (-1: none, e.g.
-// past the end or outside [r0, r1)), A's values a[u] and B's values b[u].
-// Must be called by every thread of the workgroup (it contains barriers);
-// chunks hold min(blockDim.x, QC) entries, QC the capacity of the range list
-// (kQChunk, or kQChunkWide for columns with very many B entries per product).
+// f receives the U products of a lane at once: rows r[u] (-1: past the end),
+// A's values a[u] and B's values b[u].  Ranges of unsplit columns of A reach
+// outside [r0, r1), so unless `full` f has to check the rows: a row r is
+// inside if (uint32_t)(r - r0) < r1 - r0, which -1 never is.
+// Must be called by every thread of the workgroup (it contains barriers).
+// With REUSE the ranges left in R by the previous call for the same column and
+// rows are used as they are (they must have been one chunk of one tile).
+// Positions are 32 bits with OFF32 (A has fewer than 2^29 entries), then A is
+// loaded through 32-bit byte offsets; else 64 bits.
 constexpr int kQChunk = 256;
 constexpr int kQChunkWide = 512;
+constexpr int kCountWin = 256;   // windows per tile in the counts
+constexpr int kNumWin = 128;     // and in the numeric phase, whose LDS is dear
 
-constexpr int kWinTab = 512;  // windows of 64 products with a table entry
-constexpr int64_t kFilter = 1ll << 62;  // range start flag: filter rows one by one
-
-template <int QC>
+template <int QC, int WIN, bool OFF32, bool BV>
 struct RangeLdsT {
-  int64_t start[QC];  // position in A (| kFilter for unsplit columns)
-  int32_t pref[QC + 1];
-  double bval[QC];  // B's value, stored in the first bytes of each slot
-  int16_t wst[kWinTab];  // range holding product 64 k
+  using Off = std::conditional_t<OFF32, uint32_t, int64_t>;
+  static constexpr int kQ = QC, kWin = WIN;
+  static constexpr bool kOff32 = OFF32;
+  uint64_t bits[WIN];
+  double bval[BV ? QC : 1];  // B's value, stored in the first bytes of each slot
+  Off base[QC];
+  uint16_t wst[WIN];
+  int32_t total;  // products of the last chunk
 };
-using RangeLds = RangeLdsT<kQChunk>;
-// LDS that the wide range list takes beyond the ordinary one.
-constexpr int64_t kWideExtraLds = sizeof(RangeLdsT<kQChunkWide>) - sizeof(RangeLdsT<kQChunk>);
 
-// Adapts a per-product callback f(r, a, b) to the batch form.
-template <int U, class F>
-struct EachProduct {
-  F f;
-  template <typename T>
-  __device__ __forceinline__ void operator()(const int32_t (&r)[U], const T (&a)[U], const T (&b)[U]) {
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (r[u] >= 0) f(r[u], a[u], b[u]);
-  }
-};
-template <int U, class F>
-__device__ __forceinline__ EachProduct<U, F> each_product(F f) {
-  return EachProduct<U, F>{f};
-}
-
-// Range search of a window.  At set-up every range writes its index into
-// the window table for each window (64 products) whose first product it
-// holds (the first kWinTab windows).
-//  WAVE_RUNS: each wave takes U consecutive windows per round.  The range
-//    of the wave's first product (s0) comes from the table (else a binary
-//    search); the lanes load the next 64 range starts, and ballots give each
-//    window the ranges that start inside it, so a window inside one range
-//    needs no search.  A round inside one range skips all of this and loads
-//    consecutive entries.  (If all 64 loaded starts are inside the round,
-//    the search runs over all ranges after s0.)
-//  otherwise: windows are dealt round robin to the waves, and the table
-//    bounds each window's search by the ranges of its first product and of
-//    the next window's first product.
-// With REUSE the range list left in R by the previous call for the same
-// column and row range is used as is (the column must fit one chunk).
-// Row-only passes (LOADA false) load through 32-bit byte offsets when
-// S.off32 is set; value passes do so only with VAL32 (a separate kernel
-// instantiation, so that the 64-bit path's registers are not held too).
-template <int U, typename T, bool LOADA, bool LOADB, bool REUSE = false, bool WAVE_RUNS = false, bool VAL32 = false,
-          int QC, class F>
+template <int U, typename T, bool LOADA, bool LOADB, bool REUSE, class RL, class F>
 __device__ __forceinline__ void block_products(const ProdSrc& S, const T* an, const T* bn, int64_t b0, int64_t b1,
-                                               int32_t r0, int32_t r1, bool full, RangeLdsT<QC>& R, int64_t* red,
+                                               int32_t r0, int32_t r1, bool full, RL& R, int64_t* red,
                                                const int32_t* qidx, F&& f) {
-  const int qchunk = (int)blockDim.x < QC ? (int)blockDim.x : QC;
+  using Off = typename RL::Off;
+  constexpr int kWin = RL::kWin, kTile = kWin * kWave;
+  const int qchunk = (int)blockDim.x < S.qchunk ? (int)blockDim.x : S.qchunk;
   const int lane = lane_id();
-  const int32_t nwin = (int32_t)blockDim.x / kWave;
-  const int32_t wid = __builtin_amdgcn_readfirstlane((int32_t)threadIdx.x / kWave);
+  const int tid = (int)threadIdx.x;
+  const int32_t wid = __builtin_amdgcn_readfirstlane(tid / kWave);
   for (int64_t qc = b0; qc < b1; qc += qchunk) {
     const int nq = (int)(b1 - qc < qchunk ? b1 - qc : qchunk);
-    int32_t mylen = 0;
-    if (!REUSE && (int)threadIdx.x < nq) {
-      const int i = threadIdx.x;
-      const int64_t q = qidx ? (int64_t)qidx[qc + i] : qc + i;
-      const int64_t a0 = S.a0[q];
-      int32_t e0 = 0, e1 = S.alen[q];
-      int64_t flt = 0;
-      if (!full) {
-        const int32_t sid = S.splits ? S.split[q] : -1;
-        if (sid >= 0) {
-          const int32_t* sp = S.splits + (int64_t)sid * S.sstride;
-          e0 = sp[r0 >> S.rbshift];
-          e1 = sp[r1 >= S.m ? S.sstride - 1 : (r1 >> S.rbshift)];
-        } else {
-          flt = kFilter;
-        }
-      }
-      R.start[i] = (a0 + e0) | flt;
-      if constexpr (LOADB) reinterpret_cast<T*>(&R.bval[i])[0] = bn[q];
-      mylen = e1 - e0;
-    }
-    if (!REUSE) {
-      int64_t total64;
-      const int64_t ex = block_excl_scan1((int64_t)mylen, red, &total64);
-      if ((int)threadIdx.x < nq) {
-        R.pref[threadIdx.x] = (int32_t)ex;
-        // windows whose first product falls in this range
-        const int64_t k1 = (ex + mylen + kWave - 1) / kWave;
-        for (int64_t k = (ex + kWave - 1) / kWave; k < k1 && k < kWinTab; ++k) R.wst[k] = (int16_t)threadIdx.x;
-      }
-      if (threadIdx.x == 0) R.pref[nq] = (int32_t)total64;
-      __syncthreads();
-    }
-    const int32_t total = R.pref[nq];
-    for (int32_t base = 0; base < total; base += (int32_t)blockDim.x * U) {
-      const int32_t pw = base + wid * (U * kWave);
-      // phase 1: search bounds [lo, lo + n) of every window (wave-uniform)
-      int lo[U], n[U];
-      if constexpr (WAVE_RUNS) {
-        int s0 = 0, s1 = 1;
-        if (pw < total) {
-          int l = 0;
-          if (pw / kWave < kWinTab) {
-            l = R.wst[pw / kWave];
-          } else {
-            int h = nq;
-            while (h - l > 1) {
-              const int mid = (l + h) >> 1;
-              if (R.pref[mid] <= pw)
-                l = mid;
-              else
-                h = mid;
-            }
-          }
-          s0 = __builtin_amdgcn_readfirstlane(l);
-          const int j = s0 + 1 + lane;
-          const int32_t bj = j <= nq ? R.pref[j] : 0x7fffffff;
-          const uint64_t in_round = __ballot(bj < pw + U * kWave);
-          if (in_round == 0 && pw + U * kWave <= total) {
-            // the whole round lies in range s0: consecutive products, no search
-            const int64_t st = R.start[s0];
-            const int64_t eb = (st & (kFilter - 1)) + (pw - R.pref[s0]) + lane;
-            const bool fl1 = (st & kFilter) != 0;
-            const T b1 = LOADB ? reinterpret_cast<const T*>(&R.bval[s0])[0] : T(0);
-            int32_t r[U];
-            T a[U], bv[U];
-            if (VAL32 || (!LOADA && S.off32)) {  // VAL32: the caller's A fits 29-bit positions
-              const uint32_t eb32 = (uint32_t)eb;
-#pragma unroll
-              for (int u = 0; u < U; ++u) {
-                r[u] = load_row32(S.air, eb32 + (uint32_t)(u * kWave));
-                a[u] = LOADA ? load_val32(an, eb32 + (uint32_t)(u * kWave)) : T(0);
-                bv[u] = b1;
-              }
-            } else {
-#pragma unroll
-              for (int u = 0; u < U; ++u) {
-                r[u] = S.air[eb + u * kWave];
-                a[u] = LOADA ? an[eb + u * kWave] : T(0);
-                bv[u] = b1;
-              }
-            }
-            if (fl1) {
-#pragma unroll
-              for (int u = 0; u < U; ++u)
-                if (r[u] < r0 || r[u] >= r1) r[u] = -1;
-            }
-            f(r, a, bv);
-            continue;
-          }
-          if (in_round == ~0ull) {
-            s1 = nq + 1;
-          } else {
-            // each window: the ranges starting inside it
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-              const int32_t p0 = pw + u * kWave;
-              lo[u] = s0 + __popcll(__ballot(bj <= p0));
-              n[u] = s0 + __popcll(__ballot(bj < p0 + kWave)) + 1 - lo[u];
-            }
-            s1 = -1;
+    int64_t total;
+    int64_t ex = 0;      // the thread's range holds products [ex, ex + len)
+    int32_t len = 0, rk = 0;
+    if (REUSE) {
+      total = R.total;
+    } else {
+      for (int k = tid; k < kWin; k += (int)blockDim.x) R.bits[k] = 0;
+      int64_t at = 0;
+      T bq = T(0);
+      if (tid < nq) {
+        const int64_t q = qidx ? (int64_t)qidx[qc + tid] : qc + tid;
+        const int64_t a0 = S.a0[q];
+        int32_t e0 = 0, e1 = S.alen[q];
+        if constexpr (LOADB) bq = bn[q];
+        if (!full) {
+          const int32_t sid = S.splits ? S.split[q] : -1;
+          if (sid >= 0) {
+            const int32_t* sp = S.splits + (int64_t)sid * S.sstride;
+            e0 = sp[r0 >> S.rbshift];
+            e1 = sp[r1 >= S.m ? S.sstride - 1 : (r1 >> S.rbshift)];
           }
         }
-        if (s1 >= 0) {
+        at = a0 + e0;
+        len = e1 - e0;
+      }
+      // products below bit 50, nonempty ranges above
+      int64_t sum;
+      const int64_t pre = block_excl_scan1((int64_t)len | (len > 0 ? (int64_t)1 << 50 : (int64_t)0), red, &sum);
+      ex = pre & ((1ll << 50) - 1);
+      rk = (int32_t)(pre >> 50);
+      total = sum & ((1ll << 50) - 1);
+      if (len > 0) {
+        R.base[rk] = (Off)(at - ex);
+        if constexpr (LOADB) reinterpret_cast<T*>(&R.bval[rk])[0] = bq;
+      }
+      if (tid == 0) R.total = total < kTile ? (int32_t)total : kTile;
+    }
+    for (int64_t tb = 0; tb < total; tb += kTile) {
+      if (!REUSE) {
+        if (tb > 0) {
+          __syncthreads();  // the last tile's rounds are done
+          for (int k = tid; k < kWin; k += (int)blockDim.x) R.bits[k] = 0;
+          __syncthreads();
+        }
+        if (len > 0 && ex < tb + kTile && ex + len > tb) {
+          const int32_t st = (int32_t)(ex - tb > 0 ? ex - tb : 0);
+          const int32_t en = (int32_t)(ex + len - tb < kTile ? ex + len - tb : kTile);
+          if (ex >= tb && (st & (kWave - 1)))
+            atomicOr((unsigned long long*)&R.bits[st / kWave], 1ull << ((st & (kWave - 1)) - 1));
+          for (int32_t k = (st + kWave - 1) / kWave; k * kWave < en; ++k) R.wst[k] = (uint16_t)rk;
+        }
+        __syncthreads();
+      }
+      const int32_t tt = __builtin_amdgcn_readfirstlane((int32_t)(total - tb < kTile ? total - tb : kTile));
+      const Off tbo = (Off)tb;
+      for (int32_t pw = wid * (U * kWave); pw < tt; pw += (int32_t)blockDim.x * U) {
+        int32_t r[U];
+        T a[U], bv[U];
+        if (pw + U * kWave <= tt) {
+          uint64_t w[U];
+          uint32_t own[U];
+          Off o[U];
 #pragma unroll
           for (int u = 0; u < U; ++u) {
-            lo[u] = s0;
-            n[u] = s1 - s0;
+            w[u] = R.bits[pw / kWave + u];
+            own[u] = R.wst[pw / kWave + u];
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            own[u] = __builtin_amdgcn_mbcnt_hi((uint32_t)(w[u] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)w[u], own[u]));
+            o[u] = R.base[own[u]] + (Off)(pw + u * kWave + lane) + tbo;
+            bv[u] = LOADB ? reinterpret_cast<const T*>(&R.bval[own[u]])[0] : T(0);
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            if constexpr (RL::kOff32) {
+              r[u] = load_row32(S.air, o[u]);
+              a[u] = LOADA ? load_val32(an, o[u]) : T(0);
+            } else {
+              r[u] = S.air[o[u]];
+              a[u] = LOADA ? an[o[u]] : T(0);
+            }
+          }
+        } else {  // the tile's last round of this wave
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            r[u] = -1;
+            a[u] = bv[u] = T(0);
+            const int32_t p = pw + u * kWave + lane;
+            if (pw + u * kWave < tt) {
+              const uint64_t w = R.bits[pw / kWave + u];
+              uint32_t own = R.wst[pw / kWave + u];
+              own = __builtin_amdgcn_mbcnt_hi((uint32_t)(w >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)w, own));
+              const Off o = R.base[own] + (Off)p + tbo;
+              if (p < tt) {
+                bv[u] = LOADB ? reinterpret_cast<const T*>(&R.bval[own])[0] : T(0);
+                if constexpr (RL::kOff32) {
+                  r[u] = load_row32(S.air, o);
+                  if constexpr (LOADA) a[u] = load_val32(an, o);
+                } else {
+                  r[u] = S.air[o];
+                  if constexpr (LOADA) a[u] = an[o];
+                }
+              }
+            }
           }
         }
-      } else {
-        // all table reads first (one LDS latency), then the bounds
-        int tl[U], th[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int32_t k = base / kWave + u * nwin + wid;
-          const int32_t kc = k < kWinTab - 1 ? k : kWinTab - 2;
-          tl[u] = R.wst[kc];
-          th[u] = R.wst[kc + 1];
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int32_t p0 = base + (u * nwin + wid) * kWave;
-          const int32_t k = p0 / kWave;
-          int l = 0, h = 1;
-          if (p0 >= total) {
-          } else if (k + 1 < kWinTab && p0 + kWave < total) {
-            l = tl[u];
-            h = th[u] + 1;
-          } else {
-            l = k < kWinTab ? tl[u] : 0;
-            h = nq;
-          }
-          lo[u] = __builtin_amdgcn_readfirstlane(l);
-          n[u] = __builtin_amdgcn_readfirstlane(h) - lo[u];
-        }
+        f(r, a, bv);
       }
-      // phase 2: last range with start <= p (uniform trip counts)
-      int32_t p[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int32_t pp = (WAVE_RUNS ? pw + u * kWave : base + (u * nwin + wid) * kWave) + lane;
-        p[u] = pp < total ? pp : total - 1;
-        int pos = lo[u];
-        for (int m = n[u]; m > 1;) {
-          const int half = m >> 1;
-          if (R.pref[pos + half] <= p[u]) pos += half;
-          m -= half;
-        }
-        lo[u] = pos;
-        if (pp >= total) p[u] = -1;
-      }
-      // phase 3: range data; phase 4: A's row and value
-      int64_t st[U];
-      int32_t d[U];
-      int32_t r[U];
-      T a[U], bv[U];
-      bool fl[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        st[u] = R.start[lo[u]];
-        const int32_t pf = R.pref[lo[u]];
-        fl[u] = (st[u] & kFilter) != 0;
-        d[u] = (p[u] < 0 ? total - 1 : p[u]) - pf;
-        bv[u] = LOADB ? reinterpret_cast<const T*>(&R.bval[lo[u]])[0] : T(0);
-      }
-      if (VAL32 || (!LOADA && S.off32)) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          r[u] = -1;
-          a[u] = T(0);
-          // windows wholly past the end load nothing (wave-uniform test)
-          if ((WAVE_RUNS ? pw + u * kWave : base + (u * nwin + wid) * kWave) < total) {
-            const uint32_t o = (uint32_t)st[u] + (uint32_t)d[u];  // the flag is above bit 31
-            r[u] = load_row32(S.air, o);
-            if constexpr (LOADA) a[u] = load_val32(an, o);
-          }
-        }
-      } else {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          r[u] = -1;
-          a[u] = T(0);
-          if ((WAVE_RUNS ? pw + u * kWave : base + (u * nwin + wid) * kWave) < total) {
-            const int64_t e = (st[u] & (kFilter - 1)) + d[u];
-            r[u] = S.air[e];
-            if constexpr (LOADA) a[u] = an[e];
-          }
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (p[u] < 0 || (fl[u] && (r[u] < r0 || r[u] >= r1))) r[u] = -1;
-      f(r, a, bv);
     }
     __syncthreads();
   }
@@ -943,15 +811,17 @@ __global__ void __launch_bounds__(256) k_tiny(Operand A, Operand B, const int64_
 // they are inserted.  (A pass over the table for these counts, and clearing it
 // word by word, took longer than the insertions: at 8192 products each thread
 // handles 16 products but 32 slots.)
-constexpr int kCountLds = 6912;  // static LDS of the count kernels, rounded up
+template <bool OFF32>
+using HashRanges = RangeLdsT<kQChunk, kCountWin, OFF32, false>;
 
-__global__ void k_count_hash(Operand B, ProdSrc S, const int64_t* mults,
+template <bool OFF32>
+__global__ void __launch_bounds__(1024) k_count_hash(Operand B, ProdSrc S, const int64_t* mults,
                              const int32_t* list, int64_t beg, int64_t end, int64_t multi_begin, int64_t multi_end,
                              int rbshift, int64_t nblk, uint32_t* blkcnt, int64_t* cnt, unsigned* err) {
   extern __shared__ __align__(16) unsigned char lds[];
   uint32_t* keys = (uint32_t*)lds;
   __shared__ int64_t red[1024 / kWave + 1];
-  __shared__ RangeLds s_rng;
+  __shared__ HashRanges<OFF32> s_rng;
   for (int64_t pos = beg + blockIdx.x; pos < end; pos += gridDim.x) {
     const int32_t t = list[pos];
     const int log2s = std::max(ceil_log2_u64((uint64_t)mults[t]) + 1, kHashLog2Min);  // as bin_of
@@ -968,7 +838,7 @@ __global__ void k_count_hash(Operand B, ProdSrc S, const int64_t* mults,
       for (int64_t i = threadIdx.x; i < nblk; i += blockDim.x) lblk[i] = 0;
     __syncthreads();
     int64_t mine = 0;
-    block_products<4, int, false, false, false, true>(
+    block_products<4, int, false, false, false>(
         S, nullptr, nullptr, b0, b1, 0, 0, true, s_rng, red, nullptr,
         [&](const int32_t(&r)[4], const int(&)[4], const int(&)[4]) {
           // first probes of the four windows together
@@ -1007,18 +877,33 @@ __global__ void k_count_hash(Operand B, ProdSrc S, const int64_t* mults,
 // ------------------------------------------------------------------ count: bitmap
 // One workgroup per heavy column; an LDS bitmap over (a chunk of) the row
 // space marks every row that receives a product.  Popcounts give the exact
-// column count and the per-row-block counts used to cut parts.
-__global__ void k_count_bitmap(Operand B, ProdSrc S, const int64_t* mults, const int32_t* list, const int64_t* binoff,
-                               int64_t m, int chunk_log2, int rbshift, int64_t nblk, uint32_t* blkcnt,
-                               unsigned long long* cnt, uint32_t* gbm, int64_t gwords, unsigned long long* qctr) {
+// column count and the per-row-block counts used to cut parts; the bitmap is
+// kept in HBM for the numeric phase.  One pass does all of that and clears the
+// bitmap for the next column: a lane takes 16 bytes, a wave 8192 rows, which
+// lie in one row block (rbshift >= 13 for every value type at the default part
+// budget), so a wave adds up once per 8192 rows.  (Separate passes of 4-byte
+// words with a wave sum per 2048 rows issued a third of the kernel's
+// instructions, and issuing them is what bounds it.)
+template <bool OFF32>
+using BitmapRanges = RangeLdsT<kQChunkWide, kCountWin, OFF32, false>;  // heavy columns have many B entries
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+template <bool OFF32>
+__global__ void __launch_bounds__(1024) k_count_bitmap(Operand B, ProdSrc S, const int64_t* mults, const int32_t* list,
+                                                       const int64_t* binoff, int64_t m, int chunk_log2, int rbshift,
+                                                       int64_t nblk, uint32_t* blkcnt, unsigned long long* cnt,
+                                                       uint32_t* gbm, int64_t gwords, unsigned long long* qctr) {
   extern __shared__ __align__(16) unsigned char lds[];
   uint32_t* bm = (uint32_t*)lds;
-  const int64_t chunk_rows = 1ll << chunk_log2;  // a multiple of the row block
+  u32x4* bm4 = (u32x4*)lds;
+  const int64_t chunk_rows = 1ll << chunk_log2;  // a multiple of the row block, at least 8192 or one chunk
   const int64_t nchunks = (m + chunk_rows - 1) >> chunk_log2;
   const int blk_per_chunk = (int)(chunk_rows >> rbshift);
-  uint32_t* lblk = bm + (chunk_rows >> 5);
+  const int all4 = (int)((chunk_rows + 127) >> 7);
+  uint32_t* lblk = bm + 4 * all4;
   __shared__ int64_t red[1024 / kWave + 1];
-  __shared__ RangeLdsT<kQChunkWide> s_rng;  // heavy columns have many B entries
+  __shared__ BitmapRanges<OFF32> s_rng;
+  __shared__ unsigned s_tot;
   const int64_t beg = binoff[0], end = binoff[kBinHash0];
   const int64_t ncols = end - beg;
   // workgroup w works on row chunk w mod nchunks (the grid is a multiple of
@@ -1027,73 +912,71 @@ __global__ void k_count_bitmap(Operand B, ProdSrc S, const int64_t* mults, const
   // a time by its counter qctr[chunk] (zero at launch), in list order, which
   // puts the heaviest columns first.
   const int64_t chunk = blockIdx.x % nchunks;
+  const int64_t c0 = chunk * chunk_rows;
+  const int64_t c1 = c0 + chunk_rows < m ? c0 + chunk_rows : m;
+  const uint32_t span = (uint32_t)(c1 - c0);
+  const int words4 = (int)((span + 127) >> 7);
+  const int64_t bfirst = c0 >> rbshift;
   __shared__ int64_t s_ci;
+  for (int i = threadIdx.x; i < all4; i += blockDim.x) bm4[i] = u32x4{0u, 0u, 0u, 0u};
+  for (int i = threadIdx.x; i < blk_per_chunk; i += blockDim.x) lblk[i] = 0;
   for (;;) {
-    if (threadIdx.x == 0) s_ci = (int64_t)atomicAdd(&qctr[chunk], 1ull);
+    if (threadIdx.x == 0) {
+      s_ci = (int64_t)atomicAdd(&qctr[chunk], 1ull);
+      s_tot = 0;
+    }
     __syncthreads();
     const int64_t ci = s_ci;
     if (ci >= ncols) break;
     const int64_t pos = beg + ci;
-    const int64_t c0 = chunk * chunk_rows;
-    const int64_t c1 = c0 + chunk_rows < m ? c0 + chunk_rows : m;
     const int32_t t = list[pos];
     const int64_t b0 = slot_begin(B, t), b1 = slot_begin(B, t + 1);
     uint32_t* dst = blkcnt + (pos - beg) * nblk;
-    const int words = (int)((c1 - c0 + 31) >> 5);
-    {  // 16-byte LDS stores (the LDS base is 16-byte aligned), then the ragged end
-      const int w4 = words >> 2;
-      for (int i = threadIdx.x; i < w4; i += blockDim.x) reinterpret_cast<uint4*>(bm)[i] = make_uint4(0u, 0u, 0u, 0u);
-      for (int i = (w4 << 2) + (int)threadIdx.x; i < words; i += blockDim.x) bm[i] = 0;
-    }
-    for (int i = threadIdx.x; i < blk_per_chunk; i += blockDim.x) lblk[i] = 0;
-    __syncthreads();
-    block_products<4, int, false, false, false, true>(S, nullptr, nullptr, b0, b1, (int32_t)c0, (int32_t)c1, nchunks == 1, s_rng,
-                                         red, nullptr, each_product<4>([&](int32_t r, int, int) {
-      const uint32_t d = (uint32_t)(r - (int32_t)c0);
-      if (d < (uint32_t)(c1 - c0)) atomicOr(&bm[d >> 5], 1u << (d & 31));
-    }));
-    __syncthreads();
-    int64_t mine = 0;
-    if (rbshift >= 11) {
-      // a wave's 64 words (2048 rows, 64-aligned) lie in one row block:
-      // one LDS add per wave instead of one per nonzero word at one address
-      const int lane = lane_id();
-      for (int w = (int)threadIdx.x - lane; w < words; w += blockDim.x) {
-        const int i = w + lane;
-        const int pc = i < words ? __popc(bm[i]) : 0;
-        mine += pc;
-        const int s = __builtin_amdgcn_readlane(wave_incl_scan(pc), 63);
-        if (lane == 0 && s) atomicAdd(&lblk[((int64_t)w * 32) >> rbshift], (uint32_t)s);
-      }
-    } else {
-      for (int i = threadIdx.x; i < words; i += blockDim.x) {
-        const int pc = __popc(bm[i]);
-        if (pc) {
-          mine += pc;
-          atomicAdd(&lblk[((int64_t)i * 32) >> rbshift], (uint32_t)pc);
-        }
-      }
-    }
-    int64_t ctot;
-    block_excl_scan1(mine, red, &ctot);
-    const int64_t bfirst = c0 >> rbshift;
-    for (int i = threadIdx.x; i < blk_per_chunk; i += blockDim.x)
-      if (bfirst + i < nblk) dst[bfirst + i] = lblk[i];
-    if (threadIdx.x == 0 && ctot) atomicAdd(&cnt[t], (unsigned long long)ctot);
-    if (gbm) {  // keep the column's row set for the numeric phase
-      // whole 64-bit words (gwords is even and c0 a multiple of 64 rows, so g
-      // is 8-byte aligned); a ragged chunk's last word is padded with zeros
-      uint2* g = reinterpret_cast<uint2*>(gbm + ci * gwords + (c0 >> 5));
-      const int w2 = (words + 1) >> 1;
-      for (int i = threadIdx.x; i < w2; i += blockDim.x) {
-        const int k = 2 * i;
+    block_products<4, int, false, false, false>(
+        S, nullptr, nullptr, b0, b1, (int32_t)c0, (int32_t)c1, nchunks == 1, s_rng, red, nullptr,
+        [&](const int32_t(&r)[4], const int(&)[4], const int(&)[4]) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const uint32_t d = (uint32_t)(r[u] - (int32_t)c0);
+            if (d < span) atomicOr(&bm[d >> 5], 1u << (d & 31));
+          }
+        });
+    // (block_products ends with a barrier)
+    // rows of gbm are 16-byte aligned: gwords and c0 / 32 are multiples of 4
+    u32x4* g = gbm ? (u32x4*)(gbm + ci * gwords + (c0 >> 5)) : nullptr;
+    const int lane = lane_id();
+    for (int i0 = (int)threadIdx.x - lane; i0 < words4; i0 += blockDim.x) {
+      const int i = i0 + lane;
+      u32x4 v{0u, 0u, 0u, 0u};
+      if (i < words4) {
+        v = bm4[i];
+        bm4[i] = u32x4{0u, 0u, 0u, 0u};
         // streaming (non-temporal) stores: the bitmaps are read back only by the
         // numeric phase, so they need not displace A's gathered entries from L2
-        const uint64_t pair = ((uint64_t)(k + 1 < words ? bm[k + 1] : 0u) << 32) | bm[k];
-        __builtin_nontemporal_store(pair, reinterpret_cast<uint64_t*>(g) + i);
+        if (g) __builtin_nontemporal_store(v, g + i);
+      }
+      if (rbshift >= 13) {
+        const int pc = __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
+        const int sum = __builtin_amdgcn_readlane(wave_incl_scan(pc), 63);
+        if (lane == 0 && sum) {
+          atomicAdd(&lblk[((int64_t)i0 * 128) >> rbshift], (uint32_t)sum);
+          atomicAdd(&s_tot, (unsigned)sum);
+        }
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (const int pc = __popc(v[k])) {
+            atomicAdd(&lblk[((int64_t)i * 128 + k * 32) >> rbshift], (uint32_t)pc);
+            atomicAdd(&s_tot, (unsigned)pc);
+          }
       }
     }
     __syncthreads();
+    for (int i = threadIdx.x; i < blk_per_chunk; i += blockDim.x) {
+      if (bfirst + i < nblk) dst[bfirst + i] = lblk[i];
+      lblk[i] = 0;
+    }
+    if (threadIdx.x == 0 && s_tot) atomicAdd(&cnt[t], (unsigned long long)s_tot);
   }
 }
 
@@ -1466,7 +1349,15 @@ __device__ __forceinline__ void block_bitonic_sort(uint64_t* a, int n2) {
 // popcount prefix gives each row its rank = output position, accumulate
 // values by rank, write rows and values in order.  Hash mode: accumulate
 // into an open-addressing table, then sort (row, slot) keys.
-template <int SR, typename T, int QC, bool OFF32>
+template <bool OFF32>
+using PartRanges = RangeLdsT<kQChunkWide, kNumWin, OFF32, true>;
+
+// Static LDS of the kernel, rounded up: with 32-bit positions two workgroups
+// of the default 72 KiB part budget share a CU's 160 KiB.
+constexpr int64_t kPartLds32 = 8192, kPartLds64 = 10240;
+static_assert(sizeof(PartRanges<true>) + 480 <= kPartLds32 && sizeof(PartRanges<false>) + 480 <= kPartLds64, "static LDS");
+
+template <int SR, typename T, bool OFF32>
 __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, ProdSrc S,
                                                         const int64_t* mults,
                                                         const int64_t* cnt, const Part* parts, const int64_t* qoff,
@@ -1482,7 +1373,7 @@ __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, Pr
   __shared__ Part s_batch[kPartBatch];
   __shared__ int64_t red[1024 / kWave + 1];
   __shared__ unsigned s_ctr;
-  __shared__ RangeLdsT<QC> s_rng;
+  __shared__ PartRanges<OFF32> s_rng;
   const T* an = (const T*)A.num;
   const T* bn = (const T*)B.num;
   // work queues: queue k holds parts [qoff[k], qoff[k+1]) (without qoff: one
@@ -1555,12 +1446,14 @@ __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, Pr
         for (int i = threadIdx.x; i < c; i += blockDim.x) vals[i] = SR_::ident();
       __syncthreads();
       if (!stored) {
-        block_products<8, T, false, SR_::kUsesB, false, true, OFF32>(S, an, bn, b0, b1, P.r0, P.r1, full, s_rng, red, qx,
-                                                  each_product<8>([&](int32_t r, T, T) {
-          const uint32_t d = (uint32_t)(r - P.r0);
-          atomicOr((unsigned long long*)&bm[d >> 6], 1ull << (d & 63));
-        }));
-        __syncthreads();
+        block_products<8, T, false, SR_::kUsesB, false>(
+            S, an, bn, b0, b1, P.r0, P.r1, full, s_rng, red, qx, [&](const int32_t(&r)[8], const T(&)[8], const T(&)[8]) {
+#pragma unroll
+              for (int u = 0; u < 8; ++u) {
+                const uint32_t d = (uint32_t)(r[u] - P.r0);
+                if (d < (uint32_t)span) atomicOr((unsigned long long*)&bm[d >> 6], 1ull << (d & 63));
+              }
+            });
       }
       // exclusive popcount prefix per word
       const int per = (W + blockDim.x - 1) / blockDim.x;
@@ -1583,23 +1476,24 @@ __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, Pr
           int pr[8];
 #pragma unroll
           for (int u = 0; u < 8; ++u) {
-            const int wi = r[u] >= 0 ? (int)((uint32_t)(r[u] - P.r0) >> 6) : 0;
+            const uint32_t d = (uint32_t)(r[u] - P.r0);
+            const uint32_t wi = d < (uint32_t)span ? d >> 6 : 0u;
             w[u] = bm[wi];
             pr[u] = pre[wi];
           }
 #pragma unroll
           for (int u = 0; u < 8; ++u) {
-            if (r[u] < 0) continue;
             const uint32_t d = (uint32_t)(r[u] - P.r0);
             const int rank = pr[u] + __popcll(w[u] & ((1ull << (d & 63)) - 1ull));
-            if (rank < c) SR_::lds_acc(&vals[rank], SR_::mul(a[u], bv[u]));
+            if (d < (uint32_t)span && rank < c) SR_::lds_acc(&vals[rank], SR_::mul(a[u], bv[u]));
           }
         };
-        if (!stored && b1 - b0 <= (int64_t)(blockDim.x < QC ? blockDim.x : QC))
-          block_products<8, T, SR_::kUsesA, SR_::kUsesB, true, true, OFF32>(S, an, bn, b0, b1, P.r0, P.r1, full, s_rng, red, qx, acc);
+        const int qchunk = (int)blockDim.x < S.qchunk ? (int)blockDim.x : S.qchunk;
+        // the marking pass left all ranges in LDS (one chunk, one tile)
+        if (!stored && b1 - b0 <= qchunk && s_rng.total < kNumWin * kWave)
+          block_products<8, T, SR_::kUsesA, SR_::kUsesB, true>(S, an, bn, b0, b1, P.r0, P.r1, full, s_rng, red, qx, acc);
         else
-          block_products<8, T, SR_::kUsesA, SR_::kUsesB, false, true, OFF32>(S, an, bn, b0, b1, P.r0, P.r1, full, s_rng, red, qx, acc);
-        __syncthreads();
+          block_products<8, T, SR_::kUsesA, SR_::kUsesB, false>(S, an, bn, b0, b1, P.r0, P.r1, full, s_rng, red, qx, acc);
         // C is written once, coalesced: streaming stores keep the L2 for A's gathers
         // (a part's scattered hash-mode writes stay ordinary: streamed partial lines
         // cost more than they save)
@@ -1650,21 +1544,31 @@ __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, Pr
       }
       if (threadIdx.x == 0) s_ctr = 0;
       __syncthreads();
-      block_products<4, T, SR_::kUsesA, SR_::kUsesB, false, false, OFF32>(S, an, bn, b0, b1, P.r0, P.r1, full, s_rng, red, qx,
-                                                     each_product<4>([&](int32_t r, T a, T bv) {
-        if (r < 0) return;
-        uint32_t h = hash_row(r, log2s);
-        for (uint32_t probe = 0; probe < Sz; ++probe) {
-          const uint32_t old = atomicCAS(&keys[h], 0xffffffffu, (uint32_t)r);
-          if (old == 0xffffffffu || old == (uint32_t)r) {
-            if constexpr (kVal) SR_::lds_acc(&vals[h], SR_::mul(a, bv));
-            return;
-          }
-          h = (h + 1) & (Sz - 1);
-        }
-        atomicOr(err, 16u);
-      }));
-      __syncthreads();
+      block_products<4, T, SR_::kUsesA, SR_::kUsesB, false>(
+          S, an, bn, b0, b1, P.r0, P.r1, full, s_rng, red, qx, [&](const int32_t(&r)[4], const T(&a)[4], const T(&bv)[4]) {
+            uint32_t h[4], old[4];
+            bool in[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {  // first probes of the four windows together
+              in[u] = (uint32_t)(r[u] - P.r0) < (uint32_t)span;
+              h[u] = hash_row(r[u], log2s);
+              old[u] = in[u] ? atomicCAS(&keys[h[u]], ~0u, (uint32_t)r[u]) : (uint32_t)r[u];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              for (uint32_t probe = 1; old[u] != ~0u && old[u] != (uint32_t)r[u]; ++probe) {
+                if (probe >= Sz) {
+                  atomicOr(err, 16u);
+                  in[u] = false;
+                  break;
+                }
+                h[u] = (h[u] + 1) & (Sz - 1);
+                old[u] = atomicCAS(&keys[h[u]], ~0u, (uint32_t)r[u]);
+              }
+              if constexpr (kVal)
+                if (in[u]) SR_::lds_acc(&vals[h[u]], SR_::mul(a[u], bv[u]));
+            }
+          });
       if (ranked) {
         // level 1: nonempty groups of 64 rows
         for (uint32_t i = threadIdx.x; i < Sz; i += blockDim.x) {
@@ -1998,7 +1902,6 @@ struct GemmPlan : spx_plan {
   Summary* sum = nullptr;
   unsigned long long* totals = nullptr;  // spread counters: multiplications, entries of the tiny columns
   int64_t L = 0, L_single = 0;
-  bool wide = false;  // the multi-part launch uses the wide range list
   int32_t* qlist = nullptr;  // B entries of the parts of bucketed columns, grouped by part
   uint64_t* gbm = nullptr;  // stored row bitmaps of the bitmap-counted columns
   int64_t gbm_words = 0;    // 64-bit words per stored bitmap
@@ -2110,25 +2013,22 @@ static int launch_numeric(GemmPlan* P, spx_mat* C, hipStream_t st) {
     if (n1 <= n0) continue;
     const int blk = r == 0 ? P->tune.part_threads : P->tune.single_threads;
     const int64_t L = r == 0 ? P->L : P->L_single;
-    const int per_cu = (int)std::max<int64_t>(1, std::min<int64_t>((160 * 1024) / (L + 8192), 2048 / blk));
+    const int64_t fixed = P->src.off32 ? kPartLds32 : kPartLds64;
+    const int per_cu = (int)std::max<int64_t>(1, std::min<int64_t>((160 * 1024) / (L + fixed), 2048 / blk));
     int64_t grid = std::min<int64_t>(n1 - n0, (int64_t)cus * per_cu);
     if (r == 0 && P->nslice > 1) grid = std::max<int64_t>(P->nslice, grid / P->nslice * P->nslice);
     const int64_t* qoff = r == 0 ? P->qoff_multi : nullptr;
     const int nq = qoff ? P->nq_multi : 1;
     unsigned long long* qctr = r == 0 ? P->qctr : P->qctr + kMaxQueues;
     const int batch = (int)std::max<int64_t>(1, std::min<int64_t>(kPartBatch, (n1 - n0) / (2 * grid)));
-    if (r == 0 && P->wide)
-      hipLaunchKernelGGL((k_numeric_parts<SR, T, kQChunkWide, false>), dim3((unsigned)grid), dim3(blk), (size_t)L, st,
-                         P->A, P->B, P->src, P->mults_d, P->cnt, P->parts, qoff, n0, n1, nq, P->nslice, batch, qctr, P->gbm,
-                         P->gbm_words, P->qlist, cir, cnum, err);
-    else if (P->src.off32)  // A's positions fit 29 bits: gathers through 32-bit offsets
-      hipLaunchKernelGGL((k_numeric_parts<SR, T, kQChunk, true>), dim3((unsigned)grid), dim3(blk), (size_t)L, st, P->A,
-                         P->B, P->src, P->mults_d, P->cnt, P->parts, qoff, n0, n1, nq, r == 0 ? P->nslice : 1, batch, qctr, P->gbm,
-                         P->gbm_words, P->qlist, cir, cnum, err);
+    if (P->src.off32)  // A's positions fit 29 bits: gathers through 32-bit offsets
+      hipLaunchKernelGGL((k_numeric_parts<SR, T, true>), dim3((unsigned)grid), dim3(blk), (size_t)L, st, P->A, P->B,
+                         P->src, P->mults_d, P->cnt, P->parts, qoff, n0, n1, nq, r == 0 ? P->nslice : 1, batch, qctr,
+                         P->gbm, P->gbm_words, P->qlist, cir, cnum, err);
     else
-      hipLaunchKernelGGL((k_numeric_parts<SR, T, kQChunk, false>), dim3((unsigned)grid), dim3(blk), (size_t)L, st, P->A,
-                         P->B, P->src, P->mults_d, P->cnt, P->parts, qoff, n0, n1, nq, r == 0 ? P->nslice : 1, batch, qctr, P->gbm,
-                         P->gbm_words, P->qlist, cir, cnum, err);
+      hipLaunchKernelGGL((k_numeric_parts<SR, T, false>), dim3((unsigned)grid), dim3(blk), (size_t)L, st, P->A, P->B,
+                         P->src, P->mults_d, P->cnt, P->parts, qoff, n0, n1, nq, r == 0 ? P->nslice : 1, batch, qctr,
+                         P->gbm, P->gbm_words, P->qlist, cir, cnum, err);
     SPX_HIP(hipGetLastError());
     if (r == 0) P->mark(kEvMulti, st);
   }
@@ -2231,10 +2131,14 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
   // Row blocks: the largest power of two <= 2^14 such that one dense block
   // fits a part in bitmap mode.
   int64_t L = tune.part_lds_bytes;
-  if (L > 160 * 1024 - 8192) L = 160 * 1024 - 8192;
+  if (L > 160 * 1024 - kPartLds64) L = 160 * 1024 - kPartLds64;
   int rb = 14;
   while (rb > 6 && ((1ll << rb) * sz + ((1ll << rb) / 64) * 10 + 256) > L) --rb;
   if (((1ll << rb) * sz + ((1ll << rb) / 64) * 10 + 256) > L) return fail(SPX_EINVAL, "part_lds_bytes too small");
+  const bool off32 = A->nnz < (1ll << 29) && !tune.force_off64;
+  // 64-bit ranges take 2 KiB more: leave them out of the part budget if a dense row block still fits
+  if (!off32 && ((1ll << rb) * sz + ((1ll << rb) / 64) * 10 + 256) <= L - (kPartLds64 - kPartLds32))
+    L -= kPartLds64 - kPartLds32;
   P->L = L;
   int sp_log2 = 6;
   while ((1 << sp_log2) < tune.single_part_max) ++sp_log2;
@@ -2273,7 +2177,7 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
   }
   const int32_t sstride = (int32_t)nblk + 1;
   P->src = ProdSrc{A->ir, P->bq_a0, P->bq_alen, nullptr, nullptr, sstride, rb, (int32_t)m,
-                   (A->nnz < (1ll << 29) && !tune.force_off64) ? 1 : 0};
+                   off32 ? 1 : 0, tune.range_chunk == kQChunk ? kQChunk : kQChunkWide};
   BinCfg bc{tune.tiny_max, tune.hash_count_max};
   if (nslots > 0) {
     k_slot_mults<<<grid_for(nslots * 8, 256, (int64_t)cus * 16), 256, 0, st>>>(P->B, P->bq_alen, nslots, P->mults_d,
@@ -2362,13 +2266,17 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
   // hash-counted columns: a launch per table size, so that each runs at its own
   // occupancy; few columns go in one launch sized for the largest (four launches
   // of 13 to 355 columns took 60 us one after the other)
+  ProdSrc hsrc = P->src;
+  hsrc.qchunk = kQChunk;
   const auto count_hash = [&](int bin, int64_t beg, int64_t end) -> int {
     const int log2s = kHashLog2Max - (bin - kBinHash0);
     const size_t lds = ((size_t)4 << log2s) + (nblk <= 1024 ? (size_t)nblk * 4 : 0);
     const int blk = log2s >= 15 ? 1024 : (log2s >= 13 ? std::max(tune.count_threads, 512) : tune.count_threads);
-    const int per_cu = std::max<int>(1, std::min<int>((int)((160 * 1024) / (lds + kCountLds)), 2048 / blk));
-    k_count_hash<<<(unsigned)std::min<int64_t>(end - beg, (int64_t)cus * per_cu), blk, lds, st>>>(
-        P->B, P->src, P->mults_d, P->list, beg, end, multi_begin, multi_end, rb, nblk, blkcnt, P->cnt, err);
+    const int64_t fixed = (off32 ? sizeof(HashRanges<true>) : sizeof(HashRanges<false>)) + 256;
+    const int per_cu = std::max<int>(1, std::min<int>((int)((160 * 1024) / (lds + fixed)), 2048 / blk));
+    const auto kern = off32 ? k_count_hash<true> : k_count_hash<false>;
+    kern<<<(unsigned)std::min<int64_t>(end - beg, (int64_t)cus * per_cu), blk, lds, st>>>(
+        P->B, hsrc, P->mults_d, P->list, beg, end, multi_begin, multi_end, rb, nblk, blkcnt, P->cnt, err);
     SPX_HIP(hipGetLastError());
     return SPX_OK;
   };
@@ -2379,20 +2287,24 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
     if (together) break;
   }
   if (nbitmap > 0) {
-    const size_t lds = ((size_t)1 << clog) / 8 + (((size_t)1 << clog) >> rb) * 4 + 16;
-    const int per_cu = std::max<int>(1, std::min<int>((int)((160 * 1024) / (lds + kCountLds + kWideExtraLds)), 2048 / tune.bitmap_threads));
+    const size_t lds = (((size_t)1 << clog) + 127) / 128 * 16 + (((size_t)1 << clog) >> rb) * 4 + 16;
+    const int64_t fixed = (off32 ? sizeof(BitmapRanges<true>) : sizeof(BitmapRanges<false>)) + 256;
+    const int per_cu = std::max<int>(1, std::min<int>((int)((160 * 1024) / (lds + fixed)), 2048 / tune.bitmap_threads));
     int64_t bgrid = std::min<int64_t>(nbitmap * nchunks, (int64_t)cus * per_cu);
     bgrid = std::max<int64_t>(nchunks, bgrid / nchunks * nchunks);
     // keep the bitmaps for the numeric phase when they fit the cap
-    const int64_t words = ceil_div(m, 64);
+    const int64_t words = ceil_div(m, 128) * 2;  // 16-byte rows
     if (tune.bitmap_store_mb > 0 && (double)nbitmap * words * 8.0 <= (double)tune.bitmap_store_mb * 1048576.0) {
       if (scr.get_n(nbitmap * words, &P->gbm) == SPX_OK)
         P->gbm_words = words;
       else
         P->gbm = nullptr;  // not enough memory: recompute instead
     }
-    k_count_bitmap<<<(unsigned)bgrid, tune.bitmap_threads, lds, st>>>(
-        P->B, P->src, P->mults_d, P->list, P->binoff, m, clog, rb, nblk, blkcnt, (unsigned long long*)P->cnt,
+    ProdSrc bsrc = P->src;
+    bsrc.qchunk = kQChunkWide;
+    const auto kern = off32 ? k_count_bitmap<true> : k_count_bitmap<false>;
+    kern<<<(unsigned)bgrid, tune.bitmap_threads, lds, st>>>(
+        P->B, bsrc, P->mults_d, P->list, P->binoff, m, clog, rb, nblk, blkcnt, (unsigned long long*)P->cnt,
         (uint32_t*)P->gbm, 2 * P->gbm_words, bqctr);
     SPX_HIP(hipGetLastError());
   }
@@ -2428,30 +2340,6 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
   else
     SPX_TRY(summary_sync(P, st, &hs, {{P->off + nslots, 8}, {P->zoff + nslots, 8}}, tail));
   if (hs.err & 4u) return fail(SPX_EUNSUPPORTED, "a row block is too dense for the LDS budget");
-  // Columns with many B entries per product (a tall-skinny right operand):
-  // every part walks all of its column's B entries, so range set-ups
-  // outnumber products.  Then the multi-part launch takes twice as many B
-  // entries per set-up round, and its parts are re-cut for the LDS that the
-  // larger range list leaves, if a dense row block still fits.
-  const bool want_wide = tune.range_chunk == kQChunkWide ||
-                         (tune.range_chunk == 0 && hs.cut_mults > 0 && 2 * hs.setup > hs.cut_mults);
-  if (npos > 0 && want_wide) {
-    const int64_t Lw = L - kWideExtraLds;
-    if (((1ll << rb) * sz + ((1ll << rb) / 64) * 10 + 256) <= Lw) {
-      P->wide = true;
-      P->L = Lw;
-      pc.L = Lw;
-      pc.hash_max = hash_most(Lw, sz);
-      SPX_TRY(fill_i64(reinterpret_cast<int64_t*>(&P->sum->setup), 2, 0, st));  // the cut columns may change
-      k_parts<<<pgrid, 256, 0, st>>>(
-          P->B, pc, pcs, P->list, npos, multi_begin, multi_end, cut_blocks, P->gbm ? nbitmap : 0, P->cnt, P->off, blkcnt, np,
-          nullptr, nullptr, P->mults_d, &P->sum->setup, err);
-      SPX_HIP(hipGetLastError());
-      SPX_TRY(exclusive_scan(LoadI64{np}, npos, poff, scr, st));
-      SPX_TRY(summary_sync(P, st, &hs, {{poff + npos, 8}, {poff + multi_end, 8}}, tail + 2));
-      if (hs.err & 4u) return fail(SPX_EUNSUPPORTED, "a row block is too dense for the LDS budget");
-    }
-  }
   P->mults = (int64_t)hs.mults;
   P->nnz = tail[0];
   P->nzc = tail[1];

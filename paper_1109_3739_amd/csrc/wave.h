@@ -36,7 +36,8 @@ struct ProdSrc {
   int32_t sstride;
   int32_t rbshift;
   int32_t m;
-  int32_t off32;  // 1: positions in A fit 29 bits, loads take 32-bit byte offsets
+  int32_t off32;   // 1: positions in A fit 29 bits, loads take 32-bit byte offsets
+  int32_t qchunk;  // B entries per set-up round of the block-cooperative iteration
 };
 
 __device__ __forceinline__ void wave_sync() {

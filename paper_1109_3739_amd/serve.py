@@ -137,7 +137,7 @@ def gemm_bytes(m: int, k: int, n: int, nnz_a: int, nnz_b: int, mults: int, value
     scratch = (16 * nnz_b + 64 * (n + 1)
                + 12 * (k + 1) + 4 * (nnz_a // 33 + 1) * (nblk + 3)
                + 4 * heavy * nblk
-               + min(counted * ((m + 63) // 64) * 8, bitmap_store_mb << 20)
+               + min(counted * ((m + 127) // 128) * 16, bitmap_store_mb << 20)
                + 2 * 48 * parts
                + 4 * heavy * nblk + 16 * parts + 4 * mults
                + 64 * ((max(n, k) + 2047) // 2048 + 64))
