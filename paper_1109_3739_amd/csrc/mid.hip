@@ -144,48 +144,6 @@ __global__ void __launch_bounds__(256) k_mid_count(Operand B, ProdSrc S, const i
 }
 
 // ------------------------------------------------------------------ numeric
-// Ascending bitonic sort of 64 * R keys, key lane * R + r in register r.
-// Exchanges at distances below R stay in the lane.  Phases whose direction
-// depends on the lane complement the keys of descending lanes instead of
-// selecting, so every in-lane exchange is one minimum and one maximum.
-template <int R, typename K>
-__device__ __forceinline__ void sort_regs(K (&key)[R], int lane) {
-#pragma unroll
-  for (int k = 2; k <= kWave * R; k <<= 1) {
-    const K flip = k >= R && k < kWave * R && (lane & (k / R)) ? ~K(0) : K(0);
-    if (k >= R) {
-#pragma unroll
-      for (int r = 0; r < R; ++r) key[r] ^= flip;
-    }
-#pragma unroll
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      if (j < R) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          if (r & j) continue;
-          const bool up = k >= R || (r & k) == 0;
-          const K x = key[r], y = key[r | j];
-          const K mn = x < y ? x : y, mx = x < y ? y : x;
-          key[r] = up ? mn : mx;
-          key[r | j] = up ? mx : mn;
-        }
-      } else {
-        const bool lower = (lane & (j / R)) == 0;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const K x = key[r], y = xor_lane(x, j / R);
-          const K mn = x < y ? x : y, mx = x < y ? y : x;
-          key[r] = lower ? mn : mx;
-        }
-      }
-    }
-    if (k >= R) {
-#pragma unroll
-      for (int r = 0; r < R; ++r) key[r] ^= flip;
-    }
-  }
-}
-
 // Previous lane's value (DPP wave shift; 0 in lane 0).
 __device__ __forceinline__ int lane_prev(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xF, 0xF, false); }
 

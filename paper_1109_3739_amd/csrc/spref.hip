@@ -6,25 +6,35 @@
 //     so it is a gather of A's columns -- no arithmetic;
 //   * R*(AQ): R has one nonzero per row, so every entry (i, v) of column q
 //     is copied to the rows p with I(p) = i.  The transpose of R in
-//     compressed form (for each row index i the ascending list of p with
-//     I(p) = i) is built once by sorting the pairs (I(p), p).
+//     compressed form (for each row index i the list of p with I(p) = i, in
+//     any order) is built once by a counting scatter over I.
 // Every output entry receives exactly one product (flops(R*A) = nnz(R*A)),
 // so there is no semiring addition and the values are copied bit for bit.
-// Rows of each output column are put in ascending p order by a wave-wide
-// sort (<= 64 entries), an LDS bitonic sort (<= 4096), or, for longer
-// columns, by scanning p in order and probing A(:,J(q)) by binary search.
+// A position p occurs at most once in an output column, so ordering the
+// column's (p, source) pairs by p is all that is left: by a wave in registers
+// (up to 512 entries), by rank in an LDS bitmap over the positions or an LDS
+// sort (up to 4096), or, for longer columns, by scanning p in order and
+// probing A(:,J(q)) by binary search.
 #include <algorithm>
 
 #include "common.h"
 #include "operand.h"
 #include "plan.h"
 #include "scan.h"
+#include "wave.h"
 
 namespace spx {
 
 constexpr int kRefSmall = 64;
+constexpr int kRefMid = 512;
 constexpr int kRefMedium = 4096;
-enum { kClsEmpty = 0, kClsSmall = 1, kClsMedium = 2, kClsLarge = 3, kNumCls = 4 };
+// Output classes; columns without entries are in none.
+enum { kClsSmall = 0, kClsMid = 1, kClsMedium = 2, kClsLarge = 3, kNumCls = 4 };
+// A column gathering more entries of A than kRefWide is never left to one wave.
+constexpr int32_t kRefWide = 4096;
+// Columns gathering more than kRefSplit entries are counted by kRefShare workgroups each.
+constexpr int32_t kRefSplit = 256;
+constexpr int kRefShare = 8;
 
 struct SprefPlan : spx_plan {
   explicit SprefPlan(const spx_ctx* c) : spx_plan(c, kPlanSpref) {}
@@ -32,426 +42,417 @@ struct SprefPlan : spx_plan {
   const int32_t* I = nullptr;
   const int32_t* J = nullptr;
   int64_t lenI = 0, lenJ = 0, nnz = 0;
-  int64_t* rptr = nullptr;   // [m+1] start of row index i in rpos
-  int32_t* rpos = nullptr;   // [lenI] positions p grouped by I(p), ascending
+  uint32_t* rcnt = nullptr;  // [m] positions p with I(p) = i
+  int32_t* rbeg = nullptr;   // [m] where they start in rpos (set where rcnt > 0)
+  int32_t* rpos = nullptr;   // [lenI] positions grouped by I(p)
   int64_t* qa0 = nullptr;    // [lenJ] start of A(:,J(q))
   int32_t* qlen = nullptr;   // [lenJ] its length
   int64_t* cnt = nullptr;    // [lenJ] nnz(B(:,q))
   int64_t* off = nullptr;    // [lenJ+1]
-  int32_t* list = nullptr;   // [lenJ] columns grouped by class
-  int64_t* clsoff = nullptr; // [kNumCls+1]
-  int64_t clsoff_h[kNumCls + 1] = {};
-  int64_t nwide = 0;         // columns gathering more than kRefWide entries of A
-  int32_t* wide = nullptr;   // [lenJ] those columns (the first nwide entries)
+  int32_t* list = nullptr;   // [kNumCls][lenJ] columns of each class, in any order
+  int64_t ncls[kNumCls] = {};
   unsigned* err = nullptr;
 };
 
-// Range checks of I (against m, error bit 1) and J (against n, bit 2) in one pass.
-__global__ void k_check_index(const int32_t* I, int64_t lenI, int64_t m, const int32_t* J, int64_t lenJ, int64_t n,
-                              unsigned* err) {
+// One pass over I and J: range checks (error bits 1 and 2); for every p its
+// rank among the positions seen so far of row I(p); for every q where
+// A(:,J(q)) starts and how long it is, columns longer than kRefSplit also
+// being listed (their counts start from zero).
+__global__ void k_ref_start(Operand A, const int64_t* aux, int64_t chunk, const int32_t* I, int64_t lenI,
+                            const int32_t* J, int64_t lenJ, uint32_t* rcnt, int32_t* rank, int64_t* qa0, int32_t* qlen,
+                            int64_t* cnt, int32_t* wide, unsigned long long* nwide, unsigned* err) {
   for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < lenI + lenJ;
        x += (int64_t)gridDim.x * blockDim.x) {
-    const bool in_i = x < lenI;
-    const int32_t v = in_i ? I[x] : J[x - lenI];
-    if (v < 0 || v >= (in_i ? m : n)) atomicOr(err, in_i ? 1u : 2u);
-  }
-}
-
-__global__ void k_row_hist(const int32_t* I, int64_t lenI, int64_t m, unsigned* rcnt) {
-  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < lenI; p += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t i = I[p];
-    if (i >= 0 && i < m) atomicAdd(&rcnt[i], 1u);
-  }
-}
-
-struct LoadU32 {
-  const unsigned* p;
-  __device__ int64_t operator()(int64_t i) const { return (int64_t)p[i]; }
-};
-
-// Transpose of R: the positions p of each row index i = I(p), ascending,
-// at rpos[rptr[i] ..].  A counting scatter fills each row's slots in any
-// order (its count in rcnt runs down to zero), then every row sorts its
-// own slots: rows of at most kRowShort positions by one thread in place,
-// longer ones by a workgroup (LDS bitonic sort up to kRowLds positions,
-// else one ordered pass over I that keeps the positions of that row).
-constexpr int64_t kRowShort = 16;
-constexpr int kRowLds = 4096;
-
-__global__ void k_scatter_rows(const int32_t* I, int64_t lenI, int64_t m, const int64_t* rptr, unsigned* rcnt,
-                               int32_t* rpos) {
-  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < lenI; p += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t i = I[p];
-    if (i >= 0 && i < m) rpos[rptr[i] + atomicSub(&rcnt[i], 1u) - 1] = (int32_t)p;
-  }
-}
-
-__global__ void k_sort_rows(const int64_t* rptr, int64_t m, int32_t* rpos, int32_t* longs,
-                            unsigned long long* nlong) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t r0 = rptr[i], r1 = rptr[i + 1];
-    if (r1 - r0 > kRowShort) {
-      longs[atomicAdd(nlong, 1ull)] = (int32_t)i;
-      continue;
-    }
-    for (int64_t a = r0 + 1; a < r1; ++a) {  // insertion sort
-      const int32_t x = rpos[a];
-      int64_t b = a - 1;
-      while (b >= r0 && rpos[b] > x) {
-        rpos[b + 1] = rpos[b];
-        --b;
+    if (x < lenI) {
+      const int32_t i = I[x];
+      if (i < 0 || i >= A.m)
+        atomicOr(err, 1u);
+      else
+        rank[x] = (int32_t)atomicAdd(&rcnt[i], 1u);
+    } else {
+      const int64_t q = x - lenI;
+      const int32_t k = J[q];
+      int64_t a0 = 0, a1 = 0;
+      if (k < 0 || k >= A.n)
+        atomicOr(err, 2u);
+      else
+        column_range(A, aux, chunk, k, a0, a1);
+      qa0[q] = a0;
+      qlen[q] = (int32_t)(a1 - a0);
+      if (a1 - a0 > kRefSplit) {
+        cnt[q] = 0;
+        wide[atomicAdd(nwide, 1ull)] = (int32_t)q;
       }
-      rpos[b + 1] = x;
     }
   }
 }
 
-__global__ void __launch_bounds__(256) k_sort_long_rows(const int32_t* I, int64_t lenI, const int64_t* rptr,
-                                                        const int32_t* longs, const unsigned long long* nlong,
-                                                        int32_t* rpos) {
-  __shared__ uint32_t s[kRowLds];
-  __shared__ int64_t red[256 / kWave + 1];
-  const int64_t n = (int64_t)*nlong;
-  for (int64_t w = blockIdx.x; w < n; w += gridDim.x) {
-    const int32_t i = longs[w];
-    const int64_t r0 = rptr[i], len = rptr[i + 1] - r0;
-    if (len <= kRowLds) {  // uniform
-      int p2 = 1;
-      while (p2 < len) p2 <<= 1;
-      for (int t = threadIdx.x; t < p2; t += blockDim.x) s[t] = t < len ? (uint32_t)rpos[r0 + t] : 0xffffffffu;
+// The first position of every row claims the row's slots of rpos, one atomic
+// per workgroup and round.  (A scan over all m row counts read and wrote 50 MB
+// for 2^22 rows, and left 8-byte pointers to look up twice per gathered entry.)
+constexpr int kClaimPer = 4;
+__global__ void __launch_bounds__(256) k_ref_claim(const int32_t* I, int64_t lenI, int64_t m, const uint32_t* rcnt,
+                                                   const int32_t* rank, int32_t* rbeg, unsigned* total) {
+  __shared__ uint32_t red[256 / kWave + 1];
+  __shared__ uint32_t s_base;
+  for (int64_t p0 = (int64_t)blockIdx.x * 256 * kClaimPer; p0 < lenI; p0 += (int64_t)gridDim.x * 256 * kClaimPer) {
+    int32_t i[kClaimPer];
+    uint32_t n[kClaimPer], mine = 0;
+#pragma unroll
+    for (int k = 0; k < kClaimPer; ++k) {
+      const int64_t p = p0 + k * 256 + threadIdx.x;
+      i[k] = p < lenI ? I[p] : -1;
+      if (i[k] >= m) i[k] = -1;
+      if (i[k] >= 0 && rank[p] != 0) i[k] = -1;
+    }
+#pragma unroll
+    for (int k = 0; k < kClaimPer; ++k) {
+      n[k] = i[k] >= 0 ? rcnt[i[k]] : 0;
+      mine += n[k];
+    }
+    uint32_t tot;
+    uint32_t at = block_excl_scan(mine, red, &tot);
+    if (threadIdx.x == 0) s_base = tot ? atomicAdd(total, tot) : 0;
+    __syncthreads();
+    at += s_base;
+#pragma unroll
+    for (int k = 0; k < kClaimPer; ++k) {
+      if (i[k] >= 0) rbeg[i[k]] = (int32_t)at;
+      at += n[k];
+    }
+    __syncthreads();
+  }
+}
+
+__global__ void k_ref_scatter(const int32_t* I, int64_t lenI, int64_t m, const int32_t* rank, const int32_t* rbeg,
+                              int32_t* rpos) {
+  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < lenI; p += (int64_t)gridDim.x * blockDim.x) {
+    const int32_t i = I[p];
+    if (i >= 0 && i < m) rpos[rbeg[i] + rank[p]] = (int32_t)p;
+  }
+}
+
+// nnz(B(:,q)) = sum over the entries (i, v) of A(:,J(q)) of |{p : I(p) = i}|.
+// Groups of 16 lanes take a column each (most gather a few entries); the
+// longer ones (the list wide) are shared by kRefShare workgroups each.
+__global__ void __launch_bounds__(256) k_ref_count(const Operand A, const int64_t* qa0, const int32_t* qlen,
+                                                   const uint32_t* rcnt, int64_t lenJ, const int32_t* wide,
+                                                   const unsigned long long* nwide, unsigned short_blocks,
+                                                   unsigned long long* cnt) {
+  constexpr int G = 16;
+  if (blockIdx.x < short_blocks) {
+    const int gl = lane_id() & (G - 1);
+    const int64_t grp = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / G;
+    const int64_t ngrp = (int64_t)short_blocks * blockDim.x / G;
+    for (int64_t q = grp; q < lenJ; q += ngrp) {
+      const int64_t a0 = qa0[q];
+      const int32_t al = qlen[q];
+      if (al > kRefSplit) continue;
+      int64_t s = 0;
+      for (int32_t e0 = gl; e0 < al; e0 += 4 * G) {  // four rows in flight per lane
+        int32_t i[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) i[k] = e0 + k * G < al ? A.ir[a0 + e0 + k * G] : -1;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) s += i[k] >= 0 ? rcnt[i[k]] : 0u;
+      }
+#pragma unroll
+      for (int d = 1; d < G; d <<= 1) s += __shfl_xor(s, d, G);
+      if (gl == 0) cnt[q] = (unsigned long long)s;
+    }
+  } else {
+    const unsigned lb = blockIdx.x - short_blocks, nlb = gridDim.x - short_blocks;  // nlb: a multiple of kRefShare
+    const int64_t n = (int64_t)*nwide;
+    const int32_t step = kRefShare * 256;
+    for (int64_t w = lb / kRefShare; w < n; w += nlb / kRefShare) {
+      const int32_t q = wide[w];
+      const int64_t a0 = qa0[q];
+      const int32_t al = qlen[q];
+      int64_t s = 0;
+      for (int64_t e0 = (int64_t)(lb % kRefShare) * 256 + threadIdx.x; e0 < al; e0 += 4 * step) {
+        int32_t i[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) i[k] = e0 + (int64_t)k * step < al ? A.ir[a0 + e0 + (int64_t)k * step] : -1;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) s += i[k] >= 0 ? rcnt[i[k]] : 0u;
+      }
+      s = wave_sum(s);
+      if (lane_id() == 0 && s) atomicAdd(&cnt[q], (unsigned long long)s);
+    }
+  }
+}
+
+// Class of a column with s > 0 outputs gathering al entries of A.
+__device__ __forceinline__ int ref_class(int64_t s, int32_t al) {
+  if (s > kRefMedium) return kClsLarge;
+  return al > kRefWide || s > kRefMid ? kClsMedium : s > kRefSmall ? kClsMid : kClsSmall;
+}
+
+// Column pointers (exclusive scan of cnt; carry: the scanned block sums, else
+// sums: the block sums) and the class lists in one pass.  The class counts of
+// a thread's kScanItems columns are packed in 16-bit fields, so one workgroup
+// scan ranks every column in its class and one atomic per class and workgroup
+// claims its slots.
+__global__ void __launch_bounds__(kScanThreads) k_ref_apply(const int64_t* cnt, const int32_t* qlen, int64_t n,
+                                                            const int64_t* carry, const int64_t* sums, int64_t* off,
+                                                            unsigned long long* ncls, int32_t* list) {
+  static_assert(kScanTile < (1 << 16), "16-bit class counts");
+  __shared__ int64_t red[kScanThreads / kWave + 1];
+  __shared__ uint64_t redc[kScanThreads / kWave + 1];
+  __shared__ unsigned long long s_base[kNumCls];
+  const int64_t cin = carry ? carry[blockIdx.x] : carry_from_sums(sums, blockIdx.x, red);
+  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
+  int64_t v[kScanItems];
+  int c[kScanItems];
+  int64_t s = 0;
+  uint64_t mine = 0;
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) {
+    v[k] = base + k < n ? cnt[base + k] : 0;
+    c[k] = v[k] > 0 ? ref_class(v[k], qlen[base + k]) : -1;
+    s += v[k];
+    if (c[k] >= 0) mine += 1ull << (16 * c[k]);
+  }
+  int64_t total;
+  uint64_t tot;
+  int64_t run = block_excl_scan(s, red, &total) + cin;
+  uint64_t ex = block_excl_scan(mine, redc, &tot);
+  if (threadIdx.x < kNumCls) {
+    const unsigned long long x = (tot >> (16 * threadIdx.x)) & 0xffffull;
+    s_base[threadIdx.x] = x ? atomicAdd(&ncls[threadIdx.x], x) : 0;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) {
+    if (base + k < n) off[base + k] = run;
+    run += v[k];
+    if (c[k] >= 0) {
+      list[c[k] * n + (int64_t)s_base[c[k]] + (int64_t)((ex >> (16 * c[k])) & 0xffffull)] = (int32_t)(base + k);
+      ex += 1ull << (16 * c[k]);
+    }
+  }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == blockDim.x - 1) off[n] = run;
+}
+
+// ------------------------------------------------------------------ one wave per column
+// Gathers the column's (p, source) pairs into the wave's LDS: first the
+// entries of A whose row is selected (a few in a hundred when I is short), 256
+// looked up at a time, then their positions.  Writes at most CAP pairs to p[]
+// and e[] (e: offset in A's column) and returns their number; hi and he are
+// scratch of CAP entries.
+template <int CAP>
+__device__ __forceinline__ int gather_pairs(const Operand& A, int64_t a0, int32_t al, const uint32_t* rcnt,
+                                            const int32_t* rbeg, const int32_t* rpos, int32_t* hi, int32_t* he,
+                                            int32_t* p, int32_t* e) {
+  const int lane = lane_id();
+  int nh = 0;
+  for (int32_t e0 = 0; e0 < al; e0 += 4 * kWave) {
+    int32_t i[4];
+    uint32_t rc[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int32_t x = e0 + k * kWave + lane;
+      i[k] = x < al ? A.ir[a0 + x] : -1;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) rc[k] = i[k] >= 0 ? rcnt[i[k]] : 0u;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint64_t hit = __ballot(rc[k] != 0);
+      const int h = nh + __popcll(hit & lanemask_lt());
+      if (rc[k] && h < CAP) {
+        hi[h] = i[k];
+        he[h] = e0 + k * kWave + lane;
+      }
+      nh += __popcll(hit);
+    }
+  }
+  if (nh > CAP) nh = CAP;  // cannot happen: every selected entry has an output
+  wave_sync();
+  int total = 0;
+  for (int h0 = 0; h0 < nh; h0 += kWave) {
+    const int h = h0 + lane;
+    const int32_t i = h < nh ? hi[h] : 0, x = h < nh ? he[h] : 0;
+    const int n = h < nh ? (int)rcnt[i] : 0;
+    const int32_t beg = h < nh ? rbeg[i] : 0;
+    const int incl = wave_incl_scan(n);
+    for (int r = 0; r < n; ++r) {
+      const int slot = total + incl - n + r;
+      if (slot < CAP) {
+        p[slot] = rpos[beg + r];
+        e[slot] = x;
+      }
+    }
+    total += __builtin_amdgcn_readlane(incl, kWave - 1);
+  }
+  wave_sync();
+  return total < CAP ? total : CAP;
+}
+
+// Orders the pairs by p (K: 32-bit keys when p leaves room for the slot) and
+// writes the column; hi and he take them in order, for coalesced stores.
+template <int R, typename K>
+__device__ __forceinline__ void write_sorted(const Operand& A, int64_t a0, int n, const int32_t* p, const int32_t* e,
+                                             int32_t* hi, int32_t* he, int64_t o, int vb, int32_t* bir, void* bnum) {
+  constexpr int kLog = R == 1 ? 6 : R == 2 ? 7 : R == 4 ? 8 : 9;
+  static_assert((1 << kLog) == kWave * R, "slots fill the key's low bits");
+  const int lane = lane_id();
+  K key[R];
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    const int i = k * kWave + lane;
+    key[k] = i < n ? ((K)(uint32_t)p[i] << kLog) | (K)i : ~K(0);
+  }
+  sort_regs<R, K>(key, lane);
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    const int i = lane * R + k;
+    if (i < n) {
+      hi[i] = (int32_t)(key[k] >> kLog);
+      he[i] = e[(int)(key[k] & (kWave * R - 1))];
+    }
+  }
+  wave_sync();
+  for (int i = lane; i < n; i += kWave) {
+    bir[o + i] = hi[i];
+    copy_value(A.num, a0 + he[i], bnum, o + i, vb);
+  }
+  wave_sync();  // the LDS is rewritten for the next column
+}
+
+// CLS: the small columns (at most 64 entries) or the mid ones (at most 512).
+template <int CLS>
+__global__ void __launch_bounds__(256) k_ref_wave(Operand A, const int64_t* qa0, const int32_t* qlen,
+                                                  const uint32_t* rcnt, const int32_t* rbeg, const int32_t* rpos,
+                                                  const int32_t* list, int64_t n, int64_t lenI, const int64_t* off,
+                                                  int vb, int32_t* bir, void* bnum) {
+  constexpr int CAP = CLS == kClsSmall ? kRefSmall : kRefMid;
+  __shared__ int32_t s_hi[4][CAP], s_he[4][CAP], s_p[4][CAP], s_e[4][CAP];
+  const int w = threadIdx.x / kWave;
+  int32_t *hi = s_hi[w], *he = s_he[w], *p = s_p[w], *e = s_e[w];
+  const bool narrow = lenI <= (1ll << 32) / CAP;
+  for (int64_t pos = (int64_t)blockIdx.x * 4 + w; pos < n; pos += (int64_t)gridDim.x * 4) {
+    const int32_t q = list[pos];
+    const int64_t a0 = qa0[q], o = off[q];
+    const int c = gather_pairs<CAP>(A, a0, qlen[q], rcnt, rbeg, rpos, hi, he, p, e);
+    if constexpr (CLS == kClsSmall) {
+      if (narrow)
+        write_sorted<1, uint32_t>(A, a0, c, p, e, hi, he, o, vb, bir, bnum);
+      else
+        write_sorted<1, uint64_t>(A, a0, c, p, e, hi, he, o, vb, bir, bnum);
+    } else if (!narrow) {
+      write_sorted<8, uint64_t>(A, a0, c, p, e, hi, he, o, vb, bir, bnum);
+    } else if (c <= 128) {
+      write_sorted<2, uint32_t>(A, a0, c, p, e, hi, he, o, vb, bir, bnum);
+    } else if (c <= 256) {
+      write_sorted<4, uint32_t>(A, a0, c, p, e, hi, he, o, vb, bir, bnum);
+    } else {
+      write_sorted<8, uint32_t>(A, a0, c, p, e, hi, he, o, vb, bir, bnum);
+    }
+  }
+}
+
+// ------------------------------------------------------------------ one workgroup per column
+// Columns of at most 4096 entries that gather too many entries of A, or have
+// too many outputs, for a wave.  The pairs are collected in LDS in any order
+// (slots by an LDS counter, so no thread waits for another while gathering:
+// with a block scan per round a hub column of 38312 entries took 150 us).
+// Their ranks come from a bitmap over the positions when it fits (lenI up to
+// kRankBits: one mark per pair and a popcount prefix), else from an LDS sort.
+constexpr int kRefThreads = 1024;
+constexpr int64_t kRankBits = 1 << 19;
+
+__global__ void __launch_bounds__(kRefThreads) k_ref_medium(Operand A, const int64_t* qa0, const int32_t* qlen,
+                                                            const uint32_t* rcnt, const int32_t* rbeg,
+                                                            const int32_t* rpos, const int32_t* list, int64_t n,
+                                                            int64_t lenI, const int64_t* off, int vb, int32_t* bir,
+                                                            void* bnum) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  __shared__ unsigned s_n;
+  __shared__ int32_t red[kRefThreads / kWave + 1];
+  const bool ranked = lenI <= kRankBits;
+  const int W = (int)((lenI + 63) >> 6);  // words of the bitmap
+  int32_t* s_e = (int32_t*)lds;                             // [kRefMedium] offset in A's column
+  int32_t* s_p = s_e + kRefMedium;                          // ranked: [kRefMedium] position
+  uint64_t* bm = (uint64_t*)(s_p + kRefMedium);             // ranked: [W] bitmap, then [W] 16-bit prefixes
+  uint16_t* pre = (uint16_t*)(bm + W);
+  uint64_t* s_key = (uint64_t*)(s_e + kRefMedium);          // else: [kRefMedium] (position, slot)
+  for (int64_t pos = blockIdx.x; pos < n; pos += gridDim.x) {
+    const int32_t q = list[pos];
+    const int64_t a0 = qa0[q], o = off[q];
+    const int32_t al = qlen[q];
+    if (threadIdx.x == 0) s_n = 0;
+    if (ranked)
+      for (int i = threadIdx.x; i < W; i += kRefThreads) bm[i] = 0;
+    __syncthreads();
+    for (int64_t e0 = threadIdx.x; e0 < al; e0 += 4 * kRefThreads) {
+      int32_t i[4];
+      uint32_t rc[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) i[k] = e0 + k * kRefThreads < al ? A.ir[a0 + e0 + k * kRefThreads] : -1;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) rc[k] = i[k] >= 0 ? rcnt[i[k]] : 0u;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (rc[k] == 0) continue;
+        const unsigned at = atomicAdd(&s_n, rc[k]);
+        const int32_t beg = rbeg[i[k]];
+        for (uint32_t r = 0; r < rc[k] && at + r < (unsigned)kRefMedium; ++r) {
+          const int32_t p = rpos[beg + r];
+          s_e[at + r] = (int32_t)(e0 + k * kRefThreads);
+          if (ranked) {
+            s_p[at + r] = p;
+            atomicOr((unsigned long long*)&bm[p >> 6], 1ull << (p & 63));
+          } else {
+            s_key[at + r] = ((uint64_t)(uint32_t)p << 32) | (at + r);
+          }
+        }
+      }
+    }
+    __syncthreads();
+    const int c = s_n < (unsigned)kRefMedium ? (int)s_n : kRefMedium;
+    if (ranked) {
+      const int per = (W + kRefThreads - 1) / kRefThreads;
+      const int w0 = (int)threadIdx.x * per, w1 = w0 + per < W ? w0 + per : W;
+      int32_t s = 0, tot;
+      for (int i = w0; i < w1; ++i) s += __popcll(bm[i]);
+      int32_t run = block_excl_scan1(s, red, &tot);
+      for (int i = w0; i < w1; ++i) {
+        pre[i] = (uint16_t)run;
+        run += __popcll(bm[i]);
+      }
+      __syncthreads();
+      for (int s2 = threadIdx.x; s2 < c; s2 += kRefThreads) {
+        const int32_t p = s_p[s2];
+        const int rank = pre[p >> 6] + __popcll(bm[p >> 6] & ((1ull << (p & 63)) - 1ull));
+        bir[o + rank] = p;
+        copy_value(A.num, a0 + s_e[s2], bnum, o + rank, vb);
+      }
+    } else {
+      int p2 = 64;
+      while (p2 < c) p2 <<= 1;
+      for (int s = c + (int)threadIdx.x; s < p2; s += kRefThreads) s_key[s] = ~0ull;
       __syncthreads();
       for (int k = 2; k <= p2; k <<= 1) {
         for (int j = k >> 1; j > 0; j >>= 1) {
-          for (int t = threadIdx.x; t < (p2 >> 1); t += blockDim.x) {
+          for (int t = threadIdx.x; t < (p2 >> 1); t += kRefThreads) {
             const int lo = 2 * t - (t & (j - 1));
             const int hi = lo + j;
             const bool asc = (lo & k) == 0;
-            const uint32_t x = s[lo], y = s[hi];
+            const uint64_t x = s_key[lo], y = s_key[hi];
             if ((x > y) == asc) {
-              s[lo] = y;
-              s[hi] = x;
+              s_key[lo] = y;
+              s_key[hi] = x;
             }
           }
           __syncthreads();
         }
       }
-      for (int t = threadIdx.x; t < len; t += blockDim.x) rpos[r0 + t] = (int32_t)s[t];
-      __syncthreads();
-    } else {
-      int64_t run = 0;
-      for (int64_t pc = 0; pc < lenI; pc += blockDim.x) {
-        const int64_t p = pc + threadIdx.x;
-        const int64_t f = p < lenI && I[p] == i;
-        int64_t tot;
-        const int64_t ex = block_excl_scan(f, red, &tot);
-        if (f) rpos[r0 + run + ex] = (int32_t)p;
-        run += tot;
+      for (int s = threadIdx.x; s < c; s += kRefThreads) {
+        const uint64_t k = s_key[s];
+        bir[o + s] = (int32_t)(k >> 32);
+        copy_value(A.num, a0 + s_e[k & 0xffffffffu], bnum, o + s, vb);
       }
-    }
-  }
-}
-
-// Columns gathering more entries of A than this are counted (and, with at
-// most kRefMedium outputs, extracted) by 1024-thread workgroups, so that a
-// hub column of A is not left to one wave or one small workgroup.
-constexpr int32_t kRefWide = 4096;
-
-// Where each gathered column A(:,J(q)) starts and how long it is; columns
-// longer than kRefWide are also appended to the wide list.
-__global__ void k_col_info(Operand A, const int64_t* aux, int64_t chunk, const int32_t* J, int64_t lenJ, int64_t* qa0,
-                           int32_t* qlen, int32_t* wide, unsigned long long* nwide) {
-  for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < lenJ; q += (int64_t)gridDim.x * blockDim.x) {
-    int64_t a0 = 0, a1 = 0;
-    const int32_t k = J[q];
-    if (k >= 0 && k < A.n) column_range(A, aux, chunk, k, a0, a1);
-    qa0[q] = a0;
-    qlen[q] = (int32_t)(a1 - a0);
-    if (a1 - a0 > kRefWide) wide[atomicAdd(nwide, 1ull)] = (int32_t)q;
-  }
-}
-
-// nnz(B(:,q)) = sum over the entries (i, v) of A(:,J(q)) of |{p : I(p) = i}|;
-// one wave per column.  Also classifies the column.
-
-// Output class of a column with s outputs gathering al entries of A (a wide
-// column with few outputs still goes to the workgroup path).
-__device__ __forceinline__ int ref_class(int64_t s, int32_t al) {
-  return s == 0 ? kClsEmpty : (s <= kRefSmall && al <= kRefWide) ? kClsSmall : s <= kRefMedium ? kClsMedium : kClsLarge;
-}
-
-__global__ void k_ref_count(const Operand A, const int64_t* qa0, const int32_t* qlen, const int64_t* rptr, int64_t lenJ,
-                            int64_t* cnt, unsigned long long* clscount) {
-  const int lane = lane_id();
-  const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave;
-  const int64_t nw = (int64_t)gridDim.x * blockDim.x / kWave;
-  unsigned long long n0 = 0, n1 = 0, n2 = 0, n3 = 0;  // class counts of this wave's columns
-  for (int64_t q = wave; q < lenJ; q += nw) {
-    const int64_t a0 = qa0[q];
-    const int32_t al = qlen[q];
-    if (al > kRefWide) continue;  // uniform: k_ref_count_wide's column
-    int64_t s = 0;
-    for (int32_t e0 = 0; e0 < al; e0 += 4 * kWave) {  // four rows in flight per lane
-      int32_t i[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int32_t e = e0 + k * kWave + lane;
-        i[k] = e < al ? A.ir[a0 + e] : -1;
-      }
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (i[k] >= 0) s += rptr[i[k] + 1] - rptr[i[k]];
-    }
-    s = wave_sum(s);
-    const int c = ref_class(s, al);
-    n0 += c == kClsEmpty;
-    n1 += c == kClsSmall;
-    n2 += c == kClsMedium;
-    n3 += c == kClsLarge;
-    if (lane == 0) cnt[q] = s;
-  }
-  __shared__ unsigned long long s_cls[kNumCls];  // the workgroup's class counts
-  if (threadIdx.x < kNumCls) s_cls[threadIdx.x] = 0;
-  __syncthreads();
-  if (lane == 0) {
-    if (n0) atomicAdd(&s_cls[kClsEmpty], n0);
-    if (n1) atomicAdd(&s_cls[kClsSmall], n1);
-    if (n2) atomicAdd(&s_cls[kClsMedium], n2);
-    if (n3) atomicAdd(&s_cls[kClsLarge], n3);
-  }
-  __syncthreads();
-  if (threadIdx.x < kNumCls && s_cls[threadIdx.x]) atomicAdd(&clscount[threadIdx.x], s_cls[threadIdx.x]);
-}
-
-// The wide columns' counts: one 1024-thread workgroup per column, four rows
-// in flight per thread.
-__global__ void __launch_bounds__(1024) k_ref_count_wide(const Operand A, const int64_t* qa0, const int32_t* qlen,
-                                                         const int64_t* rptr, const int32_t* wide,
-                                                         const unsigned long long* nwide, int64_t* cnt,
-                                                         unsigned long long* clscount) {
-  __shared__ int64_t red[1024 / kWave + 1];
-  const int64_t n = (int64_t)*nwide;
-  for (int64_t w = blockIdx.x; w < n; w += gridDim.x) {
-    const int32_t q = wide[w];
-    const int64_t a0 = qa0[q];
-    const int32_t al = qlen[q];
-    int64_t s = 0;
-    for (int32_t e0 = 0; e0 < al; e0 += 4 * (int32_t)blockDim.x) {
-      int32_t i[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int32_t e = e0 + k * (int32_t)blockDim.x + (int32_t)threadIdx.x;
-        i[k] = e < al ? A.ir[a0 + e] : -1;
-      }
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (i[k] >= 0) s += rptr[i[k] + 1] - rptr[i[k]];
-    }
-    int64_t tot;
-    block_excl_scan(s, red, &tot);
-    if (threadIdx.x == 0) {
-      cnt[q] = tot;
-      atomicAdd(&clscount[ref_class(tot, al)], 1ull);
-    }
-  }
-}
-
-// Columns grouped by class (any order inside a class).  A thread takes
-// kClsPer consecutive columns; the class counts of a thread are packed in
-// 16-bit fields, so one workgroup scan ranks every column in its class and
-// one atomic per class and workgroup claims the workgroup's slots.  Every
-// workgroup derives the class offsets from the counts itself; the first one
-// also stores them (clsoff, kNumCls + 1 entries).  fill must be zero.
-constexpr int kClsPer = 8;
-__global__ void __launch_bounds__(256) k_cls_fill(const int64_t* cnt, const int32_t* qlen, int64_t lenJ,
-                                                  const unsigned long long* clscount, int64_t* clsoff,
-                                                  unsigned long long* fill, int32_t* list) {
-  __shared__ uint64_t red[256 / kWave + 1];
-  __shared__ unsigned long long s_base[kNumCls];
-  __shared__ int64_t s_off[kNumCls + 1];
-  if (threadIdx.x == 0) {
-    int64_t run = 0;
-    for (int c = 0; c < kNumCls; ++c) {
-      s_off[c] = run;
-      run += (int64_t)clscount[c];
-    }
-    s_off[kNumCls] = run;
-  }
-  __syncthreads();
-  if (blockIdx.x == 0 && threadIdx.x <= kNumCls) clsoff[threadIdx.x] = s_off[threadIdx.x];
-  for (int64_t q0 = (int64_t)blockIdx.x * 256 * kClsPer; q0 < lenJ; q0 += (int64_t)gridDim.x * 256 * kClsPer) {
-    const int64_t qt = q0 + (int64_t)threadIdx.x * kClsPer;
-    int c[kClsPer];
-    uint64_t mine = 0;
-#pragma unroll
-    for (int k = 0; k < kClsPer; ++k) {
-      c[k] = qt + k < lenJ ? ref_class(cnt[qt + k], qlen[qt + k]) : -1;
-      if (c[k] >= 0) mine += 1ull << (16 * c[k]);
-    }
-    uint64_t tot;
-    uint64_t ex = block_excl_scan(mine, red, &tot);
-    if (threadIdx.x < kNumCls) {
-      const unsigned long long n = (tot >> (16 * threadIdx.x)) & 0xffffull;
-      s_base[threadIdx.x] = n ? atomicAdd(&fill[threadIdx.x], n) : 0;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < kClsPer; ++k) {
-      if (c[k] < 0) continue;
-      const int64_t slot = (int64_t)s_base[c[k]] + (int64_t)((ex >> (16 * c[k])) & 0xffffull);
-      list[s_off[c[k]] + slot] = (int32_t)(qt + k);
-      ex += 1ull << (16 * c[k]);
-    }
-    __syncthreads();
-  }
-}
-
-__device__ __forceinline__ void wsync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-__device__ __forceinline__ uint64_t wave_sort_keys(uint64_t key) {
-  const int lane = lane_id();
-#pragma unroll
-  for (int k = 2; k <= kWave; k <<= 1) {
-#pragma unroll
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      const uint64_t other = xor_lane(key, j);
-      const bool up = (lane & k) == 0;
-      const bool lower = (lane & j) == 0;
-      const uint64_t mn = other < key ? other : key;
-      const uint64_t mx = other < key ? key : other;
-      key = (lower == up) ? mn : mx;
-    }
-  }
-  return key;
-}
-
-// Columns with at most 64 entries: one wave gathers (p, source) pairs into
-// LDS, sorts them by p across its lanes and writes the column.
-__global__ void __launch_bounds__(256) k_ref_small(Operand A, const int64_t* qa0, const int32_t* qlen,
-                                                   const int64_t* rptr, const int32_t* rpos, const int32_t* list,
-                                                   const int64_t* clsoff, const int64_t* off, int vb, int32_t* bir,
-                                                   void* bnum) {
-  __shared__ int32_t s_p[4][kWave];
-  __shared__ int64_t s_e[4][kWave];
-  const int w = threadIdx.x / kWave, lane = lane_id();
-  const int64_t beg = clsoff[kClsSmall], end = clsoff[kClsSmall + 1];
-  for (int64_t pos = beg + (int64_t)blockIdx.x * 4 + w; pos < end; pos += (int64_t)gridDim.x * 4) {
-    const int32_t q = list[pos];
-    const int64_t a0 = qa0[q];
-    const int32_t al = qlen[q];
-    int total = 0;
-    for (int32_t ec = 0; ec < al; ec += kWave) {
-      const int32_t e = ec + lane;
-      int32_t i = 0;
-      int rc = 0;
-      if (e < al) {
-        i = A.ir[a0 + e];
-        rc = (int)(rptr[i + 1] - rptr[i]);
-      }
-      const int incl = wave_incl_scan(rc);
-      const int excl = incl - rc;
-      for (int r = 0; r < rc; ++r) {
-        const int slot = total + excl + r;
-        if (slot < kWave) {
-          s_p[w][slot] = rpos[rptr[i] + r];
-          s_e[w][slot] = a0 + e;
-        }
-      }
-      total += __shfl(incl, kWave - 1);
-    }
-    if (total > kWave) total = kWave;
-    wsync();
-    uint64_t key = lane < total ? ((uint64_t)(uint32_t)s_p[w][lane] << 32) | (uint32_t)lane : ~0ull;
-    key = wave_sort_keys(key);
-    if (lane < total) {
-      const int slot = (int)(key & 0xffffffffu);
-      const int64_t o = off[q] + lane;
-      bir[o] = (int32_t)(key >> 32);
-      copy_value(A.num, s_e[w][slot], bnum, o, vb);
-    }
-    wsync();
-  }
-}
-
-// Columns with at most 4096 entries: one workgroup, LDS bitonic sort.  The
-// 256-thread variant walks the medium class list and leaves out its wide
-// columns; the 1024-thread variant walks the list of wide columns (nwide
-// entries) and takes those of the medium class, so its workgroups share the
-// wide columns evenly.
-template <int BLOCK>
-__global__ void __launch_bounds__(BLOCK) k_ref_medium(Operand A, const int64_t* qa0, const int32_t* qlen,
-                                                      const int64_t* rptr, const int32_t* rpos, const int32_t* list,
-                                                      const int32_t* wide, int64_t nwide, const int64_t* clsoff,
-                                                      const int64_t* cnt, const int64_t* off, int vb, int32_t* bir,
-                                                      void* bnum) {
-  constexpr bool kWide = BLOCK > 256;
-  __shared__ uint64_t s_key[kRefMedium];
-  __shared__ int64_t s_e[kRefMedium];
-  __shared__ int64_t red[BLOCK / kWave + 1];
-  const int64_t beg = kWide ? 0 : clsoff[kClsMedium], end = kWide ? nwide : clsoff[kClsMedium + 1];
-  for (int64_t pos = beg + blockIdx.x; pos < end; pos += gridDim.x) {
-    const int32_t q = kWide ? wide[pos] : list[pos];
-    const int64_t a0 = qa0[q];
-    const int32_t al = qlen[q];
-    const int64_t c64 = cnt[q];
-    // uniform: a column of the other variant (or, in the wide list, of another class)
-    if (kWide ? (c64 == 0 || c64 > kRefMedium) : al > kRefWide) continue;
-    const int c = (int)c64;
-    int64_t total = 0;
-    // four consecutive gathered entries per thread and round, their loads in flight together
-    for (int32_t ec = 0; ec < al; ec += 4 * (int32_t)blockDim.x) {
-      const int32_t e0 = ec + 4 * (int32_t)threadIdx.x;
-      int32_t i[4];
-      int64_t rb[4], rc[4];
-      int64_t mine = 0;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) i[k] = e0 + k < al ? A.ir[a0 + e0 + k] : -1;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        rb[k] = i[k] >= 0 ? rptr[i[k]] : 0;
-        rc[k] = i[k] >= 0 ? rptr[i[k] + 1] - rb[k] : 0;
-        mine += rc[k];
-      }
-      int64_t ctot;
-      int64_t slot = total + block_excl_scan(mine, red, &ctot);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        for (int64_t r = 0; r < rc[k]; ++r, ++slot) {
-          if (slot < kRefMedium) {
-            s_key[slot] = ((uint64_t)(uint32_t)rpos[rb[k] + r] << 32) | (uint32_t)slot;
-            s_e[slot] = a0 + e0 + k;
-          }
-        }
-      }
-      total += ctot;
-    }
-    int p2 = 64;
-    while (p2 < c) p2 <<= 1;
-    for (int s = c + threadIdx.x; s < p2; s += blockDim.x) s_key[s] = ~0ull;
-    __syncthreads();
-    for (int k = 2; k <= p2; k <<= 1) {
-      for (int j = k >> 1; j > 0; j >>= 1) {
-        for (int t = threadIdx.x; t < (p2 >> 1); t += blockDim.x) {
-          const int lo = 2 * t - (t & (j - 1));
-          const int hi = lo + j;
-          const bool asc = (lo & k) == 0;
-          const uint64_t x = s_key[lo], y = s_key[hi];
-          if ((x > y) == asc) {
-            s_key[lo] = y;
-            s_key[hi] = x;
-          }
-        }
-        __syncthreads();
-      }
-    }
-    for (int s = threadIdx.x; s < c; s += blockDim.x) {
-      const uint64_t k = s_key[s];
-      const int64_t o = off[q] + s;
-      bir[o] = (int32_t)(k >> 32);
-      copy_value(A.num, s_e[k & 0xffffffffu], bnum, o, vb);
     }
     __syncthreads();
   }
@@ -460,12 +461,10 @@ __global__ void __launch_bounds__(BLOCK) k_ref_medium(Operand A, const int64_t* 
 // Long columns: walk p = 0..lenI-1 in order; B(p,q) exists iff row I(p)
 // is stored in A(:,J(q)) (binary search).  Output is in p order directly.
 __global__ void __launch_bounds__(1024) k_ref_large(Operand A, const int64_t* qa0, const int32_t* qlen,
-                                                    const int32_t* I, int64_t lenI, const int32_t* list,
-                                                    const int64_t* clsoff, const int64_t* off, int vb, int32_t* bir,
-                                                    void* bnum) {
+                                                    const int32_t* I, int64_t lenI, const int32_t* list, int64_t n,
+                                                    const int64_t* off, int vb, int32_t* bir, void* bnum) {
   __shared__ int64_t red[1024 / kWave + 1];
-  const int64_t beg = clsoff[kClsLarge], end = clsoff[kClsLarge + 1];
-  for (int64_t pos = beg + blockIdx.x; pos < end; pos += gridDim.x) {
+  for (int64_t pos = blockIdx.x; pos < n; pos += gridDim.x) {
     const int32_t q = list[pos];
     const int64_t a0 = qa0[q];
     const int32_t al = qlen[q];
@@ -530,66 +529,54 @@ extern "C" int spx_spref_plan(const spx_ctx* ctx, const spx_mat* A, const int32_
   P->lenJ = lenJ;
   const int64_t m = A->m;
   const int cus = device_cu_count();
-  unsigned* rcnt = nullptr;
-  unsigned long long *clscount = nullptr, *fill = nullptr, *nlong = nullptr;
-  int32_t* longs = nullptr;  // rows with more than kRowShort positions (at most lenI / 17)
-  SPX_TRY(scr.get_many({Scratch::part(&nlong, 2), Scratch::part(&longs, lenI / (kRowShort + 1) + 1),
-                        Scratch::part(&P->wide, lenJ),
-                        Scratch::part(&P->err, 4), Scratch::part(&rcnt, m + 1), Scratch::part(&P->rptr, m + 1),
-                        Scratch::part(&P->rpos, lenI), Scratch::part(&P->qa0, lenJ), Scratch::part(&P->qlen, lenJ),
-                        Scratch::part(&P->cnt, lenJ), Scratch::part(&P->off, lenJ + 1), Scratch::part(&P->list, lenJ),
-                        Scratch::part(&P->clsoff, kNumCls + 1), Scratch::part(&clscount, kNumCls),
-                        Scratch::part(&fill, kNumCls)}));
-  // error bits, long rows and wide columns, class counts and fills; the class
-  // offsets stay zero when J is empty (k_cls_fill writes them otherwise)
-  SPX_TRY(zero_words(st, {{P->err, 2}, {nlong, 2}, {clscount, kNumCls}, {fill, kNumCls}, {P->clsoff, kNumCls + 1}}));
-  unsigned long long* nwide = nlong + 1;
-  if (lenI + lenJ > 0) {
-    k_check_index<<<grid_for(lenI + lenJ, 256, 4096), 256, 0, st>>>(I, lenI, m, J, lenJ, A->n, P->err);
-    SPX_HIP(hipGetLastError());
-  }
-  // transpose of R: rows of I grouped by index, positions ascending
-  SPX_TRY(fill_u32(rcnt, m + 1, 0, st));
-  if (lenI > 0) {
-    k_row_hist<<<grid_for(lenI, 256, 4096), 256, 0, st>>>(I, lenI, m, rcnt);
-    SPX_HIP(hipGetLastError());
-  }
-  SPX_TRY(exclusive_scan(LoadU32{rcnt}, m, P->rptr, scr, st));
-  if (lenI > 0) {
-    k_scatter_rows<<<grid_for(lenI, 256, 4096), 256, 0, st>>>(I, lenI, m, P->rptr, rcnt, P->rpos);
-    SPX_HIP(hipGetLastError());
-    k_sort_rows<<<grid_for(m, 256, 4096), 256, 0, st>>>(P->rptr, m, P->rpos, longs, nlong);
-    SPX_HIP(hipGetLastError());
-    k_sort_long_rows<<<(unsigned)(cus * 2), 256, 0, st>>>(I, lenI, P->rptr, longs, nlong, P->rpos);
-    SPX_HIP(hipGetLastError());
-  }
-  // A*Q: the columns J(q) of A
+  unsigned long long *ncls = nullptr, *nwide = nullptr;
+  int32_t *rank = nullptr, *wide = nullptr;
+  unsigned* claimed = nullptr;
+  const int64_t nblocks = ceil_div(lenJ, kScanTile);
+  int64_t *sums = nullptr, *carry = nullptr;
+  SPX_TRY(scr.get_many({Scratch::part(&nwide, 1), Scratch::part(&ncls, kNumCls), Scratch::part(&P->err, 4),
+                        Scratch::part(&claimed, 4), Scratch::part(&P->rcnt, m + 1), Scratch::part(&P->rbeg, m),
+                        Scratch::part(&rank, lenI), Scratch::part(&P->rpos, lenI), Scratch::part(&P->qa0, lenJ),
+                        Scratch::part(&P->qlen, lenJ), Scratch::part(&P->cnt, lenJ), Scratch::part(&P->off, lenJ + 1),
+                        Scratch::part(&P->list, kNumCls * lenJ), Scratch::part(&wide, lenJ),
+                        Scratch::part(&sums, nblocks)}));
+  SPX_TRY(zero_words(st, {{nwide, 1}, {ncls, kNumCls}, {P->err, 2}, {claimed, 2}, {P->rcnt, ceil_div(m, 2)},
+                          {P->off, 1}}));
   int64_t *aux = nullptr, chunk = 1;
   SPX_TRY(build_aux(P->A, scr, st, &aux, &chunk));
-  if (lenJ > 0) {
-    k_col_info<<<grid_for(lenJ, 256, 4096), 256, 0, st>>>(P->A, aux, chunk, J, lenJ, P->qa0, P->qlen, P->wide,
-                                                          nwide);
+  if (lenI + lenJ > 0) {
+    k_ref_start<<<grid_for(lenI + lenJ, 256, 4096), 256, 0, st>>>(P->A, aux, chunk, I, lenI, J, lenJ, P->rcnt, rank,
+                                                                  P->qa0, P->qlen, P->cnt, wide, nwide, P->err);
     SPX_HIP(hipGetLastError());
-    k_ref_count_wide<<<(unsigned)(cus * 2), 1024, 0, st>>>(P->A, P->qa0, P->qlen, P->rptr, P->wide, nwide, P->cnt,
-                                                           clscount);
+  }
+  if (lenI > 0) {  // transpose of R: the positions grouped by row
+    k_ref_claim<<<grid_for(lenI, 256 * kClaimPer, 4096), 256, 0, st>>>(I, lenI, m, P->rcnt, rank, P->rbeg, claimed);
     SPX_HIP(hipGetLastError());
-    k_ref_count<<<grid_for(lenJ * kWave, 256, (int64_t)cus * 8), 256, 0, st>>>(P->A, P->qa0, P->qlen, P->rptr, lenJ,
-                                                                                P->cnt, clscount);
+    k_ref_scatter<<<grid_for(lenI, 256, 4096), 256, 0, st>>>(I, lenI, m, rank, P->rbeg, P->rpos);
     SPX_HIP(hipGetLastError());
   }
   if (lenJ > 0) {
-    k_cls_fill<<<grid_for(lenJ, 256 * kClsPer, 4096), 256, 0, st>>>(P->cnt, P->qlen, lenJ, clscount, P->clsoff,
-                                                                     fill, P->list);
+    const unsigned sb = grid_for(lenJ, 16, (int64_t)cus * 16), lb = kRefShare * std::max(1u, (unsigned)cus / 4);
+    k_ref_count<<<sb + lb, 256, 0, st>>>(P->A, P->qa0, P->qlen, P->rcnt, lenJ, wide, nwide, sb,
+                                         (unsigned long long*)P->cnt);
+    SPX_HIP(hipGetLastError());
+    if (nblocks > 1) {
+      k_scan_reduce<LoadI64><<<(unsigned)nblocks, kScanThreads, 0, st>>>(LoadI64{P->cnt}, lenJ, sums);
+      SPX_HIP(hipGetLastError());
+    }
+    if (nblocks > kFusedCarry) {
+      SPX_TRY(scr.get_n(nblocks + 1, &carry));
+      SPX_TRY(exclusive_scan(LoadI64{sums}, nblocks, carry, scr, st));
+    }
+    k_ref_apply<<<(unsigned)nblocks, kScanThreads, 0, st>>>(P->cnt, P->qlen, lenJ, carry, sums, P->off, ncls, P->list);
     SPX_HIP(hipGetLastError());
   }
-  SPX_TRY(exclusive_scan(LoadI64{P->cnt}, lenJ, P->off, scr, st));
-  int64_t h[kNumCls + 4] = {};
-  SPX_TRY(read_device_words(st, {{P->clsoff, 8, kNumCls + 1}, {P->off + lenJ, 8}, {P->err, 4}, {nwide, 8}}, h));
-  if (h[kNumCls + 2] & 1) return fail(SPX_EINVAL, "I has an index outside [0, m)");
-  if (h[kNumCls + 2] & 2) return fail(SPX_EINVAL, "J has an index outside [0, n)");
-  for (int c = 0; c <= kNumCls; ++c) P->clsoff_h[c] = h[c];
-  P->nwide = h[kNumCls + 3];
-  const int64_t nnz = h[kNumCls + 1];
+  int64_t h[kNumCls + 2] = {};
+  SPX_TRY(read_device_words(st, {{ncls, 8, kNumCls}, {P->off + lenJ, 8}, {P->err, 4}}, h));
+  if (h[kNumCls + 1] & 1) return fail(SPX_EINVAL, "I has an index outside [0, m)");
+  if (h[kNumCls + 1] & 2) return fail(SPX_EINVAL, "J has an index outside [0, n)");
+  for (int c = 0; c < kNumCls; ++c) P->ncls[c] = h[c];
+  const int64_t nnz = h[kNumCls];
   P->nnz = nnz;
   if (nnz_b) *nnz_b = nnz;
   *plan = guard.release();
@@ -610,30 +597,39 @@ extern "C" int spx_spref_exec(spx_plan* plan, spx_mat* B) {
   hipStream_t st = stream_of(&P->ctx);
   const int vb = value_size(P->A.val_t);
   const int cus = device_cu_count();
-  const int64_t* co = P->clsoff_h;
-  // the wide medium columns' few workgroups run beside the other classes
+  const int64_t* nc = P->ncls;
+  const auto list = [&](int c) { return P->list + c * P->lenJ; };
+  // the workgroup columns (few and long) run beside the one-wave classes
   SideJoin side{nullptr, st};
-  if (co[kClsMedium + 1] > co[kClsMedium] && P->nwide > 0) {
-    SPX_TRY(side_fork(st, &side.ss));
-    k_ref_medium<1024><<<(unsigned)std::min<int64_t>(P->nwide, (int64_t)cus * 2), 1024, 0, side.ss->s>>>(
-        P->A, P->qa0, P->qlen, P->rptr, P->rpos, P->list, P->wide, P->nwide, P->clsoff, P->cnt, P->off, vb, B->ir,
+  if (nc[kClsMedium] > 0) {
+    hipStream_t ms = st;
+    if (nc[kClsSmall] + nc[kClsMid] > 0) {
+      SPX_TRY(side_fork(st, &side.ss));
+      ms = side.ss->s;
+    }
+    const int64_t W = ceil_div(P->lenI, 64);
+    const size_t lds = P->lenI <= kRankBits ? (size_t)(8 * kRefMedium + 10 * W + 16) : (size_t)12 * kRefMedium;
+    const int64_t per_cu = lds > 78 * 1024 ? 1 : 2;
+    k_ref_medium<<<(unsigned)std::min<int64_t>(nc[kClsMedium], (int64_t)cus * per_cu), kRefThreads, lds, ms>>>(
+        P->A, P->qa0, P->qlen, P->rcnt, P->rbeg, P->rpos, list(kClsMedium), nc[kClsMedium], P->lenI, P->off, vb, B->ir,
         B->num);
     SPX_HIP(hipGetLastError());
   }
-  if (co[kClsSmall + 1] > co[kClsSmall]) {
-    k_ref_small<<<grid_for(co[kClsSmall + 1] - co[kClsSmall], 4, (int64_t)cus * 16), 256, 0, st>>>(
-        P->A, P->qa0, P->qlen, P->rptr, P->rpos, P->list, P->clsoff, P->off, vb, B->ir, B->num);
-    SPX_HIP(hipGetLastError());
-  }
-  if (co[kClsMedium + 1] > co[kClsMedium]) {
-    k_ref_medium<256><<<grid_for(co[kClsMedium + 1] - co[kClsMedium], 1, (int64_t)cus * 2), 256, 0, st>>>(
-        P->A, P->qa0, P->qlen, P->rptr, P->rpos, P->list, P->wide, P->nwide, P->clsoff, P->cnt, P->off, vb, B->ir,
+  if (nc[kClsSmall] > 0) {
+    k_ref_wave<kClsSmall><<<grid_for(nc[kClsSmall], 4, (int64_t)cus * 16), 256, 0, st>>>(
+        P->A, P->qa0, P->qlen, P->rcnt, P->rbeg, P->rpos, list(kClsSmall), nc[kClsSmall], P->lenI, P->off, vb, B->ir,
         B->num);
     SPX_HIP(hipGetLastError());
   }
-  if (co[kClsLarge + 1] > co[kClsLarge]) {
-    k_ref_large<<<grid_for(co[kClsLarge + 1] - co[kClsLarge], 1, (int64_t)cus * 2), 1024, 0, st>>>(
-        P->A, P->qa0, P->qlen, P->I, P->lenI, P->list, P->clsoff, P->off, vb, B->ir, B->num);
+  if (nc[kClsMid] > 0) {
+    k_ref_wave<kClsMid><<<grid_for(nc[kClsMid], 4, (int64_t)cus * 8), 256, 0, st>>>(
+        P->A, P->qa0, P->qlen, P->rcnt, P->rbeg, P->rpos, list(kClsMid), nc[kClsMid], P->lenI, P->off, vb, B->ir,
+        B->num);
+    SPX_HIP(hipGetLastError());
+  }
+  if (nc[kClsLarge] > 0) {
+    k_ref_large<<<grid_for(nc[kClsLarge], 1, (int64_t)cus * 2), 1024, 0, st>>>(
+        P->A, P->qa0, P->qlen, P->I, P->lenI, list(kClsLarge), nc[kClsLarge], P->off, vb, B->ir, B->num);
     SPX_HIP(hipGetLastError());
   }
   SPX_TRY(side.join());

@@ -146,13 +146,13 @@ def gemm_bytes(m: int, k: int, n: int, nnz_a: int, nnz_b: int, mults: int, value
 
 def spref_bytes(m: int, len_i: int, len_j: int, gathered: int, rep: int, value_bytes: int = 8) -> int:
     """Upper bound of the device memory of B = A(I, J): the output and the
-    plan's scratch (row histogram and pointers, sorted positions of I, the
-    per-column data of J)."""
+    plan's scratch (row counts and starts, ranks and grouped positions of I,
+    the per-column data and class lists of J)."""
     cap = 1024
     while cap < len_i:
         cap <<= 1
     out = (len_j + 1) * 8 + gathered * rep * (4 + value_bytes)
-    scratch = 12 * (m + 1) + 4 * len_i + 8 * cap + 40 * (len_j + 1) + 64 * ((m + 2047) // 2048 + 64)
+    scratch = 8 * (m + 1) + 8 * len_i + 8 * cap + 52 * (len_j + 1) + 64 * ((m + 2047) // 2048 + 64)
     return out + scratch + ARENA + ALLOC_SLACK
 
 
