@@ -134,16 +134,17 @@ __global__ void k_ref_scatter(const int32_t* I, int64_t lenI, int64_t m, const i
 
 // nnz(B(:,q)) = sum over the entries (i, v) of A(:,J(q)) of |{p : I(p) = i}|.
 // Groups of 16 lanes take a column each (most gather a few entries); the
-// longer ones (the list wide) are shared by kRefShare workgroups each.
+// longer ones (the list wide) are shared by kRefShare workgroups each, the
+// first wide_blocks ones.
 __global__ void __launch_bounds__(256) k_ref_count(const Operand A, const int64_t* qa0, const int32_t* qlen,
                                                    const uint32_t* rcnt, int64_t lenJ, const int32_t* wide,
-                                                   const unsigned long long* nwide, unsigned short_blocks,
+                                                   const unsigned long long* nwide, unsigned wide_blocks,
                                                    unsigned long long* cnt) {
   constexpr int G = 16;
-  if (blockIdx.x < short_blocks) {
+  if (blockIdx.x >= wide_blocks) {
     const int gl = lane_id() & (G - 1);
-    const int64_t grp = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / G;
-    const int64_t ngrp = (int64_t)short_blocks * blockDim.x / G;
+    const int64_t grp = ((int64_t)(blockIdx.x - wide_blocks) * blockDim.x + threadIdx.x) / G;
+    const int64_t ngrp = (int64_t)(gridDim.x - wide_blocks) * blockDim.x / G;
     for (int64_t q = grp; q < lenJ; q += ngrp) {
       const int64_t a0 = qa0[q];
       const int32_t al = qlen[q];
@@ -161,7 +162,7 @@ __global__ void __launch_bounds__(256) k_ref_count(const Operand A, const int64_
       if (gl == 0) cnt[q] = (unsigned long long)s;
     }
   } else {
-    const unsigned lb = blockIdx.x - short_blocks, nlb = gridDim.x - short_blocks;  // nlb: a multiple of kRefShare
+    const unsigned lb = blockIdx.x, nlb = wide_blocks;  // a multiple of kRefShare
     const int64_t n = (int64_t)*nwide;
     const int32_t step = kRefShare * 256;
     for (int64_t w = lb / kRefShare; w < n; w += nlb / kRefShare) {
@@ -385,15 +386,15 @@ __global__ void __launch_bounds__(kRefThreads) k_ref_medium(Operand A, const int
     if (ranked)
       for (int i = threadIdx.x; i < W; i += kRefThreads) bm[i] = 0;
     __syncthreads();
-    for (int64_t e0 = threadIdx.x; e0 < al; e0 += 4 * kRefThreads) {
-      int32_t i[4];
-      uint32_t rc[4];
+    for (int64_t e0 = threadIdx.x; e0 < al; e0 += 8 * kRefThreads) {  // eight entries in flight per thread
+      int32_t i[8];
+      uint32_t rc[8];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) i[k] = e0 + k * kRefThreads < al ? A.ir[a0 + e0 + k * kRefThreads] : -1;
+      for (int k = 0; k < 8; ++k) i[k] = e0 + k * kRefThreads < al ? A.ir[a0 + e0 + k * kRefThreads] : -1;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) rc[k] = i[k] >= 0 ? rcnt[i[k]] : 0u;
+      for (int k = 0; k < 8; ++k) rc[k] = i[k] >= 0 ? rcnt[i[k]] : 0u;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
+      for (int k = 0; k < 8; ++k) {
         if (rc[k] == 0) continue;
         const unsigned at = atomicAdd(&s_n, rc[k]);
         const int32_t beg = rbeg[i[k]];
@@ -556,8 +557,9 @@ extern "C" int spx_spref_plan(const spx_ctx* ctx, const spx_mat* A, const int32_
     SPX_HIP(hipGetLastError());
   }
   if (lenJ > 0) {
-    const unsigned sb = grid_for(lenJ, 16, (int64_t)cus * 16), lb = kRefShare * std::max(1u, (unsigned)cus / 4);
-    k_ref_count<<<sb + lb, 256, 0, st>>>(P->A, P->qa0, P->qlen, P->rcnt, lenJ, wide, nwide, sb,
+    const unsigned sb = grid_for(lenJ, 16, (int64_t)cus * 16);
+    const unsigned lb = kRefShare * grid_for(std::min(lenJ, A->nnz / kRefSplit), 1, cus);
+    k_ref_count<<<sb + lb, 256, 0, st>>>(P->A, P->qa0, P->qlen, P->rcnt, lenJ, wide, nwide, lb,
                                          (unsigned long long*)P->cnt);
     SPX_HIP(hipGetLastError());
     if (nblocks > 1) {
