@@ -333,6 +333,37 @@ __device__ __forceinline__ T block_excl_scan1(T v, T* red, T* total) {
   return before + incl - v;
 }
 
+// Two such sums behind the same barrier (a, then b into *preb).
+template <typename A, typename B>
+__device__ __forceinline__ A block_excl_scan1(A a, A* reda, A* tota, B b, B* redb, B* preb, B* totb) {
+  const int lane = lane_id();
+  const int wid = threadIdx.x / kWave;
+  const int nw = blockDim.x / kWave;
+  const A ia = wave_incl_scan(a);
+  const B ib = wave_incl_scan(b);
+  if (lane == kWave - 1) {
+    reda[wid] = ia;
+    redb[wid] = ib;
+  }
+  __syncthreads();
+  A beforea = A(0), alla = A(0);
+  B beforeb = B(0), allb = B(0);
+  for (int k = 0; k < nw; ++k) {
+    const A x = reda[k];
+    const B y = redb[k];
+    if (k < wid) {
+      beforea += x;
+      beforeb += y;
+    }
+    alla += x;
+    allb += y;
+  }
+  *tota = alla;
+  *totb = allb;
+  *preb = beforeb + ib - b;
+  return beforea + ia - a;
+}
+
 // ---------------------------------------------------------------- semirings
 // mul: product of A(i,k) and B(k,j); add: combine into an accumulator;
 // lds_acc: atomic combine into LDS; ident: value of an untouched slot.

@@ -109,17 +109,17 @@ constexpr int64_t kLongSlot = 256;
 constexpr int kLongShare = 16;
 
 // Calls f(q) for the B entries of the columns list[multi_begin, multi_end)
-// with at most kLongSlot entries (workgroups below short_blocks), and of all
-// columns in longs (the others, a multiple of kLongShare).
+// with at most kLongSlot entries, and of all columns in longs (the first
+// long_blocks workgroups, a multiple of kLongShare).
 template <class F>
 __device__ __forceinline__ void for_multi_entries(const Operand& B, const int32_t* list, int64_t multi_begin,
                                                   int64_t multi_end, const int32_t* longs, int64_t nlong,
-                                                  unsigned short_blocks, F&& f) {
-  if (blockIdx.x < short_blocks) {
+                                                  unsigned long_blocks, F&& f) {
+  if (blockIdx.x >= long_blocks) {
     constexpr int G = 16;
     const int gl = lane_id() & (G - 1);
-    const int64_t grp = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / G;
-    const int64_t ngrp = (int64_t)short_blocks * blockDim.x / G;
+    const int64_t grp = ((int64_t)(blockIdx.x - long_blocks) * blockDim.x + threadIdx.x) / G;
+    const int64_t ngrp = (int64_t)(gridDim.x - long_blocks) * blockDim.x / G;
     for (int64_t pos = multi_begin + grp; pos < multi_end; pos += ngrp) {
       const int32_t t = list[pos];
       const int64_t b0 = slot_begin(B, t), b1 = slot_begin(B, t + 1);
@@ -127,7 +127,7 @@ __device__ __forceinline__ void for_multi_entries(const Operand& B, const int32_
       for (int64_t q = b0 + gl; q < b1; q += 4 * G) f(q, G, b1);
     }
   } else {
-    const unsigned lb = blockIdx.x - short_blocks, nlb = gridDim.x - short_blocks;
+    const unsigned lb = blockIdx.x, nlb = long_blocks;
     for (int64_t i = lb / kLongShare; i < nlong; i += nlb / kLongShare) {
       const int32_t t = longs[i];
       const int64_t b0 = slot_begin(B, t), b1 = slot_begin(B, t + 1);
@@ -140,8 +140,8 @@ __device__ __forceinline__ void for_multi_entries(const Operand& B, const int32_
 __global__ void __launch_bounds__(256) k_split_mark(Operand A, Operand B, const int64_t* aux, int64_t chunk,
                                                     const int32_t* list, int64_t multi_begin, int64_t multi_end,
                                                     const int32_t* longs, const unsigned long long* nlong,
-                                                    unsigned short_blocks, const int32_t* bq_alen, int32_t* flag) {
-  for_multi_entries(B, list, multi_begin, multi_end, longs, (int64_t)*nlong, short_blocks,
+                                                    unsigned long_blocks, const int32_t* bq_alen, int32_t* flag) {
+  for_multi_entries(B, list, multi_begin, multi_end, longs, (int64_t)*nlong, long_blocks,
                     [&](int64_t q, int64_t step, int64_t end) {  // four entries in flight
     int32_t al[4], k[4];
 #pragma unroll
@@ -173,7 +173,7 @@ __global__ void k_split_rows(int64_t nslots, const int64_t* sid_off, int32_t* fl
 __global__ void __launch_bounds__(256) k_split_assign(Operand A, Operand B, const int64_t* aux, int64_t chunk,
                                                       const int32_t* list, int64_t multi_begin, int64_t multi_end,
                                                       const int32_t* longs, const unsigned long long* nlong,
-                                                      unsigned short_blocks, int flat, const int32_t* bq_alen,
+                                                      unsigned long_blocks, int flat, const int32_t* bq_alen,
                                                       const int32_t* flag, int32_t* bq_split) {
   auto four = [&](int64_t q, int64_t step, int64_t end) {
     int32_t al[4], k[4], sid[4];
@@ -193,7 +193,7 @@ __global__ void __launch_bounds__(256) k_split_assign(Operand A, Operand B, cons
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < B.nnz; q += 4 * stride) four(q, stride, B.nnz);
   } else {
-    for_multi_entries(B, list, multi_begin, multi_end, longs, (int64_t)*nlong, short_blocks, four);
+    for_multi_entries(B, list, multi_begin, multi_end, longs, (int64_t)*nlong, long_blocks, four);
   }
 }
 
@@ -401,9 +401,9 @@ __device__ __forceinline__ T load_val32(const T* an, uint32_t o) {
 // thread: all threads load, in parallel, their entry's range in A (start,
 // length -- from the split table for long columns of A -- and B's value), and
 // a scan numbers the chunk's products 0..total-1 and the nonempty ranges.
-// Products are taken in windows of 64 (one per lane of a wave), U consecutive
-// windows per wave and round, all loads of a round in flight together; a chunk
-// with more than WIN windows is taken in tiles of WIN.
+// Products are taken in windows of 64 (one per lane of a wave), U windows per
+// wave and round, all loads of a round in flight together; a chunk with more
+// than WIN windows is taken in tiles of WIN.
 // Which range a lane's product lies in comes from a bit per product: wst[k] is
 // the (nonempty) range holding the first product of window k, and bits[k] has
 // bit i - 1 set when a range starts at product i >= 1 of the window, so lane i
@@ -419,8 +419,6 @@ __device__ __forceinline__ T load_val32(const T* an, uint32_t o) {
 // outside [r0, r1), so unless `full` f has to check the rows: a row r is
 // inside if (uint32_t)(r - r0) < r1 - r0, which -1 never is.
 // Must be called by every thread of the workgroup (it contains barriers).
-// With REUSE the ranges left in R by the previous call for the same column and
-// rows are used as they are (they must have been one chunk of one tile).
 // Positions are 32 bits with OFF32 (A has fewer than 2^29 entries), then A is
 // loaded through 32-bit byte offsets; else 64 bits.
 constexpr int kQChunk = 256;
@@ -437,132 +435,148 @@ struct RangeLdsT {
   double bval[BV ? QC : 1];  // B's value, stored in the first bytes of each slot
   Off base[QC];
   uint16_t wst[WIN];
-  int32_t total;  // products of the last chunk
 };
 
-template <int U, typename T, bool LOADA, bool LOADB, bool REUSE, class RL, class F>
-__device__ __forceinline__ void block_products(const ProdSrc& S, const T* an, const T* bn, int64_t b0, int64_t b1,
-                                               int32_t r0, int32_t r1, bool full, RL& R, int64_t* red,
-                                               const int32_t* qidx, F&& f) {
+// Range in A of B entry q restricted to rows [r0, r1) (the whole column unless
+// it is split): its start and length, and B's value.
+template <typename T, bool LOADB>
+__device__ __forceinline__ void load_range(const ProdSrc& S, const T* bn, int64_t q, int32_t r0, int32_t r1, bool full,
+                                           int64_t& at, int32_t& len, T& bq) {
+  const int64_t a0 = S.a0[q];
+  int32_t e0 = 0, e1 = S.alen[q];
+  const int32_t sid = !full && S.splits ? S.split[q] : -1;
+  if constexpr (LOADB) bq = bn[q];
+  if (sid >= 0) {
+    const int32_t* sp = S.splits + (int64_t)sid * S.sstride;
+    e0 = sp[r0 >> S.rbshift];
+    e1 = sp[r1 >= S.m ? S.sstride - 1 : (r1 >> S.rbshift)];
+  }
+  at = a0 + e0;
+  len = e1 - e0;
+}
+
+// Products of a chunk in the low bits of a scan value, nonempty ranges above.
+constexpr int kRangeBits = 50;
+__device__ __forceinline__ int64_t range_word(int32_t len) {
+  return (int64_t)len | (len > 0 ? (int64_t)1 << kRangeBits : (int64_t)0);
+}
+
+// The rounds of one chunk of `total` products.  The thread's range holds
+// products [ex, ex + len) and is nonempty range rk of the chunk (len 0: none);
+// R.base and R.bval hold the ranges (this thread's written by the caller), and
+// R.bits is zero, both as of the caller's last barrier or this thread's own
+// writes.  With set false bits and wst are as the previous call left them.
+// Ends with a barrier.
+template <int U, typename T, bool LOADA, bool LOADB, class RL, class F>
+__device__ __forceinline__ void product_tiles(const ProdSrc& S, const T* an, bool set, int64_t total, int64_t ex,
+                                              int32_t len, int32_t rk, RL& R, F&& f) {
   using Off = typename RL::Off;
   constexpr int kWin = RL::kWin, kTile = kWin * kWave;
-  const int qchunk = (int)blockDim.x < S.qchunk ? (int)blockDim.x : S.qchunk;
   const int lane = lane_id();
   const int tid = (int)threadIdx.x;
-  const int32_t wid = __builtin_amdgcn_readfirstlane(tid / kWave);
-  for (int64_t qc = b0; qc < b1; qc += qchunk) {
-    const int nq = (int)(b1 - qc < qchunk ? b1 - qc : qchunk);
-    int64_t total;
-    int64_t ex = 0;      // the thread's range holds products [ex, ex + len)
-    int32_t len = 0, rk = 0;
-    if (REUSE) {
-      total = R.total;
-    } else {
-      for (int k = tid; k < kWin; k += (int)blockDim.x) R.bits[k] = 0;
-      int64_t at = 0;
-      T bq = T(0);
-      if (tid < nq) {
-        const int64_t q = qidx ? (int64_t)qidx[qc + tid] : qc + tid;
-        const int64_t a0 = S.a0[q];
-        int32_t e0 = 0, e1 = S.alen[q];
-        if constexpr (LOADB) bq = bn[q];
-        if (!full) {
-          const int32_t sid = S.splits ? S.split[q] : -1;
-          if (sid >= 0) {
-            const int32_t* sp = S.splits + (int64_t)sid * S.sstride;
-            e0 = sp[r0 >> S.rbshift];
-            e1 = sp[r1 >= S.m ? S.sstride - 1 : (r1 >> S.rbshift)];
-          }
-        }
-        at = a0 + e0;
-        len = e1 - e0;
-      }
-      // products below bit 50, nonempty ranges above
-      int64_t sum;
-      const int64_t pre = block_excl_scan1((int64_t)len | (len > 0 ? (int64_t)1 << 50 : (int64_t)0), red, &sum);
-      ex = pre & ((1ll << 50) - 1);
-      rk = (int32_t)(pre >> 50);
-      total = sum & ((1ll << 50) - 1);
-      if (len > 0) {
-        R.base[rk] = (Off)(at - ex);
-        if constexpr (LOADB) reinterpret_cast<T*>(&R.bval[rk])[0] = bq;
-      }
-      if (tid == 0) R.total = total < kTile ? (int32_t)total : kTile;
-    }
-    for (int64_t tb = 0; tb < total; tb += kTile) {
-      if (!REUSE) {
-        if (tb > 0) {
-          __syncthreads();  // the last tile's rounds are done
-          for (int k = tid; k < kWin; k += (int)blockDim.x) R.bits[k] = 0;
-          __syncthreads();
-        }
-        if (len > 0 && ex < tb + kTile && ex + len > tb) {
-          const int32_t st = (int32_t)(ex - tb > 0 ? ex - tb : 0);
-          const int32_t en = (int32_t)(ex + len - tb < kTile ? ex + len - tb : kTile);
-          if (ex >= tb && (st & (kWave - 1)))
-            atomicOr((unsigned long long*)&R.bits[st / kWave], 1ull << ((st & (kWave - 1)) - 1));
-          for (int32_t k = (st + kWave - 1) / kWave; k * kWave < en; ++k) R.wst[k] = (uint16_t)rk;
-        }
+  const int32_t wid = __builtin_amdgcn_readfirstlane(tid / kWave), nw = (int32_t)blockDim.x / kWave;
+  for (int64_t tb = 0; tb < total; tb += kTile) {
+    if (set) {
+      if (tb > 0) {
+        __syncthreads();  // the last tile's rounds are done
+        for (int k = tid; k < kWin; k += (int)blockDim.x) R.bits[k] = 0;
         __syncthreads();
       }
-      const int32_t tt = __builtin_amdgcn_readfirstlane((int32_t)(total - tb < kTile ? total - tb : kTile));
-      const Off tbo = (Off)tb;
-      for (int32_t pw = wid * (U * kWave); pw < tt; pw += (int32_t)blockDim.x * U) {
-        int32_t r[U];
-        T a[U], bv[U];
-        if (pw + U * kWave <= tt) {
-          uint64_t w[U];
-          uint32_t own[U];
-          Off o[U];
+      if (len > 0 && ex < tb + kTile && ex + len > tb) {
+        const int32_t st = (int32_t)(ex - tb > 0 ? ex - tb : 0);
+        const int32_t en = (int32_t)(ex + len - tb < kTile ? ex + len - tb : kTile);
+        if (ex >= tb && (st & (kWave - 1)))
+          atomicOr((unsigned long long*)&R.bits[st / kWave], 1ull << ((st & (kWave - 1)) - 1));
+        for (int32_t k = (st + kWave - 1) / kWave; k * kWave < en; ++k) R.wst[k] = (uint16_t)rk;
+      }
+      __syncthreads();
+    }
+    const int32_t tt = __builtin_amdgcn_readfirstlane((int32_t)(total - tb < kTile ? total - tb : kTile));
+    const int32_t nwin = (tt + kWave - 1) / kWave;
+    const Off tbo = (Off)tb;
+    for (int32_t base = 0; base < nwin; base += U * nw) {
+      // a full round gives each wave U consecutive windows (which share lines of A),
+      // the last one deals the windows round robin, so that all waves have as many
+      const bool whole = (base + U * nw) * kWave <= tt;
+      const int32_t k0 = whole ? base + wid * U : base + wid, step = whole ? 1 : nw;
+      if (k0 >= nwin) break;
+      int32_t r[U], p[U];
+      T a[U], bv[U];
+      uint64_t w[U];
+      uint32_t own[U];
+      Off o[U];
 #pragma unroll
-          for (int u = 0; u < U; ++u) {
-            w[u] = R.bits[pw / kWave + u];
-            own[u] = R.wst[pw / kWave + u];
-          }
+      for (int u = 0; u < U; ++u) {
+        const int32_t k = k0 + u * step < nwin ? k0 + u * step : nwin - 1;
+        w[u] = R.bits[k];
+        own[u] = R.wst[k];
+        p[u] = k * kWave + lane;
+      }
 #pragma unroll
-          for (int u = 0; u < U; ++u) {
-            own[u] = __builtin_amdgcn_mbcnt_hi((uint32_t)(w[u] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)w[u], own[u]));
-            o[u] = R.base[own[u]] + (Off)(pw + u * kWave + lane) + tbo;
-            bv[u] = LOADB ? reinterpret_cast<const T*>(&R.bval[own[u]])[0] : T(0);
-          }
+      for (int u = 0; u < U; ++u) {
+        own[u] = __builtin_amdgcn_mbcnt_hi((uint32_t)(w[u] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)w[u], own[u]));
+        o[u] = R.base[own[u]] + (Off)(p[u] < tt ? p[u] : tt - 1) + tbo;
+        bv[u] = LOADB ? reinterpret_cast<const T*>(&R.bval[own[u]])[0] : T(0);
+      }
 #pragma unroll
-          for (int u = 0; u < U; ++u) {
-            if constexpr (RL::kOff32) {
-              r[u] = load_row32(S.air, o[u]);
-              a[u] = LOADA ? load_val32(an, o[u]) : T(0);
-            } else {
-              r[u] = S.air[o[u]];
-              a[u] = LOADA ? an[o[u]] : T(0);
-            }
-          }
-        } else {  // the tile's last round of this wave
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            r[u] = -1;
-            a[u] = bv[u] = T(0);
-            const int32_t p = pw + u * kWave + lane;
-            if (pw + u * kWave < tt) {
-              const uint64_t w = R.bits[pw / kWave + u];
-              uint32_t own = R.wst[pw / kWave + u];
-              own = __builtin_amdgcn_mbcnt_hi((uint32_t)(w >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)w, own));
-              const Off o = R.base[own] + (Off)p + tbo;
-              if (p < tt) {
-                bv[u] = LOADB ? reinterpret_cast<const T*>(&R.bval[own])[0] : T(0);
-                if constexpr (RL::kOff32) {
-                  r[u] = load_row32(S.air, o);
-                  if constexpr (LOADA) a[u] = load_val32(an, o);
-                } else {
-                  r[u] = S.air[o];
-                  if constexpr (LOADA) a[u] = an[o];
-                }
-              }
-            }
+      for (int u = 0; u < U; ++u) {
+        r[u] = -1;
+        a[u] = T(0);
+        if (k0 + u * step < nwin) {  // uniform
+          if constexpr (RL::kOff32) {
+            r[u] = load_row32(S.air, o[u]);
+            if constexpr (LOADA) a[u] = load_val32(an, o[u]);
+          } else {
+            r[u] = S.air[o[u]];
+            if constexpr (LOADA) a[u] = an[o[u]];
           }
         }
-        f(r, a, bv);
       }
+      if (!whole) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (p[u] >= tt) r[u] = -1;
+      }
+      f(r, a, bv);
     }
-    __syncthreads();
+  }
+  __syncthreads();
+}
+
+// `first`, if given, receives the first chunk's total products and whether it
+// is the only one and of one tile, so that its ranges stay in R.
+struct FirstChunk {
+  int32_t total;
+  bool all;
+};
+
+template <int U, typename T, bool LOADA, bool LOADB, class RL, class F>
+__device__ __forceinline__ void block_products(const ProdSrc& S, const T* an, const T* bn, int64_t b0, int64_t b1,
+                                               int32_t r0, int32_t r1, bool full, RL& R, int64_t* red,
+                                               const int32_t* qidx, FirstChunk* first, F&& f) {
+  using Off = typename RL::Off;
+  const int qchunk = (int)blockDim.x < S.qchunk ? (int)blockDim.x : S.qchunk;
+  const int tid = (int)threadIdx.x;
+  for (int64_t qc = b0; qc < b1; qc += qchunk) {
+    const int nq = (int)(b1 - qc < qchunk ? b1 - qc : qchunk);
+    for (int k = tid; k < RL::kWin; k += (int)blockDim.x) R.bits[k] = 0;
+    int64_t at = 0;
+    int32_t len = 0;
+    T bq = T(0);
+    if (tid < nq) load_range<T, LOADB>(S, bn, qidx ? (int64_t)qidx[qc + tid] : qc + tid, r0, r1, full, at, len, bq);
+    int64_t sum;
+    const int64_t pre = block_excl_scan1(range_word(len), red, &sum);
+    const int64_t ex = pre & (((int64_t)1 << kRangeBits) - 1), total = sum & (((int64_t)1 << kRangeBits) - 1);
+    const int32_t rk = (int32_t)(pre >> kRangeBits);
+    if (len > 0) {
+      R.base[rk] = (Off)(at - ex);
+      if constexpr (LOADB) reinterpret_cast<T*>(&R.bval[rk])[0] = bq;
+    }
+    if (first && qc == b0) {
+      first->all = b1 - b0 <= qchunk && total <= RL::kWin * kWave;
+      first->total = (int32_t)total;
+    }
+    product_tiles<U, T, LOADA, LOADB>(S, an, true, total, ex, len, rk, R, f);
   }
 }
 
@@ -815,7 +829,7 @@ template <bool OFF32>
 using HashRanges = RangeLdsT<kQChunk, kCountWin, OFF32, false>;
 
 template <bool OFF32>
-__global__ void __launch_bounds__(1024) k_count_hash(Operand B, ProdSrc S, const int64_t* mults,
+__global__ void __launch_bounds__(1024, 8) k_count_hash(Operand B, ProdSrc S, const int64_t* mults,
                              const int32_t* list, int64_t beg, int64_t end, int64_t multi_begin, int64_t multi_end,
                              int rbshift, int64_t nblk, uint32_t* blkcnt, int64_t* cnt, unsigned* err) {
   extern __shared__ __align__(16) unsigned char lds[];
@@ -838,8 +852,8 @@ __global__ void __launch_bounds__(1024) k_count_hash(Operand B, ProdSrc S, const
       for (int64_t i = threadIdx.x; i < nblk; i += blockDim.x) lblk[i] = 0;
     __syncthreads();
     int64_t mine = 0;
-    block_products<4, int, false, false, false>(
-        S, nullptr, nullptr, b0, b1, 0, 0, true, s_rng, red, nullptr,
+    block_products<4, int, false, false>(
+        S, nullptr, nullptr, b0, b1, 0, 0, true, s_rng, red, nullptr, nullptr,
         [&](const int32_t(&r)[4], const int(&)[4], const int(&)[4]) {
           // first probes of the four windows together
           uint32_t h[4], old[4];
@@ -889,7 +903,7 @@ using BitmapRanges = RangeLdsT<kQChunkWide, kCountWin, OFF32, false>;  // heavy 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 template <bool OFF32>
-__global__ void __launch_bounds__(1024) k_count_bitmap(Operand B, ProdSrc S, const int64_t* mults, const int32_t* list,
+__global__ void __launch_bounds__(1024, 8) k_count_bitmap(Operand B, ProdSrc S, const int64_t* mults, const int32_t* list,
                                                        const int64_t* binoff, int64_t m, int chunk_log2, int rbshift,
                                                        int64_t nblk, uint32_t* blkcnt, unsigned long long* cnt,
                                                        uint32_t* gbm, int64_t gwords, unsigned long long* qctr) {
@@ -932,8 +946,8 @@ __global__ void __launch_bounds__(1024) k_count_bitmap(Operand B, ProdSrc S, con
     const int32_t t = list[pos];
     const int64_t b0 = slot_begin(B, t), b1 = slot_begin(B, t + 1);
     uint32_t* dst = blkcnt + (pos - beg) * nblk;
-    block_products<4, int, false, false, false>(
-        S, nullptr, nullptr, b0, b1, (int32_t)c0, (int32_t)c1, nchunks == 1, s_rng, red, nullptr,
+    block_products<4, int, false, false>(
+        S, nullptr, nullptr, b0, b1, (int32_t)c0, (int32_t)c1, nchunks == 1, s_rng, red, nullptr, nullptr,
         [&](const int32_t(&r)[4], const int(&)[4], const int(&)[4]) {
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
@@ -960,6 +974,17 @@ __global__ void __launch_bounds__(1024) k_count_bitmap(Operand B, ProdSrc S, con
         const int sum = __builtin_amdgcn_readlane(wave_incl_scan(pc), 63);
         if (lane == 0 && sum) {
           atomicAdd(&lblk[((int64_t)i0 * 128) >> rbshift], (uint32_t)sum);
+          atomicAdd(&s_tot, (unsigned)sum);
+        }
+      } else if (rbshift >= 7) {
+        // row blocks of 2^(rbshift - 7) lanes: the last lane of each adds its block's sum
+        const int pc = __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
+        const int g = 1 << (rbshift - 7);
+        const int incl = wave_incl_scan(pc);
+        const int before = __shfl(incl, (lane - g) & (kWave - 1));
+        const int sum = lane >= g ? incl - before : incl;
+        if ((lane & (g - 1)) == g - 1 && sum) {
+          atomicAdd(&lblk[((int64_t)i * 128) >> rbshift], (uint32_t)sum);
           atomicAdd(&s_tot, (unsigned)sum);
         }
       } else {
@@ -1002,6 +1027,9 @@ struct PartCfg {
   int64_t slice_blocks;  // row blocks per slice (parts never straddle slices); 0: one slice
   int32_t nslice;
   int32_t hash_max;  // most outputs of a hash-mode part that fits L (0: none)
+  int64_t hash_span; // most rows it may span
+  int32_t note;      // bytes per output that parts leave for noted rows
+  int32_t pad;
 };
 
 __device__ __forceinline__ int64_t bitmap_bytes(const PartCfg& p, int64_t span, int64_t c) {
@@ -1011,6 +1039,11 @@ __device__ __forceinline__ int64_t bitmap_bytes(const PartCfg& p, int64_t span, 
 __device__ __forceinline__ bool bitmap_ok(const PartCfg& p, int64_t span, int64_t c) {
   return c < 65536 && bitmap_bytes(p, span, c) <= p.L;
 }
+// Bitmap mode with the products' rows noted beside the values: 2 more bytes per
+// output (see k_numeric_parts).
+__device__ __forceinline__ bool noted_ok(const PartCfg& p, int64_t span, int64_t c) {
+  return c < 65536 && bitmap_bytes(p, span, c) + p.note * c <= p.L;
+}
 // Rows a hash-mode part may span for the two-level rank (longer: sorted).
 constexpr int64_t kRankSpan = 1ll << 20;
 
@@ -1018,10 +1051,12 @@ __host__ __device__ inline int64_t hash_bytes(int64_t p2, int64_t sz) {  // p2: 
   const int64_t S = 2 * p2;
   return S * 4 + ((S * sz + 7) & ~7ll) + p2 * 10 + (kRankSpan >> 9) + (kRankSpan >> 11) + 64;
 }
-__device__ __forceinline__ bool hash_ok(const PartCfg& p, int64_t c) { return c <= p.hash_max; }
+__device__ __forceinline__ bool hash_ok(const PartCfg& p, int64_t span, int64_t c) {
+  return c <= p.hash_max && span <= p.hash_span;
+}
 
 __device__ __forceinline__ int choose_mode(const PartCfg& p, int64_t span, int64_t c) {
-  const bool bok = bitmap_ok(p, span, c), hok = hash_ok(p, c);
+  const bool bok = bitmap_ok(p, span, c), hok = hash_ok(p, span, c);
   if (bok && hok) {
     const int64_t lg = c > 1 ? ceil_log2_u64((uint64_t)c) : 1;
     const int64_t bitmap_cost = ((span + 63) >> 6) * 3;
@@ -1032,7 +1067,8 @@ __device__ __forceinline__ int choose_mode(const PartCfg& p, int64_t span, int64
 }
 
 // Cuts one column into parts, greedily over its row blocks: a part grows while
-// it still fits the LDS budget in one of the two modes.  One wave: its lanes
+// it still fits the LDS budget in one of the two modes (in bitmap mode with the
+// noted rows; a single row block may go without).  One wave: its lanes
 // test 64 ends of the part at once (whether a part fits only changes from yes
 // to no as it grows).  blk: the column's row-block counts, in LDS or global
 // memory; with PREF, their inclusive prefix sums.  Returns the number of parts;
@@ -1054,7 +1090,7 @@ __device__ int64_t cut_parts(const PartCfg& p, const uint32_t* blk, int32_t t, i
       const uint32_t ci = PREF ? x - before : c + (uint32_t)wave_incl_scan((int32_t)x);
       const int64_t r1 = (i + 1) * RB < p.m ? (i + 1) * RB : p.m;
       const bool fits = i < nblk && (i == b || (!(sb && i % sb == 0) &&
-                                                (ci <= (uint32_t)p.hash_max || bitmap_ok(p, r1 - b * RB, ci))));
+                                                (hash_ok(p, r1 - b * RB, ci) || noted_ok(p, r1 - b * RB, ci))));
       const uint64_t no = __ballot(!fits);
       f = no ? __ffsll((long long)no) - 1 : kWave;
       if (f > 0) c = (uint32_t)__builtin_amdgcn_readlane((int)ci, f - 1);
@@ -1065,7 +1101,7 @@ __device__ int64_t cut_parts(const PartCfg& p, const uint32_t* blk, int32_t t, i
       const int64_t r0 = b * RB;
       const int64_t r1 = e * RB < p.m ? e * RB : p.m;
       if (lane == 0) {
-        if (!bitmap_ok(p, r1 - r0, c) && !hash_ok(p, c)) atomicOr(err, 4u);
+        if (!bitmap_ok(p, r1 - r0, c) && !hash_ok(p, r1 - r0, c)) atomicOr(err, 4u);
         if (out) {
           Part P;
           P.off = base_off + run;
@@ -1110,7 +1146,7 @@ __global__ void __launch_bounds__(256) k_parts(Operand B, PartCfg p, PartCfg ps,
   // a column in one part
   auto whole = [&](int64_t pos, int32_t t, int64_t c, const PartCfg& q) {
     if (!parts) {
-      if (!(bitmap_ok(q, q.m, c) || hash_ok(q, c))) atomicOr(err, 4u);
+      if (!(bitmap_ok(q, q.m, c) || hash_ok(q, q.m, c))) atomicOr(err, 4u);
       return;
     }
     Part P;
@@ -1132,7 +1168,7 @@ __global__ void __launch_bounds__(256) k_parts(Operand B, PartCfg p, PartCfg ps,
       const int32_t t = list[pos];
       const int64_t c = cnt[t];
       int64_t np = c > 0;
-      if (c > 0 && !(bitmap_ok(p, p.m, c) || hash_ok(p, c))) {
+      if (c > 0 && !(bitmap_ok(p, p.m, c) || hash_ok(p, p.m, c))) {
         const int64_t cb0 = slot_begin(B, t), nb = slot_begin(B, t + 1) - cb0;
         const uint32_t* blk = blkcnt + (pos - multi_begin) * p.nblk;
         if (p.nblk <= kCutBlk) {
@@ -1364,7 +1400,8 @@ __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, Pr
                                                         int64_t plo, int64_t phi, int nq, int nhome, int batch,
                                                         unsigned long long* qctr,
                                                         const uint64_t* gbm, int64_t gbm_words,
-                                                        const int32_t* qlist, int32_t* cir, T* cnum, unsigned* err) {
+                                                        const int32_t* qlist, int64_t part_lds, int32_t* cir, T* cnum,
+                                                        unsigned* err) {
   using SR_ = Semiring<SR, T>;
   constexpr bool kVal = SR != SPX_OR_AND;
   extern __shared__ __align__(16) unsigned char lds[];
@@ -1372,6 +1409,7 @@ __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, Pr
   __shared__ int s_nbat;
   __shared__ Part s_batch[kPartBatch];
   __shared__ int64_t red[1024 / kWave + 1];
+  __shared__ int32_t red32[1024 / kWave + 1];
   __shared__ unsigned s_ctr;
   __shared__ PartRanges<OFF32> s_rng;
   const T* an = (const T*)A.num;
@@ -1410,7 +1448,18 @@ __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, Pr
     if ((int)threadIdx.x < nbat) s_batch[threadIdx.x] = parts[pfirst + threadIdx.x];
     __syncthreads();
     for (int bi = 0; bi < nbat; ++bi) {
-    const Part P = s_batch[bi];
+    Part P;
+    {
+      const Part& Q = s_batch[bi];
+      P.off = uniform(Q.off);
+      P.c = uniform(Q.c);
+      P.r0 = uniform(Q.r0);
+      P.r1 = uniform(Q.r1);
+      P.mode = uniform(Q.mode);
+      P.bmi = uniform(Q.bmi);
+      P.nb = uniform(Q.nb);
+      P.b0 = uniform(Q.b0);
+    }
     const int64_t b0 = P.b0, b1 = P.b0 + P.nb;
     const int32_t* qx = (P.mode & 2) ? qlist : nullptr;  // a bucketed part visits only its bucket
     const int64_t span = (int64_t)P.r1 - P.r0;
@@ -1422,19 +1471,64 @@ __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, Pr
       uint64_t* bm = (uint64_t*)lds;
       uint16_t* pre = (uint16_t*)(bm + W);
       T* vals = (T*)(lds + W * 8 + ((W * 2 + 7) & ~7));
+      // Rows in rank order.  Where the part leaves room for them (2 bytes per output),
+      // every product notes the low 16 bits of its row beside its value; the high bits
+      // follow from the ranks at the multiples of 65536 rows.  Else, and for patterns,
+      // the rows are read off the bitmap: its words hold one or two rows each, so lanes
+      // wait for the fullest word at every step (about 50 vector instructions per 64
+      // outputs against 12).
+      uint16_t* low = (uint16_t*)(vals + c);
+      const bool noted = kVal && (char*)(low + c) <= (char*)lds + part_lds;
+      // rank of each product's row: all bitmap words first, then the adds
+      auto acc = [&](const int32_t (&r)[8], const T (&a)[8], const T (&bv)[8]) {
+        uint64_t w[8];
+        int pr[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const uint32_t d = (uint32_t)(r[u] - P.r0);
+          const uint32_t wi = d < (uint32_t)span ? d >> 6 : 0u;
+          w[u] = bm[wi];
+          pr[u] = pre[wi];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const uint32_t d = (uint32_t)(r[u] - P.r0);
+          const int rank = pr[u] + __popcll(w[u] & ((1ull << (d & 63)) - 1ull));
+          if (d < (uint32_t)span && rank < c) {
+            SR_::lds_acc(&vals[rank], SR_::mul(a[u], bv[u]));
+            if (noted) low[rank] = (uint16_t)d;  // the same from every product of the row
+          }
+        }
+      };
       // the row set: the count phase's stored bitmap, else marked here
       const bool stored = gbm != nullptr && P.bmi >= 0;
+      const int qchunk = (int)blockDim.x < S.qchunk ? (int)blockDim.x : S.qchunk;
+      // A stored part of one chunk loads its ranges and its bitmap together and numbers
+      // both in one scan: the part waits on a chain of memory latencies (two workgroups
+      // fit a CU), and this takes one of them and three barriers out.
+      const bool fused = kVal && stored && b1 - b0 <= qchunk;
+      FirstChunk marked{0, false};
+      int64_t at = 0;
+      int32_t len = 0;
+      T bq = T(0);
+      if (fused) {
+        if ((int)threadIdx.x < P.nb) {
+          const int64_t q = qx ? (int64_t)qx[b0 + threadIdx.x] : b0 + threadIdx.x;
+          load_range<T, SR_::kUsesB>(S, bn, q, P.r0, P.r1, full, at, len, bq);
+        }
+        for (int k = threadIdx.x; k < kNumWin; k += blockDim.x) s_rng.bits[k] = 0;
+      }
       if (stored) {
         const uint64_t* g = gbm + (int64_t)P.bmi * gbm_words + (P.r0 >> 6);
-        for (int i0 = threadIdx.x; i0 < W; i0 += 4 * blockDim.x) {  // 4 loads in flight per thread
-          uint64_t v[4];
+        for (int i0 = threadIdx.x; i0 < W; i0 += 8 * blockDim.x) {  // 8 loads in flight per thread
+          uint64_t v[8];
 #pragma unroll
-          for (int k = 0; k < 4; ++k) {
+          for (int k = 0; k < 8; ++k) {
             const int i = i0 + k * (int)blockDim.x;
             v[k] = i < W ? g[i] : 0ull;
           }
 #pragma unroll
-          for (int k = 0; k < 4; ++k) {
+          for (int k = 0; k < 8; ++k) {
             const int i = i0 + k * (int)blockDim.x;
             if (i < W) bm[i] = v[k];
           }
@@ -1446,8 +1540,8 @@ __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, Pr
         for (int i = threadIdx.x; i < c; i += blockDim.x) vals[i] = SR_::ident();
       __syncthreads();
       if (!stored) {
-        block_products<8, T, false, SR_::kUsesB, false>(
-            S, an, bn, b0, b1, P.r0, P.r1, full, s_rng, red, qx, [&](const int32_t(&r)[8], const T(&)[8], const T(&)[8]) {
+        block_products<8, T, false, SR_::kUsesB>(
+            S, an, bn, b0, b1, P.r0, P.r1, full, s_rng, red, qx, &marked, [&](const int32_t(&r)[8], const T(&)[8], const T(&)[8]) {
 #pragma unroll
               for (int u = 0; u < 8; ++u) {
                 const uint32_t d = (uint32_t)(r[u] - P.r0);
@@ -1455,51 +1549,68 @@ __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, Pr
               }
             });
       }
-      // exclusive popcount prefix per word
+      // exclusive popcount prefix per word (and the numbers of the ranges)
       const int per = (W + blockDim.x - 1) / blockDim.x;
       const int w0 = threadIdx.x * per;
       const int w1 = w0 + per < W ? w0 + per : W;
-      int64_t s = 0;
+      int32_t s = 0, tot;
       for (int i = w0; i < w1; ++i) s += __popcll(bm[i]);
-      int64_t tot;
-      int64_t run = block_excl_scan1(s, red, &tot);
+      int64_t rsum = 0, rpre = 0;
+      int32_t run = block_excl_scan1(s, red32, &tot, range_word(len), red, &rpre, &rsum);
       for (int i = w0; i < w1; ++i) {
         pre[i] = (uint16_t)run;
         run += __popcll(bm[i]);
       }
       if (threadIdx.x == 0 && tot != c) atomicOr(err, 8u);
-      __syncthreads();
       if constexpr (kVal) {
-        // rank of each product's row: all bitmap words first, then the adds
-        auto acc = [&](const int32_t (&r)[8], const T (&a)[8], const T (&bv)[8]) {
-          uint64_t w[8];
-          int pr[8];
-#pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            const uint32_t d = (uint32_t)(r[u] - P.r0);
-            const uint32_t wi = d < (uint32_t)span ? d >> 6 : 0u;
-            w[u] = bm[wi];
-            pr[u] = pre[wi];
+        if (!fused) __syncthreads();
+        // the chunks of ranges: those loaded above, those the marking pass left in LDS,
+        // or loaded now
+        for (int64_t qc = b0; qc < b1; qc += qchunk) {
+          int64_t total = marked.total, ex = 0;
+          int32_t rk = 0;
+          if (!marked.all) {
+            if (!fused) {
+              for (int k = threadIdx.x; k < kNumWin; k += blockDim.x) s_rng.bits[k] = 0;
+              len = 0;
+              if (qc + threadIdx.x < b1 && (int)threadIdx.x < qchunk) {
+                const int64_t q = qx ? (int64_t)qx[qc + threadIdx.x] : qc + threadIdx.x;
+                load_range<T, SR_::kUsesB>(S, bn, q, P.r0, P.r1, full, at, len, bq);
+              }
+              rpre = block_excl_scan1(range_word(len), red, &rsum);
+            }
+            total = rsum & (((int64_t)1 << kRangeBits) - 1);
+            ex = rpre & (((int64_t)1 << kRangeBits) - 1);
+            rk = (int32_t)(rpre >> kRangeBits);
+            if (len > 0) {
+              s_rng.base[rk] = (typename PartRanges<OFF32>::Off)(at - ex);
+              if constexpr (SR_::kUsesB) reinterpret_cast<T*>(&s_rng.bval[rk])[0] = bq;
+            }
           }
-#pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            const uint32_t d = (uint32_t)(r[u] - P.r0);
-            const int rank = pr[u] + __popcll(w[u] & ((1ull << (d & 63)) - 1ull));
-            if (d < (uint32_t)span && rank < c) SR_::lds_acc(&vals[rank], SR_::mul(a[u], bv[u]));
-          }
-        };
-        const int qchunk = (int)blockDim.x < S.qchunk ? (int)blockDim.x : S.qchunk;
-        // the marking pass left all ranges in LDS (one chunk, one tile)
-        if (!stored && b1 - b0 <= qchunk && s_rng.total < kNumWin * kWave)
-          block_products<8, T, SR_::kUsesA, SR_::kUsesB, true>(S, an, bn, b0, b1, P.r0, P.r1, full, s_rng, red, qx, acc);
-        else
-          block_products<8, T, SR_::kUsesA, SR_::kUsesB, false>(S, an, bn, b0, b1, P.r0, P.r1, full, s_rng, red, qx, acc);
+          product_tiles<8, T, SR_::kUsesA, SR_::kUsesB>(S, an, !marked.all, total, ex, len, rk, s_rng, acc);
+        }
         // C is written once, coalesced: streaming stores keep the L2 for A's gathers
         // (a part's scattered hash-mode writes stay ordinary: streamed partial lines
         // cost more than they save)
         for (int i = threadIdx.x; i < c; i += blockDim.x) __builtin_nontemporal_store(vals[i], &cnum[P.off + i]);
+        if (noted) {
+          const int nhi = (int)((span - 1) >> 16);  // pre[1024 k]: rank of the first row at or above 65536 k
+          int32_t hi = P.r0;
+          int k = 0, next = nhi > 0 ? (int)pre[1024] : 0x7fffffff;
+          for (int i = threadIdx.x; i < c; i += blockDim.x) {
+            while (i >= next) {
+              ++k;
+              hi += 65536;
+              next = k < nhi ? (int)pre[1024 * (k + 1)] : 0x7fffffff;
+            }
+            __builtin_nontemporal_store(hi + (int32_t)low[i], &cir[P.off + i]);
+          }
+          __syncthreads();
+          continue;
+        }
         __syncthreads();
       }
+      if constexpr (!kVal) __syncthreads();
       // rows in rank order: staged in the value area, then written coalesced
       int32_t* rows = (int32_t*)vals;
       for (int i = w0; i < w1; ++i) {
@@ -1534,18 +1645,19 @@ __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, Pr
       uint64_t* l1w = (uint64_t*)(tail + p2 * 10);
       uint16_t* l1p = (uint16_t*)(tail + p2 * 10 + (kRankSpan >> 9));
       uint64_t* sortb = (uint64_t*)tail;
-      for (uint32_t i = threadIdx.x; i < Sz; i += blockDim.x) {
-        keys[i] = 0xffffffffu;
-        if constexpr (kVal) vals[i] = SR_::ident();
-      }
+      // (Sz is a multiple of 128, so 16 bytes at a time)
+      for (uint32_t i = threadIdx.x; i < Sz / 4; i += blockDim.x)
+        reinterpret_cast<uint4*>(keys)[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
+      if constexpr (kVal)
+        for (uint32_t i = threadIdx.x; i < Sz; i += blockDim.x) vals[i] = SR_::ident();
       if (ranked) {
         for (int i = threadIdx.x; i < p2; i += blockDim.x) l2w[i] = 0;
         for (int i = threadIdx.x; i < n1; i += blockDim.x) l1w[i] = 0;
       }
       if (threadIdx.x == 0) s_ctr = 0;
       __syncthreads();
-      block_products<4, T, SR_::kUsesA, SR_::kUsesB, false>(
-          S, an, bn, b0, b1, P.r0, P.r1, full, s_rng, red, qx, [&](const int32_t(&r)[4], const T(&a)[4], const T(&bv)[4]) {
+      block_products<4, T, SR_::kUsesA, SR_::kUsesB>(
+          S, an, bn, b0, b1, P.r0, P.r1, full, s_rng, red, qx, nullptr, [&](const int32_t(&r)[4], const T(&a)[4], const T(&bv)[4]) {
             uint32_t h[4], old[4];
             bool in[4];
 #pragma unroll
@@ -1567,24 +1679,19 @@ __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, Pr
               }
               if constexpr (kVal)
                 if (in[u]) SR_::lds_acc(&vals[h[u]], SR_::mul(a[u], bv[u]));
+              if (ranked && in[u] && old[u] == ~0u) {  // a new row: level 1 marks its group
+                const uint32_t g = (uint32_t)(r[u] - P.r0) >> 6;
+                atomicOr((unsigned long long*)&l1w[g >> 6], 1ull << (g & 63));
+              }
             }
           });
       if (ranked) {
-        // level 1: nonempty groups of 64 rows
-        for (uint32_t i = threadIdx.x; i < Sz; i += blockDim.x) {
-          const uint32_t key = keys[i];
-          if (key != 0xffffffffu) {
-            const uint32_t g = (key - (uint32_t)P.r0) >> 6;
-            atomicOr((unsigned long long*)&l1w[g >> 6], 1ull << (g & 63));
-          }
-        }
-        __syncthreads();
+        int64_t ng;  // nonempty groups
         {
           const int per = (n1 + (int)blockDim.x - 1) / (int)blockDim.x;
           const int w0 = threadIdx.x * per, w1 = w0 + per < n1 ? w0 + per : n1;
           int64_t sum = 0;
           for (int w = w0; w < w1; ++w) sum += __popcll(l1w[w]);
-          int64_t ng;
           int64_t run = block_excl_scan1(sum, red, &ng);
           for (int w = w0; w < w1; ++w) {
             l1p[w] = (uint16_t)run;
@@ -1592,20 +1699,45 @@ __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, Pr
           }
         }
         __syncthreads();
-        // level 2: the rows of each nonempty group
-        for (uint32_t i = threadIdx.x; i < Sz; i += blockDim.x) {
-          const uint32_t key = keys[i];
-          if (key != 0xffffffffu) {
-            const uint32_t d = key - (uint32_t)P.r0, g = d >> 6;
-            const int gi = l1p[g >> 6] + __popcll(l1w[g >> 6] & ((1ull << (g & 63)) - 1ull));
-            if (gi < p2) atomicOr((unsigned long long*)&l2w[gi], 1ull << (d & 63));
+        // level 2: the rows of each nonempty group.  Threads hold the keys of
+        // their slots from here on (eight each; a part with more writes straight
+        // from the table below).
+        const bool held = Sz <= 8 * blockDim.x;
+        uint32_t key[8];
+        auto group = [&](uint32_t k) {  // index of row k's group among the nonempty ones
+          const uint32_t g = (k - (uint32_t)P.r0) >> 6;
+          return (int)l1p[g >> 6] + __popcll(l1w[g >> 6] & ((1ull << (g & 63)) - 1ull));
+        };
+        if (held) {
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            const uint32_t i = q * blockDim.x + threadIdx.x;
+            uint4 v = make_uint4(~0u, ~0u, ~0u, ~0u);
+            if (i < Sz / 4) v = reinterpret_cast<const uint4*>(keys)[i];
+            key[4 * q] = v.x;
+            key[4 * q + 1] = v.y;
+            key[4 * q + 2] = v.z;
+            key[4 * q + 3] = v.w;
           }
+#pragma unroll
+          for (int k = 0; k < 8; ++k)
+            if (key[k] != ~0u) {
+              const int gi = group(key[k]);
+              if (gi < p2) atomicOr((unsigned long long*)&l2w[gi], 1ull << ((key[k] - (uint32_t)P.r0) & 63));
+            }
+        } else {
+          for (uint32_t i = threadIdx.x; i < Sz; i += blockDim.x)
+            if (keys[i] != ~0u) {
+              const int gi = group(keys[i]);
+              if (gi < p2) atomicOr((unsigned long long*)&l2w[gi], 1ull << ((keys[i] - (uint32_t)P.r0) & 63));
+            }
         }
         __syncthreads();
         int64_t found;
         {
-          const int per = (p2 + (int)blockDim.x - 1) / (int)blockDim.x;
-          const int w0 = threadIdx.x * per, w1 = w0 + per < p2 ? w0 + per : p2;
+          const int n2 = ng < p2 ? (int)ng : p2;
+          const int per = (n2 + (int)blockDim.x - 1) / (int)blockDim.x;
+          const int w0 = threadIdx.x * per, w1 = w0 + per < n2 ? w0 + per : n2;
           int64_t sum = 0;
           for (int w = w0; w < w1; ++w) sum += __popcll(l2w[w]);
           int64_t run = block_excl_scan1(sum, red, &found);
@@ -1616,18 +1748,43 @@ __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, Pr
         }
         __syncthreads();
         if (threadIdx.x == 0 && found != c) atomicOr(err, 32u);
-        // rank = output position
-        for (uint32_t i = threadIdx.x; i < Sz; i += blockDim.x) {
-          const uint32_t key = keys[i];
-          if (key != 0xffffffffu) {
-            const uint32_t d = key - (uint32_t)P.r0, g = d >> 6;
-            const int gi = l1p[g >> 6] + __popcll(l1w[g >> 6] & ((1ull << (g & 63)) - 1ull));
-            if (gi < p2) {
-              const int rank = l2p[gi] + __popcll(l2w[gi] & ((1ull << (d & 63)) - 1ull));
-              if (rank < c) {
-                cir[P.off + rank] = (int32_t)key;
-                if constexpr (kVal) cnum[P.off + rank] = vals[i];
-              }
+        auto rank_of = [&](uint32_t k) {  // output position of row k, c or more if it has none
+          const int gi = group(k);
+          return gi < p2 ? (int)l2p[gi] + __popcll(l2w[gi] & ((1ull << ((k - (uint32_t)P.r0) & 63)) - 1ull)) : c;
+        };
+        if (held) {
+          // values and rows go through the LDS in rank order, over the table, so that
+          // C is written coalesced (straight from the table, 64 lanes wrote to as many lines)
+          T v[8];
+          if constexpr (kVal) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+              v[k] = key[k] != ~0u ? vals[4 * ((k / 4) * blockDim.x + threadIdx.x) + k % 4] : T(0);
+          }
+          __syncthreads();
+          T* vout = vals;  // 2 c values fit there, so c values and c rows do
+          int32_t* rout = kVal ? (int32_t*)(vals + c) : (int32_t*)keys;
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            if (key[k] == ~0u) continue;
+            const int rank = rank_of(key[k]);
+            if (rank < c) {
+              rout[rank] = (int32_t)key[k];
+              if constexpr (kVal) vout[rank] = v[k];
+            }
+          }
+          __syncthreads();
+          for (int i = threadIdx.x; i < c; i += blockDim.x) {
+            __builtin_nontemporal_store(rout[i], &cir[P.off + i]);
+            if constexpr (kVal) __builtin_nontemporal_store(vout[i], &cnum[P.off + i]);
+          }
+        } else {
+          for (uint32_t i = threadIdx.x; i < Sz; i += blockDim.x) {
+            if (keys[i] == ~0u) continue;
+            const int rank = rank_of(keys[i]);
+            if (rank < c) {
+              cir[P.off + rank] = (int32_t)keys[i];
+              if constexpr (kVal) cnum[P.off + rank] = vals[i];
             }
           }
         }
@@ -2024,11 +2181,11 @@ static int launch_numeric(GemmPlan* P, spx_mat* C, hipStream_t st) {
     if (P->src.off32)  // A's positions fit 29 bits: gathers through 32-bit offsets
       hipLaunchKernelGGL((k_numeric_parts<SR, T, true>), dim3((unsigned)grid), dim3(blk), (size_t)L, st, P->A, P->B,
                          P->src, P->mults_d, P->cnt, P->parts, qoff, n0, n1, nq, r == 0 ? P->nslice : 1, batch, qctr,
-                         P->gbm, P->gbm_words, P->qlist, cir, cnum, err);
+                         P->gbm, P->gbm_words, P->qlist, L, cir, cnum, err);
     else
       hipLaunchKernelGGL((k_numeric_parts<SR, T, false>), dim3((unsigned)grid), dim3(blk), (size_t)L, st, P->A, P->B,
                          P->src, P->mults_d, P->cnt, P->parts, qoff, n0, n1, nq, r == 0 ? P->nslice : 1, batch, qctr,
-                         P->gbm, P->gbm_words, P->qlist, cir, cnum, err);
+                         P->gbm, P->gbm_words, P->qlist, L, cir, cnum, err);
     SPX_HIP(hipGetLastError());
     if (r == 0) P->mark(kEvMulti, st);
   }
@@ -2236,8 +2393,9 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
     SPX_TRY(zero_words(st, {{blkcnt, ceil_div(nmulti * nblk, 2)}, {flag, split ? ceil_div(nslots_a, 2) : 0},
                             {bqctr, nbitmap > 0 ? nchunks : 0}}));
   if (split) {
-    const unsigned sb = grid_for(nmulti, 16, (int64_t)cus * 16), lb = kLongShare * std::max(1u, (unsigned)cus / 4);
-    k_split_mark<<<sb + lb, 256, 0, st>>>(P->A, P->B, P->aux, chunk, P->list, multi_begin, multi_end, longs, nlong, sb,
+    const unsigned sb = grid_for(nmulti, 16, (int64_t)cus * 16);
+    const unsigned lb = kLongShare * grid_for(std::min(nslots, B->nnz / kLongSlot), 1, cus);
+    k_split_mark<<<sb + lb, 256, 0, st>>>(P->A, P->B, P->aux, chunk, P->list, multi_begin, multi_end, longs, nlong, lb,
                                           P->bq_alen, flag);
     SPX_HIP(hipGetLastError());
     SPX_TRY(exclusive_scan(LoadFlag{flag}, nslots_a, sid_off, scr, st));
@@ -2245,7 +2403,7 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
     SPX_HIP(hipGetLastError());
     const int flat = nmulti > nslots / 64;
     k_split_assign<<<flat ? grid_for(B->nnz, 1024, (int64_t)cus * 16) : sb + lb, 256, 0, st>>>(
-        P->A, P->B, P->aux, chunk, P->list, multi_begin, multi_end, longs, nlong, sb, flat, P->bq_alen, flag,
+        P->A, P->B, P->aux, chunk, P->list, multi_begin, multi_end, longs, nlong, lb, flat, P->bq_alen, flag,
         P->bq_split);
     SPX_HIP(hipGetLastError());
     k_split_fill<<<grid_for(std::min(nslots_a, B->nnz) * kWave, 256, (int64_t)cus * 32), 256, 0, st>>>(
@@ -2318,8 +2476,14 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
   nslice = (int)ceil_div(nblk, slice_blocks);
   if (nslice <= 1) slice_blocks = 0;
   P->nslice = nslice;
-  PartCfg pc{L, m, sz, rb, nblk, slice_blocks, nslice, hash_most(L, sz)};
-  PartCfg pcs{P->L_single, m, sz, rb, nblk, 0, nslice, hash_most(P->L_single, sz)};
+  // Parts leave room for noted rows (9% more parts) where every workgroup gets many
+  // of them: scale-20 product 35.0 -> 33.1 ms, but 128 columns in 1014 parts, two
+  // for each workgroup, 214 -> 246 us.
+  const int32_t note = sz > 0 && nmulti >= 16 * (int64_t)cus ? 2 : 0;
+  // a hash part of more than kRankSpan rows has to sort its rows, so columns of a
+  // few times as many rows are rather cut there
+  PartCfg pc{L, m, sz, rb, nblk, slice_blocks, nslice, hash_most(L, sz), m <= 4 * kRankSpan ? kRankSpan : m, note, 0};
+  PartCfg pcs{P->L_single, m, sz, rb, nblk, 0, nslice, hash_most(P->L_single, sz), m, 0, 0};
   const unsigned cut_blocks = nmulti > 0 ? grid_for(nmulti, 4, (int64_t)cus * 8) : 0;
   const unsigned pgrid = cut_blocks + (npos > multi_end ? grid_for(npos - multi_end, 256, (int64_t)cus * 8) : 0);
   if (npos > 0) {

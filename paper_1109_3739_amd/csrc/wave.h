@@ -40,6 +40,14 @@ struct ProdSrc {
   int32_t qchunk;  // B entries per set-up round of the block-cooperative iteration
 };
 
+// A value known to be the same in every lane, moved to scalar registers (values
+// read from LDS or memory otherwise stay in vector registers).
+__device__ __forceinline__ int32_t uniform(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ int64_t uniform(int64_t v) {
+  return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int32_t)(v >> 32)) << 32) |
+                   (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)v));
+}
+
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
