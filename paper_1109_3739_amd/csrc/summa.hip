@@ -10,14 +10,17 @@
 // stages), so no partial C_ij is written, re-read or merged.
 //
 // The plan builds the two concatenated patterns once:
-//   * left:  DCSC, m x sum(b_k); the nonempty columns of every A_k, moved to
+//   * left:  DCSC, m x sum(b_k); the stored columns of every A_k, moved to
 //            the stage's column range (its row ids and values are A_k's,
-//            one after the other);
+//            one after the other).  A CSC block's empty columns are listed too:
+//            a look-up finds them with length zero, and leaving them out would
+//            take a scan and a read-back of their number;
 //   * right: CSC, sum(b_k) x n; column j lists B_1(:,j), B_2(:,j) + b_1, ...
 //            in stage order, so rows stay ascending.
 // and a SpGEMM plan over them.  Exec copies the values of the stage blocks
 // into the concatenations and runs the SpGEMM numeric phase.
 #include <algorithm>
+#include <cstring>
 #include <vector>
 
 #include "common.h"
@@ -34,14 +37,15 @@ struct SumPlan : spx_plan {
   }
   int32_t count = 0;
   int vb_a = 0, vb_b = 0;
-  std::vector<Operand> a_h, b_h;      // the stage blocks
-  std::vector<int64_t> anz_h, bnz_h;  // nnz bases of the stages (count+1)
+  std::vector<Operand> a_h, b_h;  // the stage blocks
+  std::vector<int64_t> base_h;    // nnz bases of the A_k and B_k, slot bases, column bases (count+1 each)
+  std::vector<char> table_h;      // those, as copied to the device
   Operand* a_d = nullptr;
   Operand* b_d = nullptr;
+  int64_t* anzb = nullptr;   // [count+1] nnz bases of the A_k
   int64_t* bnzb = nullptr;   // [count+1] nnz bases of the B_k
   int64_t* slotb = nullptr;  // [count+1] slot bases of the A_k
   int64_t* colb = nullptr;   // [count+1] column bases of the A_k (= row bases of the B_k)
-  int64_t* anzb = nullptr;   // [count+1] nnz bases of the A_k
   int32_t* ajc = nullptr;
   int64_t* acp = nullptr;
   int32_t* air = nullptr;
@@ -53,87 +57,121 @@ struct SumPlan : spx_plan {
   spx_plan* gemm = nullptr;
 };
 
-__device__ __forceinline__ int stage_of(const int64_t* base, int count, int64_t x) {
-  int lo = 0, hi = count;  // last k with base[k] <= x
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (base[mid] <= x)
-      lo = mid;
-    else
-      hi = mid;
-  }
-  return lo;
-}
-
-// 1 for a nonempty slot of the concatenated left operand (slot i of all stages).
-struct LoadNonempty {
-  const Operand* a;
-  const int64_t* slotb;
-  int count;
-  __device__ int64_t operator()(int64_t i) const {
-    const int k = stage_of(slotb, count, i);
-    const int64_t t = i - slotb[k];
-    return slot_begin(a[k], t + 1) > slot_begin(a[k], t);
-  }
-};
-
-// Writes the DCSC column ids and pointers of the left concatenation.
-__global__ void k_sum_left(const Operand* a, const int64_t* slotb, const int64_t* colb, const int64_t* anzb,
-                           const int64_t* pos, int count, int32_t* jc, int64_t* cp) {
+// The left concatenation: column ids and pointers of every stage's slots, and
+// the row ids of its entries.  The work of a stage is small (8 stages of 2^17
+// columns: 0.9 M entries), so launches bound the plan: one takes all stages here
+// and below (stage = blockIdx.y).  With a launch or copy per stage that product
+// took 1.68 ms, with these 1.39.
+__global__ void k_sum_left(const Operand* a, const int64_t* slotb, const int64_t* colb, const int64_t* anzb, int count,
+                           int32_t* jc, int64_t* cp, int32_t* ir) {
   for (int k = blockIdx.y; k < count; k += gridDim.y) {
     const Operand X = a[k];
-    const int64_t ns = slotb[k + 1] - slotb[k];
-    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < ns; t += (int64_t)gridDim.x * blockDim.x) {
-      const int64_t s0 = slot_begin(X, t);
-      if (slot_begin(X, t + 1) == s0) continue;
-      const int64_t p = pos[slotb[k] + t];
-      jc[p] = (int32_t)(colb[k] + slot_col(X, t));
-      cp[p] = anzb[k] + s0;
+    const int64_t ns = slotb[k + 1] - slotb[k], ne = anzb[k + 1] - anzb[k];
+    const int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t t = i0; t < ns; t += step) {
+      jc[slotb[k] + t] = (int32_t)(colb[k] + slot_col(X, t));
+      cp[slotb[k] + t] = anzb[k] + slot_begin(X, t);
     }
+    for (int64_t e = i0; e < ne; e += step) ir[anzb[k] + e] = X.ir[e];
+    if (k == count - 1 && i0 == 0) cp[slotb[count]] = anzb[count];
   }
 }
 
-// Column lengths of the right concatenation (B_k share the n columns).
-__global__ void k_sum_right_count(Operand X, int64_t* cnt) {
-  const int64_t ns = nslots_of(X);
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < ns; t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t len = slot_begin(X, t + 1) - slot_begin(X, t);
-    if (len > 0)
-      atomicAdd(reinterpret_cast<unsigned long long*>(&cnt[slot_col(X, t)]), (unsigned long long)len);
+// Column lengths of the stages [k0, k0 + g) of B (which share the n columns):
+// len[(k - k0) n + j], zero on entry.
+__global__ void k_sum_right_count(const Operand* b, int k0, int g, int64_t n, uint32_t* len) {
+  for (int k = blockIdx.y; k < g; k += gridDim.y) {
+    const Operand X = b[k0 + k];
+    const int64_t ns = nslots_of(X);
+    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < ns; t += (int64_t)gridDim.x * blockDim.x)
+      len[k * n + slot_col(X, t)] = (uint32_t)(slot_begin(X, t + 1) - slot_begin(X, t));
   }
 }
 
-// Appends B_k's columns (rows moved down by the stage's row base) at each
-// column's cursor.  One wave per slot; stages run one launch after the
-// other, so every column's cursor has one writer per launch.
-__global__ void __launch_bounds__(256) k_sum_right_place(Operand X, int64_t rowb, int64_t* cur, int32_t* ir,
-                                                         int64_t* map) {
-  const int64_t ns = nslots_of(X);
-  const int lane = threadIdx.x % kWave;
+// Per column: the lengths become the stages' offsets in the column (after the
+// cnt[j] entries of earlier stages, if `more`), and cnt[j] what they end at.
+__global__ void k_sum_right_offsets(int g, bool more, int64_t n, uint32_t* len, int64_t* cnt) {
+  for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < n; j += (int64_t)gridDim.x * blockDim.x) {
+    uint32_t run = more ? (uint32_t)cnt[j] : 0;  // a column has fewer than 2^31 entries (its rows are below 2^31)
+    for (int k = 0; k < g; ++k) {
+      const uint32_t x = len[k * n + j];
+      len[k * n + j] = run;
+      run += x;
+    }
+    cnt[j] = run;
+  }
+}
+
+// Places every stage's columns (rows moved down by the stage's row base) at
+// their offsets.  A wave takes four slots at a time, one per 16-lane group;
+// slots of more than 64 entries then take the whole wave.
+__global__ void __launch_bounds__(256) k_sum_right_place(const Operand* b, const int64_t* colb, const int64_t* bnzb,
+                                                         int k0, int g, int64_t n, const int64_t* bcp, const uint32_t* off,
+                                                         int32_t* ir, int64_t* map) {
+  const int lane = lane_id(), gl = lane & 15;
   const int64_t w0 = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave;
   const int64_t nw = (int64_t)gridDim.x * blockDim.x / kWave;
-  for (int64_t t = w0; t < ns; t += nw) {
-    const int64_t s0 = slot_begin(X, t), s1 = slot_begin(X, t + 1);
-    if (s1 == s0) continue;
-    const int64_t j = slot_col(X, t);
-    const int64_t dst = cur[j];
-    for (int64_t e = s0 + lane; e < s1; e += kWave) {
-      ir[dst + (e - s0)] = (int32_t)(X.ir[e] + rowb);
-      map[e] = dst + (e - s0);
+  for (int kk = blockIdx.y; kk < g; kk += gridDim.y) {
+    const int k = k0 + kk;
+    const Operand X = b[k];
+    const int64_t ns = nslots_of(X), rowb = colb[k];
+    int64_t* mp = map + bnzb[k];
+    for (int64_t base = w0 * 4; base < ns; base += nw * 4) {
+      const int64_t t = base + (lane >> 4);
+      int64_t s0 = 0, s1 = 0, dst = 0;
+      if (t < ns) {
+        s0 = slot_begin(X, t);
+        s1 = slot_begin(X, t + 1);
+        const int64_t j = slot_col(X, t);
+        dst = bcp[j] + off[kk * n + j];
+      }
+      const bool whole = s1 - s0 > kWave;
+      if (!whole)
+        for (int64_t e = s0 + gl; e < s1; e += 16) {
+          ir[dst + (e - s0)] = (int32_t)(X.ir[e] + rowb);
+          mp[e] = dst + (e - s0);
+        }
+      uint64_t rest = __ballot(whole && gl == 0);
+      while (rest) {  // uniform
+        const int src = __ffsll((unsigned long long)rest) - 1;
+        rest &= rest - 1;
+        const int64_t a0 = __shfl(s0, src), a1 = __shfl(s1, src), d = __shfl(dst, src);
+        for (int64_t e = a0 + lane; e < a1; e += kWave) {
+          ir[d + (e - a0)] = (int32_t)(X.ir[e] + rowb);
+          mp[e] = d + (e - a0);
+        }
+      }
     }
-    if (lane == 0) cur[j] = dst + (s1 - s0);
   }
 }
 
-// Values of the right concatenation: stage k scatters through its map.
-__global__ void k_sum_right_vals(const Operand* b, const int64_t* bnzb, const int64_t* map, int count, int vb,
-                                 void* out) {
+// Values of both concatenations: the left one's stages lie one after the
+// other, the right one's scatter through the map.
+__global__ void k_sum_vals(const Operand* a, const int64_t* anzb, int va, void* aout, const Operand* b,
+                           const int64_t* bnzb, const int64_t* map, int vb, void* bout, int count) {
+  const int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
   for (int k = blockIdx.y; k < count; k += gridDim.y) {
-    const int64_t len = bnzb[k + 1] - bnzb[k];
-    const void* src = b[k].num;
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < len; e += (int64_t)gridDim.x * blockDim.x)
-      copy_value(src, e, out, map[bnzb[k] + e], vb);
+    if (va) {
+      const int64_t len = anzb[k + 1] - anzb[k];
+      const void* src = a[k].num;
+      for (int64_t e = i0; e < len; e += step) copy_value(src, e, aout, anzb[k] + e, va);
+    }
+    if (vb) {
+      const int64_t len = bnzb[k + 1] - bnzb[k];
+      const void* src = b[k].num;
+      for (int64_t e = i0; e < len; e += step) copy_value(src, e, bout, map[bnzb[k] + e], vb);
+    }
   }
+}
+
+// Words of the table of column lengths: all stages of an 8 x 8 grid's blocks of
+// 2^20 columns, and 256 MiB at most unless one stage alone takes more.
+constexpr int64_t kLenTable = 1ll << 26;
+
+// Grid over the elements of the largest stage (x) and the stages (y).
+static dim3 stage_grid(int64_t widest, int per_block, int count) {
+  return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(widest, per_block), 2048)),
+              (unsigned)std::min(count, 64));
 }
 
 const spx_plan* sum_plan_inner(const spx_plan* plan) { return static_cast<const SumPlan*>(plan)->gemm; }
@@ -178,92 +216,79 @@ extern "C" int spx_spgemm_sum_plan(const spx_ctx* ctx, int32_t count, const spx_
   P->vb_a = value_size(A[0].val_t);
   P->vb_b = value_size(B[0].val_t);
   const int64_t m = A[0].m, n = B[0].n;
-  std::vector<int64_t> slotb(count + 1, 0), colb(count + 1, 0);
-  P->anz_h.assign(count + 1, 0);
-  P->bnz_h.assign(count + 1, 0);
+  P->base_h.assign(4 * (count + 1), 0);
+  int64_t* const anzb = P->base_h.data();
+  int64_t *const bnzb = anzb + count + 1, *const slotb = bnzb + count + 1, *const colb = slotb + count + 1;
+  int64_t wide_a = 0, wide_b = 0, wide_bs = 0;  // largest stage: A's slots or entries, B's entries, B's slots
   for (int k = 0; k < count; ++k) {
     P->a_h.push_back(make_operand(&A[k]));
     P->b_h.push_back(make_operand(&B[k]));
     slotb[k + 1] = slotb[k] + nslots_of(P->a_h[k]);
     colb[k + 1] = colb[k] + A[k].n;
-    P->anz_h[k + 1] = P->anz_h[k] + A[k].nnz;
-    P->bnz_h[k + 1] = P->bnz_h[k] + B[k].nnz;
+    anzb[k + 1] = anzb[k] + A[k].nnz;
+    bnzb[k + 1] = bnzb[k] + B[k].nnz;
+    wide_a = std::max({wide_a, nslots_of(P->a_h[k]), A[k].nnz});
+    wide_b = std::max(wide_b, B[k].nnz);
+    wide_bs = std::max(wide_bs, nslots_of(P->b_h[k]));
   }
   slots = slotb[count];
-  // stage tables on the device (the host vectors live as long as the plan)
-  SPX_TRY(scr.get_n(count, &P->a_d));
-  SPX_TRY(scr.get_n(count + 1, &P->slotb));
-  SPX_TRY(scr.get_n(count + 1, &P->colb));
-  SPX_TRY(scr.get_n(count + 1, &P->anzb));
-  SPX_TRY(scr.get_n(count, &P->b_d));
-  SPX_TRY(scr.get_n(count + 1, &P->bnzb));
-  SPX_HIP(hipMemcpyAsync(P->a_d, P->a_h.data(), sizeof(Operand) * count, hipMemcpyHostToDevice, st));
-  SPX_HIP(hipMemcpyAsync(P->b_d, P->b_h.data(), sizeof(Operand) * count, hipMemcpyHostToDevice, st));
-  SPX_HIP(hipMemcpyAsync(P->bnzb, P->bnz_h.data(), 8 * (count + 1), hipMemcpyHostToDevice, st));
-  std::vector<int64_t> tables(3 * (count + 1));
-  std::copy(slotb.begin(), slotb.end(), tables.begin());
-  std::copy(colb.begin(), colb.end(), tables.begin() + (count + 1));
-  std::copy(P->anz_h.begin(), P->anz_h.end(), tables.begin() + 2 * (count + 1));
-  SPX_HIP(hipMemcpyAsync(P->slotb, tables.data(), 8 * (count + 1), hipMemcpyHostToDevice, st));
-  SPX_HIP(hipMemcpyAsync(P->colb, tables.data() + (count + 1), 8 * (count + 1), hipMemcpyHostToDevice, st));
-  SPX_HIP(hipMemcpyAsync(P->anzb, tables.data() + 2 * (count + 1), 8 * (count + 1), hipMemcpyHostToDevice, st));
+  // the columns' lengths are tabled for a group of stages at a time
+  const int group = (int)std::clamp<int64_t>(kLenTable / std::max<int64_t>(n, 1), 1, count);
+  // stage tables in one copy (the host bytes live as long as the plan)
+  const size_t ops = sizeof(Operand) * count, bases = sizeof(int64_t) * P->base_h.size();
+  P->table_h.resize(2 * ops + bases);
+  std::memcpy(P->table_h.data(), P->a_h.data(), ops);
+  std::memcpy(P->table_h.data() + ops, P->b_h.data(), ops);
+  std::memcpy(P->table_h.data() + 2 * ops, P->base_h.data(), bases);
+  char* table = nullptr;
+  int64_t* cnt = nullptr;
+  uint32_t* len = nullptr;
+  SPX_TRY(scr.get_many({Scratch::part(&table, (int64_t)P->table_h.size()), Scratch::part(&P->ajc, slots),
+                        Scratch::part(&P->acp, slots + 1), Scratch::part(&P->air, anz), Scratch::part(&cnt, n),
+                        Scratch::part(&P->bcp, n + 1), Scratch::part(&P->bir, bnz), Scratch::part(&P->bmap, bnz),
+                        Scratch::part(&len, group * n + 1)}));
+  if (P->vb_a) SPX_TRY(scr.get(std::max<int64_t>(anz, 1) * P->vb_a, &P->anum));
+  if (P->vb_b) SPX_TRY(scr.get(std::max<int64_t>(bnz, 1) * P->vb_b, &P->bnum));
+  static_assert(sizeof(Operand) % sizeof(int64_t) == 0, "the bases follow the operands");
+  P->a_d = reinterpret_cast<Operand*>(table);
+  P->b_d = P->a_d + count;
+  P->anzb = reinterpret_cast<int64_t*>(table + 2 * ops);
+  P->bnzb = P->anzb + count + 1;
+  P->slotb = P->bnzb + count + 1;
+  P->colb = P->slotb + count + 1;
+  SPX_HIP(hipMemcpyAsync(table, P->table_h.data(), P->table_h.size(), hipMemcpyHostToDevice, st));
 
   // left concatenation (DCSC)
-  int64_t* pos = nullptr;
-  SPX_TRY(scr.get_n(slots + 1, &pos));
-  SPX_TRY(exclusive_scan(LoadNonempty{P->a_d, P->slotb, count}, slots, pos, scr, st));
-  int64_t nzc_a = 0;
-  SPX_HIP(hipMemcpyAsync(&nzc_a, pos + slots, 8, hipMemcpyDeviceToHost, st));
-  SPX_HIP(hipStreamSynchronize(st));  // tables and nzc_a are read below
-  SPX_TRY(scr.get_n(std::max<int64_t>(nzc_a, 1), &P->ajc));
-  SPX_TRY(scr.get_n(nzc_a + 1, &P->acp));
-  SPX_TRY(scr.get_n(std::max<int64_t>(anz, 1), &P->air));
-  if (P->vb_a) SPX_TRY(scr.get(std::max<int64_t>(anz, 1) * P->vb_a, &P->anum));
-  if (slots > 0) {
-    const unsigned gy = (unsigned)std::min<int>(count, 64);
-    int64_t widest = 0;
-    for (const Operand& X : P->a_h) widest = std::max(widest, nslots_of(X));
-    dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(widest, 256), 1024)), gy);
-    k_sum_left<<<grid, 256, 0, st>>>(P->a_d, P->slotb, P->colb, P->anzb, pos, count, P->ajc, P->acp);
-    SPX_HIP(hipGetLastError());
-  }
-  SPX_TRY(fill_i64(P->acp + nzc_a, 1, anz, st));
-  for (int k = 0; k < count; ++k)
-    if (A[k].nnz > 0)
-      SPX_HIP(hipMemcpyAsync(P->air + P->anz_h[k], A[k].ir, 4 * A[k].nnz, hipMemcpyDeviceToDevice, st));
-
+  k_sum_left<<<stage_grid(wide_a, 256, count), 256, 0, st>>>(P->a_d, P->slotb, P->colb, P->anzb, count, P->ajc, P->acp,
+                                                             P->air);
+  SPX_HIP(hipGetLastError());
   // right concatenation (CSC)
-  int64_t* cnt = nullptr;
-  int64_t* cur = nullptr;
-  SPX_TRY(scr.get_n(std::max<int64_t>(n, 1), &cnt));
-  SPX_TRY(scr.get_n(n + 1, &P->bcp));
-  SPX_TRY(scr.get_n(n + 1, &cur));
-  SPX_TRY(scr.get_n(std::max<int64_t>(bnz, 1), &P->bir));
-  SPX_TRY(scr.get_n(std::max<int64_t>(bnz, 1), &P->bmap));
-  if (P->vb_b) SPX_TRY(scr.get(std::max<int64_t>(bnz, 1) * P->vb_b, &P->bnum));
-  SPX_TRY(fill_i64(cnt, n, 0, st));
-  for (int k = 0; k < count; ++k) {
-    const int64_t ns = nslots_of(P->b_h[k]);
-    if (ns == 0 || B[k].nnz == 0) continue;
-    k_sum_right_count<<<grid_for(ns, 256, 4096), 256, 0, st>>>(P->b_h[k], cnt);
+  auto offsets = [&](int k0, int g) -> int {
+    SPX_TRY(zero_words(st, {{len, ceil_div(g * n, 2)}}));
+    k_sum_right_count<<<stage_grid(wide_bs, 256, g), 256, 0, st>>>(P->b_d, k0, g, n, len);
     SPX_HIP(hipGetLastError());
-  }
+    k_sum_right_offsets<<<grid_for(n, 256, 4096), 256, 0, st>>>(g, k0 > 0, n, len, cnt);
+    SPX_HIP(hipGetLastError());
+    return SPX_OK;
+  };
+  if (n > 0)
+    for (int k0 = 0; k0 < count; k0 += group) SPX_TRY(offsets(k0, std::min(group, count - k0)));
   SPX_TRY(exclusive_scan(LoadI64{cnt}, n, P->bcp, scr, st));
-  SPX_HIP(hipMemcpyAsync(cur, P->bcp, 8 * (n + 1), hipMemcpyDeviceToDevice, st));
-  for (int k = 0; k < count; ++k) {
-    const int64_t ns = nslots_of(P->b_h[k]);
-    if (ns == 0 || B[k].nnz == 0) continue;
-    k_sum_right_place<<<grid_for(ns * kWave, 256, 8192), 256, 0, st>>>(P->b_h[k], colb[k], cur, P->bir,
-                                                                        P->bmap + P->bnz_h[k]);
-    SPX_HIP(hipGetLastError());
-  }
+  if (bnz > 0)
+    for (int k0 = 0; k0 < count; k0 += group) {
+      const int g = std::min(group, count - k0);
+      if (group < count) SPX_TRY(offsets(k0, g));
+      k_sum_right_place<<<stage_grid(wide_bs, 16, g), 256, 0, st>>>(P->b_d, P->colb, P->bnzb, k0, g, n, P->bcp, len,
+                                                                    P->bir, P->bmap);
+      SPX_HIP(hipGetLastError());
+    }
 
   // one SpGEMM over the concatenations
   spx_mat Ac{}, Bc{};
   Ac.m = m;
   Ac.n = inner;
   Ac.nnz = anz;
-  Ac.nzc = nzc_a;
+  Ac.nzc = slots;
   Ac.fmt = SPX_DCSC;
   Ac.ptr_t = SPX_PTR_I64;
   Ac.val_t = A[0].val_t;
@@ -291,20 +316,12 @@ extern "C" int spx_spgemm_sum_exec(spx_plan* plan, spx_mat* C) {
   if (!plan || plan->kind != kPlanSum) return fail(SPX_EINVAL, "not a stage-sum plan");
   auto* P = static_cast<SumPlan*>(plan);
   hipStream_t st = stream_of(&P->ctx);
-  if (P->vb_a) {
-    for (int k = 0; k < P->count; ++k) {
-      const int64_t len = P->anz_h[k + 1] - P->anz_h[k];
-      if (len > 0)
-        SPX_HIP(hipMemcpyAsync(static_cast<char*>(P->anum) + P->anz_h[k] * P->vb_a, P->a_h[k].num, len * P->vb_a,
-                               hipMemcpyDeviceToDevice, st));
-    }
-  }
-  if (P->vb_b && P->bnz_h[P->count] > 0) {
-    int64_t widest = 0;
-    for (int k = 0; k < P->count; ++k) widest = std::max(widest, P->bnz_h[k + 1] - P->bnz_h[k]);
-    dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(widest, 256), 2048)),
-              (unsigned)std::min<int>(P->count, 64));
-    k_sum_right_vals<<<grid, 256, 0, st>>>(P->b_d, P->bnzb, P->bmap, P->count, P->vb_b, P->bnum);
+  int64_t widest = 0;
+  for (int k = 0; k < P->count; ++k)
+    widest = std::max({widest, P->vb_a ? P->a_h[k].nnz : 0, P->vb_b ? P->b_h[k].nnz : 0});
+  if (widest > 0) {
+    k_sum_vals<<<stage_grid(widest, 256, P->count), 256, 0, st>>>(P->a_d, P->anzb, P->vb_a, P->anum, P->b_d, P->bnzb,
+                                                                  P->bmap, P->vb_b, P->bnum, P->count);
     SPX_HIP(hipGetLastError());
   }
   return spx_spgemm_exec(P->gemm, C);
