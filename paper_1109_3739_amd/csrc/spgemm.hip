@@ -584,67 +584,44 @@ __device__ __forceinline__ uint32_t hash_row(int32_t r, int log2s) {
   return ((uint32_t)r * 0x9E3779B1u) >> (32 - log2s);
 }
 
-// ------------------------------------------------------------------ count: tiny (one wave)
-template <int G>
-__device__ __forceinline__ int group_incl_scan(int v, int) {
-  return group_scan<G>(v, 0, [](int x, int y) { return x + y; });
-}
+// ------------------------------------------------------------------ tiny columns (lane groups)
+struct TinyCol {
+  int64_t b0, b1, o;  // B range and output offset
+  int32_t t, m;       // column (slot of B), -1: none; products
+};
 
-template <int G, typename K>
-__device__ __forceinline__ K group_sort(K key, int gl) {  // ascending bitonic sort, one key per lane
-#pragma unroll
-  for (int k = 2; k <= G; k <<= 1) {
-#pragma unroll
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      const K other = xor_lane(key, j);
-      const bool up = (gl & k) == 0;
-      const bool lower = (gl & j) == 0;
-      const K mn = other < key ? other : key;
-      const K mx = other < key ? key : other;
-      key = (lower == up) ? mn : mx;
-    }
-  }
-  return key;
-}
+template <typename T>
+struct TinyLds {  // of one wave
+  TinyCol col[kWave];
+  int32_t row[kWave];
+  int32_t aux[kWave];
+  T val[kWave];
+};
 
-// One tiny column (at most G products) in a group of G lanes: the group
-// gathers every product into LDS; the count (COUNT) inserts the rows into a
-// small LDS table and counts the distinct ones; the numeric pass sorts the
-// (row, product index) keys, sums each run of equal rows in product order
-// -- the order of Algorithm 1 -- and writes the column.  The column's B
-// range [b0, b1) and output offset come from the caller.
-template <int G, int SR, typename T, bool COUNT>
-__device__ __forceinline__ void tiny_column(const Operand& A, const Operand& B, const int64_t* bq_a0,
-                                            const int32_t* bq_alen, int32_t t, int64_t b0, int64_t b1,
-                                            int64_t obase, int64_t* cnt, int32_t* cir, T* cnum, int32_t* s_row,
-                                            int32_t* s_aux, T* s_val, uint32_t* s_tab) {
+// The products of a column, one per lane of its group, when they don't fit the
+// block layout: lane gl takes product gl of the column's list.  Returns its
+// row, -1 past the end.
+template <int G, int SR, typename T, bool VAL>
+__device__ __forceinline__ int32_t tiny_listed(const Operand& A, const Operand& B, const int64_t* bq_a0,
+                                               const int32_t* bq_alen, int64_t b0, int64_t b1, TinyLds<T>& L, T& val) {
   using S = Semiring<SR, T>;
-  constexpr bool kVal = SR != SPX_OR_AND;
-  const int lane = lane_id();
-  const int gl = lane & (G - 1);
-  const int gb = lane & ~(G - 1);
-  s_row += gb;
-  s_aux += gb;
-  s_val += gb;
+  const int lane = lane_id(), gl = lane & (G - 1), gb = lane & ~(G - 1);
+  int32_t *const s_row = L.row + gb, *const s_aux = L.aux + gb;
+  T* const s_val = L.val + gb;
   const T* an = (const T*)A.num;
   const T* bn = (const T*)B.num;
   int total = 0;
-  for (int64_t qc = b0; qc < b1; qc += G) {
+  // groups of one wave go on until the longest is done (a group past its end has no products)
+  for (int64_t qc = b0; __any(qc < b1); qc += G) {
     const int64_t q = qc + gl;
     const bool inq = q < b1;
-    // each lane loads its own B entry's A range (and value) next to its
-    // length; the lanes that take the products get them by shuffles
     const int al = inq ? bq_alen[q] : 0;
     const int64_t qa0 = inq ? bq_a0[q] : 0;
     T qb = T(0);
-    if constexpr (kVal && S::kUsesB) qb = inq ? bn[q] : T(0);
-    const int incl = group_incl_scan<G>(al, gl);
+    if constexpr (VAL && S::kUsesB) qb = inq ? bn[q] : T(0);
+    const int incl = group_scan<G>(al, 0, [](int x, int y) { return x + y; });
     const int excl = incl - al;
-    // the group's total: its last lane, read as a scalar (lanes of an idle
-    // half may hold stale values, which only that half would read)
-    const int ctot = G == 64 ? __builtin_amdgcn_readlane(incl, 63)
-                             : (lane < 32 ? __builtin_amdgcn_readlane(incl, 31) : __builtin_amdgcn_readlane(incl, 63));
-    if (ctot == 0) continue;
+    const int ctot = __shfl(incl, G - 1, G);
     s_aux[gl] = -1;
     wave_sync();
     if (al > 0 && excl < G) s_aux[excl] = gl;
@@ -654,167 +631,181 @@ __device__ __forceinline__ void tiny_column(const Operand& A, const Operand& B, 
     const int ostart = __shfl(excl, src, G);
     const int64_t ea0 = __shfl(qa0, src, G);
     T bv = T(0);
-    if constexpr (kVal && S::kUsesB) bv = __shfl(qb, src, G);
+    if constexpr (VAL && S::kUsesB) bv = __shfl(qb, src, G);
     if (gl < ctot && total + gl < G) {
       const int64_t e = ea0 + (gl - ostart);
       s_row[total + gl] = A.ir[e];
-      if constexpr (kVal) {
-        const T a = S::kUsesA ? an[e] : T(0);
-        s_val[total + gl] = S::mul(a, bv);
-      }
+      if constexpr (VAL) s_val[total + gl] = S::mul(S::kUsesA ? an[e] : T(0), bv);
     }
     total += ctot;
     wave_sync();
   }
-  if (total > G) total = G;  // cannot happen: the caller checked the column's products
-  if constexpr (COUNT) {
-    // distinct rows: each lane inserts its product's row into the group's
-    // table of 2G slots (linear probing; a row is below 2^31, so the empty
-    // mark never matches); the lanes that claimed a slot hold the distinct rows
-    uint32_t* tab = s_tab + 2 * gb;
-    tab[gl] = 0xffffffffu;
-    tab[gl + G] = 0xffffffffu;
-    wave_sync();
-    bool fresh = false;
-    if (gl < total) {
-      const uint32_t r = (uint32_t)s_row[gl];
-      uint32_t h = (r * 0x9E3779B1u) >> (32 - (G == 64 ? 7 : 6));
-      for (;;) {
-        const uint32_t old = atomicCAS(&tab[h], 0xffffffffu, r);
-        if (old == 0xffffffffu) {
-          fresh = true;
-          break;
-        }
-        if (old == r) break;
-        h = (h + 1) & (2 * G - 1);
+  if constexpr (VAL) val = gl < total ? s_val[gl] : T(0);
+  return gl < total ? s_row[gl] : -1;
+}
+
+// Columns k .. k + 64/G - 1 of the wave's table (at most G products each), one
+// per group of G lanes.  Lanes take the products of the column's B entries in
+// blocks: W = the largest power of two for which the entries of every group fit;
+// lane p of block i takes product p of entry i, so a lane finds its product by
+// its own number and every block is ascending before the sort.  (Columns with an
+// A column longer than W list their products first.)  The numeric pass sorts
+// (row, lane) keys and sums each run of equal rows in product order -- the order
+// of Algorithm 1 --, the count sorts the rows and counts the first of each run.
+template <int G, int SR, typename T, bool COUNT>
+__device__ __forceinline__ void tiny_group(const Operand& A, const Operand& B, const int64_t* bq_a0,
+                                           const int32_t* bq_alen, int k, int kend, int64_t* cnt, int32_t* cir,
+                                           T* cnum, TinyLds<T>& L, const LaneSides& sides) {
+  using S = Semiring<SR, T>;
+  constexpr bool kVal = SR != SPX_OR_AND && !COUNT;
+  const int lane = lane_id(), gl = lane & (G - 1), gb = lane & ~(G - 1);
+  const int mine = k + lane / G;
+  int64_t b0 = 0, b1 = 0, obase = 0;
+  int32_t t = -1;
+  if (mine < kend) {
+    const TinyCol& c = L.col[mine];
+    b0 = c.b0;
+    b1 = c.b1;
+    t = c.t;
+    if constexpr (!COUNT) obase = c.o;
+  }
+  const int nb = b1 - b0 > G ? G + 1 : (int)(b1 - b0);
+  int most = __builtin_amdgcn_readfirstlane(nb);
+#pragma unroll
+  for (int g = G; g < kWave; g += G) most = max(most, __builtin_amdgcn_readlane(nb, g));
+  int32_t row = -1;
+  T val = T(0);
+  int sorted = 1;
+  bool blocks = false;
+  if (most <= G) {  // uniform
+    const int lw = (G == 64 ? 6 : (G == 32 ? 5 : 4)) - (most <= 1 ? 0 : 32 - __builtin_clz((unsigned)most - 1));
+    const int64_t q = b0 + (gl >> lw);
+    const bool inq = q < b1;
+    const int al = inq ? bq_alen[q] : 0;
+    int64_t e = inq ? bq_a0[q] : 0;
+    T bv = T(0);
+    if constexpr (kVal && S::kUsesB) bv = inq ? ((const T*)B.num)[q] : T(0);
+    blocks = __ballot(al > 1 << lw) == 0;
+    if (blocks) {  // uniform
+      sorted = 1 << lw;
+      const int p = gl & (sorted - 1);
+      e += p;
+      if (p < al) {
+        row = A.ir[e];
+        if constexpr (kVal) val = S::mul(S::kUsesA ? ((const T*)A.num)[e] : T(0), bv);
       }
     }
-    const uint64_t gmask = G == 64 ? ~0ull : (0xffffffffull << gb);
-    const uint64_t fm = __ballot(fresh) & gmask;
-    if (gl == 0) cnt[t] = __popcll(fm);
-    wave_sync();
-    return;
   }
-  // sort (row, product index): 32-bit keys when the rows leave 6 bits for
-  // the index (the count needs the rows only)
-  int32_t row;
-  int idx;
-  if (COUNT || A.m <= (1ll << 25)) {
-    const uint32_t k32 = gl < total ? (COUNT ? (uint32_t)s_row[gl] : ((uint32_t)s_row[gl] << 6) | gl) : 0xffffffffu;
-    const uint32_t key = group_sort<G, uint32_t>(k32, gl);
-    row = COUNT ? (int32_t)key : (int32_t)(key >> 6);
-    idx = COUNT ? 0 : (int)(key & 63u);
+  if (!blocks) row = tiny_listed<G, SR, T, kVal>(A, B, bq_a0, bq_alen, b0, b1, L, val);
+  // sorted rows; idx: the lane (of the group) whose product this is
+  bool valid;
+  int idx = 0;
+  if (COUNT) {
+    row = (int32_t)sort_runs<G>((uint32_t)row, sorted, sides);  // -1, the largest key, past the end
+    valid = row >= 0;
+  } else if (A.m <= (1ll << 25)) {  // 32-bit keys while the rows leave 6 bits for the lane
+    const uint32_t key = sort_runs<G>(row < 0 ? ~0u : ((uint32_t)row << 6) | (uint32_t)gl, sorted, sides);
+    valid = key != ~0u;
+    row = (int32_t)(key >> 6);
+    idx = (int)(key & 63u);
   } else {
-    const uint64_t k64 = gl < total ? (((uint64_t)(uint32_t)s_row[gl]) << 32) | (uint32_t)gl : ~0ull;
-    const uint64_t key = group_sort<G, uint64_t>(k64, gl);
+    const uint64_t key = sort_runs<G>(row < 0 ? ~(uint64_t)0 : ((uint64_t)(uint32_t)row << 32) | (uint32_t)gl, sorted, sides);
+    valid = key != ~(uint64_t)0;
     row = (int32_t)(key >> 32);
-    idx = (int)(key & 0xffffffffu);
+    idx = (int)((uint32_t)key & 63u);
   }
   // the previous lane's row (DPP wave shift; lane 0 of a group never uses it)
   const int32_t prev = __builtin_amdgcn_update_dpp(0, row, 0x138, 0xF, 0xF, false);  // wave_shr:1
-  const bool valid = gl < total;
   const bool head = valid && (gl == 0 || prev != row);
-  const uint64_t gmask = G == 64 ? ~0ull : (0xffffffffull << gb);
-  const uint64_t hm = __ballot(head) & gmask;
-  if (COUNT) {
-    if (gl == 0) cnt[t] = __popcll(hm);
-  } else {
-    // every lane holds its sorted product's value; a head lane folds its run
-    // left to right (product order) from the values of the lanes after it
-    const uint64_t hg = hm >> gb;  // the group's heads, bit gl for lane gl
-    const uint64_t later = gl + 1 < 64 ? hg >> (gl + 1) : 0ull;
-    const int run = !head ? 0 : (later ? __ffsll((long long)later) : total - gl);
-    T acc = T(0);
-    if constexpr (kVal) {
-      const T v = valid ? s_val[idx] : T(0);
-      acc = v;
-      int mr = run;  // longest run of the wave
-#pragma unroll
-      for (int j = 32; j > 0; j >>= 1) {
-        const int t = (int)xor_lane_u32((uint32_t)mr, j);
-        mr = t > mr ? t : mr;
-      }
-      const int maxrun = __builtin_amdgcn_readfirstlane(mr);
-      T x = v;  // after d steps: the value of lane gl + d (inside the group while d < run)
-      for (int d = 1; d < maxrun; ++d) {
-        x = lane_next(x);
-        if (d < run) acc = S::add(acc, x);
-      }
+  const uint64_t hm = __ballot(head);
+  // heads of this lane's group, and those before the lane
+  uint32_t below;
+  if constexpr (G == 64) {
+    below = __builtin_amdgcn_mbcnt_hi((uint32_t)(hm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hm, 0));
+    if (COUNT) {
+      if (gl == 0 && t >= 0) cnt[t] = __popcll(hm);
+      return;
     }
-    if (head) {
-      const int64_t o = obase + __popcll(hm & lanemask_lt());
-      cir[o] = row;
-      if constexpr (kVal) cnum[o] = acc;
+  } else {
+    const uint32_t hg = (lane < 32 ? (uint32_t)hm : (uint32_t)(hm >> 32)) >> (gb & 31);
+    if (COUNT) {
+      if (gl == 0 && t >= 0) cnt[t] = __popc(G == 16 ? hg & 0xffffu : hg);
+      return;
+    }
+    below = __popc(hg & ((1u << gl) - 1u));
+  }
+  if constexpr (kVal) {
+    // every lane holds its sorted product's value; step d adds the value of lane
+    // + d while that lane goes on with this lane's run
+    T x = __shfl(val, gb + idx);
+    val = x;
+    const uint64_t cont = __ballot(valid && !head);
+    for (uint64_t later = cont >> 1, more = later; more; later >>= 1, more &= later) {
+      x = lane_next(x);
+      const T sum = S::add(val, x);
+      if (lane_of_mask(more)) val = sum;
     }
   }
-  wave_sync();
+  if (head) {
+    const int64_t o = obase + below;
+    cir[o] = row;
+    if constexpr (kVal) cnum[o] = val;
+  }
 }
 
-// Tiny columns (at most 64 products), by pairs of consecutive columns of
-// the bin: two columns of at most 32 products each share a wave (one per
-// half), otherwise they are done one after the other.  A wave takes up to
-// 64 pairs at a time (fewer when the bin is too small to give every wave
-// 64): lane k loads pair k's column ids, products, B ranges and output
-// offsets into the wave's LDS table (two load levels for all of them), and
-// the pair loop reads them from there, so a column waits only on its B
-// entries' A ranges and then A's rows and values.
+// Tiny columns (at most 64 products).  A wave takes up to 64 columns at a time
+// (fewer when the bin is too small to give every wave 64): lane k loads column
+// k's id, products, B range and output offset (two load levels for all of
+// them) into the wave's LDS table, ordered by products: columns of at most 16
+// are then done four at a time, of at most 32 two at a time, the others one by
+// one, and a column waits only on its B entries' A ranges and then A's rows and
+// values.  Half the time is instruction issue, the rest those two waits.  512
+// Galerkin levels (A P with 56 products a column, then P^T (A P) with 32): numeric
+// 7.36 + 4.16 -> 4.44 + 2.80 ms, count 2.57 + 1.55 -> 2.01 + 1.33 ms against a sort of
+// all 64 lanes after a scan for the lanes' products (the count: a table of rows).
+// Loading the next columns' ranges early took more registers than it hid: 4.37 +
+// 2.58 and 2.95 + 1.73 ms.  The grid is as long as there are columns, up to 64
+// workgroups a CU: with 16 the last of three rounds was mostly empty.
 template <int SR, typename T, bool COUNT>
 __global__ void __launch_bounds__(256) k_tiny(Operand A, Operand B, const int64_t* bq_a0, const int32_t* bq_alen,
                                               const int64_t* mults, const int32_t* list, const int64_t* binoff,
                                               int64_t* cnt, const int64_t* off, int32_t* cir, T* cnum) {
-  __shared__ int32_t s_row[4][kWave];
-  __shared__ int32_t s_aux[4][kWave];
-  __shared__ T s_val[4][kWave];
-  struct PairRow {
-    int32_t t[2];
-    int32_t m[2];  // products (a tiny column's fit 32 bits)
-    int64_t b0[2], b1[2], o[2];
-  };
-  __shared__ PairRow s_pair[4][kWave];
-  __shared__ uint32_t s_tab[4][2 * kWave];  // the count's distinct-row tables
-  const int w = threadIdx.x / kWave, lane = lane_id();
-  const int64_t beg = binoff[kBinTiny], end = binoff[kBinTiny + 1];
-  const int64_t npairs = (end - beg + 1) / 2;
-  const int64_t wave = (int64_t)blockIdx.x * 4 + w, nwaves = (int64_t)gridDim.x * 4;
-  const int64_t per = std::min<int64_t>(kWave, std::max<int64_t>(1, (npairs + nwaves - 1) / nwaves));
-  for (int64_t c0 = wave * per; c0 < npairs; c0 += nwaves * per) {
-    {  // lane k: pair c0 + k
-      const int64_t pos = beg + 2 * (c0 + lane);
-      PairRow r{};
-      r.m[1] = -1;  // no second column
-      if (lane < per && c0 + lane < npairs) {
-        for (int h = 0; h < 2; ++h) {
-          if (pos + h >= end) break;
-          const int32_t t = list[pos + h];
-          r.t[h] = t;
-          r.m[h] = (int32_t)mults[t];
-          r.b0[h] = slot_begin(B, t);
-          r.b1[h] = slot_begin(B, t + 1);
-          r.o[h] = COUNT ? 0 : off[t];
-        }
-      }
-      s_pair[w][lane] = r;
+  __shared__ TinyLds<T> s_lds[4];
+  const int lane = lane_id();
+  TinyLds<T>& L = s_lds[threadIdx.x / kWave];
+  const LaneSides sides;
+  const int64_t beg = binoff[kBinTiny], ncols = binoff[kBinTiny + 1] - beg;
+  constexpr int kWaves = 4;
+  const int w = threadIdx.x / kWave;
+  // the waves of a block take every fourth column of its share each, so that
+  // neighbouring columns, which often share lines of A and always those of C, are done together
+  const int64_t nwaves = (int64_t)gridDim.x * kWaves;
+  const int64_t per = std::min<int64_t>(kWave, std::max<int64_t>(2, (ncols + nwaves - 1) / nwaves));
+  for (int64_t c0 = blockIdx.x * kWaves * per; c0 < ncols; c0 += nwaves * per) {
+    const int64_t left = ncols - c0 - w;
+    const int n = left <= 0 ? 0 : (int)std::min<int64_t>(per, (left + kWaves - 1) / kWaves);
+    TinyCol c{};
+    c.m = kWave;
+    if (lane < n) {
+      c.t = list[beg + c0 + kWaves * lane + w];
+      c.m = (int32_t)mults[c.t];
+      c.b0 = slot_begin(B, c.t);
+      c.b1 = slot_begin(B, c.t + 1);
+      c.o = COUNT ? 0 : off[c.t];
     }
+    const uint64_t m16 = __ballot(lane < n && c.m <= 16), m32 = __ballot(lane < n && c.m > 16 && c.m <= 32);
+    const uint64_t m64 = __ballot(lane < n && c.m > 32);
+    const int n16 = __popcll(m16), n32 = n16 + __popcll(m32);
+    const uint64_t same = c.m <= 16 ? m16 : (c.m <= 32 ? m32 : m64);
+    if (lane < n) L.col[(c.m <= 16 ? 0 : (c.m <= 32 ? n16 : n32)) + __popcll(same & lanemask_lt())] = c;
     wave_sync();
-    const int np = (int)std::min<int64_t>(per, npairs - c0);
-    for (int k = 0; k < np; ++k) {
-      const PairRow& r = s_pair[w][k];
-      const int32_t m1 = __builtin_amdgcn_readfirstlane(r.m[1]);
-      const bool has1 = m1 >= 0;
-      const int32_t m0 = __builtin_amdgcn_readfirstlane(r.m[0]);
-      if (has1 && m0 <= 32 && m1 <= 32) {
-        const int h = lane < 32 ? 0 : 1;
-        tiny_column<32, SR, T, COUNT>(A, B, bq_a0, bq_alen, r.t[h], r.b0[h], r.b1[h], r.o[h], cnt, cir, cnum,
-                                      s_row[w], s_aux[w], s_val[w], s_tab[w]);
-      } else {
-        tiny_column<64, SR, T, COUNT>(A, B, bq_a0, bq_alen, r.t[0], r.b0[0], r.b1[0], r.o[0], cnt, cir, cnum,
-                                      s_row[w], s_aux[w], s_val[w], s_tab[w]);
-        if (has1)
-          tiny_column<64, SR, T, COUNT>(A, B, bq_a0, bq_alen, r.t[1], r.b0[1], r.b1[1], r.o[1], cnt, cir, cnum,
-                                        s_row[w], s_aux[w], s_val[w], s_tab[w]);
-      }
-    }
-    wave_sync();  // the table is rewritten for the next 64 pairs
+    for (int k = 0; k < n16; k += 4)
+      tiny_group<16, SR, T, COUNT>(A, B, bq_a0, bq_alen, k, n16, cnt, cir, cnum, L, sides);
+    for (int k = n16; k < n32; k += 2)
+      tiny_group<32, SR, T, COUNT>(A, B, bq_a0, bq_alen, k, n32, cnt, cir, cnum, L, sides);
+    for (int k = n32; k < n; ++k)
+      tiny_group<64, SR, T, COUNT>(A, B, bq_a0, bq_alen, k, n, cnt, cir, cnum, L, sides);
+    wave_sync();  // the table is rewritten for the next columns
   }
 }
 
@@ -2196,7 +2187,7 @@ static int launch_numeric(GemmPlan* P, spx_mat* C, hipStream_t st) {
   P->mark(kEvParts, st);
   const int64_t ntiny = P->binoff_h[kBinTiny + 1] - P->binoff_h[kBinTiny];
   if (ntiny > 0) {
-    hipLaunchKernelGGL((k_tiny<SR, T, false>), dim3(grid_for(ntiny, 8, (int64_t)cus * 16)), dim3(256), 0, st, P->A,
+    hipLaunchKernelGGL((k_tiny<SR, T, false>), dim3(grid_for(ntiny, 8, (int64_t)cus * 64)), dim3(256), 0, st, P->A,
                        P->B, P->bq_a0, P->bq_alen, P->mults_d, P->list, P->binoff, P->cnt, P->off, cir, cnum);
     SPX_HIP(hipGetLastError());
   }
@@ -2416,7 +2407,7 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
   // exact counts
   const int64_t ntiny = bo[kBinTiny + 1] - bo[kBinTiny];
   if (ntiny > 0) {
-    k_tiny<SPX_OR_AND, float, true><<<grid_for(ntiny, 8, (int64_t)cus * 16), 256, 0, st>>>(
+    k_tiny<SPX_OR_AND, float, true><<<grid_for(ntiny, 8, (int64_t)cus * 64), 256, 0, st>>>(
         P->A, P->B, P->bq_a0, P->bq_alen, P->mults_d, P->list, P->binoff, P->cnt, nullptr, nullptr, nullptr);
     SPX_HIP(hipGetLastError());
   }
