@@ -323,9 +323,6 @@ extern "C" int spx_batch_plan(const spx_ctx* ctx, int32_t count, const spx_mat* 
   spx_ctx c2 = ctx ? *ctx : spx_ctx{};
   c2.validate = 0;
   SPX_TRY(spx_spgemm_plan(&c2, &Ac, &Bc, semiring, SPX_CSC, tuning, &P->gemm, &nnz, &nzc));
-  spx_plan_info info;
-  SPX_TRY(spx_plan_get_info(P->gemm, &info));
-  (void)info;
   // output nnz base of every product: the offsets of its first column
   int64_t* cb = nullptr;
   SPX_TRY(scr.get_n(count + 1, &cb));

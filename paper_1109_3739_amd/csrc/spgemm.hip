@@ -327,6 +327,105 @@ __global__ void __launch_bounds__(256) k_slot_mults_long(Operand B, const int32_
   if (threadIdx.x == 0 && acc) atomicAdd(spread(total), (unsigned long long)acc);
 }
 
+// Up to kSmallSlots slots: launches and their gaps bound the plan (4096 columns of 8
+// entries: 13 launches of 2 to 6 us, 106 us a pass, 76 with 9), so three launches take
+// the place of seven: one finds the ranges and the products, a wave for each slot, and
+// one workgroup each bins the columns and scans their counts.  The line lies where
+// one workgroup's work passes the launches it saves: 2^14 columns of an R-MAT graph took
+// 308 us this way, 271 by the separate launches.
+constexpr int kSmallSlots = 8192;
+constexpr int kSmallPer = kSmallSlots / 1024;
+
+// k_rowinfo and k_slot_mults of a small plan.  Columns are at most kSmallSlots
+// long here, 32 rounds of a wave with four loads in flight a lane; the ones above
+// kLongSlot are listed as by k_slot_mults.
+__global__ void __launch_bounds__(256) k_slots_small(Operand A, Operand B, const int64_t* aux, int64_t chunk,
+                                                     int64_t* bq_a0, int32_t* bq_alen, int nslots, int64_t* mults,
+                                                     unsigned long long* total, int32_t* longs,
+                                                     unsigned long long* nlong, unsigned* err) {
+  constexpr int U = 4;
+  const int lane = lane_id();
+  const int t = (int)((blockIdx.x * blockDim.x + threadIdx.x) / kWave);
+  int64_t sum = 0;
+  if (t < nslots) {
+    const int64_t b0 = slot_begin(B, t), b1 = slot_begin(B, t + 1);
+    for (int64_t q = b0 + lane; q < b1; q += U * kWave) {
+      int32_t k[U];
+      int64_t a0[U], a1[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) k[u] = q + u * kWave < b1 ? B.ir[q + u * kWave] : -1;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        a0[u] = a1[u] = 0;
+        if (k[u] >= 0 && k[u] < A.n) {
+          const int64_t slot = column_slot(A, aux, chunk, k[u]);
+          if (slot >= 0) {
+            a0[u] = load_ptr(A.cp, A.ptr_t, slot);
+            a1[u] = load_ptr(A.cp, A.ptr_t, slot + 1);
+          }
+        } else if (q + u * kWave < b1) {
+          atomicOr(err, 1u);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (q + u * kWave < b1) {
+          bq_a0[q + u * kWave] = a0[u];
+          bq_alen[q + u * kWave] = (int32_t)(a1[u] - a0[u]);
+          sum += (int32_t)(a1[u] - a0[u]);
+        }
+    }
+    sum = wave_sum(sum);
+    if (lane == 0) {
+      mults[t] = sum;
+      if (b1 - b0 > kLongSlot) longs[atomicAdd(nlong, 1ull)] = t;
+    }
+  }
+  add_total(sum, lane == 0, total);
+}
+
+// Bins, offsets and list (as k_bin_count and k_bin_fill) by one workgroup of 1024.
+__global__ void __launch_bounds__(1024) k_bin_small(const int64_t* mults, int nslots, BinCfg cfg, int64_t* binoff,
+                                                    int32_t* list) {
+  static_assert(kNumBins < kWave, "a wave scans the bins");
+  __shared__ int hist[kWave];
+  const int lane = lane_id();
+  if (threadIdx.x < kWave) hist[threadIdx.x] = 0;
+  int b[kSmallPer], rank[kSmallPer];
+#pragma unroll
+  for (int k = 0; k < kSmallPer; ++k) {
+    const int t = k * 1024 + threadIdx.x;
+    b[k] = t < nslots ? bin_of(mults[t], cfg) : -1;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kSmallPer; ++k) {
+    uint64_t rest = __ballot(b[k] >= 0);
+    rank[k] = 0;
+    while (rest) {  // one atomic for the lanes of a bin
+      const int first = __ffsll((unsigned long long)rest) - 1;
+      const int bin = __builtin_amdgcn_readlane(b[k], first);
+      const uint64_t same = __ballot(b[k] == bin);
+      int base = 0;
+      if (lane == first) base = atomicAdd(&hist[bin], __popcll(same));
+      base = __builtin_amdgcn_readlane(base, first);
+      if (b[k] == bin) rank[k] = base + __popcll(same & lanemask_lt());
+      rest &= ~same;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < kWave) {
+    const int n = hist[lane];
+    const int off = group_scan<kWave>(n, 0, [](int x, int y) { return x + y; }) - n;
+    hist[lane] = off;
+    if (lane <= kNumBins) binoff[lane] = off;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kSmallPer; ++k)
+    if (b[k] >= 0) list[hist[b[k]] + rank[k]] = k * 1024 + threadIdx.x;
+}
+
 // Counting sort of slots into bins: histogram, offsets, fill.
 __global__ void k_bin_count(const int64_t* mults, int64_t nslots, BinCfg cfg, unsigned long long* counts) {
   __shared__ unsigned hist[kNumBins];
@@ -1933,6 +2032,47 @@ __global__ void __launch_bounds__(kScanThreads) k_cnt_apply(const int64_t* cnt, 
   }
 }
 
+// Both for up to kSmallSlots columns, by one workgroup of 1024.
+__global__ void __launch_bounds__(1024) k_cnt_small(const int64_t* cnt, const int64_t* col_mults, int64_t tiny_max, int n,
+                                                    int64_t* off, int64_t* zoff, int zfull,
+                                                    const unsigned long long* totals, unsigned long long* mults,
+                                                    unsigned long long* nnz_tiny) {
+  __shared__ int64_t red[1024 / kWave + 1];
+  const int per = (n + 1023) / 1024;  // columns per thread
+  const int base = (int)threadIdx.x * per;
+  int64_t v[kSmallPer];
+  int64_t s = 0, z = 0, ti = 0;
+#pragma unroll
+  for (int k = 0; k < kSmallPer; ++k) {
+    const bool in = k < per && base + k < n;
+    v[k] = in ? cnt[base + k] : 0;
+    const int64_t mu = in ? col_mults[base + k] : 0;
+    s += v[k];
+    z += v[k] > 0;
+    if (mu <= tiny_max) ti += v[k];
+  }
+  int64_t total, ztotal, titotal;
+  block_excl_scan(ti, red, &titotal);
+  int64_t run = block_excl_scan(s, red, &total);
+  int64_t zrun = block_excl_scan(z, red, &ztotal);
+#pragma unroll
+  for (int k = 0; k < kSmallPer; ++k)
+    if (k < per && base + k < n) {
+      off[base + k] = run;
+      if (zfull) zoff[base + k] = zrun;
+      run += v[k];
+      zrun += v[k] > 0;
+    }
+  if (threadIdx.x == 0) {
+    unsigned long long m = 0;
+    for (int i = 0; i < kSpread; ++i) m += totals[i * 16];
+    *mults = m;
+    *nnz_tiny = (unsigned long long)titotal;
+    off[n] = total;
+    zoff[n] = ztotal;
+  }
+}
+
 __global__ void k_parts_sum(const Part* parts, int64_t n, unsigned long long* out) {
   int64_t s = 0;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
@@ -2094,6 +2234,12 @@ static int32_t hash_most(int64_t L, int64_t sz) {
 static int scan_counts(GemmPlan* P, Scratch& scr, hipStream_t st) {
   const int64_t n = P->nslots;
   if (n <= 0) return zero_words(st, {{P->off, 1}, {P->zoff, 1}});
+  if (n <= kSmallSlots) {
+    k_cnt_small<<<1, 1024, 0, st>>>(P->cnt, P->mults_d, P->tune.tiny_max, (int)n, P->off, P->zoff, P->c_fmt == SPX_DCSC,
+                                    P->totals, &P->sum->mults, &P->sum->nnz_tiny);
+    SPX_HIP(hipGetLastError());
+    return SPX_OK;
+  }
   const int64_t nb = ceil_div(n, kScanTile);
   int64_t *sums = nullptr, *zsums = nullptr, *carry = nullptr, *zcarry = nullptr;
   SPX_TRY(scr.get_many({Scratch::part(&sums, nb), Scratch::part(&zsums, nb)}));
@@ -2318,25 +2464,33 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
   // AUX index for a DCSC A
   int64_t chunk = 1;
   SPX_TRY(build_aux(P->A, scr, st, &P->aux, &chunk));
-  if (B->nnz > 0) {
-    k_rowinfo<<<grid_for(B->nnz, 256, (int64_t)cus * 32), 256, 0, st>>>(P->A, P->B, P->aux, chunk, P->bq_a0,
-                                                                         P->bq_alen, err);
-    SPX_HIP(hipGetLastError());
-  }
   const int32_t sstride = (int32_t)nblk + 1;
   P->src = ProdSrc{A->ir, P->bq_a0, P->bq_alen, nullptr, nullptr, sstride, rb, (int32_t)m,
                    off32 ? 1 : 0, tune.range_chunk == kQChunk ? kQChunk : kQChunkWide};
   BinCfg bc{tune.tiny_max, tune.hash_count_max};
-  if (nslots > 0) {
+  const bool small = nslots <= kSmallSlots;
+  if (nslots > 0 && small && B->m <= kSmallSlots) {
+    k_slots_small<<<grid_for(nslots, 4), 256, 0, st>>>(P->A, P->B, P->aux, chunk, P->bq_a0, P->bq_alen, (int)nslots,
+                                                       P->mults_d, P->totals, longs, nlong, err);
+    SPX_HIP(hipGetLastError());
+  } else if (nslots > 0) {
+    if (B->nnz > 0) {
+      k_rowinfo<<<grid_for(B->nnz, 256, (int64_t)cus * 32), 256, 0, st>>>(P->A, P->B, P->aux, chunk, P->bq_a0,
+                                                                           P->bq_alen, err);
+      SPX_HIP(hipGetLastError());
+    }
     k_slot_mults<<<grid_for(nslots * 8, 256, (int64_t)cus * 16), 256, 0, st>>>(P->B, P->bq_alen, nslots, P->mults_d,
                                                                               P->totals, longs, nlong);
     SPX_HIP(hipGetLastError());
     k_slot_mults_long<<<(unsigned)cus * 8, 256, 0, st>>>(P->B, P->bq_alen, longs, nlong, P->mults_d, P->totals);
     SPX_HIP(hipGetLastError());
+  }
+  if (nslots > 0 && small) {
+    k_bin_small<<<1, 1024, 0, st>>>(P->mults_d, (int)nslots, bc, P->binoff, P->list);
+    SPX_HIP(hipGetLastError());
+  } else if (nslots > 0) {
     k_bin_count<<<grid_for(nslots, 256, (int64_t)cus * 8), 256, 0, st>>>(P->mults_d, nslots, bc, bincount);
     SPX_HIP(hipGetLastError());
-  }
-  if (nslots > 0) {
     k_bin_fill<<<grid_for(ceil_div(nslots, kFillPer), 256, (int64_t)cus * 8), 256, 0, st>>>(
         P->mults_d, nslots, bc, bincount, P->binoff, binfill, P->list);
     SPX_HIP(hipGetLastError());
