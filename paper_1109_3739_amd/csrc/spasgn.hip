@@ -20,6 +20,7 @@
 // entries by (row, position in B), so a row's values are added to A's value
 // in B's storage order.
 #include <algorithm>
+#include <numeric>
 #include <type_traits>
 
 #include "common.h"
@@ -180,8 +181,7 @@ struct SpasgnPlan : spx_plan {
   int64_t lenI = 0, lenJ = 0, nnz = 0, nmod = 0, ndrop = 0;
   int32_t* lastI = nullptr;  // [m] last p with I(p) = i, or -1
   int32_t* lastJ = nullptr;  // [n]
-  int64_t* cnt = nullptr;    // [n]
-  int64_t* off = nullptr;    // [n+1] = C.cp
+  int64_t* carry = nullptr;  // modified columns before each block of kScanTile columns (null: one block)
   int32_t* mod = nullptr;    // [n] modified columns
   int64_t* dcnt = nullptr;   // [nmod] dropped entries per modified column
   int64_t* doff = nullptr;   // [nmod+1]
@@ -200,8 +200,8 @@ struct SpasgnPlan : spx_plan {
   int64_t* lastseg = nullptr; // [ntiles] dropped entries of each tile's last column
   int64_t* colb = nullptr;    // [nmod] A's entry range of each modified column
   int64_t* cole = nullptr;
-  int64_t* runshift = nullptr;  // [nmod+1] output shift of the unmodified run before modified column u
-  int64_t* mshift = nullptr;    // [nmod] off[j] - cp[j] of modified column u
+  int64_t* shift = nullptr;  // [nmod+1] entries inserted less dropped before modified column u: what it and the
+                             // unmodified columns before it move by in C
   unsigned* err = nullptr;
   unsigned long long* nmod_d = nullptr;
 };
@@ -234,26 +234,11 @@ __global__ void k_last_occ(const int32_t* I, int64_t lenI, int64_t m, int32_t* l
   }
 }
 
-// Unmodified columns keep their length (modified ones are counted later);
-// *modent (when given) accumulates the entries of the modified columns.
-__global__ void k_asgn_cols(Operand A, const int32_t* lastJ, int64_t* cnt, unsigned long long* modent) {
-  int64_t mine = 0;
+// Unmodified columns keep their length (modified ones are counted later).
+__global__ void k_asgn_cols(Operand A, const int32_t* lastJ, int64_t* cnt) {
   for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < A.n; j += (int64_t)gridDim.x * blockDim.x) {
     const int64_t len = slot_begin(A, j + 1) - slot_begin(A, j);
-    const bool m = lastJ[j] >= 0;
-    cnt[j] = m ? 0 : len;
-    mine += m ? len : 0;
-  }
-  if (modent) {  // one atomic per workgroup
-    __shared__ int64_t red[256 / kWave];
-    mine = wave_sum(mine);
-    if (lane_id() == 0) red[threadIdx.x / kWave] = mine;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      int64_t t = 0;
-      for (int w = 0; w < (int)(blockDim.x / kWave); ++w) t += red[w];
-      if (t) atomicAdd(modent, (unsigned long long)t);
-    }
+    cnt[j] = lastJ[j] >= 0 ? 0 : len;
   }
 }
 
@@ -268,19 +253,28 @@ struct LoadModified {
 // of the modified flags; null for a single block), ranks its own flags with
 // a block scan and writes its columns.  The last thread of the last block
 // leaves the total in *nmod.  Items are taken kScanItems consecutive per
-// thread, as by k_scan_apply.
-__global__ void __launch_bounds__(kScanThreads) k_list_modified(const int32_t* lastJ, int64_t n, const int64_t* carry,
-                                                                int32_t* mod, unsigned long long* nmod) {
+// thread, as by k_scan_apply.  modent (when given) receives the entries of the
+// modified columns, spread over kEntSpread counters 128 bytes apart (one counter
+// would serialise the workgroups' atomics).
+constexpr int kEntSpread = 8;
+__global__ void __launch_bounds__(kScanThreads) k_list_modified(Operand A, const int32_t* lastJ, int64_t n,
+                                                                const int64_t* carry, int32_t* mod,
+                                                                unsigned long long* nmod, unsigned long long* modent) {
   __shared__ int64_t red[kScanThreads / kWave + 1];
   const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
   bool f[kScanItems];
-  int64_t s = 0;
+  int64_t s = 0, ent = 0;
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
     f[k] = base + k < n && lastJ[base + k] >= 0;
     s += f[k];
+    if (modent && f[k]) ent += slot_begin(A, base + k + 1) - slot_begin(A, base + k);
   }
   int64_t total;
+  if (modent) {  // uniform
+    block_excl_scan(ent, red, &total);
+    if (threadIdx.x == 0 && total) atomicAdd(modent + blockIdx.x % kEntSpread * 16, (unsigned long long)total);
+  }
   int64_t run = block_excl_scan(s, red, &total) + (carry ? carry[blockIdx.x] : 0);
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k)
@@ -288,13 +282,11 @@ __global__ void __launch_bounds__(kScanThreads) k_list_modified(const int32_t* l
   if (blockIdx.x == gridDim.x - 1 && threadIdx.x == blockDim.x - 1) *nmod = (unsigned long long)run;
 }
 
-// Lists the modified columns and leaves their number in *nmod.
-int list_modified(const Operand& A, const int32_t* lastJ, int64_t* cnt, int32_t* mod, unsigned long long* nmod,
-                  unsigned long long* modent, Scratch& scr, hipStream_t st) {
+// Lists the modified columns and leaves their number in *nmod (and *carry_out).
+int list_modified(const Operand& A, const int32_t* lastJ, int32_t* mod, unsigned long long* nmod,
+                  unsigned long long* modent, int64_t** carry_out, Scratch& scr, hipStream_t st) {
   const int64_t n = A.n;
   if (n == 0) return fill_i64(reinterpret_cast<int64_t*>(nmod), 1, 0, st);
-  k_asgn_cols<<<grid_for(n, 256, (int64_t)device_cu_count() * 4), 256, 0, st>>>(A, lastJ, cnt, modent);
-  SPX_HIP(hipGetLastError());
   const int64_t nblocks = ceil_div(n, kScanTile);
   int64_t* carry = nullptr;
   if (nblocks > 1) {
@@ -305,8 +297,9 @@ int list_modified(const Operand& A, const int32_t* lastJ, int64_t* cnt, int32_t*
     SPX_HIP(hipGetLastError());
     SPX_TRY(exclusive_scan(LoadI64{sums}, nblocks, carry, scr, st));
   }
-  k_list_modified<<<(unsigned)nblocks, kScanThreads, 0, st>>>(lastJ, n, carry, mod, nmod);
+  k_list_modified<<<(unsigned)nblocks, kScanThreads, 0, st>>>(A, lastJ, n, carry, mod, nmod, modent);
   SPX_HIP(hipGetLastError());
+  if (carry_out) *carry_out = carry;
   return SPX_OK;
 }
 
@@ -479,7 +472,8 @@ __device__ __forceinline__ int32_t staged_rank(const P* s_end, int32_t nst, int3
 // dropped entries before it: the merged-order tile counts those among its
 // own entries with a scan and, for a column begun in earlier tiles, adds
 // their dropped counts of it (recorded per tile by the plan's count pass).
-// A kept entry lands at off[j] + kept rank + the inserted rows below it (a
+// With off[j] = A.cp[j] + shift[u] the start of C(:,j), a kept entry lands at
+// off[j] + kept rank + the inserted rows below it (a
 // binary search in the column's sorted inserted keys); a dropped one records
 // its row at its rank in the column's list of dropped rows (ascending, as
 // A's rows are).  The inserted entry of sorted rank s and row r lands at
@@ -574,18 +568,16 @@ __device__ __forceinline__ uint64_t group16_sort_u64(uint64_t key) {
 }
 
 // Per modified column: the inserted entries (B entries whose row index is
-// the last occurrence in I), their count icnt, the column's output length
-// cnt[j] = nnz(A(:,j)) - dropped + inserted, and B's column start kbase.
+// the last occurrence in I), their count icnt, and B's column start kbase.
 // A wave takes four columns at a time, one per 16-lane group: a B column of
 // at most 16 entries has its keys (row << 32 | position in the B column)
 // sorted within the group and stored at ikeys[kbase ..].  The others are
 // then taken by the whole wave, one by one: up to 64 entries sorted across
 // the wave, longer ones counted and put on the big list (sorted by
 // k_asgn_big_keys or, past kAsgnMaxInsert, k_asgn_huge_keys).
-__global__ void __launch_bounds__(256) k_asgn_keys(Operand A, Operand B, const int32_t* I, const int32_t* lastI,
+__global__ void __launch_bounds__(256) k_asgn_keys(Operand B, const int32_t* I, const int32_t* lastI,
                                                    const int32_t* lastJ, const int32_t* mod, int64_t nmod,
-                                                   const unsigned long long* dcnt, int64_t* icnt, int64_t* kbase,
-                                                   uint64_t* ikeys, int64_t* cnt, int32_t* big,
+                                                   int64_t* icnt, int64_t* kbase, uint64_t* ikeys, int32_t* big,
                                                    unsigned long long* nbig) {
   const int lane = lane_id(), g = lane >> 4, gl = lane & 15;
   const int64_t wave = __builtin_amdgcn_readfirstlane((int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave));
@@ -593,11 +585,9 @@ __global__ void __launch_bounds__(256) k_asgn_keys(Operand A, Operand B, const i
   for (int64_t base = wave * 4; base < nmod; base += nwaves * 4) {
     const int64_t u = base + g;
     const bool has = u < nmod;
-    int32_t j = 0;
     int64_t b0 = 0, b1 = 0;
     if (has) {
-      j = mod[u];
-      const int32_t q = lastJ[j];
+      const int32_t q = lastJ[mod[u]];
       b0 = slot_begin(B, q);
       b1 = slot_begin(B, q + 1);
     }
@@ -615,7 +605,6 @@ __global__ void __launch_bounds__(256) k_asgn_keys(Operand A, Operand B, const i
       if (gl == 0) {
         icnt[u] = ins_g;
         kbase[u] = b0;
-        cnt[j] = slot_begin(A, j + 1) - slot_begin(A, j) - (int64_t)dcnt[u] + ins_g;
       }
     }
     uint64_t rest = __ballot(has && !small && gl == 0);
@@ -650,7 +639,6 @@ __global__ void __launch_bounds__(256) k_asgn_keys(Operand A, Operand B, const i
       if (lane == 0) {
         icnt[v] = ins;
         kbase[v] = c0;
-        cnt[jv] = slot_begin(A, jv + 1) - slot_begin(A, jv) - (int64_t)dcnt[v] + ins;
         if (c1 - c0 > kWave) big[atomicAdd(nbig, 1ull)] = (int32_t)v;
       }
     }
@@ -703,25 +691,18 @@ __global__ void __launch_bounds__(256) k_asgn_huge_keys(Operand B, const int32_t
   }
 }
 
-// Output shifts for the fill tiles: runshift[u] = off[c0] - cp[c0] for the
-// run of unmodified columns c0 = mod[u-1] + 1 .. mod[u] - 1, and
-// mshift[u] = off[mod[u]] - cp[mod[u]].
-__global__ void k_asgn_shifts(Operand A, const int32_t* mod, int64_t nmod, const int64_t* off, const int64_t* colb,
-                              int64_t* runshift, int64_t* mshift) {
-  for (int64_t u = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; u <= nmod; u += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t c0 = u == 0 ? 0 : (int64_t)mod[u - 1] + 1;
-    runshift[u] = off[c0] - slot_begin(A, c0);
-    if (u < nmod) mshift[u] = off[mod[u]] - colb[u];
-  }
-}
+// What modified column u adds to the shift of the columns after it.
+struct LoadShift {
+  const int64_t *icnt, *dcnt;
+  __device__ int64_t operator()(int64_t u) const { return icnt[u] - dcnt[u]; }
+};
 
 // Fill pass over the tiles: unmodified runs are copied with their output
 // shift; entries of modified columns are kept or dropped as described above.
 template <int VB>
 __global__ void __launch_bounds__(kTileThreads) k_asgn_fill(Operand A, const int32_t* lastI, const int64_t* colb,
-                                                            const int64_t* cole, const int64_t* runshift,
-                                                            const int64_t* mshift, int64_t nmod, const int64_t* tmod,
-                                                            int64_t nt, const int64_t* lastseg,
+                                                            const int64_t* cole, const int64_t* shift, int64_t nmod,
+                                                            const int64_t* tmod, int64_t nt, const int64_t* lastseg,
                                                             const int64_t* icnt, const int64_t* kbase,
                                                             const uint64_t* ikeys, const int64_t* doff,
                                                             int32_t* drows, int32_t* cir, void* cnum) {
@@ -730,8 +711,7 @@ __global__ void __launch_bounds__(kTileThreads) k_asgn_fill(Operand A, const int
   __shared__ int16_t s_beg[kTileItems + 1];
   __shared__ int16_t s_end[kTileItems + 1];
   __shared__ int16_t s_dbase[kTileItems + 1];   // dropped entries of the tile before the column's first
-  __shared__ int64_t s_shift[kTileItems + 1];   // output shift of the run before staged column i
-  __shared__ int64_t s_mshift[kTileItems + 1];  // off[c] - cp[c] of staged column i
+  __shared__ int64_t s_shift[kTileItems + 1];   // output shift of staged column i and the run before it
   __shared__ int32_t s_wt[kTilePer][kWaves];    // dropped entries per wave and round
   __shared__ int64_t s_red[kWaves];
   __shared__ int64_t s_a0;
@@ -751,12 +731,11 @@ __global__ void __launch_bounds__(kTileThreads) k_asgn_fill(Operand A, const int
     }
     for (int64_t i = threadIdx.x; i <= sp.ue - sp.us; i += kTileThreads) {
       const int64_t r = sp.us + i;
-      s_shift[i] = runshift[r];
+      s_shift[i] = shift[r];
       if (i < sp.nst) {
         const int64_t cb = colb[r];
         s_beg[i] = (int16_t)tile_rel(cb, sp.es);
         s_end[i] = (int16_t)tile_rel(cole[r], sp.es);
-        s_mshift[i] = mshift[r];
         if (i == 0) s_a0 = cb;
       }
     }
@@ -833,7 +812,7 @@ __global__ void __launch_bounds__(kTileThreads) k_asgn_fill(Operand A, const int
           else
             b = mid;
         }
-        dst = e + s_mshift[lo[k]] - db + a;
+        dst = e + s_shift[lo[k]] - db + a;
       }
       __builtin_nontemporal_store(row[k], &cir[dst]);  // C is written once: streaming stores
       if (VB) __builtin_nontemporal_store(val[k], &out[dst]);
@@ -845,7 +824,7 @@ __global__ void __launch_bounds__(kTileThreads) k_asgn_fill(Operand A, const int
 // One inserted entry: key of sorted rank s in modified column u.
 __device__ __forceinline__ void asgn_insert_one(const Operand& A, const Operand& B, const int32_t* mod, int64_t u,
                                                 int64_t s, const int64_t* kbase, const uint64_t* ikeys,
-                                                const int64_t* off, const int64_t* doff, const int32_t* drows, int vb,
+                                                const int64_t* shift, const int64_t* doff, const int32_t* drows, int vb,
                                                 int32_t* cir, void* cnum) {
   const int32_t j = mod[u];
   const int64_t a0 = slot_begin(A, j), alen = slot_begin(A, j + 1) - a0;
@@ -853,7 +832,7 @@ __device__ __forceinline__ void asgn_insert_one(const Operand& A, const Operand&
   const int64_t kb = kbase[u];
   const uint64_t key = ikeys[kb + s];
   const int32_t r = (int32_t)(key >> 32);
-  const int64_t o = off[j] + s + rows_below(A.ir + a0, alen, r) - rows_below(drows + d0, dlen, r);
+  const int64_t o = a0 + shift[u] + s + rows_below(A.ir + a0, alen, r) - rows_below(drows + d0, dlen, r);
   cir[o] = r;
   copy_value(B.num, kb + (int64_t)(key & 0xffffffffu), cnum, o, vb);
 }
@@ -863,7 +842,7 @@ __device__ __forceinline__ void asgn_insert_one(const Operand& A, const Operand&
 // key of rank s); a column above 16 then takes the whole wave.
 __global__ void __launch_bounds__(256) k_asgn_insert(Operand A, Operand B, const int32_t* mod, int64_t nmod,
                                                      const int64_t* icnt, const int64_t* kbase,
-                                                     const uint64_t* ikeys, const int64_t* off, const int64_t* doff,
+                                                     const uint64_t* ikeys, const int64_t* shift, const int64_t* doff,
                                                      const int32_t* drows, int vb, int32_t* cir, void* cnum) {
   const int lane = lane_id(), g = lane >> 4, gl = lane & 15;
   const int64_t wave = __builtin_amdgcn_readfirstlane((int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave));
@@ -871,12 +850,12 @@ __global__ void __launch_bounds__(256) k_asgn_insert(Operand A, Operand B, const
   for (int64_t base = wave * 4; base < nmod; base += nwaves * 4) {
     const int64_t u = base + g;
     const int64_t n = u < nmod ? icnt[u] : 0;
-    if (n <= 16 && gl < n) asgn_insert_one(A, B, mod, u, gl, kbase, ikeys, off, doff, drows, vb, cir, cnum);
+    if (n <= 16 && gl < n) asgn_insert_one(A, B, mod, u, gl, kbase, ikeys, shift, doff, drows, vb, cir, cnum);
     uint64_t rest = __ballot(n > 16 && n <= kAsgnSmall && gl == 0);
     while (rest) {  // uniform
       const int64_t v = base + (__ffsll((unsigned long long)rest) - 1) / 16;
       rest &= rest - 1;
-      if (lane < icnt[v]) asgn_insert_one(A, B, mod, v, lane, kbase, ikeys, off, doff, drows, vb, cir, cnum);
+      if (lane < icnt[v]) asgn_insert_one(A, B, mod, v, lane, kbase, ikeys, shift, doff, drows, vb, cir, cnum);
     }
   }
 }
@@ -884,7 +863,7 @@ __global__ void __launch_bounds__(256) k_asgn_insert(Operand A, Operand B, const
 // Inserted entries of the big-list columns above 64: one workgroup each.
 __global__ void __launch_bounds__(256) k_asgn_insert_big(Operand A, Operand B, const int32_t* mod, const int32_t* big,
                                                          int64_t nbig, const int64_t* icnt, const int64_t* kbase,
-                                                         const uint64_t* ikeys, const int64_t* off,
+                                                         const uint64_t* ikeys, const int64_t* shift,
                                                          const int64_t* doff, const int32_t* drows, int vb,
                                                          int32_t* cir, void* cnum) {
   for (int64_t w = blockIdx.x; w < nbig; w += gridDim.x) {
@@ -892,7 +871,7 @@ __global__ void __launch_bounds__(256) k_asgn_insert_big(Operand A, Operand B, c
     const int64_t n = icnt[u];
     if (n <= kAsgnSmall) continue;  // uniform: k_asgn_insert's column
     for (int64_t s = threadIdx.x; s < n; s += blockDim.x)
-      asgn_insert_one(A, B, mod, u, s, kbase, ikeys, off, doff, drows, vb, cir, cnum);
+      asgn_insert_one(A, B, mod, u, s, kbase, ikeys, shift, doff, drows, vb, cir, cnum);
   }
 }
 
@@ -900,8 +879,8 @@ int launch_asgn_fill(const SpasgnPlan* P, int vb, int32_t* cir, void* cnum, hipS
   if (P->ntiles == 0) return SPX_OK;
   const unsigned grid = (unsigned)std::min<int64_t>(P->ntiles, (int64_t)device_cu_count() * 32);
 #define SPX_ASGN_FILL(VB)                                                                                          \
-  k_asgn_fill<VB><<<grid, kTileThreads, 0, st>>>(P->A, P->lastI, P->colb, P->cole, P->runshift, P->mshift,       \
-                                                 P->nmod, P->tmod, P->ntiles, P->lastseg, P->icnt, P->kbase,      \
+  k_asgn_fill<VB><<<grid, kTileThreads, 0, st>>>(P->A, P->lastI, P->colb, P->cole, P->shift, P->nmod, P->tmod,  \
+                                                 P->ntiles, P->lastseg, P->icnt, P->kbase,      \
                                                  P->ikeys, P->doff, P->drows, cir, cnum)
   if (vb == 8)
     SPX_ASGN_FILL(8);
@@ -917,6 +896,38 @@ int launch_asgn_fill(const SpasgnPlan* P, int vb, int32_t* cir, void* cnum, hipS
 __global__ void k_asgn_write_cp(const int64_t* off, int64_t n, void* cp, int32_t ptr_t) {
   for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j <= n; j += (int64_t)gridDim.x * blockDim.x)
     store_ptr(cp, ptr_t, j, off[j]);
+}
+
+// C's column pointers of SpAsgn: a column moves by the shift of the modified
+// columns before it, which the block ranks as k_list_modified did.
+__global__ void __launch_bounds__(kScanThreads) k_asgn_shift_cp(Operand A, const int32_t* lastJ, const int64_t* carry,
+                                                                const int64_t* shift, void* cp, int32_t ptr_t) {
+  __shared__ int64_t red[kScanThreads / kWave + 1];
+  __shared__ int16_t s_rank[kScanTile + 1];  // modified columns of the block before each
+  const int64_t n = A.n, base = (int64_t)blockIdx.x * kScanTile;
+  const int first = (int)threadIdx.x * kScanItems;
+  bool f[kScanItems];
+  int64_t c = 0;
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) {
+    f[k] = base + first + k < n && lastJ[base + first + k] >= 0;
+    c += f[k];
+  }
+  int64_t total;
+  int run = (int)block_excl_scan(c, red, &total);
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) {
+    s_rank[first + k] = (int16_t)run;
+    run += f[k];
+  }
+  if (threadIdx.x == 0) s_rank[kScanTile] = (int16_t)total;
+  __syncthreads();
+  const int64_t before = carry ? carry[blockIdx.x] : 0;
+  const int items = (int)std::min<int64_t>(kScanTile, n - base);
+  for (int i = threadIdx.x; i < items; i += kScanThreads)
+    store_ptr(cp, ptr_t, base + i, slot_begin(A, base + i) + shift[before + s_rank[i]]);
+  if (base + items == n && threadIdx.x == 0)
+    store_ptr(cp, ptr_t, n, slot_begin(A, n) + shift[before + s_rank[items]]);
 }
 
 // ------------------------------------------------------------ extend-add
@@ -1524,20 +1535,24 @@ extern "C" int spx_spasgn_plan(const spx_ctx* ctx, const spx_mat* A, const int32
   P->lenJ = lenJ;
   const int64_t m = A->m, n = A->n;
   const int cus = device_cu_count();
-  SPX_TRY(scr.get_many({Scratch::part(&P->err, 4), Scratch::part(&P->nmod_d, 2), Scratch::part(&P->lastI, m),
-                        Scratch::part(&P->lastJ, n), Scratch::part(&P->cnt, n), Scratch::part(&P->off, n + 1),
-                        Scratch::part(&P->mod, n)}));
+  constexpr int kCounters = 16 + kEntSpread * 16;  // modified columns; their entries, spread
+  SPX_TRY(scr.get_many({Scratch::part(&P->err, 4), Scratch::part(&P->nmod_d, kCounters), Scratch::part(&P->lastI, m),
+                        Scratch::part(&P->lastJ, n), Scratch::part(&P->mod, n)}));
   k_index_init<<<grid_for(std::max(m, n), 1024, 4096), 256, 0, st>>>(P->lastI, m, P->lastJ, n, nullptr, 0, P->err,
-                                                                     P->nmod_d, 2);
-  SPX_HIP(hipGetLastError());  // (counters: modified columns, their entries)
+                                                                     P->nmod_d, kCounters);
+  SPX_HIP(hipGetLastError());
   if (lenI > 0 || lenJ > 0) {
     const dim3 grid(grid_for(std::max(lenI, lenJ), 256, 4096), 2);
     k_last_occ<<<grid, 256, 0, st>>>(I, lenI, m, P->lastI, J, lenJ, n, P->lastJ, P->err);
     SPX_HIP(hipGetLastError());
   }
-  SPX_TRY(list_modified(P->A, P->lastJ, P->cnt, P->mod, P->nmod_d, P->nmod_d + 1, scr, st));
-  int64_t h1[3] = {0, 0, 0};
-  SPX_TRY(read_device_words(st, {{P->nmod_d, 8}, {P->err, 4}, {P->nmod_d + 1, 8}}, h1));
+  unsigned long long* const ent = P->nmod_d + 16;
+  SPX_TRY(list_modified(P->A, P->lastJ, P->mod, P->nmod_d, ent, &P->carry, scr, st));
+  static_assert(kEntSpread == 8, "counters read below");
+  int64_t h1[2 + kEntSpread] = {};
+  SPX_TRY(read_device_words(st, {{P->nmod_d, 8}, {P->err, 4}, {ent, 8}, {ent + 16, 8}, {ent + 32, 8}, {ent + 48, 8},
+                                 {ent + 64, 8}, {ent + 80, 8}, {ent + 96, 8}, {ent + 112, 8}}, h1));
+  const int64_t modent = std::accumulate(h1 + 2, h1 + 2 + kEntSpread, (int64_t)0);
   if (h1[1] & 1) return fail(SPX_EINVAL, "I has an index outside [0, m)");
   if (h1[1] & 2) return fail(SPX_EINVAL, "J has an index outside [0, n)");
   P->nmod = h1[0];
@@ -1545,12 +1560,12 @@ extern "C" int spx_spasgn_plan(const spx_ctx* ctx, const spx_mat* A, const int32
   P->ntiles = tile_count(P->A, nm);
   // dropped entries are at most the modified columns' entries
   SPX_TRY(scr.get_many({Scratch::part(&P->tmod, P->ntiles + 1), Scratch::part(&P->colb, nm),
-                        Scratch::part(&P->cole, nm), Scratch::part(&P->drows, h1[2]),
+                        Scratch::part(&P->cole, nm), Scratch::part(&P->drows, modent),
                         Scratch::part(&P->dcnt, nm), Scratch::part(&P->lastseg, P->ntiles),
                         Scratch::part(&P->doff, nm + 1), Scratch::part(&P->icnt, nm), Scratch::part(&P->kbase, nm),
                         Scratch::part(&P->ikeys, P->B.nnz), Scratch::part(&P->big, nm),
                         Scratch::part(&P->hoff, nm + 1), Scratch::part(&P->nbig_d, 1),
-                        Scratch::part(&P->runshift, nm + 1), Scratch::part(&P->mshift, nm)}));
+                        Scratch::part(&P->shift, nm + 1)}));
   SPX_TRY(copy_tiles(P->A, P->mod, nm, P->ntiles, P->tmod, P->colb, P->cole, st));
   SPX_TRY(zero_words(st, {{P->dcnt, nm}, {P->nbig_d, 1}}));
   if (P->nmod > 0 && P->ntiles > 0) {
@@ -1562,21 +1577,17 @@ extern "C" int spx_spasgn_plan(const spx_ctx* ctx, const spx_mat* A, const int32
   }
   if (P->nmod > 0) {
     k_asgn_keys<<<(unsigned)std::min<int64_t>(ceil_div(P->nmod, (int64_t)16), (int64_t)cus * 16), 256, 0, st>>>(
-        P->A, P->B, I, P->lastI, P->lastJ, P->mod, P->nmod, reinterpret_cast<const unsigned long long*>(P->dcnt),
-        P->icnt, P->kbase, P->ikeys, P->cnt, P->big, P->nbig_d);
+        P->B, I, P->lastI, P->lastJ, P->mod, P->nmod, P->icnt, P->kbase, P->ikeys, P->big, P->nbig_d);
     SPX_HIP(hipGetLastError());
   }
-  SPX_TRY(exclusive_scan(LoadI64{P->cnt}, n, P->off, scr, st));
+  SPX_TRY(exclusive_scan(LoadShift{P->icnt, P->dcnt}, P->nmod, P->shift, scr, st));
   SPX_TRY(exclusive_scan(LoadI64{P->dcnt}, P->nmod, P->doff, scr, st));
   // key segments of the huge columns (big-list order; entries past nbig are empty)
   SPX_TRY(exclusive_scan(HugeCap{P->icnt, P->big, P->nbig_d}, P->nmod, P->hoff, scr, st));
-  k_asgn_shifts<<<grid_for(P->nmod + 1, 256, 65536), 256, 0, st>>>(P->A, P->mod, P->nmod, P->off, P->colb,
-                                                                   P->runshift, P->mshift);
-  SPX_HIP(hipGetLastError());
   int64_t tail[4] = {0, 0, 0, 0};
-  SPX_TRY(read_device_words(st, {{P->off + n, 8}, {P->doff + P->nmod, 8}, {P->nbig_d, 8}, {P->hoff + P->nmod, 8}},
+  SPX_TRY(read_device_words(st, {{P->shift + nm, 8}, {P->doff + P->nmod, 8}, {P->nbig_d, 8}, {P->hoff + P->nmod, 8}},
                             tail));
-  P->nnz = tail[0];
+  P->nnz = P->A.nnz + tail[0];
   P->ndrop = tail[1];
   P->nbig = tail[2];
   P->nhuge_keys = tail[3];
@@ -1613,16 +1624,17 @@ extern "C" int spx_spasgn_exec(spx_plan* plan, spx_mat* C) {
   SPX_TRY(launch_asgn_fill(P, vb, C->ir, C->num, st));
   if (P->nmod > 0) {
     k_asgn_insert<<<(unsigned)std::min<int64_t>(ceil_div(P->nmod, (int64_t)16), (int64_t)cus * 16), 256, 0, st>>>(
-        P->A, P->B, P->mod, P->nmod, P->icnt, P->kbase, P->ikeys, P->off, P->doff, P->drows, vb, C->ir, C->num);
+        P->A, P->B, P->mod, P->nmod, P->icnt, P->kbase, P->ikeys, P->shift, P->doff, P->drows, vb, C->ir, C->num);
     SPX_HIP(hipGetLastError());
   }
   if (P->nbig > 0) {
     k_asgn_insert_big<<<(unsigned)std::min<int64_t>(P->nbig, (int64_t)cus * 4), 256, 0, st>>>(
-        P->A, P->B, P->mod, P->big, P->nbig, P->icnt, P->kbase, P->ikeys, P->off, P->doff, P->drows, vb, C->ir,
+        P->A, P->B, P->mod, P->big, P->nbig, P->icnt, P->kbase, P->ikeys, P->shift, P->doff, P->drows, vb, C->ir,
         C->num);
     SPX_HIP(hipGetLastError());
   }
-  k_asgn_write_cp<<<grid_for(P->A.n + 1, 256, 65536), 256, 0, st>>>(P->off, P->A.n, C->cp, C->ptr_t);
+  k_asgn_shift_cp<<<grid_for(P->A.n, kScanTile), kScanThreads, 0, st>>>(P->A, P->lastJ, P->carry, P->shift, C->cp,
+                                                                        C->ptr_t);
   SPX_HIP(hipGetLastError());
   return SPX_OK;
 }
@@ -1671,7 +1683,11 @@ extern "C" int spx_extend_add_plan(const spx_ctx* ctx, const spx_mat* A, const i
     k_ea_index<<<grid, 256, 0, st>>>(I, lenI, m, J, lenJ, n, P->lastJ, P->qcnt, P->err);
     SPX_HIP(hipGetLastError());
   }
-  SPX_TRY(list_modified(P->A, P->lastJ, P->cnt, P->mod, P->nmod_d, nullptr, scr, st));
+  if (n > 0) {
+    k_asgn_cols<<<grid_for(n, 256, (int64_t)device_cu_count() * 4), 256, 0, st>>>(P->A, P->lastJ, P->cnt);
+    SPX_HIP(hipGetLastError());
+  }
+  SPX_TRY(list_modified(P->A, P->lastJ, P->mod, P->nmod_d, nullptr, nullptr, scr, st));
   int64_t h1[2] = {0, 0};
   SPX_TRY(read_device_words(st, {{P->nmod_d, 8}, {P->err, 4}}, h1));
   if (h1[1] & 1) return fail(SPX_EINVAL, "I has an index outside [0, m)");
