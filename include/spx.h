@@ -105,8 +105,9 @@ typedef struct spx_ctx {
 /* Tuning knobs of the SpGEMM kernels (NULL = built-in defaults, which
  * spx_default_tuning() returns).  Output columns are binned by their
  * number of multiplications mu (an upper bound on their output size):
- *   tiny_max         mu <= tiny_max (<= 64): formed by one 64-lane wave that
- *                    sorts the column's products
+ *   tiny_max         mu <= tiny_max (<= 64): formed by 16, 32 or 64 lanes of a
+ *                    wave, which sort the column's products (a whole wave
+ *                    sorts up to 512 in the same way)
  *   hash_count_max   mu <= hash_count_max (<= 16384): exact count through an
  *                    LDS hash table; larger columns through an LDS bitmap
  *   single_part_max  power of two in [64, 4096]: columns with mu at most this
@@ -297,8 +298,9 @@ int spx_batch_spgemm(const spx_ctx* ctx, int32_t count, const spx_mat* A, const 
  * spx_spref_plan returns nnz(B); spx_spref_exec fills B (CSC, lenI x lenJ,
  * caller-allocated: cp [lenJ+1], ir [nnz], num [nnz]).  SPX_EINVAL if an
  * index is out of range (checked on the device during the plan).
- * spx_spref_exec may put the columns that gather more than 4096 entries of
- * A on a second stream of the calling host thread (created on first use);
+ * spx_spref_exec may put the columns that a workgroup forms (those of more
+ * than 512 entries, or gathering more than 4096 entries of A) on a second
+ * stream of the calling host thread (created on first use);
  * that work is joined back into ctx->stream by an event before the call
  * returns, so everything enqueued on ctx->stream afterwards sees it.      */
 int spx_spref_plan(const spx_ctx* ctx, const spx_mat* A, const int32_t* I, int64_t lenI, const int32_t* J,

@@ -91,8 +91,9 @@ __global__ void k_map_rows(const int32_t* ir, int64_t nnz, const int32_t* agg, i
 }
 
 // The same through the blocks of the map, a quarter byte per vertex: those of
-// 2^23 vertices are 2 MiB and stay in every L2, the map itself is 32 MiB.  Reads of the
-// map at random rows bounded the kernel: 66 M entries of R-MAT took 790 us, now 352.
+// 2^23 vertices are 2 MiB and stay in every L2, the map itself is 32 MiB.  Reads
+// of the map at random rows bounded the kernel: 66 M entries of R-MAT took 790 us,
+// now 352.
 __global__ void k_map_rows_blocks(const int32_t* ir, int64_t nnz, const AggBlock* blocks, int32_t* out) {
   constexpr int U = 4;  // rows in flight
   const int64_t step = (int64_t)gridDim.x * blockDim.x;

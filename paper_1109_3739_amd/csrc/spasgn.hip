@@ -507,8 +507,8 @@ __device__ __forceinline__ int64_t count_dropped(const Operand& A, const int32_t
 // counts the last column's entries, and adds its part of columns that lie in
 // several tiles.  The others take the columns that lie in one tile, four to a
 // wave.  Both wait on chains of three loads, so what counts is how many are in
-// flight: with a workgroup for each tile, which searched the column of each of its entries, 69 M
-// entries with 236 k modified columns took 105 us, now 63.
+// flight: with a workgroup for each tile, which searched the column of each of
+// its entries, 69 M entries with 236 k modified columns took 105 us, now 63.
 __global__ void __launch_bounds__(256) k_asgn_drop_count(Operand A, const int32_t* lastI, const int64_t* colb,
                                                          const int64_t* cole, int64_t nmod, const int64_t* tmod,
                                                          int64_t nt, unsigned cut_blocks, unsigned long long* dcnt,

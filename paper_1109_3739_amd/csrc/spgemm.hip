@@ -13,14 +13,16 @@
 // Two phases.
 //   plan (symbolic): per-entry lookup of A's columns, per-column number of
 //     multiplications, binning of the columns by that count, exact output
-//     counts (a wave-wide sort for tiny columns, an LDS hash for medium ones,
-//     an LDS bitmap over the row space for heavy ones, which also yields
-//     per-row-block counts), int64 scan into column pointers, and a list of
-//     row-range "parts" (each fits one workgroup's LDS) for the numeric phase.
-//   exec (numeric): tiny columns are re-formed by their wave and written;
-//     every part is accumulated in LDS either through a bitmap over its row
-//     range (rank of a row = popcount prefix, which also yields sorted
-//     output) or through a hash table followed by an LDS bitonic sort.
+//     counts (a sort in registers for tiny columns (lane groups) and mid ones
+//     (a wave), an LDS hash for medium ones, an LDS bitmap over the row space
+//     for heavy ones, which also yields per-row-block counts), int64 scan into
+//     column pointers, and a list of row-range "parts" (each fits one
+//     workgroup's LDS) for the numeric phase.
+//   exec (numeric): tiny and mid columns are sorted again, with their values,
+//     and written; every part is accumulated in LDS either through a bitmap
+//     over its row range (rank of a row = popcount prefix, which also yields
+//     sorted output) or through a hash table, whose rows a two-level bitmap
+//     ranks (above 2^20 rows an LDS sort orders them).
 #include <algorithm>
 #include <cstring>
 #include <memory>
@@ -41,7 +43,7 @@ namespace spx {
 //   0 .. 40   bitmap-counted columns, id = 40 - floor(log2 mu)
 //   41 .. 48  hash-counted columns, table of 2^(15 - (id - 41)) keys; the last
 //             three (at most kMidMax products) are mid columns, one wave each
-//   49        tiny columns (mu <= tiny_max, at most 64): one wave each
+//   49        tiny columns (mu <= tiny_max, at most 64): groups of 16 to 64 lanes
 //   50        columns without products
 constexpr int kBinHash0 = 41;
 constexpr int kBinTiny = 49;
