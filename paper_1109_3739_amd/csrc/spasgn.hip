@@ -234,14 +234,6 @@ __global__ void k_last_occ(const int32_t* I, int64_t lenI, int64_t m, int32_t* l
   }
 }
 
-// Unmodified columns keep their length (modified ones are counted later).
-__global__ void k_asgn_cols(Operand A, const int32_t* lastJ, int64_t* cnt) {
-  for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < A.n; j += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t len = slot_begin(A, j + 1) - slot_begin(A, j);
-    cnt[j] = lastJ[j] >= 0 ? 0 : len;
-  }
-}
-
 // 1 for a column that receives B's entries.
 struct LoadModified {
   const int32_t* lastJ;
@@ -893,13 +885,8 @@ int launch_asgn_fill(const SpasgnPlan* P, int vb, int32_t* cir, void* cnum, hipS
   return SPX_OK;
 }
 
-__global__ void k_asgn_write_cp(const int64_t* off, int64_t n, void* cp, int32_t ptr_t) {
-  for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j <= n; j += (int64_t)gridDim.x * blockDim.x)
-    store_ptr(cp, ptr_t, j, off[j]);
-}
-
-// C's column pointers of SpAsgn: a column moves by the shift of the modified
-// columns before it, which the block ranks as k_list_modified did.
+// C's column pointers: a column moves by the shift of the modified columns
+// before it, which the block ranks as k_list_modified did.
 __global__ void __launch_bounds__(kScanThreads) k_asgn_shift_cp(Operand A, const int32_t* lastJ, const int64_t* carry,
                                                                 const int64_t* shift, void* cp, int32_t ptr_t) {
   __shared__ int64_t red[kScanThreads / kWave + 1];
@@ -939,10 +926,12 @@ struct ExtAddPlan : spx_plan {
   int32_t sr = 0;
   int32_t* lastJ = nullptr;  // [n] >= 0 for the columns that receive B entries
   int32_t* qcnt = nullptr;   // [n] number of q with J(q) = j
-  int64_t* qoff = nullptr;   // [n+1]
+  int64_t* qoff = nullptr;   // [n+1] start (and, at j + 1, end) of each modified column's list; others unset
   int32_t* qlist = nullptr;  // [lenJ] the q of each column, grouped by column
-  int64_t* cnt = nullptr;    // [n]
-  int64_t* off = nullptr;    // [n+1] = C.cp
+  int64_t* cnt = nullptr;    // [n] nnz(C(:,j)) of the modified columns; others unset
+  int64_t* off = nullptr;    // [n] C.cp of the modified columns; others unset
+  int64_t* carry = nullptr;  // modified columns before each block of kScanTile columns (null: one block)
+  int64_t* shift = nullptr;  // [nmod+1] rows added before modified column u
   int32_t* mod = nullptr;    // [n] modified columns
   int32_t* rest = nullptr;   // modified columns (indices into mod) beyond k_ea_wave's reach
   unsigned long long* nrest_d = nullptr;
@@ -999,10 +988,28 @@ __global__ void k_scatter_q(const int32_t* J, int64_t lenJ, const int64_t* qoff,
   }
 }
 
-struct LoadI32 {
-  const int32_t* p;
-  __device__ int64_t operator()(int64_t i) const { return p[i]; }
+// Lists of the q by column are laid out by modified column.
+struct LoadQ {
+  const int32_t *qcnt, *mod;
+  __device__ int64_t operator()(int64_t u) const { return qcnt[mod[u]]; }
 };
+__global__ void k_ea_qoff(const int32_t* mod, int64_t nmod, const int64_t* start, int64_t* qoff) {
+  for (int64_t u = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; u < nmod; u += (int64_t)gridDim.x * blockDim.x) {
+    qoff[mod[u]] = start[u];
+    qoff[mod[u] + 1] = start[u + 1];  // the start of column mod[u] + 1, if that is modified, too
+  }
+}
+
+// Rows added to modified column u, and where the columns start in C.
+struct LoadAdded {
+  const int64_t *cnt, *colb, *cole;
+  const int32_t* mod;
+  __device__ int64_t operator()(int64_t u) const { return cnt[mod[u]] - (cole[u] - colb[u]); }
+};
+__global__ void k_ea_offsets(const int32_t* mod, int64_t nmod, const int64_t* colb, const int64_t* shift, int64_t* off) {
+  for (int64_t u = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; u < nmod; u += (int64_t)gridDim.x * blockDim.x)
+    off[mod[u]] = colb[u] + shift[u];
+}
 
 // One modified column j of extend-add from its landing entries, given as
 // keys (I(p) << 32 | e), e the entry's position in B, sorted ascending in
@@ -1359,8 +1366,9 @@ __global__ void __launch_bounds__(256) k_ea_huge(Operand A, Operand B, const int
 // the landing values of its own row in key order.  The other modified
 // columns' entries are left to the column kernels.
 template <bool kVals, typename T, class Acc>
-__global__ void __launch_bounds__(kTileThreads) k_ea_tiles(Operand A, Operand B, const int32_t* mod, int64_t nmod,
-                                                           const int64_t* tmod, int64_t nt, const int64_t* off,
+__global__ void __launch_bounds__(kTileThreads) k_ea_tiles(Operand A, Operand B, const int64_t* colb,
+                                                           const int64_t* cole, int64_t nmod, const int64_t* tmod,
+                                                           int64_t nt, const int64_t* shift,
                                                            const int32_t* lw, const int64_t* hoff,
                                                            const uint64_t* hkeys, const int32_t* hhead,
                                                            const int32_t* hnin, const int64_t* hnu, int32_t* cir,
@@ -1368,8 +1376,7 @@ __global__ void __launch_bounds__(kTileThreads) k_ea_tiles(Operand A, Operand B,
   __shared__ int16_t s_beg[kTileItems + 1];
   __shared__ int16_t s_end[kTileItems + 1];
   __shared__ int32_t s_lw[kTileItems + 1];
-  __shared__ int64_t s_shift[kTileItems + 1];  // output shift of the run before staged column i
-  __shared__ int64_t s_mo[kTileItems + 1];     // off[c] - cp[c] of a long staged column
+  __shared__ int64_t s_shift[kTileItems + 1];  // output shift of staged column i and the run before it
   const T* anum = static_cast<const T*>(A.num);
   const T* bnum = static_cast<const T*>(B.num);
   for (int64_t t = blockIdx.x; t < nt; t += gridDim.x) {
@@ -1385,15 +1392,11 @@ __global__ void __launch_bounds__(kTileThreads) k_ea_tiles(Operand A, Operand B,
     }
     for (int64_t i = threadIdx.x; i <= sp.ue - sp.us; i += kTileThreads) {
       const int64_t r = sp.us + i;
-      const int64_t c0 = r == 0 ? 0 : (int64_t)mod[r - 1] + 1;
-      s_shift[i] = off[c0] - slot_begin(A, c0);
+      s_shift[i] = shift[r];
       if (i < sp.nst) {
-        const int64_t c = mod[r];
-        const int64_t cb = slot_begin(A, c);
-        s_beg[i] = (int16_t)tile_rel(cb, sp.es);
-        s_end[i] = (int16_t)tile_rel(slot_begin(A, c + 1), sp.es);
+        s_beg[i] = (int16_t)tile_rel(colb[r], sp.es);
+        s_end[i] = (int16_t)tile_rel(cole[r], sp.es);
         s_lw[i] = lw[r];
-        s_mo[i] = off[c] - cb;
       }
     }
     __syncthreads();
@@ -1425,7 +1428,7 @@ __global__ void __launch_bounds__(kTileThreads) k_ea_tiles(Operand A, Operand B,
         else
           b = mid;
       }
-      const int64_t dst = e + s_mo[lo] + hnin[seg + a];
+      const int64_t dst = e + s_shift[lo] + hnin[seg + a];
       cir[dst] = row;
       if (kVals) {
         T acc = vals[k];
@@ -1457,7 +1460,7 @@ int launch_ea(const ExtAddPlan* P, int32_t* cir, void* cnum, hipStream_t st, boo
   }
   if (kFill && P->ntiles > 0) {  // unmodified runs and the long columns' A entries
     k_ea_tiles<kVals, T, Acc><<<(unsigned)std::min<int64_t>(P->ntiles, (int64_t)cus * 32), kTileThreads, 0, st>>>(
-        P->A, P->B, P->mod, P->nmod, P->tmod, P->ntiles, P->off, P->lw, P->hoff, P->hkeys, P->hhead, P->hnin, P->hnu,
+        P->A, P->B, P->colb, P->cole, P->nmod, P->tmod, P->ntiles, P->shift, P->lw, P->hoff, P->hkeys, P->hhead, P->hnin, P->hnu,
         cir, out);
     SPX_HIP(hipGetLastError());
   }
@@ -1683,21 +1686,23 @@ extern "C" int spx_extend_add_plan(const spx_ctx* ctx, const spx_mat* A, const i
     k_ea_index<<<grid, 256, 0, st>>>(I, lenI, m, J, lenJ, n, P->lastJ, P->qcnt, P->err);
     SPX_HIP(hipGetLastError());
   }
-  if (n > 0) {
-    k_asgn_cols<<<grid_for(n, 256, (int64_t)device_cu_count() * 4), 256, 0, st>>>(P->A, P->lastJ, P->cnt);
-    SPX_HIP(hipGetLastError());
-  }
-  SPX_TRY(list_modified(P->A, P->lastJ, P->mod, P->nmod_d, nullptr, nullptr, scr, st));
+  SPX_TRY(list_modified(P->A, P->lastJ, P->mod, P->nmod_d, nullptr, &P->carry, scr, st));
   int64_t h1[2] = {0, 0};
   SPX_TRY(read_device_words(st, {{P->nmod_d, 8}, {P->err, 4}}, h1));
   if (h1[1] & 1) return fail(SPX_EINVAL, "I has an index outside [0, m)");
   if (h1[1] & 2) return fail(SPX_EINVAL, "J has an index outside [0, n)");
   P->nmod = h1[0];
   P->ntiles = tile_count(P->A, P->nmod);
+  int64_t* qstart = nullptr;
   SPX_TRY(scr.get_many({Scratch::part(&P->tmod, P->ntiles + 1), Scratch::part(&P->colb, P->nmod),
-                        Scratch::part(&P->cole, P->nmod)}));
+                        Scratch::part(&P->cole, P->nmod), Scratch::part(&P->shift, P->nmod + 1),
+                        Scratch::part(&qstart, P->nmod + 1)}));
   SPX_TRY(copy_tiles(P->A, P->mod, P->nmod, P->ntiles, P->tmod, P->colb, P->cole, st));
-  SPX_TRY(exclusive_scan(LoadI32{P->qcnt}, n, P->qoff, scr, st));
+  SPX_TRY(exclusive_scan(LoadQ{P->qcnt, P->mod}, P->nmod, qstart, scr, st));
+  if (P->nmod > 0) {
+    k_ea_qoff<<<grid_for(P->nmod, 256, 65536), 256, 0, st>>>(P->mod, P->nmod, qstart, P->qoff);
+    SPX_HIP(hipGetLastError());
+  }
   if (lenJ > 0) {
     k_scatter_q<<<grid_for(lenJ, 256, 4096), 256, 0, st>>>(J, lenJ, P->qoff, P->qcnt, P->qlist);
     SPX_HIP(hipGetLastError());
@@ -1730,10 +1735,14 @@ extern "C" int spx_extend_add_plan(const spx_ctx* ctx, const spx_mat* A, const i
     SPX_HIP(hipGetLastError());
     SPX_TRY(dispatch_ea<false>(P, nullptr, nullptr, st, true));
   }
-  SPX_TRY(exclusive_scan(LoadI64{P->cnt}, n, P->off, scr, st));
-  int64_t total = 0;
-  SPX_TRY(read_device_words(st, {{P->off + n, 8}}, &total));
-  P->nnz = total;
+  SPX_TRY(exclusive_scan(LoadAdded{P->cnt, P->colb, P->cole, P->mod}, P->nmod, P->shift, scr, st));
+  if (P->nmod > 0) {
+    k_ea_offsets<<<grid_for(P->nmod, 256, 65536), 256, 0, st>>>(P->mod, P->nmod, P->colb, P->shift, P->off);
+    SPX_HIP(hipGetLastError());
+  }
+  int64_t added = 0;
+  SPX_TRY(read_device_words(st, {{P->shift + P->nmod, 8}}, &added));
+  P->nnz = P->A.nnz + added;
   if (nnz_c) *nnz_c = P->nnz;
   *plan = guard.release();
   return SPX_OK;
@@ -1753,7 +1762,8 @@ extern "C" int spx_extend_add_exec(spx_plan* plan, spx_mat* C) {
   hipStream_t st = stream_of(&P->ctx);
   SPX_TRY(dispatch_ea<true>(P, C->ir, C->num, st, false));  // tiles, then the column kernels
   if (P->nmod > 0) SPX_TRY(dispatch_ea<true>(P, C->ir, C->num, st, true));
-  k_asgn_write_cp<<<grid_for(P->A.n + 1, 256, 65536), 256, 0, st>>>(P->off, P->A.n, C->cp, C->ptr_t);
+  k_asgn_shift_cp<<<grid_for(P->A.n, kScanTile), kScanThreads, 0, st>>>(P->A, P->lastJ, P->carry, P->shift, C->cp,
+                                                                        C->ptr_t);
   SPX_HIP(hipGetLastError());
   return SPX_OK;
 }

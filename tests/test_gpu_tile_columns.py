@@ -41,3 +41,18 @@ def test_columns_around_tiles(spx, lens, picked):
     B = _matrix(rng, 3500, rng.integers(0, 9, J.size))
     got = spx.spasgn(spx.from_host(A), I, J, spx.from_host(B)).to_host_csc()
     assert_same_csc(got, oracle.spasgn(A, I, J, B), exact_values=True, what=f"{lens[:6]} {picked}")
+
+
+@pytest.mark.parametrize("picked", ["none", "first", "last", "every", "some"])
+@pytest.mark.parametrize("n", [1, 2047, 2048, 2049, 4096])
+def test_extend_add_around_blocks(spx, n, picked):
+    rng = np.random.default_rng(n)
+    lens = rng.integers(0, 5, n)
+    lens[n // 2] = 1500  # an A column over tiles, and past the column kernels
+    A = _matrix(rng, 1600, lens)
+    J = {"none": [], "first": [0], "last": [n - 1] * 3, "every": rng.permutation(n), "some": rng.integers(0, n, 40)}[picked]
+    J, I = np.asarray(J, np.int32), rng.integers(0, 1600, 90).astype(np.int32)
+    B = _matrix(rng, 90, rng.integers(0, 80 if picked == "some" else 6, J.size)) if J.size \
+        else W.from_triples([], [], np.empty(0, np.int64), 90, 0)
+    got = spx.extend_add(spx.from_host(A), I, J, spx.from_host(B)).to_host_csc()
+    assert_same_csc(got, oracle.extend_add(A, I, J, B), exact_values=True, what=f"{n} {picked}")
