@@ -7,6 +7,7 @@
 
 #include <initializer_list>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "spx.h"
@@ -366,7 +367,11 @@ __device__ __forceinline__ A block_excl_scan1(A a, A* reda, A* tota, B b, B* red
 
 // ---------------------------------------------------------------- semirings
 // mul: product of A(i,k) and B(k,j); add: combine into an accumulator;
-// lds_acc: atomic combine into LDS; ident: value of an untouched slot.
+// lds_acc: atomic combine into LDS; ident: value of an untouched slot;
+// fold: what lds_acc leaves of a slot that holds acc, in registers.  The LDS
+// minimum of floats passes over a NaN and takes -0 for less than +0, whatever
+// the order of the products; add, as Algorithm 1, keeps a NaN that comes first
+// and the first of two zeros.
 // ident is the exact neutral element of add, so that a slot started from it
 // and combined with the products ends where a fold started from the first
 // product ends (Algorithm 1 starts each accumulator from its first product).
@@ -381,6 +386,7 @@ struct Semiring<SPX_PLUS_TIMES, T> {
   static constexpr bool kUsesA = true, kUsesB = true;
   __device__ static T mul(T a, T b) { return a * b; }
   __device__ static T add(T acc, T x) { return acc + x; }
+  __device__ static T fold(T acc, T x) { return acc + x; }
   __device__ static T ident() { return -T(0); }
   __device__ static void lds_acc(T* p, T x) {
     __hip_atomic_fetch_add(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -391,6 +397,7 @@ struct Semiring<SPX_PLUS_TIMES, int64_t> {
   static constexpr bool kUsesA = true, kUsesB = true;
   __device__ static int64_t mul(int64_t a, int64_t b) { return (int64_t)((uint64_t)a * (uint64_t)b); }
   __device__ static int64_t add(int64_t acc, int64_t x) { return (int64_t)((uint64_t)acc + (uint64_t)x); }
+  __device__ static int64_t fold(int64_t acc, int64_t x) { return add(acc, x); }
   __device__ static int64_t ident() { return 0; }
   __device__ static void lds_acc(int64_t* p, int64_t x) {
     __hip_atomic_fetch_add(reinterpret_cast<unsigned long long*>(p), (unsigned long long)x, __ATOMIC_RELAXED,
@@ -410,6 +417,11 @@ __device__ __forceinline__ int64_t pos_inf<int64_t>() { return INT64_MAX; }
 template <typename T>
 struct MinAcc {
   __device__ static T add(T acc, T x) { return x < acc ? x : acc; }
+  // from ident on, acc is never a NaN
+  __device__ static T fold(T acc, T x) {
+    if constexpr (std::is_floating_point_v<T>) return x < acc || (x == acc && __builtin_signbit(x)) ? x : acc;
+    return add(acc, x);
+  }
   __device__ static T ident() { return pos_inf<T>(); }
   __device__ static void lds_acc(T* p, T x) {
     __hip_atomic_fetch_min(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);

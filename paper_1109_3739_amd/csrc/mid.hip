@@ -205,6 +205,8 @@ __device__ __forceinline__ void mid_column(const Operand& A, const Operand& B, c
   wave_sync();
   int32_t* rows = reinterpret_cast<int32_t*>(s_v);
   int rank = hincl - nh - 1;  // the run that reaches into this lane
+  // Lanes cut a run into pieces, so a piece starts from the neutral element and folds
+  // as the LDS does: started from its own first product, a NaN there hid the rest.
   T lead = T(0), acc = T(0);
   bool leads = false;
 #pragma unroll
@@ -213,12 +215,12 @@ __device__ __forceinline__ void mid_column(const Operand& A, const Operand& B, c
     if (head[k]) {
       ++rank;
       rows[rank] = row[k];
-      acc = v[k];
+      acc = SR_::fold(SR_::ident(), v[k]);
     } else if (k == 0) {
-      acc = v[0];
+      acc = SR_::fold(SR_::ident(), v[0]);
       leads = in;
     } else if (in) {
-      acc = SR_::add(acc, v[k]);
+      acc = SR_::fold(acc, v[k]);
     }
     if constexpr (kVal) {
       const bool last = k == R - 1 || head[k + 1 < R ? k + 1 : k] || lane * R + k + 1 >= total;

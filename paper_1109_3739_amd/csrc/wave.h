@@ -13,6 +13,7 @@ struct Semiring<SPX_OR_AND, T> {
   static constexpr bool kUsesA = false, kUsesB = false;
   __device__ static T mul(T a, T) { return a; }
   __device__ static T add(T acc, T) { return acc; }
+  __device__ static T fold(T acc, T) { return acc; }
   __device__ static T ident() { return T(0); }
   __device__ static void lds_acc(T*, T) {}
 };
