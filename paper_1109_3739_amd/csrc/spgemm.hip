@@ -1002,7 +1002,9 @@ __global__ void __launch_bounds__(1024, 8) k_count_bitmap(Operand B, ProdSrc S, 
   extern __shared__ __align__(16) unsigned char lds[];
   uint32_t* bm = (uint32_t*)lds;
   u32x4* bm4 = (u32x4*)lds;
-  const int64_t chunk_rows = 1ll << chunk_log2;  // a multiple of the row block, at least 8192 or one chunk
+  // a multiple of the row block and of the 128 rows of one 16-byte store: a chunk's
+  // last store would else reach into the next chunk's rows, or the next column's bitmap
+  const int64_t chunk_rows = 1ll << chunk_log2;
   const int64_t nchunks = (m + chunk_rows - 1) >> chunk_log2;
   const int blk_per_chunk = (int)(chunk_rows >> rbshift);
   const int all4 = (int)((chunk_rows + 127) >> 7);
@@ -2512,7 +2514,7 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
     SPX_TRY(scr.get_n(nmulti * nblk + 1, &blkcnt));
   }
   const int64_t nbitmap = bo[kBinHash0] - bo[0];
-  // bitmap chunks: a power of two of rows, a multiple of the row block;
+  // bitmap chunks: a power of two of rows, a multiple of the row block and of 128;
   // 0 = one chunk per row slice
   int want = tune.bitmap_chunk_log2;
   if (want <= 0) {  // auto: one chunk per row slice, at most 2^18 rows (four workgroups per CU)
@@ -2520,8 +2522,9 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
     while ((1ll << want) < ceil_div(m, std::max(1, P->nslice_req))) ++want;
     want = std::min(want, 18);
   }
-  int clog = std::max<int>(rb, std::min<int>(want, 20));
-  while (clog > rb && (1ll << (clog - 1)) >= m) --clog;
+  const int clog_min = std::max(rb, 7);  // whole 16-byte stores (k_count_bitmap)
+  int clog = std::max<int>(clog_min, std::min<int>(want, 20));
+  while (clog > clog_min && (1ll << (clog - 1)) >= m) --clog;
   const int64_t nchunks = std::max<int64_t>(1, ceil_div(m, 1ll << clog));
   unsigned long long* bqctr = nullptr;  // per-chunk column counters of the bitmap count
   if (nbitmap > 0) SPX_TRY(scr.get_n(nchunks, &bqctr));
