@@ -2189,7 +2189,8 @@ struct GemmPlan : spx_plan {
   int64_t* binoff = nullptr;
   Part* parts = nullptr;
   int64_t* qoff_multi = nullptr;  // bounds of the multi-part launch's queues (several row slices only)
-  unsigned long long* qctr = nullptr;
+  unsigned long long* qctr = nullptr;  // [kMaxQueues + 1] zero between execs
+  bool queues_spent = false;           // unless an exec failed and could not clear them (see QueueGuard)
   int32_t nq_multi = 1, nslice = 1, nslice_req = 1;
   Summary* sum = nullptr;
   unsigned long long* totals = nullptr;  // spread counters: multiplications, entries of the tiny columns
@@ -2197,6 +2198,17 @@ struct GemmPlan : spx_plan {
   int32_t* qlist = nullptr;  // B entries of the parts of bucketed columns, grouped by part
   uint64_t* gbm = nullptr;  // stored row bitmaps of the bitmap-counted columns
   int64_t gbm_words = 0;    // 64-bit words per stored bitmap
+};
+
+// The last launch of an exec clears the queue counters for the next one.  An exec
+// that returns before it leaves this to clear them: the next one would else find
+// the queues empty and skip its parts without an error.
+struct QueueGuard {
+  GemmPlan* plan;
+  hipStream_t st;
+  ~QueueGuard() {
+    if (plan) plan->queues_spent = zero_words(st, {{plan->qctr, kMaxQueues + 1}}) != SPX_OK;
+  }
 };
 
 int check_mat(const spx_mat* X, const char* name) {
@@ -2305,7 +2317,7 @@ static int launch_numeric(GemmPlan* P, spx_mat* C, hipStream_t st) {
   unsigned* err = &P->sum->err;
   const int cus = device_cu_count();
   // parts of multi-part columns [0, psplit), single-part columns [psplit, nparts)
-  // (the queue counters are zero: cleared by the plan, then by every exec's last launch)
+  // (the queue counters are zero: cleared by the plan, then by every exec's last launch or QueueGuard)
   for (int r = 0; r < 2; ++r) {
     const int64_t n0 = r == 0 ? 0 : P->psplit, n1 = r == 0 ? P->psplit : P->nparts;
     if (n1 <= n0) continue;
@@ -2743,6 +2755,9 @@ extern "C" int spx_spgemm_exec(spx_plan* plan, spx_mat* C) {
   C->nnz = P->nnz;
   C->nzc = C->fmt == SPX_DCSC ? P->nzc : 0;
   hipStream_t st = stream_of(&P->ctx);
+  if (P->queues_spent) SPX_TRY(zero_words(st, {{P->qctr, kMaxQueues + 1}}));
+  P->queues_spent = false;
+  QueueGuard queues{P, st};
   P->mark(kEvExec0, st);
   P->ran_parts = P->ran_tiny = false;
   if (P->nnz > 0) SPX_TRY(dispatch_numeric(P, C, st));
@@ -2764,6 +2779,7 @@ extern "C" int spx_spgemm_exec(spx_plan* plan, spx_mat* C) {
       SPX_TRY(fill_u32((uint32_t*)C->cp, 1, 0, st));
   }
   SPX_HIP(hipGetLastError());
+  queues.plan = nullptr;
   P->mark(kEvPtr, st);
   return SPX_OK;
 }
