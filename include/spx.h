@@ -156,7 +156,8 @@ typedef struct spx_tuning {
   int32_t force_off64;
 } spx_tuning;
 
-/* Statistics of a SpGEMM plan, available once the plan call returned. */
+/* Statistics of a SpGEMM plan, available once the plan call returned: asking for
+ * them reads host memory only, from any thread and also while a stream is captured. */
 typedef struct spx_plan_info {
   int64_t mults;          /* total number of multiplications (sum over columns) */
   int64_t nnz;            /* nnz(C) */

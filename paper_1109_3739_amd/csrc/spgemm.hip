@@ -1225,18 +1225,19 @@ __device__ int64_t cut_parts(const PartCfg& p, const uint32_t* blk, int32_t t, i
 // counts in LDS (a thread each, walking them one by one in memory, took 0.21 ms
 // on R-MAT scale 20, and 57 us on 128 long columns); the others the rest, a
 // thread each.
-// In the counting pass, setup_acc (if given) receives the sums over the cut
-// columns of (B entries x parts) and of their multiplications, which tell
-// how many range set-ups the multi-part launch makes per product.
+// In the counting pass, acc (if given) receives the entries of C in the columns
+// with row-block counts, and the sums over the cut columns of (B entries x parts)
+// and of their multiplications, which tell how many range set-ups the multi-part
+// launch makes per product.
 constexpr int kCutBlk = 1024;  // row blocks held in LDS (more are read from memory)
 
 __global__ void __launch_bounds__(256) k_parts(Operand B, PartCfg p, PartCfg ps, const int32_t* list, int64_t npos,
                                                int64_t multi_begin, int64_t multi_end, unsigned cut_blocks, int64_t nbm,
                                                const int64_t* cnt, const int64_t* off, const uint32_t* blkcnt,
                                                int64_t* nparts, const int64_t* poff, Part* parts, const int64_t* mults,
-                                               unsigned long long* setup_acc, unsigned* err) {
+                                               unsigned long long* acc, unsigned* err) {
   __shared__ uint32_t s_blk[4][kCutBlk];  // prefix sums of the counts
-  unsigned long long my_setup = 0, my_mults = 0;
+  unsigned long long my_nnz = 0, my_setup = 0, my_mults = 0;
   // a column in one part
   auto whole = [&](int64_t pos, int32_t t, int64_t c, const PartCfg& q) {
     if (!parts) {
@@ -1262,6 +1263,7 @@ __global__ void __launch_bounds__(256) k_parts(Operand B, PartCfg p, PartCfg ps,
       const int32_t t = list[pos];
       const int64_t c = cnt[t];
       int64_t np = c > 0;
+      if (lane == 0) my_nnz += (unsigned long long)c;
       if (c > 0 && !(bitmap_ok(p, p.m, c) || hash_ok(p, p.m, c))) {
         const int64_t cb0 = slot_begin(B, t), nb = slot_begin(B, t + 1) - cb0;
         const uint32_t* blk = blkcnt + (pos - multi_begin) * p.nblk;
@@ -1279,7 +1281,7 @@ __global__ void __launch_bounds__(256) k_parts(Operand B, PartCfg p, PartCfg ps,
         const int32_t bmi = pos - multi_begin < nbm ? (int32_t)(pos - multi_begin) : -1;
         np = p.nblk <= kCutBlk ? cut_parts<true>(p, s_blk[w], t, off[t], out, bmi, cb0, (int32_t)nb, err)
                                : cut_parts<false>(p, blk, t, off[t], out, bmi, cb0, (int32_t)nb, err);
-        if (setup_acc && np > 1 && lane == 0) {
+        if (acc && np > 1 && lane == 0) {
           my_setup += (unsigned long long)nb * (unsigned long long)np;
           my_mults += (unsigned long long)mults[t];
         }
@@ -1299,14 +1301,15 @@ __global__ void __launch_bounds__(256) k_parts(Operand B, PartCfg p, PartCfg ps,
       if (!parts) nparts[pos] = c > 0;
     }
   }
-  if (setup_acc) {  // one pair of atomics per workgroup
-    __shared__ unsigned long long s_acc[2];
-    if (threadIdx.x < 2) s_acc[threadIdx.x] = 0;
+  if (acc) {  // at most three atomics per workgroup
+    __shared__ unsigned long long s_acc[3];
+    if (threadIdx.x < 3) s_acc[threadIdx.x] = 0;
     __syncthreads();
-    if (my_setup) atomicAdd(&s_acc[0], my_setup);
-    if (my_mults) atomicAdd(&s_acc[1], my_mults);
+    if (my_nnz) atomicAdd(&s_acc[0], my_nnz);
+    if (my_setup) atomicAdd(&s_acc[1], my_setup);
+    if (my_mults) atomicAdd(&s_acc[2], my_mults);
     __syncthreads();
-    if (threadIdx.x < 2 && s_acc[threadIdx.x]) atomicAdd(&setup_acc[threadIdx.x], s_acc[threadIdx.x]);
+    if (threadIdx.x < 3 && s_acc[threadIdx.x]) atomicAdd(&acc[threadIdx.x], s_acc[threadIdx.x]);
   }
 }
 
@@ -2077,14 +2080,6 @@ __global__ void __launch_bounds__(1024) k_cnt_small(const int64_t* cnt, const in
   }
 }
 
-__global__ void k_parts_sum(const Part* parts, int64_t n, unsigned long long* out) {
-  int64_t s = 0;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    s += parts[i].c;
-  s = wave_sum(s);
-  if (lane_id() == 0 && s) atomicAdd(out, (unsigned long long)s);
-}
-
 // Counting sort of the multi-part list by row slice (work queue).
 __global__ void k_part_hist(const Part* parts, int64_t n, unsigned long long* hist) {
   __shared__ unsigned h[66];
@@ -2144,7 +2139,7 @@ namespace spx {
 struct Summary {
   unsigned long long mults;
   unsigned long long nnz_tiny;
-  unsigned long long nnz_multi;
+  unsigned long long nnz_multi;  // entries of C in columns with row-block counts; k_parts adds this and the next two
   unsigned long long setup;      // sum over cut columns of (B entries x parts)
   unsigned long long cut_mults;  // multiplications of the cut columns
   unsigned err;
@@ -2654,7 +2649,7 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
     k_parts<<<pgrid, 256, 0, st>>>(P->B, pc, pcs, P->list, npos, multi_begin, multi_end,
                                                                     cut_blocks, P->gbm ? nbitmap : 0, P->cnt,
                                                                     P->off, blkcnt, np, nullptr, nullptr, P->mults_d,
-                                                                    &P->sum->setup, err);
+                                                                    &P->sum->nnz_multi, err);
     SPX_HIP(hipGetLastError());
     SPX_TRY(exclusive_scan(LoadI64{np}, npos, poff, scr, st));
   }
@@ -2672,6 +2667,7 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
   P->nparts = tail[2];
   P->psplit = tail[3];
   P->nnz_tiny = (int64_t)hs.nnz_tiny;
+  P->nnz_multi = (int64_t)hs.nnz_multi;
   if (P->nparts > 0) {
     SPX_TRY(scr.get_n(P->nparts, &P->parts));
     k_parts<<<pgrid, 256, 0, st>>>(P->B, pc, pcs, P->list, npos, multi_begin, multi_end,
@@ -2731,7 +2727,6 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
                                hipMemcpyDeviceToDevice, st));
       P->parts = sorted;
     }
-    if (P->psplit > 0) P->nnz_multi = -1;  // summed up by spx_plan_get_info
   }
   P->mark(kEvPlan1, st);
   if (nnz_c) *nnz_c = P->nnz;
@@ -2813,16 +2808,7 @@ extern "C" int spx_plan_get_info(const spx_plan* plan, spx_plan_info* info) {
   if (plan->kind == kPlanSum) plan = sum_plan_inner(plan);
   if (plan->kind == kPlanContract) plan = contract_plan_inner(plan);
   if (plan->kind != kPlanGemm) return SPX_OK;
-  auto* P = const_cast<GemmPlan*>(static_cast<const GemmPlan*>(plan));
-  if (P->nnz_multi < 0) {
-    hipStream_t st = stream_of(&P->ctx);
-    SPX_TRY(fill_i64((int64_t*)&P->sum->nnz_multi, 1, 0, st));
-    k_parts_sum<<<grid_for(P->psplit, 256, 1024), 256, 0, st>>>(P->parts, P->psplit, &P->sum->nnz_multi);
-    SPX_HIP(hipGetLastError());
-    int64_t v = 0;
-    SPX_TRY(read_device_words(st, {{&P->sum->nnz_multi, 8}}, &v));
-    P->nnz_multi = v;
-  }
+  auto* P = static_cast<const GemmPlan*>(plan);
   const int64_t* bo = P->binoff_h;
   info->mults = P->mults;
   info->nnz = P->nnz;
