@@ -38,7 +38,7 @@ struct SumPlan : spx_plan {
   int32_t count = 0;
   int vb_a = 0, vb_b = 0;
   std::vector<Operand> a_h, b_h;  // the stage blocks
-  std::vector<int64_t> base_h;    // nnz bases of the A_k and B_k, slot bases, column bases (count+1 each)
+  std::vector<int64_t> base_h;    // nnz bases of the A_k and B_k, slot bases, column bases, B's slot bases (count+1 each)
   std::vector<char> table_h;      // those, as copied to the device
   Operand* a_d = nullptr;
   Operand* b_d = nullptr;
@@ -46,6 +46,7 @@ struct SumPlan : spx_plan {
   int64_t* bnzb = nullptr;   // [count+1] nnz bases of the B_k
   int64_t* slotb = nullptr;  // [count+1] slot bases of the A_k
   int64_t* colb = nullptr;   // [count+1] column bases of the A_k (= row bases of the B_k)
+  int64_t* bslotb = nullptr;  // [count+1] slot bases of the B_k
   int32_t* ajc = nullptr;
   int64_t* acp = nullptr;
   int32_t* air = nullptr;
@@ -77,23 +78,23 @@ __global__ void k_sum_left(const Operand* a, const int64_t* slotb, const int64_t
   }
 }
 
-// Column lengths of the stages [k0, k0 + g) of B (which share the n columns):
-// len[(k - k0) n + j], zero on entry.
-__global__ void k_sum_right_count(const Operand* b, int k0, int g, int64_t n, uint32_t* len) {
-  for (int k = blockIdx.y; k < g; k += gridDim.y) {
-    const Operand X = b[k0 + k];
+// Column lengths of all stages of B (which share the n columns): len[k n + j],
+// zero on entry.
+__global__ void k_sum_right_count(const Operand* b, int count, int64_t n, uint32_t* len) {
+  for (int k = blockIdx.y; k < count; k += gridDim.y) {
+    const Operand X = b[k];
     const int64_t ns = nslots_of(X);
     for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < ns; t += (int64_t)gridDim.x * blockDim.x)
       len[k * n + slot_col(X, t)] = (uint32_t)(slot_begin(X, t + 1) - slot_begin(X, t));
   }
 }
 
-// Per column: the lengths become the stages' offsets in the column (after the
-// cnt[j] entries of earlier stages, if `more`), and cnt[j] what they end at.
-__global__ void k_sum_right_offsets(int g, bool more, int64_t n, uint32_t* len, int64_t* cnt) {
+// Per column: the lengths become the stages' offsets in the column, and cnt[j]
+// what they end at.
+__global__ void k_sum_right_offsets(int count, int64_t n, uint32_t* len, int64_t* cnt) {
   for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < n; j += (int64_t)gridDim.x * blockDim.x) {
-    uint32_t run = more ? (uint32_t)cnt[j] : 0;  // a column has fewer than 2^31 entries (its rows are below 2^31)
-    for (int k = 0; k < g; ++k) {
+    uint32_t run = 0;  // a column has fewer than 2^31 entries (its rows are below 2^31)
+    for (int k = 0; k < count; ++k) {
       const uint32_t x = len[k * n + j];
       len[k * n + j] = run;
       run += x;
@@ -102,17 +103,28 @@ __global__ void k_sum_right_offsets(int g, bool more, int64_t n, uint32_t* len, 
   }
 }
 
+// The offsets of one stage's stored columns only, off[t] for slot t, where
+// cnt[j] holds the entries of the stages before it (one launch per stage, in order).
+__global__ void k_sum_right_chain(Operand X, int64_t* cnt, uint32_t* off) {
+  const int64_t ns = nslots_of(X);
+  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < ns; t += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t j = slot_col(X, t), before = cnt[j];
+    off[t] = (uint32_t)before;
+    cnt[j] = before + slot_begin(X, t + 1) - slot_begin(X, t);
+  }
+}
+
 // Places every stage's columns (rows moved down by the stage's row base) at
-// their offsets.  A wave takes four slots at a time, one per 16-lane group;
-// slots of more than 64 entries then take the whole wave.
+// their offsets: off[k n + j], or with bslot off[bslot[k] + t].  A wave takes
+// four slots at a time, one per 16-lane group; slots of more than 64 entries
+// then take the whole wave.
 __global__ void __launch_bounds__(256) k_sum_right_place(const Operand* b, const int64_t* colb, const int64_t* bnzb,
-                                                         int k0, int g, int64_t n, const int64_t* bcp, const uint32_t* off,
-                                                         int32_t* ir, int64_t* map) {
+                                                         int count, int64_t n, const int64_t* bcp, const uint32_t* off,
+                                                         const int64_t* bslot, int32_t* ir, int64_t* map) {
   const int lane = lane_id(), gl = lane & 15;
   const int64_t w0 = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave;
   const int64_t nw = (int64_t)gridDim.x * blockDim.x / kWave;
-  for (int kk = blockIdx.y; kk < g; kk += gridDim.y) {
-    const int k = k0 + kk;
+  for (int k = blockIdx.y; k < count; k += gridDim.y) {
     const Operand X = b[k];
     const int64_t ns = nslots_of(X), rowb = colb[k];
     int64_t* mp = map + bnzb[k];
@@ -123,7 +135,7 @@ __global__ void __launch_bounds__(256) k_sum_right_place(const Operand* b, const
         s0 = slot_begin(X, t);
         s1 = slot_begin(X, t + 1);
         const int64_t j = slot_col(X, t);
-        dst = bcp[j] + off[kk * n + j];
+        dst = bcp[j] + off[bslot ? bslot[k] + t : k * n + j];
       }
       const bool whole = s1 - s0 > kWave;
       if (!whole)
@@ -164,9 +176,19 @@ __global__ void k_sum_vals(const Operand* a, const int64_t* anzb, int va, void* 
   }
 }
 
-// Words of the table of column lengths: all stages of an 8 x 8 grid's blocks of
-// 2^20 columns, and 256 MiB at most unless one stage alone takes more.
-constexpr int64_t kLenTable = 1ll << 26;
+// Where a stage's part of a column begins comes from a table of all stages' column
+// lengths (two launches for all stages), or from a launch per stage over its stored
+// columns only.  The table is taken while the stages store at least an eighth of its
+// columns, so that no pass or buffer is proportional to (stages x columns) of
+// hypersparse blocks; and while it is short all the same, since launches are dear.
+// Plan and exec by table | by stage: 8 stages of 2^17 entries, DCSC, n = 2^20 416 | 433
+// us, 2^21 488 | 470, 2^24 1630 | 1230; 64 of 2^14, n = 2^19 649 | 720; in CSC, n = 2^22
+// 2515 | 2835.  Always by table, n = 2^27 took 19.2 ms, now 6.9.
+constexpr int64_t kLenCols = 1ll << 20;
+constexpr int64_t kLenTable = 1ll << 26;  // words, 256 MiB
+static bool by_table(int64_t stored, int64_t n, int count) {
+  return 8 * stored >= n * count || (n <= kLenCols && n * count <= kLenTable);
+}
 
 // Grid over the elements of the largest stage (x) and the stages (y).
 static dim3 stage_grid(int64_t widest, int per_block, int count) {
@@ -216,9 +238,10 @@ extern "C" int spx_spgemm_sum_plan(const spx_ctx* ctx, int32_t count, const spx_
   P->vb_a = value_size(A[0].val_t);
   P->vb_b = value_size(B[0].val_t);
   const int64_t m = A[0].m, n = B[0].n;
-  P->base_h.assign(4 * (count + 1), 0);
+  P->base_h.assign(5 * (count + 1), 0);
   int64_t* const anzb = P->base_h.data();
   int64_t *const bnzb = anzb + count + 1, *const slotb = bnzb + count + 1, *const colb = slotb + count + 1;
+  int64_t* const bslotb = colb + count + 1;
   int64_t wide_a = 0, wide_b = 0, wide_bs = 0;  // largest stage: A's slots or entries, B's entries, B's slots
   for (int k = 0; k < count; ++k) {
     P->a_h.push_back(make_operand(&A[k]));
@@ -227,13 +250,13 @@ extern "C" int spx_spgemm_sum_plan(const spx_ctx* ctx, int32_t count, const spx_
     colb[k + 1] = colb[k] + A[k].n;
     anzb[k + 1] = anzb[k] + A[k].nnz;
     bnzb[k + 1] = bnzb[k] + B[k].nnz;
+    bslotb[k + 1] = bslotb[k] + nslots_of(P->b_h[k]);
     wide_a = std::max({wide_a, nslots_of(P->a_h[k]), A[k].nnz});
     wide_b = std::max(wide_b, B[k].nnz);
     wide_bs = std::max(wide_bs, nslots_of(P->b_h[k]));
   }
   slots = slotb[count];
-  // the columns' lengths are tabled for a group of stages at a time
-  const int group = (int)std::clamp<int64_t>(kLenTable / std::max<int64_t>(n, 1), 1, count);
+  const bool tabled = by_table(bslotb[count], n, count);
   // stage tables in one copy (the host bytes live as long as the plan)
   const size_t ops = sizeof(Operand) * count, bases = sizeof(int64_t) * P->base_h.size();
   P->table_h.resize(2 * ops + bases);
@@ -242,11 +265,11 @@ extern "C" int spx_spgemm_sum_plan(const spx_ctx* ctx, int32_t count, const spx_
   std::memcpy(P->table_h.data() + 2 * ops, P->base_h.data(), bases);
   char* table = nullptr;
   int64_t* cnt = nullptr;
-  uint32_t* len = nullptr;
+  uint32_t* off = nullptr;  // offsets of the stages' columns: the table, or one per stored column
   SPX_TRY(scr.get_many({Scratch::part(&table, (int64_t)P->table_h.size()), Scratch::part(&P->ajc, slots),
                         Scratch::part(&P->acp, slots + 1), Scratch::part(&P->air, anz), Scratch::part(&cnt, n),
                         Scratch::part(&P->bcp, n + 1), Scratch::part(&P->bir, bnz), Scratch::part(&P->bmap, bnz),
-                        Scratch::part(&len, group * n + 1)}));
+                        Scratch::part(&off, tabled ? count * n + 1 : bslotb[count])}));
   if (P->vb_a) SPX_TRY(scr.get(std::max<int64_t>(anz, 1) * P->vb_a, &P->anum));
   if (P->vb_b) SPX_TRY(scr.get(std::max<int64_t>(bnz, 1) * P->vb_b, &P->bnum));
   static_assert(sizeof(Operand) % sizeof(int64_t) == 0, "the bases follow the operands");
@@ -256,6 +279,7 @@ extern "C" int spx_spgemm_sum_plan(const spx_ctx* ctx, int32_t count, const spx_
   P->bnzb = P->anzb + count + 1;
   P->slotb = P->bnzb + count + 1;
   P->colb = P->slotb + count + 1;
+  P->bslotb = P->colb + count + 1;
   SPX_HIP(hipMemcpyAsync(table, P->table_h.data(), P->table_h.size(), hipMemcpyHostToDevice, st));
 
   // left concatenation (DCSC)
@@ -263,25 +287,27 @@ extern "C" int spx_spgemm_sum_plan(const spx_ctx* ctx, int32_t count, const spx_
                                                              P->air);
   SPX_HIP(hipGetLastError());
   // right concatenation (CSC)
-  auto offsets = [&](int k0, int g) -> int {
-    SPX_TRY(zero_words(st, {{len, ceil_div(g * n, 2)}}));
-    k_sum_right_count<<<stage_grid(wide_bs, 256, g), 256, 0, st>>>(P->b_d, k0, g, n, len);
+  if (n > 0 && tabled) {
+    SPX_TRY(zero_words(st, {{off, ceil_div(count * n, 2)}}));
+    k_sum_right_count<<<stage_grid(wide_bs, 256, count), 256, 0, st>>>(P->b_d, count, n, off);
     SPX_HIP(hipGetLastError());
-    k_sum_right_offsets<<<grid_for(n, 256, 4096), 256, 0, st>>>(g, k0 > 0, n, len, cnt);
+    k_sum_right_offsets<<<grid_for(n, 256, 4096), 256, 0, st>>>(count, n, off, cnt);
     SPX_HIP(hipGetLastError());
-    return SPX_OK;
-  };
-  if (n > 0)
-    for (int k0 = 0; k0 < count; k0 += group) SPX_TRY(offsets(k0, std::min(group, count - k0)));
-  SPX_TRY(exclusive_scan(LoadI64{cnt}, n, P->bcp, scr, st));
-  if (bnz > 0)
-    for (int k0 = 0; k0 < count; k0 += group) {
-      const int g = std::min(group, count - k0);
-      if (group < count) SPX_TRY(offsets(k0, g));
-      k_sum_right_place<<<stage_grid(wide_bs, 16, g), 256, 0, st>>>(P->b_d, P->colb, P->bnzb, k0, g, n, P->bcp, len,
-                                                                    P->bir, P->bmap);
+  } else if (n > 0) {
+    SPX_TRY(zero_words(st, {{cnt, n}}));
+    for (int k = 0; k < count; ++k) {
+      const int64_t ns = nslots_of(P->b_h[k]);
+      if (ns == 0 || B[k].nnz == 0) continue;
+      k_sum_right_chain<<<grid_for(ns, 256, 4096), 256, 0, st>>>(P->b_h[k], cnt, off + bslotb[k]);
       SPX_HIP(hipGetLastError());
     }
+  }
+  SPX_TRY(exclusive_scan(LoadI64{cnt}, n, P->bcp, scr, st));
+  if (bnz > 0) {
+    k_sum_right_place<<<stage_grid(wide_bs, 16, count), 256, 0, st>>>(P->b_d, P->colb, P->bnzb, count, n, P->bcp, off,
+                                                                      tabled ? nullptr : P->bslotb, P->bir, P->bmap);
+    SPX_HIP(hipGetLastError());
+  }
 
   // one SpGEMM over the concatenations
   spx_mat Ac{}, Bc{};
