@@ -1105,7 +1105,7 @@ struct Part {
   int32_t t;     // slot of B / output column
   int32_t c;     // outputs in the part
   int32_t r0, r1;  // row range [r0, r1)
-  int32_t mode;  // bit 0: 0 = bitmap, 1 = hash; bit 1: [b0, b0 + nb) indexes the bucket list
+  int32_t mode;  // bit 0: 0 = bitmap, 1 = hash; bit 1: [b0, b0 + nb) indexes the bucket list; bit 2: notes rows
   int32_t slice; // row slice of the part (work queue), nslice = any
   int32_t bmi;   // index of the column's stored row bitmap, -1 if none
   int32_t nb;    // B entries of the column: [b0, b0 + nb) (or the part's bucket)
@@ -1160,6 +1160,14 @@ __device__ __forceinline__ int choose_mode(const PartCfg& p, int64_t span, int64
   return bok ? 0 : 1;
 }
 
+// Whether the parts of a column note a row with every product (see k_numeric_parts):
+// a store per product, against a walk of the bitmap per output.  4096 columns of d
+// products from each of d columns of A over 4096 rows, f64, with notes | without: 4
+// products an output (d = 128) 377 | 395 us, 9 563 | 575, 16 807 | 796, 36 1568 | 1506,
+// 64 2517 | 2393 (f32 7779 | 6405).
+constexpr int64_t kNoteMost = 16;
+__device__ __forceinline__ int note_mode(int64_t mults, int64_t c) { return mults <= kNoteMost * c ? 4 : 0; }
+
 // Cuts one column into parts, greedily over its row blocks: a part grows while
 // it still fits the LDS budget in one of the two modes (in bitmap mode with the
 // noted rows; a single row block may go without).  One wave: its lanes
@@ -1168,8 +1176,8 @@ __device__ __forceinline__ int choose_mode(const PartCfg& p, int64_t span, int64
 // memory; with PREF, their inclusive prefix sums.  Returns the number of parts;
 // writes them if out is given.
 template <bool PREF>
-__device__ int64_t cut_parts(const PartCfg& p, const uint32_t* blk, int32_t t, int64_t base_off, Part* out, int32_t bmi,
-                             int64_t b0, int32_t nb, unsigned* err) {
+__device__ int64_t cut_parts(const PartCfg& p, const uint32_t* blk, int32_t t, int64_t base_off, Part* out, int note,
+                             int32_t bmi, int64_t b0, int32_t nb, unsigned* err) {
   const int64_t RB = 1ll << p.rbshift;
   const int lane = lane_id();
   const int32_t nblk = (int32_t)p.nblk, sb = (int32_t)p.slice_blocks;
@@ -1203,7 +1211,7 @@ __device__ int64_t cut_parts(const PartCfg& p, const uint32_t* blk, int32_t t, i
           P.c = (int32_t)c;
           P.r0 = (int32_t)r0;
           P.r1 = (int32_t)r1;
-          P.mode = choose_mode(p, r1 - r0, c);
+          P.mode = choose_mode(p, r1 - r0, c) | note;
           P.slice = p.slice_blocks ? (int32_t)(b / p.slice_blocks) : 0;
           P.bmi = bmi;
           P.b0 = b0;
@@ -1250,7 +1258,7 @@ __global__ void __launch_bounds__(256) k_parts(Operand B, PartCfg p, PartCfg ps,
     P.c = (int32_t)c;
     P.r0 = 0;
     P.r1 = (int32_t)q.m;
-    P.mode = choose_mode(q, q.m, c);
+    P.mode = choose_mode(q, q.m, c) | note_mode(mults[t], c);
     P.slice = q.nslice;  // full row range: any queue
     P.bmi = pos - multi_begin < nbm ? (int32_t)(pos - multi_begin) : -1;
     P.b0 = slot_begin(B, t);
@@ -1279,8 +1287,9 @@ __global__ void __launch_bounds__(256) k_parts(Operand B, PartCfg p, PartCfg ps,
         }
         Part* out = parts ? parts + poff[pos] : nullptr;
         const int32_t bmi = pos - multi_begin < nbm ? (int32_t)(pos - multi_begin) : -1;
-        np = p.nblk <= kCutBlk ? cut_parts<true>(p, s_blk[w], t, off[t], out, bmi, cb0, (int32_t)nb, err)
-                               : cut_parts<false>(p, blk, t, off[t], out, bmi, cb0, (int32_t)nb, err);
+        const int note = note_mode(mults[t], c);
+        np = p.nblk <= kCutBlk ? cut_parts<true>(p, s_blk[w], t, off[t], out, note, bmi, cb0, (int32_t)nb, err)
+                               : cut_parts<false>(p, blk, t, off[t], out, note, bmi, cb0, (int32_t)nb, err);
         if (acc && np > 1 && lane == 0) {
           my_setup += (unsigned long long)nb * (unsigned long long)np;
           my_mults += (unsigned long long)mults[t];
@@ -1568,14 +1577,14 @@ __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, Pr
       uint64_t* bm = (uint64_t*)lds;
       uint16_t* pre = (uint16_t*)(bm + W);
       T* vals = (T*)(lds + W * 8 + ((W * 2 + 7) & ~7));
-      // Rows in rank order.  Where the part leaves room for them (2 bytes per output),
-      // every product notes the low 16 bits of its row beside its value; the high bits
-      // follow from the ranks at the multiples of 65536 rows.  Else, and for patterns,
-      // the rows are read off the bitmap: its words hold one or two rows each, so lanes
-      // wait for the fullest word at every step (about 50 vector instructions per 64
-      // outputs against 12).
+      // Rows in rank order.  Where the part leaves room for them (2 bytes per output) and
+      // the column has not too many products for an output (note_mode), every product
+      // notes the low 16 bits of its row beside its value; the high bits follow from the
+      // ranks at the multiples of 65536 rows.  Else, and for patterns, the rows are read
+      // off the bitmap: its words hold one or two rows each, so lanes wait for the
+      // fullest word at every step (about 50 vector instructions per 64 outputs against 12).
       uint16_t* low = (uint16_t*)(vals + c);
-      const bool noted = kVal && (char*)(low + c) <= (char*)lds + part_lds;
+      const bool noted = kVal && (P.mode & 4) && (char*)(low + c) <= (char*)lds + part_lds;
       // rank of each product's row: all bitmap words first, then the adds
       auto acc = [&](const int32_t (&r)[8], const T (&a)[8], const T (&bv)[8]) {
         uint64_t w[8];
