@@ -1774,19 +1774,23 @@ __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, Pr
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-              for (uint32_t probe = 1; old[u] != ~0u && old[u] != (uint32_t)r[u]; ++probe) {
-                if (probe >= Sz) {
-                  atomicOr(err, 16u);
-                  in[u] = false;
-                  break;
-                }
-                h[u] = (h[u] + 1) & (Sz - 1);
-                old[u] = atomicCAS(&keys[h[u]], ~0u, (uint32_t)r[u]);
+              if (!in[u]) continue;
+              const uint32_t key = (uint32_t)r[u];
+              uint32_t at = h[u], was = old[u];
+              // a loop over two scalars (with an exit that wrote to the arrays, the compiler
+              // moved all of them at every probe: 2000 products took 23.4k cycles, 17.8k
+              // without batched first probes)
+              for (uint32_t left = Sz; was != ~0u && was != key && left; --left) {
+                at = (at + 1) & (Sz - 1);
+                was = atomicCAS(&keys[at], ~0u, key);
               }
-              if constexpr (kVal)
-                if (in[u]) SR_::lds_acc(&vals[h[u]], SR_::mul(a[u], bv[u]));
-              if (ranked && in[u] && old[u] == ~0u) {  // a new row: level 1 marks its group
-                const uint32_t g = (uint32_t)(r[u] - P.r0) >> 6;
+              if (was != ~0u && was != key) {
+                atomicOr(err, 16u);
+                continue;
+              }
+              if constexpr (kVal) SR_::lds_acc(&vals[at], SR_::mul(a[u], bv[u]));
+              if (ranked && was == ~0u) {  // a new row: level 1 marks its group
+                const uint32_t g = (key - (uint32_t)P.r0) >> 6;
                 atomicOr((unsigned long long*)&l1w[g >> 6], 1ull << (g & 63));
               }
             }
