@@ -1233,19 +1233,18 @@ __device__ int64_t cut_parts(const PartCfg& p, const uint32_t* blk, int32_t t, i
 // counts in LDS (a thread each, walking them one by one in memory, took 0.21 ms
 // on R-MAT scale 20, and 57 us on 128 long columns); the others the rest, a
 // thread each.
-// In the counting pass, acc (if given) receives the entries of C in the columns
-// with row-block counts, and the sums over the cut columns of (B entries x parts)
-// and of their multiplications, which tell how many range set-ups the multi-part
-// launch makes per product.
+// In the counting pass, setup_acc (if given) receives the sums over the cut
+// columns of (B entries x parts) and of their multiplications, which tell
+// how many range set-ups the multi-part launch makes per product.
 constexpr int kCutBlk = 1024;  // row blocks held in LDS (more are read from memory)
 
 __global__ void __launch_bounds__(256) k_parts(Operand B, PartCfg p, PartCfg ps, const int32_t* list, int64_t npos,
                                                int64_t multi_begin, int64_t multi_end, unsigned cut_blocks, int64_t nbm,
                                                const int64_t* cnt, const int64_t* off, const uint32_t* blkcnt,
                                                int64_t* nparts, const int64_t* poff, Part* parts, const int64_t* mults,
-                                               unsigned long long* acc, unsigned* err) {
+                                               unsigned long long* setup_acc, unsigned* err) {
   __shared__ uint32_t s_blk[4][kCutBlk];  // prefix sums of the counts
-  unsigned long long my_nnz = 0, my_setup = 0, my_mults = 0;
+  unsigned long long my_setup = 0, my_mults = 0;
   // a column in one part
   auto whole = [&](int64_t pos, int32_t t, int64_t c, const PartCfg& q) {
     if (!parts) {
@@ -1271,7 +1270,6 @@ __global__ void __launch_bounds__(256) k_parts(Operand B, PartCfg p, PartCfg ps,
       const int32_t t = list[pos];
       const int64_t c = cnt[t];
       int64_t np = c > 0;
-      if (lane == 0) my_nnz += (unsigned long long)c;
       if (c > 0 && !(bitmap_ok(p, p.m, c) || hash_ok(p, p.m, c))) {
         const int64_t cb0 = slot_begin(B, t), nb = slot_begin(B, t + 1) - cb0;
         const uint32_t* blk = blkcnt + (pos - multi_begin) * p.nblk;
@@ -1287,10 +1285,10 @@ __global__ void __launch_bounds__(256) k_parts(Operand B, PartCfg p, PartCfg ps,
         }
         Part* out = parts ? parts + poff[pos] : nullptr;
         const int32_t bmi = pos - multi_begin < nbm ? (int32_t)(pos - multi_begin) : -1;
-        const int note = note_mode(mults[t], c);
+        const int note = parts ? note_mode(mults[t], c) : 0;
         np = p.nblk <= kCutBlk ? cut_parts<true>(p, s_blk[w], t, off[t], out, note, bmi, cb0, (int32_t)nb, err)
                                : cut_parts<false>(p, blk, t, off[t], out, note, bmi, cb0, (int32_t)nb, err);
-        if (acc && np > 1 && lane == 0) {
+        if (setup_acc && np > 1 && lane == 0) {
           my_setup += (unsigned long long)nb * (unsigned long long)np;
           my_mults += (unsigned long long)mults[t];
         }
@@ -1310,15 +1308,14 @@ __global__ void __launch_bounds__(256) k_parts(Operand B, PartCfg p, PartCfg ps,
       if (!parts) nparts[pos] = c > 0;
     }
   }
-  if (acc) {  // at most three atomics per workgroup
-    __shared__ unsigned long long s_acc[3];
-    if (threadIdx.x < 3) s_acc[threadIdx.x] = 0;
+  if (setup_acc) {  // one pair of atomics per workgroup
+    __shared__ unsigned long long s_acc[2];
+    if (threadIdx.x < 2) s_acc[threadIdx.x] = 0;
     __syncthreads();
-    if (my_nnz) atomicAdd(&s_acc[0], my_nnz);
-    if (my_setup) atomicAdd(&s_acc[1], my_setup);
-    if (my_mults) atomicAdd(&s_acc[2], my_mults);
+    if (my_setup) atomicAdd(&s_acc[0], my_setup);
+    if (my_mults) atomicAdd(&s_acc[1], my_mults);
     __syncthreads();
-    if (threadIdx.x < 3 && s_acc[threadIdx.x]) atomicAdd(&acc[threadIdx.x], s_acc[threadIdx.x]);
+    if (threadIdx.x < 2 && s_acc[threadIdx.x]) atomicAdd(&setup_acc[threadIdx.x], s_acc[threadIdx.x]);
   }
 }
 
@@ -1968,16 +1965,28 @@ __global__ void k_write_dcsc(Operand B, const int64_t* cnt, const int64_t* off, 
   }
 }
 
+struct Summary {
+  unsigned long long mults;
+  unsigned long long nnz_tiny;
+  unsigned long long nnz_multi;  // entries of C in columns with row-block counts
+  unsigned long long setup;      // sum over cut columns of (B entries x parts)
+  unsigned long long cut_mults;  // multiplications of the cut columns
+  unsigned err;
+  unsigned pad;
+};
+
 // Column pointers from the exact counts: off = exclusive scan of cnt, zoff =
-// of the nonempty flags (DCSC output; else only its total), nnz_tiny = sum over
-// the columns of 1..tiny_max products.  One pass of block sums and one that
-// applies them, for all three results (a scan each and a sum took five launches).
+// of the nonempty flags (DCSC output; else only its total), nnz_tiny and nnz_multi =
+// sums over the columns of at most tiny_max products and over those of more than
+// multi_min (which get row-block counts).  One pass of block sums and one that
+// applies them, for all results (a scan each and a sum took five launches).
+// totals: the spread counters of the multiplications, nnz_tiny and nnz_multi.
 __global__ void __launch_bounds__(kScanThreads) k_cnt_reduce(const int64_t* cnt, const int64_t* mults, int64_t tiny_max,
-                                                             int64_t n, int64_t* sums, int64_t* zsums,
-                                                             unsigned long long* nnz_tiny) {
-  __shared__ int64_t red[3][kScanThreads / kWave];
+                                                             int64_t multi_min, int64_t n, int64_t* sums,
+                                                             int64_t* zsums, unsigned long long* totals) {
+  __shared__ int64_t red[4][kScanThreads / kWave];
   const int64_t base = (int64_t)blockIdx.x * kScanTile;
-  int64_t s = 0, z = 0, ti = 0;
+  int64_t s = 0, z = 0, ti = 0, mu = 0;
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
     const int64_t i = base + (int64_t)k * kScanThreads + threadIdx.x;
@@ -1985,17 +1994,21 @@ __global__ void __launch_bounds__(kScanThreads) k_cnt_reduce(const int64_t* cnt,
       const int64_t c = cnt[i];
       s += c;
       z += c > 0;
-      if (mults[i] <= tiny_max) ti += c;
+      const int64_t m = mults[i];
+      if (m <= tiny_max) ti += c;
+      if (m > multi_min) mu += c;
     }
   }
   s = wave_sum(s);
   z = wave_sum(z);
   ti = wave_sum(ti);
+  mu = wave_sum(mu);
   const int w = threadIdx.x / kWave;
   if (lane_id() == 0) {
     red[0][w] = s;
     red[1][w] = z;
     red[2][w] = ti;
+    red[3][w] = mu;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -2003,25 +2016,27 @@ __global__ void __launch_bounds__(kScanThreads) k_cnt_reduce(const int64_t* cnt,
       s += red[0][k];
       z += red[1][k];
       ti += red[2][k];
+      mu += red[3][k];
     }
     sums[blockIdx.x] = s;
     zsums[blockIdx.x] = z;
-    if (ti) atomicAdd(spread(nnz_tiny), (unsigned long long)ti);
+    if (ti) atomicAdd(spread(totals + kSpreadWords), (unsigned long long)ti);
+    if (mu) atomicAdd(spread(totals + 2 * kSpreadWords), (unsigned long long)mu);
   }
 }
 
 // carry / zcarry: the scanned block sums; else sums / zsums: the block sums.
-// Also adds up the spread totals of the multiplications and of nnz_tiny.
+// Also adds up the spread totals.
 __global__ void __launch_bounds__(kScanThreads) k_cnt_apply(const int64_t* cnt, int64_t n, const int64_t* carry,
                                                             const int64_t* zcarry, const int64_t* sums,
                                                             const int64_t* zsums, int64_t* off, int64_t* zoff,
                                                             int zfull, const unsigned long long* totals,
-                                                            unsigned long long* mults, unsigned long long* nnz_tiny) {
+                                                            Summary* sum) {
   __shared__ int64_t red[kScanThreads / kWave + 1];
-  if (blockIdx.x == 0 && threadIdx.x < 2) {
+  if (blockIdx.x == 0 && threadIdx.x < 3) {
     unsigned long long s = 0;
     for (int i = 0; i < kSpread; ++i) s += totals[threadIdx.x * kSpreadWords + i * 16];
-    *(threadIdx.x == 0 ? mults : nnz_tiny) = s;
+    *(threadIdx.x == 0 ? &sum->mults : threadIdx.x == 1 ? &sum->nnz_tiny : &sum->nnz_multi) = s;
   }
   const int64_t cin = carry ? carry[blockIdx.x] : carry_from_sums(sums, blockIdx.x, red);
   const int64_t zin = zcarry ? zcarry[blockIdx.x] : carry_from_sums(zsums, blockIdx.x, red);
@@ -2053,15 +2068,14 @@ __global__ void __launch_bounds__(kScanThreads) k_cnt_apply(const int64_t* cnt, 
 }
 
 // Both for up to kSmallSlots columns, by one workgroup of 1024.
-__global__ void __launch_bounds__(1024) k_cnt_small(const int64_t* cnt, const int64_t* col_mults, int64_t tiny_max, int n,
-                                                    int64_t* off, int64_t* zoff, int zfull,
-                                                    const unsigned long long* totals, unsigned long long* mults,
-                                                    unsigned long long* nnz_tiny) {
+__global__ void __launch_bounds__(1024) k_cnt_small(const int64_t* cnt, const int64_t* col_mults, int64_t tiny_max,
+                                                    int64_t multi_min, int n, int64_t* off, int64_t* zoff, int zfull,
+                                                    const unsigned long long* totals, Summary* sum) {
   __shared__ int64_t red[1024 / kWave + 1];
   const int per = (n + 1023) / 1024;  // columns per thread
   const int base = (int)threadIdx.x * per;
   int64_t v[kSmallPer];
-  int64_t s = 0, z = 0, ti = 0;
+  int64_t s = 0, z = 0, ti = 0, mi = 0;
 #pragma unroll
   for (int k = 0; k < kSmallPer; ++k) {
     const bool in = k < per && base + k < n;
@@ -2070,9 +2084,11 @@ __global__ void __launch_bounds__(1024) k_cnt_small(const int64_t* cnt, const in
     s += v[k];
     z += v[k] > 0;
     if (mu <= tiny_max) ti += v[k];
+    if (mu > multi_min) mi += v[k];
   }
-  int64_t total, ztotal, titotal;
+  int64_t total, ztotal, titotal, mitotal;
   block_excl_scan(ti, red, &titotal);
+  block_excl_scan(mi, red, &mitotal);
   int64_t run = block_excl_scan(s, red, &total);
   int64_t zrun = block_excl_scan(z, red, &ztotal);
 #pragma unroll
@@ -2086,8 +2102,9 @@ __global__ void __launch_bounds__(1024) k_cnt_small(const int64_t* cnt, const in
   if (threadIdx.x == 0) {
     unsigned long long m = 0;
     for (int i = 0; i < kSpread; ++i) m += totals[i * 16];
-    *mults = m;
-    *nnz_tiny = (unsigned long long)titotal;
+    sum->mults = m;
+    sum->nnz_tiny = (unsigned long long)titotal;
+    sum->nnz_multi = (unsigned long long)mitotal;
     off[n] = total;
     zoff[n] = ztotal;
   }
@@ -2149,16 +2166,6 @@ using namespace spx;
 
 namespace spx {
 
-struct Summary {
-  unsigned long long mults;
-  unsigned long long nnz_tiny;
-  unsigned long long nnz_multi;  // entries of C in columns with row-block counts; k_parts adds this and the next two
-  unsigned long long setup;      // sum over cut columns of (B entries x parts)
-  unsigned long long cut_mults;  // multiplications of the cut columns
-  unsigned err;
-  unsigned pad;
-};
-
 enum { kEvPlan0, kEvPlan1, kEvExec0, kEvMulti, kEvParts, kEvTiny, kEvPtr, kNumEv };
 
 struct GemmPlan : spx_plan {
@@ -2201,7 +2208,7 @@ struct GemmPlan : spx_plan {
   bool queues_spent = false;           // unless an exec failed and could not clear them (see QueueGuard)
   int32_t nq_multi = 1, nslice = 1, nslice_req = 1;
   Summary* sum = nullptr;
-  unsigned long long* totals = nullptr;  // spread counters: multiplications, entries of the tiny columns
+  unsigned long long* totals = nullptr;  // spread counters: multiplications, entries of the tiny and the cut columns
   int64_t L = 0, L_single = 0;
   int32_t* qlist = nullptr;  // B entries of the parts of bucketed columns, grouped by part
   uint64_t* gbm = nullptr;  // stored row bitmaps of the bitmap-counted columns
@@ -2257,18 +2264,21 @@ static int32_t hash_most(int64_t L, int64_t sz) {
 // Column pointers of C (see k_cnt_reduce).
 static int scan_counts(GemmPlan* P, Scratch& scr, hipStream_t st) {
   const int64_t n = P->nslots;
+  // the products above which a column gets row-block counts (see multi_end)
+  const int64_t multi_min =
+      std::min<int64_t>(P->tune.hash_count_max, std::max<int64_t>(P->tune.single_part_max, kMidMax));
   if (n <= 0) return zero_words(st, {{P->off, 1}, {P->zoff, 1}});
   if (n <= kSmallSlots) {
-    k_cnt_small<<<1, 1024, 0, st>>>(P->cnt, P->mults_d, P->tune.tiny_max, (int)n, P->off, P->zoff, P->c_fmt == SPX_DCSC,
-                                    P->totals, &P->sum->mults, &P->sum->nnz_tiny);
+    k_cnt_small<<<1, 1024, 0, st>>>(P->cnt, P->mults_d, P->tune.tiny_max, multi_min, (int)n, P->off, P->zoff,
+                                    P->c_fmt == SPX_DCSC, P->totals, P->sum);
     SPX_HIP(hipGetLastError());
     return SPX_OK;
   }
   const int64_t nb = ceil_div(n, kScanTile);
   int64_t *sums = nullptr, *zsums = nullptr, *carry = nullptr, *zcarry = nullptr;
   SPX_TRY(scr.get_many({Scratch::part(&sums, nb), Scratch::part(&zsums, nb)}));
-  k_cnt_reduce<<<(unsigned)nb, kScanThreads, 0, st>>>(P->cnt, P->mults_d, P->tune.tiny_max, n, sums, zsums,
-                                                      P->totals + kSpreadWords);
+  k_cnt_reduce<<<(unsigned)nb, kScanThreads, 0, st>>>(P->cnt, P->mults_d, P->tune.tiny_max, multi_min, n, sums, zsums,
+                                                      P->totals);
   SPX_HIP(hipGetLastError());
   if (nb > kFusedCarry) {
     SPX_TRY(scr.get_many({Scratch::part(&carry, nb + 1), Scratch::part(&zcarry, nb + 1)}));
@@ -2276,8 +2286,7 @@ static int scan_counts(GemmPlan* P, Scratch& scr, hipStream_t st) {
     SPX_TRY(exclusive_scan(LoadI64{zsums}, nb, zcarry, scr, st));
   }
   k_cnt_apply<<<(unsigned)nb, kScanThreads, 0, st>>>(P->cnt, n, carry, zcarry, sums, zsums, P->off, P->zoff,
-                                                     P->c_fmt == SPX_DCSC, P->totals, &P->sum->mults,
-                                                     &P->sum->nnz_tiny);
+                                                     P->c_fmt == SPX_DCSC, P->totals, P->sum);
   SPX_HIP(hipGetLastError());
   return SPX_OK;
 }
@@ -2478,11 +2487,11 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
                         Scratch::part(&P->list, nslots), Scratch::part(&P->binoff, kNumBins + 1),
                         Scratch::part(&bincount, kNumBins), Scratch::part(&binfill, kNumBins),
                         Scratch::part(&longs, std::max<int64_t>(nslots, 1)), Scratch::part(&nlong, 1),
-                        Scratch::part(&P->qctr, kMaxQueues + 1), Scratch::part(&P->totals, 2 * kSpreadWords)}));
+                        Scratch::part(&P->qctr, kMaxQueues + 1), Scratch::part(&P->totals, 3 * kSpreadWords)}));
   // bin offsets stay zero when there are no slots (k_bin_fill writes them otherwise)
   SPX_TRY(zero_words(st, {{P->sum, (int64_t)(sizeof(Summary) / 8)}, {bincount, kNumBins}, {binfill, kNumBins},
                           {P->cnt, std::max<int64_t>(nslots, 1)}, {nlong, 1}, {P->binoff, kNumBins + 1},
-                          {P->qctr, kMaxQueues + 1}, {P->totals, 2 * kSpreadWords}}));
+                          {P->qctr, kMaxQueues + 1}, {P->totals, 3 * kSpreadWords}}));
   unsigned* err = &P->sum->err;
 
   // AUX index for a DCSC A
@@ -2662,7 +2671,7 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
     k_parts<<<pgrid, 256, 0, st>>>(P->B, pc, pcs, P->list, npos, multi_begin, multi_end,
                                                                     cut_blocks, P->gbm ? nbitmap : 0, P->cnt,
                                                                     P->off, blkcnt, np, nullptr, nullptr, P->mults_d,
-                                                                    &P->sum->nnz_multi, err);
+                                                                    &P->sum->setup, err);
     SPX_HIP(hipGetLastError());
     SPX_TRY(exclusive_scan(LoadI64{np}, npos, poff, scr, st));
   }

@@ -37,3 +37,23 @@ def test_info_during_capture_and_from_threads(spx, scale):
         torch.cuda.synchronize()
         assert x.tolist() == [k + 1.0] * 4
     plan.close()
+
+
+# columns cut into row ranges: more products than single_part_max (512 at least), or than
+# the hash count takes; a plan of up to 8192 columns and one of more
+@pytest.mark.parametrize("scale", [12, 14])
+@pytest.mark.parametrize("tune,above", [({}, 1024), (dict(single_part_max=2048), 2048), (dict(single_part_max=64), 512),
+                                        (dict(hash_count_max=700), 700),
+                                        (dict(tiny_max=0, hash_count_max=0), 0)])
+def test_entries_of_cut_columns(spx, scale, tune, above):
+    A = W.rmat(scale, 8, seed=7)
+    ref = oracle.spgemm_csc(A, A, nthreads=8)
+    mults = np.add.reduceat(np.append(np.diff(A.cp)[A.ir], 0), A.cp[:-1]) * (np.diff(A.cp) > 0)
+    t = spx.default_tuning()
+    for k, v in tune.items():
+        setattr(t, k, v)
+    plan = spx.GemmPlan(spx.from_host(A), spx.from_host(A), tuning=t)
+    info = plan.info()
+    plan.close()
+    assert info["nnz_multi"] == np.diff(ref.cp)[mults > above].sum()
+    assert info["nnz_tiny"] == np.diff(ref.cp)[mults <= t.tiny_max].sum()
