@@ -1121,7 +1121,7 @@ struct PartCfg {
   int64_t slice_blocks;  // row blocks per slice (parts never straddle slices); 0: one slice
   int32_t nslice;
   int32_t hash_max;  // most outputs of a hash-mode part that fits L (0: none)
-  int64_t hash_span; // most rows it may span
+  int64_t hash_span; // most rows it may span (set per cut column, see span_limit)
   int32_t note;      // bytes per output that parts leave for noted rows
   int32_t pad;
 };
@@ -1147,6 +1147,19 @@ __host__ __device__ inline int64_t hash_bytes(int64_t p2, int64_t sz) {  // p2: 
 }
 __device__ __forceinline__ bool hash_ok(const PartCfg& p, int64_t span, int64_t c) {
   return c <= p.hash_max && span <= p.hash_span;
+}
+
+// Most rows of the hash parts of a column with c outputs.  Parts of more than kRankSpan
+// rows sort their rows, so the column is rather cut there, unless that makes more than
+// three times the parts that its outputs need.  Cut | sorted: 100,000 columns of 2000
+// outputs (one part's worth) over 2^21 rows 6.6 | 9.3 ms, 2^21.5 (three spans) 7.9 | 9.3,
+// 2^22 (four) 9.8 | 9.3, 2^23 16.8 | 9.4; 300 of 30,000 (15 parts) over 2^24 rows, 16 spans,
+// 0.52 | 0.74, 2^25 0.81 | 0.94; R-MAT scale 23 with 2 edges a vertex squared 232 | 243,
+// by this rule 209.
+__device__ __forceinline__ int64_t span_limit(const PartCfg& p, int64_t c) {
+  const int64_t spans = (p.m + kRankSpan - 1) / kRankSpan;
+  const int64_t need = p.hash_max > 0 ? ((uint32_t)c + (uint32_t)p.hash_max - 1) / (uint32_t)p.hash_max : 0;
+  return spans <= 3 * need ? kRankSpan : p.m;
 }
 
 __device__ __forceinline__ int choose_mode(const PartCfg& p, int64_t span, int64_t c) {
@@ -1270,7 +1283,9 @@ __global__ void __launch_bounds__(256) k_parts(Operand B, PartCfg p, PartCfg ps,
       const int32_t t = list[pos];
       const int64_t c = cnt[t];
       int64_t np = c > 0;
-      if (c > 0 && !(bitmap_ok(p, p.m, c) || hash_ok(p, p.m, c))) {
+      PartCfg q = p;
+      q.hash_span = span_limit(p, c);
+      if (c > 0 && !(bitmap_ok(q, q.m, c) || hash_ok(q, q.m, c))) {
         const int64_t cb0 = slot_begin(B, t), nb = slot_begin(B, t + 1) - cb0;
         const uint32_t* blk = blkcnt + (pos - multi_begin) * p.nblk;
         if (p.nblk <= kCutBlk) {
@@ -1286,15 +1301,15 @@ __global__ void __launch_bounds__(256) k_parts(Operand B, PartCfg p, PartCfg ps,
         Part* out = parts ? parts + poff[pos] : nullptr;
         const int32_t bmi = pos - multi_begin < nbm ? (int32_t)(pos - multi_begin) : -1;
         const int note = parts ? note_mode(mults[t], c) : 0;
-        np = p.nblk <= kCutBlk ? cut_parts<true>(p, s_blk[w], t, off[t], out, note, bmi, cb0, (int32_t)nb, err)
-                               : cut_parts<false>(p, blk, t, off[t], out, note, bmi, cb0, (int32_t)nb, err);
+        np = p.nblk <= kCutBlk ? cut_parts<true>(q, s_blk[w], t, off[t], out, note, bmi, cb0, (int32_t)nb, err)
+                               : cut_parts<false>(q, blk, t, off[t], out, note, bmi, cb0, (int32_t)nb, err);
         if (setup_acc && np > 1 && lane == 0) {
           my_setup += (unsigned long long)nb * (unsigned long long)np;
           my_mults += (unsigned long long)mults[t];
         }
         wave_sync();
       } else if (c > 0 && lane == 0) {
-        whole(pos, t, c, p);
+        whole(pos, t, c, q);
       }
       if (!parts && lane == 0) nparts[pos] = np;
     }
@@ -2659,9 +2674,7 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
   // of them: scale-20 product 35.0 -> 33.1 ms, but 128 columns in 1014 parts, two
   // for each workgroup, 214 -> 246 us.
   const int32_t note = sz > 0 && nmulti >= 16 * (int64_t)cus ? 2 : 0;
-  // a hash part of more than kRankSpan rows has to sort its rows, so columns of a
-  // few times as many rows are rather cut there
-  PartCfg pc{L, m, sz, rb, nblk, slice_blocks, nslice, hash_most(L, sz), m <= 4 * kRankSpan ? kRankSpan : m, note, 0};
+  PartCfg pc{L, m, sz, rb, nblk, slice_blocks, nslice, hash_most(L, sz), m, note, 0};
   PartCfg pcs{P->L_single, m, sz, rb, nblk, 0, nslice, hash_most(P->L_single, sz), m, 0, 0};
   const unsigned cut_blocks = nmulti > 0 ? grid_for(nmulti, 4, (int64_t)cus * 8) : 0;
   const unsigned pgrid = cut_blocks + (npos > multi_end ? grid_for(npos - multi_end, 256, (int64_t)cus * 8) : 0);

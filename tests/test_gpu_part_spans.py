@@ -37,16 +37,20 @@ def product(spx, m, per_a, ncols_a, per, cols, semiring, values, seed, last_row=
     return ref, info
 
 
-# columns of 2000 products at most: few enough for one hash part.  Up to 2^22 rows they are
-# cut where 2^20 rows end, above they stay whole.
-@pytest.mark.parametrize("m", [1 << 20, (1 << 20) + 1, 3 << 20, 4 << 20, (4 << 20) + 1, (1 << 24) + 77])
+# 2000 products a column, one hash part's worth: cut where 2^20 rows end while that makes
+# at most three parts.  5000 products, three parts' worth: while it makes at most nine.
+@pytest.mark.parametrize("m,per_a,cut", [(1 << 20, 500, True), ((1 << 20) + 1, 500, True), (3 << 20, 500, True),
+                                         ((3 << 20) + 1, 500, False), ((1 << 24) + 77, 500, False),
+                                         (9 << 20, 1250, True), ((9 << 20) + 1, 1250, False)])
 @pytest.mark.parametrize("semiring,values", KINDS)
-def test_hash_part_spans(spx, m, semiring, values):
-    ref, info = product(spx, m, 500, 8, 4, 12, semiring, values, seed=m % 1013)
-    column = np.repeat(np.arange(12), np.diff(ref.cp))
-    assert np.diff(ref.cp).min() > 1024 and np.diff(ref.cp).max() <= 2048
-    spans = np.unique(column * 64 + (ref.ir >> 20)).size if m <= 4 << 20 else 12
-    assert info["multi_parts"] == spans
+def test_hash_part_spans(spx, m, per_a, cut, semiring, values):
+    cols = 12
+    ref, info = product(spx, m, per_a, 8, 4, cols, semiring, values, seed=m % 1013)
+    outputs = np.diff(ref.cp)
+    need = -(-4 * per_a // 2048)
+    assert outputs.min() > max(1024, 2048 * (need - 1)) and outputs.max() <= 2048 * need
+    spans = np.unique(np.repeat(np.arange(cols), outputs) * 64 + (ref.ir >> 20)).size
+    assert info["multi_parts"] == (spans if cut else need * cols)
 
 
 # 5400 products over 500000 rows: two bitmap parts of 250000 rows or more to a column.
