@@ -217,9 +217,12 @@ __global__ void k_split_fill(Operand A, const int64_t* nsplit_d, const int32_t* 
     const int32_t al = (int32_t)(slot_begin(A, k + 1) - a0);
     const int32_t* col = A.ir + a0;
     int32_t* out = splits + sidx * sstride;
-    // rounds of the walk against dependent loads of the searches
+    // rounds of the walk against dependent loads of the searches.  Product whose A has
+    // columns of this length, walked | searched: 10^4 entries over 2^20 rows (156 rounds, 42
+    // loads) 289 | 241 us, over 2^25 rows (156, 910) 591 | 722; 10^5 over 2^25 (1562, 1105) 1110
+    // | 780; 10^6 over 2^20 (15625, 60) 6896 | 3517; 10^3 over 2^23 (15, 170) 355 | 396.
     const int32_t searches = (sstride + kWave - 1) / kWave * (floor_log2_u64((uint64_t)al) + 1);
-    if (al / kWave > 2 * searches) {
+    if (al / kWave > searches) {
       for (int32_t b = lane; b < sstride; b += kWave) {
         int32_t lo = 0, hi = al;
         if (b == sstride - 1) lo = al;
@@ -2595,6 +2598,9 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
     SPX_TRY(exclusive_scan(LoadFlag{flag}, nslots_a, sid_off, scr, st));
     k_split_rows<<<grid_for(nslots_a, 256, (int64_t)cus * 32), 256, 0, st>>>(nslots_a, sid_off, flag, slot_of_split);
     SPX_HIP(hipGetLastError());
+    // flat where such columns are not rare: R-MAT 2^20 squared (most are) 134 us by list, 38
+    // flat; 16,384 columns, all such, 3.25 | 3.03 ms in all; among 2^20 columns no difference
+    // from n/65536 to n/4 of them, where B has two entries a column
     const int flat = nmulti > nslots / 64;
     k_split_assign<<<flat ? grid_for(B->nnz, 1024, (int64_t)cus * 16) : sb + lb, 256, 0, st>>>(
         P->A, P->B, P->aux, chunk, P->list, multi_begin, multi_end, longs, nlong, lb, flat, P->bq_alen, flag,
@@ -2670,9 +2676,11 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
   nslice = (int)ceil_div(nblk, slice_blocks);
   if (nslice <= 1) slice_blocks = 0;
   P->nslice = nslice;
-  // Parts leave room for noted rows (9% more parts) where every workgroup gets many
-  // of them: scale-20 product 35.0 -> 33.1 ms, but 128 columns in 1014 parts, two
-  // for each workgroup, 214 -> 246 us.
+  // Parts leave room for noted rows (9% more parts) where every workgroup gets many of
+  // them.  Without | with room, in all: R-MAT scale 20 squared 47.8 | 45.9 ms, scale 18 5.94 |
+  // 5.82, scale 16 equal; 16,384 columns through R-MAT 2.73 | 2.65, 2048 514 | 503 us; but
+  // through uniform columns, whose bitmap words are evenly full, 2048 541 | 564 us and
+  // 16,384 2.87 | 3.03 ms.
   const int32_t note = sz > 0 && nmulti >= 16 * (int64_t)cus ? 2 : 0;
   PartCfg pc{L, m, sz, rb, nblk, slice_blocks, nslice, hash_most(L, sz), m, note, 0};
   PartCfg pcs{P->L_single, m, sz, rb, nblk, 0, nslice, hash_most(P->L_single, sz), m, 0, 0};
