@@ -106,19 +106,22 @@ typedef struct spx_ctx {
  * spx_default_tuning() returns).  Output columns are binned by their
  * number of multiplications mu (an upper bound on their output size):
  *   tiny_max         mu <= tiny_max (<= 64): formed by 16, 32 or 64 lanes of a
- *                    wave, which sort the column's products (a whole wave
- *                    sorts up to 512 in the same way)
+ *                    wave, which sort the column's products.  Hash-counted
+ *                    columns of up to 512 products are formed by a wave each.
  *   hash_count_max   mu <= hash_count_max (<= 16384): exact count through an
  *                    LDS hash table; larger columns through an LDS bitmap
  *   single_part_max  power of two in [64, 4096]: columns with mu at most this
  *                    are accumulated as one part (LDS hash or bitmap sized
- *                    for it); larger columns are cut into row-range parts
+ *                    for it); larger columns are cut into row-range parts.
+ *                    Values below 512 act as 512, and at 512 no column is left
+ *                    for the single-part launch
  *   part_lds_bytes   LDS budget of one part of a larger column
  *   *_threads        workgroup sizes (multiples of 64, at most 1024) of the
  *                    hash count, bitmap count, multi-part and single-part
  *                    numeric kernels
- *   bitmap_chunk_log2  rows per work item of the bitmap count (log2); 0: one
- *                    chunk per row slice, at most 2^18 rows
+ *   bitmap_chunk_log2  rows per work item of the bitmap count (log2), at least
+ *                    128 and one row block; 0: one chunk per row slice, at most
+ *                    2^18 rows
  *   xcd_slices       the row space is cut into this many slices (parts never
  *                    straddle one); workgroup w serves slice w mod xcd_slices
  *                    first, so each XCD's L2 holds one slice of A (1: off)

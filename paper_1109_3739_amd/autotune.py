@@ -23,7 +23,7 @@ from . import BatchPlan, GemmPlan, default_tuning
 CANDIDATES: List[Dict[str, int]] = [
     {},
     {"tiny_max": 32},
-    {"single_part_max": 256, "single_threads": 256},
+    {"single_part_max": 512},
     {"single_part_max": 2048, "single_threads": 512},
     {"hash_count_max": 4096},
     {"part_lds_bytes": 144 * 1024, "part_threads": 1024},
@@ -82,6 +82,17 @@ def _time(fn: Callable[[], None], reps: int) -> float:
     return best
 
 
+# A candidate has to be faster than the defaults by more than repeated timings differ.
+MARGIN = 0.02
+
+
+def pick(results):
+    """Fastest of [(seconds, candidate)], but the defaults ({}) unless it beats them by MARGIN."""
+    best = min(results, key=lambda x: x[0])
+    default = next((r for r in results if r[1] == {}), best)
+    return default if best[0] > (1 - MARGIN) * default[0] else best
+
+
 def tune_batch(As, Bs, semiring: str = "plus_times", candidates: Optional[List[Dict[str, int]]] = None,
                reps: int = 2, use_cache: bool = True):
     """Best tuning for the batch (A_i, B_i); returns (spx_tuning, info dict)."""
@@ -105,7 +116,7 @@ def tune_batch(As, Bs, semiring: str = "plus_times", candidates: Optional[List[D
             results.append((_time(run, reps), cand))
         except Exception as e:  # a candidate the workload cannot use (e.g. LDS limits)
             results.append((float("inf"), {**cand, "error": str(e)[:80]}))
-    best_t, best = min(results, key=lambda x: x[0])
+    best_t, best = pick(results)
     entry = {"tuning": {k: v for k, v in best.items() if k != "error"}, "seconds": best_t,
              "tried": [{"cand": c, "seconds": s} for s, c in results]}
     if use_cache:
@@ -138,7 +149,7 @@ def tune_single(A, B, semiring: str = "plus_times", candidates: Optional[List[Di
             results.append((_time(run, reps), cand))
         except Exception as e:
             results.append((float("inf"), {**cand, "error": str(e)[:80]}))
-    best_t, best = min(results, key=lambda x: x[0])
+    best_t, best = pick(results)
     entry = {"tuning": {k: v for k, v in best.items() if k != "error"}, "seconds": best_t,
              "tried": [{"cand": c, "seconds": s} for s, c in results]}
     if use_cache:

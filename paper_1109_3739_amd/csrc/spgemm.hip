@@ -13,13 +13,13 @@
 // Two phases.
 //   plan (symbolic): per-entry lookup of A's columns, per-column number of
 //     multiplications, binning of the columns by that count, exact output
-//     counts (a sort in registers for tiny columns (lane groups) and mid ones
-//     (a wave), an LDS hash for medium ones, an LDS bitmap over the row space
-//     for heavy ones, which also yields per-row-block counts), int64 scan into
-//     column pointers, and a list of row-range "parts" (each fits one
-//     workgroup's LDS) for the numeric phase.
-//   exec (numeric): tiny and mid columns are sorted again, with their values,
-//     and written; every part is accumulated in LDS either through a bitmap
+//     counts (a sort in registers for tiny columns (lane groups), an LDS hash
+//     for mid ones (a wave's table) and medium ones (a workgroup's), an LDS
+//     bitmap over the row space for heavy ones, which also yields per-row-block
+//     counts), int64 scan into column pointers, and a list of row-range "parts"
+//     (each fits one workgroup's LDS) for the numeric phase.
+//   exec (numeric): tiny and mid columns are sorted with their values and
+//     written; every part is accumulated in LDS either through a bitmap
 //     over its row range (rank of a row = popcount prefix, which also yields
 //     sorted output) or through a hash table, whose rows a two-level bitmap
 //     ranks (above 2^20 rows an LDS sort orders them).
@@ -998,7 +998,7 @@ using BitmapRanges = RangeLdsT<kQChunkWide, kCountWin, OFF32, false>;  // heavy 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 template <bool OFF32>
-__global__ void __launch_bounds__(1024, 8) k_count_bitmap(Operand B, ProdSrc S, const int64_t* mults, const int32_t* list,
+__global__ void __launch_bounds__(1024, 8) k_count_bitmap(Operand B, ProdSrc S, const int32_t* list,
                                                        const int64_t* binoff, int64_t m, int chunk_log2, int rbshift,
                                                        int64_t nblk, uint32_t* blkcnt, unsigned long long* cnt,
                                                        uint32_t* gbm, int64_t gwords, unsigned long long* qctr) {
@@ -1505,7 +1505,8 @@ __device__ __forceinline__ void block_bitonic_sort(uint64_t* a, int n2) {
 // One workgroup per part (dynamic work queue).  Bitmap mode: mark rows,
 // popcount prefix gives each row its rank = output position, accumulate
 // values by rank, write rows and values in order.  Hash mode: accumulate
-// into an open-addressing table, then sort (row, slot) keys.
+// into an open-addressing table, then rank its rows by a two-level bitmap
+// (up to kRankSpan rows) or sort (row, slot) keys.
 template <bool OFF32>
 using PartRanges = RangeLdsT<kQChunkWide, kNumWin, OFF32, true>;
 
@@ -1516,8 +1517,7 @@ static_assert(sizeof(PartRanges<true>) + 480 <= kPartLds32 && sizeof(PartRanges<
 
 template <int SR, typename T, bool OFF32>
 __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, ProdSrc S,
-                                                        const int64_t* mults,
-                                                        const int64_t* cnt, const Part* parts, const int64_t* qoff,
+                                                        const Part* parts, const int64_t* qoff,
                                                         int64_t plo, int64_t phi, int nq, int nhome, int batch,
                                                         unsigned long long* qctr,
                                                         const uint64_t* gbm, int64_t gbm_words,
@@ -1585,7 +1585,6 @@ __global__ void __launch_bounds__(1024) k_numeric_parts(Operand A, Operand B, Pr
     const int32_t* qx = (P.mode & 2) ? qlist : nullptr;  // a bucketed part visits only its bucket
     const int64_t span = (int64_t)P.r1 - P.r0;
     const bool full = (P.r0 == 0 && P.r1 == (int32_t)A.m);
-    // products in this part ~ mults * c / cnt
     const int c = P.c;
     if ((P.mode & 1) == 0) {
       const int W = (int)((span + 63) >> 6);
@@ -2368,11 +2367,11 @@ static int launch_numeric(GemmPlan* P, spx_mat* C, hipStream_t st) {
     const int batch = (int)std::max<int64_t>(1, std::min<int64_t>(kPartBatch, (n1 - n0) / (2 * grid)));
     if (P->src.off32)  // A's positions fit 29 bits: gathers through 32-bit offsets
       hipLaunchKernelGGL((k_numeric_parts<SR, T, true>), dim3((unsigned)grid), dim3(blk), (size_t)L, st, P->A, P->B,
-                         P->src, P->mults_d, P->cnt, P->parts, qoff, n0, n1, nq, r == 0 ? P->nslice : 1, batch, qctr,
+                         P->src, P->parts, qoff, n0, n1, nq, r == 0 ? P->nslice : 1, batch, qctr,
                          P->gbm, P->gbm_words, P->qlist, L, cir, cnum, err);
     else
       hipLaunchKernelGGL((k_numeric_parts<SR, T, false>), dim3((unsigned)grid), dim3(blk), (size_t)L, st, P->A, P->B,
-                         P->src, P->mults_d, P->cnt, P->parts, qoff, n0, n1, nq, r == 0 ? P->nslice : 1, batch, qctr,
+                         P->src, P->parts, qoff, n0, n1, nq, r == 0 ? P->nslice : 1, batch, qctr,
                          P->gbm, P->gbm_words, P->qlist, L, cir, cnum, err);
     SPX_HIP(hipGetLastError());
     if (r == 0) P->mark(kEvMulti, st);
@@ -2662,7 +2661,7 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
     bsrc.qchunk = kQChunkWide;
     const auto kern = off32 ? k_count_bitmap<true> : k_count_bitmap<false>;
     kern<<<(unsigned)bgrid, tune.bitmap_threads, lds, st>>>(
-        P->B, bsrc, P->mults_d, P->list, P->binoff, m, clog, rb, nblk, blkcnt, (unsigned long long*)P->cnt,
+        P->B, bsrc, P->list, P->binoff, m, clog, rb, nblk, blkcnt, (unsigned long long*)P->cnt,
         (uint32_t*)P->gbm, 2 * P->gbm_words, bqctr);
     SPX_HIP(hipGetLastError());
   }
