@@ -2089,6 +2089,8 @@ __global__ void __launch_bounds__(1024) k_cnt_small(const int64_t* cnt, const in
                                                     int64_t multi_min, int n, int64_t* off, int64_t* zoff, int zfull,
                                                     const unsigned long long* totals, Summary* sum) {
   __shared__ int64_t red[1024 / kWave + 1];
+  __shared__ unsigned long long s_tot[2];  // entries of the tiny and of the cut columns
+  if (threadIdx.x < 2) s_tot[threadIdx.x] = 0;
   const int per = (n + 1023) / 1024;  // columns per thread
   const int base = (int)threadIdx.x * per;
   int64_t v[kSmallPer];
@@ -2103,10 +2105,14 @@ __global__ void __launch_bounds__(1024) k_cnt_small(const int64_t* cnt, const in
     if (mu <= tiny_max) ti += v[k];
     if (mu > multi_min) mi += v[k];
   }
-  int64_t total, ztotal, titotal, mitotal;
-  block_excl_scan(ti, red, &titotal);
-  block_excl_scan(mi, red, &mitotal);
+  ti = wave_incl_scan(ti);
+  mi = wave_incl_scan(mi);
+  int64_t total, ztotal;
   int64_t run = block_excl_scan(s, red, &total);
+  if (lane_id() == kWave - 1) {
+    if (ti) atomicAdd(&s_tot[0], (unsigned long long)ti);
+    if (mi) atomicAdd(&s_tot[1], (unsigned long long)mi);
+  }
   int64_t zrun = block_excl_scan(z, red, &ztotal);
 #pragma unroll
   for (int k = 0; k < kSmallPer; ++k)
@@ -2120,8 +2126,8 @@ __global__ void __launch_bounds__(1024) k_cnt_small(const int64_t* cnt, const in
     unsigned long long m = 0;
     for (int i = 0; i < kSpread; ++i) m += totals[i * 16];
     sum->mults = m;
-    sum->nnz_tiny = (unsigned long long)titotal;
-    sum->nnz_multi = (unsigned long long)mitotal;
+    sum->nnz_tiny = s_tot[0];
+    sum->nnz_multi = s_tot[1];
     off[n] = total;
     zoff[n] = ztotal;
   }
