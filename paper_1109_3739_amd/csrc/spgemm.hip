@@ -2682,7 +2682,7 @@ extern "C" int spx_spgemm_plan(const spx_ctx* ctx, const spx_mat* A, const spx_m
   if (nslice <= 1) slice_blocks = 0;
   P->nslice = nslice;
   // Parts leave room for noted rows (9% more parts) where every workgroup gets many of
-  // them.  Without | with room, in all: R-MAT scale 20 squared 47.8 | 45.9 ms, scale 18 5.94 |
+  // them.  Without | with room, in all: R-MAT scale 20 squared 46.3 | 45.5 ms, scale 18 5.94 |
   // 5.82, scale 16 equal; 16,384 columns through R-MAT 2.73 | 2.65, 2048 514 | 503 us; but
   // through uniform columns, whose bitmap words are evenly full, 2048 541 | 564 us and
   // 16,384 2.87 | 3.03 ms.
